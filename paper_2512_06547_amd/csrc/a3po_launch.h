@@ -81,9 +81,6 @@ inline void carve_loss_ws(LossArgs &a, void *workspace, int64_t T)
     a.ws_scratch = ws + lay.scratch;
 }
 
-// true when the single-pass register-resident kernel can take these rows
-bool rows_fit_on_chip(int dt, int64_t V, int64_t ld, const void *z, const void *dz);
-
 hipError_t launch_loss_prep(const LossArgs &a, hipStream_t s);
 hipError_t launch_loss_rows(const LossArgs &a, hipStream_t s);
 hipError_t launch_loss_finish(const LossArgs &a, hipStream_t s);

@@ -66,6 +66,52 @@ __device__ __forceinline__ void mask_tail(uint4 &v, int rem)
     v = make_uint4(w[0], w[1], w[2], w[3]);
 }
 
+// EDGE: rows that do not start and end on 128-byte lines (a row stride that is no multiple of 128 bytes: odd
+// vocabularies, views).  The row is cut into a head of single elements up to the first line of its gradient, a body
+// of whole vectors from there, and a tail of single elements; head and tail elements take one lane each (wavefront 0
+// holds the head, wavefronts 1 and 2 the tail), so the body needs no partial vector and every wavefront's store
+// covers whole lines.  The cut follows the gradient's address, because stores that straddle lines cost more than
+// loads that do; the logits may sit at any other element alignment (the loads then straddle, nothing else changes).
+// The cut differs from row to row: the number of body vectors by up to 8 over all rows of a matrix.  NSWEEP is
+// (fewest body vectors) / 1024 + 1, so sweeps 0 .. NSWEEP-2 are full in every row; a row with more vectors than
+// NSWEEP sweeps hold leaves the surplus in its tail (at most 64 + 7 elements).
+constexpr int kLineBytes = 128;
+constexpr int kEdgeTail0 = kWave;      // first thread of the tail
+
+struct EdgeSpan {
+    int head, nbody, tail;  // elements, vectors, elements
+};
+
+template <typename DT>
+__device__ __forceinline__ EdgeSpan edge_span(const char *out_row, int V, int max_body)
+{
+    EdgeSpan e;
+    const uint32_t to_line = (0u - (uint32_t)reinterpret_cast<uintptr_t>(out_row)) & (kLineBytes - 1);
+    e.head = min(V, (int)(to_line / DT::kBytes));
+    e.nbody = min(max_body, (V - e.head) / DT::kPerVec);
+    e.tail = V - e.head - e.nbody * DT::kPerVec;
+    return e;
+}
+
+// the column of the edge element this thread holds, or -1
+template <typename DT>
+__device__ __forceinline__ int edge_column(const EdgeSpan &e, int tid)
+{
+    if (tid < e.head) return tid;
+    if (tid >= kEdgeTail0 && tid - kEdgeTail0 < e.tail) return e.head + e.nbody * DT::kPerVec + tid - kEdgeTail0;
+    return -1;
+}
+
+// 16 bytes from an address that is only aligned to the element
+typedef u32x4_t u32x4_elem_t __attribute__((aligned(2)));
+template <bool ANY>
+__device__ __forceinline__ uint4 row_load(const char *p)
+{
+    if constexpr (!ANY) return stream_load(p);
+    const u32x4_t t = __builtin_nontemporal_load(reinterpret_cast<const u32x4_elem_t *>(p));
+    return make_uint4(t.x, t.y, t.z, t.w);
+}
+
 // ENT adds the policy entropy of each counted row, H = lse - sum_j p_j z_j.  The sum rides on the
 // backward pass, which evaluates every p_j anyway: one extra multiply-add per element, wave
 // partials in LDS, and thread 0 finishes the row's entropy after the *next* row's barrier (by then
@@ -78,7 +124,7 @@ __device__ __forceinline__ void mask_tail(uint4 &v, int rem)
 // such row is too short a burst to keep the memory system busy between a workgroup's barrier, queue claim and
 // per-token arithmetic (+12 % at 32,000 bfloat16 columns, +26 % at 16,000; with longer rows two workgroups are slower).
 constexpr int kTwoRowSweeps = 4;
-template <typename DT, int NSWEEP, bool ENT>
+template <typename DT, int NSWEEP, bool ENT, bool EDGE>
 __global__ __launch_bounds__(kRowThreads, NSWEEP <= kTwoRowSweeps ? 8 : 4) void loss_rows_kernel(
     const void *z, void *dz, int64_t T, int64_t V, int64_t ld, const TokenRecord *__restrict__ records,
     int32_t current_version, float clip_eps, int prox_mode, const WsHeader *__restrict__ hdr,
@@ -96,13 +142,13 @@ __global__ __launch_bounds__(kRowThreads, NSWEEP <= kTwoRowSweeps ? 8 : 4) void 
     const int tid = threadIdx.x;
     const int lane = tid & (kWave - 1), wave = tid / kWave;
     const uint32_t voff = (uint32_t)tid * 16u;
-    const int nfull = (int)(V / EPV);  // complete vectors in a row
-    const int rem = (int)(V % EPV);    // elements in the ragged tail vector (0 = none)
-    // this thread's vector of the last sweep, relative to the row's end
+    const int nfull = (int)(V / EPV);             // complete vectors in a row
+    const int rem = EDGE ? 0 : (int)(V % EPV);    // elements in the ragged tail vector (0 = none)
+    // this thread's vector of the last sweep, relative to the row's end (EDGE: set per row)
     const int last_idx = LAST * kRowThreads + tid;
-    const bool last_full = last_idx < nfull;               // a complete vector
+    bool last_full = last_idx < nfull;                     // a complete vector
     const bool last_tail = rem != 0 && last_idx == nfull;  // the ragged tail vector
-    const bool last_any = last_full || last_tail;
+    bool last_any = last_full || last_tail;
     const float inv_n = hdr->inv_n;
     const size_t row_bytes = (size_t)ld * DT::kBytes;
     int parity = 0;
@@ -134,26 +180,38 @@ __global__ __launch_bounds__(kRowThreads, NSWEEP <= kTwoRowSweeps ? 8 : 4) void 
         unsigned int claimed = 0;
         if (tid == 0) claimed = atomicAdd(row_queue, 1u);
         __builtin_amdgcn_sched_barrier(0);
+        // (EDGE: these point at the row's first body vector, `head` elements into the row)
         char *out_row = reinterpret_cast<char *>(dz) + (size_t)row * row_bytes;
         const char *in_row = reinterpret_cast<const char *>(z) + (size_t)row * row_bytes;
+        EdgeSpan span = {0, 0, 0};
+        if constexpr (EDGE) {
+            span = edge_span<DT>(out_row, (int)V, NSWEEP * kRowThreads);
+            out_row += span.head * DT::kBytes;
+            in_row += span.head * DT::kBytes;
+            last_full = last_any = last_idx < span.nbody;
+        }
+        auto edge_at = [&]() { return edge_column<DT>(span, tid) - span.head; };  // valid where has_edge
+        const bool has_edge = EDGE && edge_column<DT>(span, tid) >= 0;
         const int row_par = parity;
 
         uint4 v[NSWEEP];
         float g = 0.0f, lse = 0.0f, zy = 0.0f, row_max = 0.0f, nls2 = 0.0f;
-        uint32_t zy_bits = 0;
+        uint32_t zy_bits = 0, edge_bits = 0;
         int64_t next = T;
         if (live) {  // uniform over the workgroup
             // ---- issue every load of the row: the chosen logit, the partial sweep, the full sweeps ----
             // (scheduling barriers pin the issue order so that the forward pass below can
             // consume vectors in arrival order while later ones are still in flight)
-            zy_bits = load_raw<DT>(in_row, y);
+            zy_bits = load_raw<DT>(in_row, y - span.head);
+            if constexpr (EDGE)
+                if (has_edge) edge_bits = load_raw<DT>(in_row, edge_at());
             __builtin_amdgcn_sched_barrier(0);
             v[LAST] = neg_inf_vec<DT>();
-            if (last_any) v[LAST] = stream_load(in_row + (size_t)LAST * kSweepBytes + voff);
+            if (last_any) v[LAST] = row_load<EDGE>(in_row + (size_t)LAST * kSweepBytes + voff);
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
             for (int k = 0; k < LAST - STASH; ++k) {
-                v[k] = stream_load(in_row + (size_t)k * kSweepBytes + voff);
+                v[k] = row_load<EDGE>(in_row + (size_t)k * kSweepBytes + voff);
                 __builtin_amdgcn_sched_barrier(0);
             }
 
@@ -166,7 +224,7 @@ __global__ __launch_bounds__(kRowThreads, NSWEEP <= kTwoRowSweeps ? 8 : 4) void 
                 fold<EPV>(acc, f);
                 if constexpr (STASH > 0) {
                     stash[0][tid] = v[LAST];
-                    v[LAST - STASH] = stream_load(in_row + (size_t)(LAST - STASH) * kSweepBytes + voff);
+                    v[LAST - STASH] = row_load<EDGE>(in_row + (size_t)(LAST - STASH) * kSweepBytes + voff);
                 }
             }
             if (tid == 0) next_row[parity] = claimed;  // the claim was issued before the row's loads
@@ -180,10 +238,16 @@ __global__ __launch_bounds__(kRowThreads, NSWEEP <= kTwoRowSweeps ? 8 : 4) void 
                     if (k + 1 < STASH) {
                         stash[k + 1][tid] = v[k];
                         v[LAST - STASH + k + 1] =
-                            stream_load(in_row + (size_t)(LAST - STASH + k + 1) * kSweepBytes + voff);
+                            row_load<EDGE>(in_row + (size_t)(LAST - STASH + k + 1) * kSweepBytes + voff);
                     }
                 }
                 __builtin_amdgcn_sched_barrier(0);
+            }
+            if constexpr (EDGE) {
+                if (has_edge) {
+                    float f[1] = {raw_to_float<DT>(edge_bits)};
+                    fold<1>(acc, f);
+                }
             }
             zy = raw_to_float<DT>(zy_bits);
             acc = wave_reduce(acc);
@@ -245,6 +309,8 @@ __global__ __launch_bounds__(kRowThreads, NSWEEP <= kTwoRowSweeps ? 8 : 4) void 
             } else if (last_tail) {
                 for (int e = 0; e < rem; ++e) store_elem<DT>(out_row, (int64_t)nfull * EPV + e, 0.0f);
             }
+            if constexpr (EDGE)
+                if (has_edge) store_elem<DT>(out_row, edge_at(), 0.0f);
             row = next;
             continue;
         }
@@ -286,8 +352,18 @@ __global__ __launch_bounds__(kRowThreads, NSWEEP <= kTwoRowSweeps ? 8 : 4) void 
         }
         // The chosen column gets +g.  The thread that stored the vector holding column y
         // rewrites that one element afterwards (same thread, same address: program order).
-        if (g != 0.0f && tid == ((y / EPV) & (kRowThreads - 1)))
-            store_elem<DT>(out_row, y, neg_g * exp2_hw(fmaf(zy - row_max, kLog2e, nls2)) + g);
+        const int yb = y - span.head;
+        bool y_in_body = true;
+        if constexpr (EDGE) {
+            y_in_body = yb >= 0 && yb < span.nbody * EPV;
+            if (has_edge) {
+                float f[1] = {raw_to_float<DT>(edge_bits)};
+                backward_vec<1, ENT>(f, neg_g, row_max, nls2, pz);
+                store_elem<DT>(out_row, edge_at(), edge_at() == yb ? f[0] + g : f[0]);
+            }
+        }
+        if (g != 0.0f && y_in_body && tid == ((yb / EPV) & (kRowThreads - 1)))
+            store_elem<DT>(out_row, yb, neg_g * exp2_hw(fmaf(zy - row_max, kLog2e, nls2)) + g);
         if constexpr (ENT) {
 #pragma unroll
             for (int off = kWave / 2; off > 0; off >>= 1) pz += __shfl_xor(pz, off, kWave);
@@ -329,7 +405,7 @@ typedef __attribute__((address_space(3))) void *rows_lds_ptr_t;
 
 __device__ __forceinline__ uint4 cached_load(const char *p) { return *reinterpret_cast<const uint4 *>(p); }
 
-template <typename DT, bool ENT>
+template <typename DT, bool ENT, bool EDGE>
 __global__ __launch_bounds__(kRowThreads) void loss_rows_long_kernel(
     const void *z, void *dz, int64_t T, int64_t V, int64_t ld, const TokenRecord *__restrict__ records,
     int32_t current_version, float clip_eps, int prox_mode, const WsHeader *__restrict__ hdr,
@@ -347,11 +423,11 @@ __global__ __launch_bounds__(kRowThreads) void loss_rows_long_kernel(
     const int lane = tid & (kWave - 1), wave = tid / kWave;
     const int wave_s = __builtin_amdgcn_readfirstlane(wave);
     const uint32_t voff = (uint32_t)tid * 16u;
-    const int nfull = (int)(V / EPV);
-    const int rem = (int)(V % EPV);
-    const int nvec = nfull + (rem != 0);
-    const int nsweep = (nvec + kRowThreads - 1) / kRowThreads;                    // > kMaxVec
-    const int lds_sweeps = min(kLongLds, nsweep - NREG);                      // >= 2
+    int nfull = (int)(V / EPV);              // (EDGE: nfull = nvec = the row's body vectors, set per row)
+    const int rem = EDGE ? 0 : (int)(V % EPV);
+    int nvec = nfull + (rem != 0);
+    const int nsweep = (nvec + kRowThreads - 1) / kRowThreads;                    // >= kMaxVec, the first kMaxVec - 1 full
+    const int lds_sweeps = min(kLongLds, nsweep - NREG);                      // >= 1
     const int tail0 = NREG + lds_sweeps;                                      // first streamed sweep
     const int tail_batches = (nsweep - tail0 + kLongTailUnroll - 1) / kLongTailUnroll;
     const float inv_n = hdr->inv_n;
@@ -385,10 +461,20 @@ __global__ __launch_bounds__(kRowThreads) void loss_rows_long_kernel(
         __builtin_amdgcn_sched_barrier(0);
         char *out_row = reinterpret_cast<char *>(dz) + (size_t)row * row_bytes;
         const char *in_row = reinterpret_cast<const char *>(z) + (size_t)row * row_bytes;
+        EdgeSpan span = {0, 0, 0};
+        if constexpr (EDGE) {
+            span = edge_span<DT>(out_row, (int)V, 0x7FFFFFFF);
+            out_row += span.head * DT::kBytes;
+            in_row += span.head * DT::kBytes;
+            nfull = nvec = span.nbody;
+        }
+        auto edge_at = [&]() { return edge_column<DT>(span, tid) - span.head; };  // valid where has_edge
+        const bool has_edge = EDGE && edge_column<DT>(span, tid) >= 0;
         const int row_par = parity;
 
         uint4 v[NREG];
         float g = 0.0f, lse = 0.0f, zy = 0.0f, row_max = 0.0f, nls2 = 0.0f;
+        uint32_t edge_bits = 0;
         int64_t next = T;
         if (live) {
             // a copy of the thread index the compiler cannot see through: the addresses of the direct loads are
@@ -396,7 +482,9 @@ __global__ __launch_bounds__(kRowThreads) void loss_rows_long_kernel(
             // across the whole row loop
             int tid_r = tid;
             asm volatile("" : "+v"(tid_r));
-            const uint32_t zy_bits = load_raw<DT>(in_row, y);
+            const uint32_t zy_bits = load_raw<DT>(in_row, y - span.head);
+            if constexpr (EDGE)
+                if (has_edge) edge_bits = load_raw<DT>(in_row, edge_at());
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
             for (int k = 0; k < NREG; ++k) {
@@ -455,6 +543,12 @@ __global__ __launch_bounds__(kRowThreads) void loss_rows_long_kernel(
                     float f[EPV];
                     unpack<DT>(t[u], f);
                     fold<EPV>(acc, f);
+                }
+            }
+            if constexpr (EDGE) {
+                if (has_edge) {
+                    float f[1] = {raw_to_float<DT>(edge_bits)};
+                    fold<1>(acc, f);
                 }
             }
             zy = raw_to_float<DT>(zy_bits);
@@ -518,6 +612,8 @@ __global__ __launch_bounds__(kRowThreads) void loss_rows_long_kernel(
                     for (int e = 0; e < rem; ++e) store_elem<DT>(out_row, (int64_t)nfull * EPV + e, 0.0f);
                 }
             }
+            if constexpr (EDGE)
+                if (has_edge) store_elem<DT>(out_row, edge_at(), 0.0f);
             row = next;
             continue;
         }
@@ -567,8 +663,18 @@ __global__ __launch_bounds__(kRowThreads) void loss_rows_long_kernel(
             }
         }
         // the chosen column gets +g from the thread that stored its vector (same thread, same address: program order)
-        if (g != 0.0f && tid == ((y / EPV) & (kRowThreads - 1)))
-            store_elem<DT>(out_row, y, neg_g * exp2_hw(fmaf(zy - row_max, kLog2e, nls2)) + g);
+        const int yb = y - span.head;
+        bool y_in_body = true;
+        if constexpr (EDGE) {
+            y_in_body = yb >= 0 && yb < span.nbody * EPV;
+            if (has_edge) {
+                float f[1] = {raw_to_float<DT>(edge_bits)};
+                backward_vec<1, ENT>(f, neg_g, row_max, nls2, pz);
+                store_elem<DT>(out_row, edge_at(), edge_at() == yb ? f[0] + g : f[0]);
+            }
+        }
+        if (g != 0.0f && y_in_body && tid == ((yb / EPV) & (kRowThreads - 1)))
+            store_elem<DT>(out_row, yb, neg_g * exp2_hw(fmaf(zy - row_max, kLog2e, nls2)) + g);
         if constexpr (ENT) {
 #pragma unroll
             for (int off = kWave / 2; off > 0; off >>= 1) pz += __shfl_xor(pz, off, kWave);
@@ -586,8 +692,8 @@ __global__ __launch_bounds__(kRowThreads) void loss_rows_long_kernel(
 }
 
 // ---------------------------------------------------------------------------------------
-// Multi-pass fallback for rows the fused kernel cannot hold (unaligned stride, very large
-// V): element-wise accesses, three reads of the row (max, sum, gradient).  Same results up
+// Multi-pass fallback for rows too long for the registers whose logits and gradient differ in alignment:
+// element-wise accesses, three reads of the row (max, sum, gradient).  Same results up
 // to summation order.  Any blockDim.x that is a multiple of 64 up to 1024.
 template <typename DT>
 __global__ __launch_bounds__(kRowThreads) void loss_rows_generic_kernel(const LossArgs a)
@@ -657,7 +763,8 @@ __global__ __launch_bounds__(kRowThreads) void loss_rows_generic_kernel(const Lo
 
 // ---------------------------------------------------------------------------------------
 // Forward only: log-sum-exp and chosen-token gather, one 256-thread workgroup per row,
-// rows dealt round-robin.  `vec` selects 16-byte loads (aligned rows) or element loads.
+// rows dealt round-robin.  A row is read as whole 16-byte vectors from its first 16-byte boundary on; the elements
+// before (rows of a stride or base that is no multiple of 16 bytes) and after the vectors are read singly.
 constexpr int kFwdThreads = 256;
 constexpr int kFwdWaves = kFwdThreads / kWave;
 constexpr int kFwdUnroll = 8;  // 16-byte vectors in flight per thread
@@ -665,46 +772,45 @@ constexpr int kFwdUnroll = 8;  // 16-byte vectors in flight per thread
 template <typename DT, bool ENT>
 __global__ __launch_bounds__(kFwdThreads) void logprob_rows_kernel(const void *z, int64_t T, int64_t V, int64_t ld,
                                                                     const int32_t *chosen, float *logp, float *lse_out,
-                                                                    void *chosen_logit, float *ent_out, int vec)
+                                                                    void *chosen_logit, float *ent_out)
 {
     constexpr int EPV = DT::kPerVec;
     using Acc = typename RowAcc<ENT>::type;
     __shared__ float red[3 * kFwdWaves];
     const int tid = threadIdx.x;
-    const int nfull = (int)(V / EPV);
     const size_t row_bytes = (size_t)ld * DT::kBytes;
 
     for (int64_t row = blockIdx.x; row < T; row += gridDim.x) {
         const char *in_row = reinterpret_cast<const char *>(z) + (size_t)row * row_bytes;
         Acc acc;
         seed(acc);
-        if (vec) {
-            int idx = tid;
-            for (; idx + (kFwdUnroll - 1) * kFwdThreads < nfull; idx += kFwdUnroll * kFwdThreads) {
-                uint4 v[kFwdUnroll];
+        const int head = (int)min(V, (int64_t)((0u - (uint32_t)reinterpret_cast<uintptr_t>(in_row)) & 15u) / DT::kBytes);
+        const int nfull = (int)(V - head) / EPV;
+        const char *body = in_row + head * DT::kBytes;
+        int idx = tid;
+        for (; idx + (kFwdUnroll - 1) * kFwdThreads < nfull; idx += kFwdUnroll * kFwdThreads) {
+            uint4 v[kFwdUnroll];
 #pragma unroll
-                for (int u = 0; u < kFwdUnroll; ++u) v[u] = stream_load(in_row + (size_t)(idx + u * kFwdThreads) * 16);
+            for (int u = 0; u < kFwdUnroll; ++u) v[u] = stream_load(body + (size_t)(idx + u * kFwdThreads) * 16);
 #pragma unroll
-                for (int u = 0; u < kFwdUnroll; ++u) {
-                    float f[EPV];
-                    unpack<DT>(v[u], f);
-                    fold<EPV>(acc, f);
-                }
-            }
-            for (; idx < nfull; idx += kFwdThreads) {
+            for (int u = 0; u < kFwdUnroll; ++u) {
                 float f[EPV];
-                unpack<DT>(stream_load(in_row + (size_t)idx * 16), f);
+                unpack<DT>(v[u], f);
                 fold<EPV>(acc, f);
             }
-            for (int64_t j = (int64_t)nfull * EPV + tid; j < V; j += kFwdThreads) {
-                float f[1] = {load_elem<DT>(in_row, j)};
-                fold<1>(acc, f);
-            }
-        } else {
-            for (int64_t j = tid; j < V; j += kFwdThreads) {
-                float f[1] = {load_elem<DT>(in_row, j)};
-                fold<1>(acc, f);
-            }
+        }
+        for (; idx < nfull; idx += kFwdThreads) {
+            float f[EPV];
+            unpack<DT>(stream_load(body + (size_t)idx * 16), f);
+            fold<EPV>(acc, f);
+        }
+        if (tid < head) {
+            float f[1] = {load_elem<DT>(in_row, tid)};
+            fold<1>(acc, f);
+        }
+        for (int64_t j = head + (int64_t)nfull * EPV + tid; j < V; j += kFwdThreads) {
+            float f[1] = {load_elem<DT>(in_row, j)};
+            fold<1>(acc, f);
         }
         const Acc tot = block_allreduce<kFwdWaves>(acc, red);
         if (tid == 0) {
@@ -741,59 +847,59 @@ static int device_cu_count()
 
 static bool aligned16(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 
-bool rows_fit_on_chip(int dt, int64_t V, int64_t ld, const void *z, const void *dz)
+// How the rows of a call are handled.
+struct RowPlan {
+    enum Kind { kRegisters, kLong, kElements } kind;
+    bool edge;   // cut rows at the lines of the gradient (see EdgeSpan)
+    int sweeps;  // kRegisters: template argument NSWEEP
+};
+
+// Rows whose base and stride are multiples of 16 bytes are taken whole; others are cut at lines.  A row whose body
+// needs more than kMaxVec sweeps goes through the long kernel, whose direct loads into LDS want 16-byte addresses:
+// logits and gradient must then have the same alignment within 16 bytes.  What is left (a long row of which they do
+// not) is taken element by element.
+template <typename DT>
+static RowPlan plan_rows(const LossArgs &a)
 {
-    const int64_t esz = dt == A3PO_F32 ? 4 : 2;
-    const int64_t epv = 16 / esz;
-    const int64_t nvec = (V + epv - 1) / epv;
-    return aligned16(z) && aligned16(dz) && (ld * esz) % 16 == 0 && nvec <= (int64_t)kMaxVec * kRowThreads;
+    constexpr int64_t EPV = DT::kPerVec;
+    const bool whole = aligned16(a.z) && aligned16(a.dz) && (a.ld * DT::kBytes) % 16 == 0;
+    if (whole) {
+        const int64_t sweeps = ((a.V + EPV - 1) / EPV + kRowThreads - 1) / kRowThreads;
+        return sweeps <= kMaxVec ? RowPlan{RowPlan::kRegisters, false, (int)sweeps} : RowPlan{RowPlan::kLong, false, 0};
+    }
+    const int64_t head_max = kLineBytes / DT::kBytes - 1;
+    const int64_t sweeps = (a.V > head_max ? a.V - head_max : 0) / EPV / kRowThreads + 1;
+    if (sweeps <= kMaxVec) return {RowPlan::kRegisters, true, (int)sweeps};
+    const bool same = ((reinterpret_cast<uintptr_t>(a.z) ^ reinterpret_cast<uintptr_t>(a.dz)) & 15u) == 0;
+    return {same ? RowPlan::kLong : RowPlan::kElements, true, 0};
 }
 
-template <typename DT>
-static hipError_t launch_loss_rows_t(const LossArgs &a, hipStream_t s)
+template <typename DT, bool EDGE>
+static hipError_t launch_long_rows(const LossArgs &a, unsigned grid, hipStream_t s)
 {
-    const int64_t nvec = (a.V + DT::kPerVec - 1) / DT::kPerVec;
-    const int cus = device_cu_count();
-    const unsigned grid = (unsigned)(a.T < (int64_t)cus ? a.T : (int64_t)cus);
-    if (!rows_fit_on_chip(a.dt, a.V, a.ld, a.z, a.dz)) {
-        if (aligned16(a.z) && aligned16(a.dz) && (a.ld * DT::kBytes) % 16 == 0) {
-            // aligned but too long for the registers: registers + LDS + a streamed tail
-            const RowOutputs lout = {a.logp_out, a.prox_out, a.ws_obj, a.ws_iw, a.ent_out, a.ws_flags};
-            const WsHeader *lhdr = reinterpret_cast<const WsHeader *>(a.ws_header);
-            static LdsLimitState lds_limit[2];
-            const void *kernel = a.ent_out ? reinterpret_cast<const void *>(&loss_rows_long_kernel<DT, true>)
-                                           : reinterpret_cast<const void *>(&loss_rows_long_kernel<DT, false>);
-            const hipError_t attr_err = ensure_lds_limit(kernel, kLongLdsBytes, lds_limit[a.ent_out ? 1 : 0]);
-            if (attr_err != hipSuccess) return attr_err;
-            if (a.ent_out)
-                hipLaunchKernelGGL((loss_rows_long_kernel<DT, true>), dim3(grid), dim3(kRowThreads), kLongLdsBytes, s,
-                                   a.z, a.dz, a.T, a.V, a.ld, a.ws_records, a.current_version, a.clip_eps, a.prox_mode,
-                                   lhdr, row_queue_of(a.ws_header), lout);
-            else
-                hipLaunchKernelGGL((loss_rows_long_kernel<DT, false>), dim3(grid), dim3(kRowThreads), kLongLdsBytes, s,
-                                   a.z, a.dz, a.T, a.V, a.ld, a.ws_records, a.current_version, a.clip_eps, a.prox_mode,
-                                   lhdr, row_queue_of(a.ws_header), lout);
-            return hipGetLastError();
-        }
-        hipLaunchKernelGGL((loss_rows_generic_kernel<DT>), dim3(grid * 2 > a.T ? (unsigned)a.T : grid * 2),
-                           dim3(kRowThreads), 0, s, a);
-        return hipGetLastError();
-    }
-    const int sweeps = (int)((nvec + kRowThreads - 1) / kRowThreads);
-    const int64_t resident = (int64_t)cus * (sweeps <= kTwoRowSweeps ? 2 : 1);
-    const unsigned row_grid = (unsigned)(a.T < resident ? a.T : resident);
+    const RowOutputs out = {a.logp_out, a.prox_out, a.ws_obj, a.ws_iw, a.ent_out, a.ws_flags};
+    const WsHeader *hdr = reinterpret_cast<const WsHeader *>(a.ws_header);
+    static LdsLimitState lds_limit[2];
+    auto *kernel = a.ent_out ? loss_rows_long_kernel<DT, true, EDGE> : loss_rows_long_kernel<DT, false, EDGE>;
+    const hipError_t attr_err =
+        ensure_lds_limit(reinterpret_cast<const void *>(kernel), kLongLdsBytes, lds_limit[a.ent_out ? 1 : 0]);
+    if (attr_err != hipSuccess) return attr_err;
+    hipLaunchKernelGGL(kernel, dim3(grid), dim3(kRowThreads), kLongLdsBytes, s, a.z, a.dz, a.T, a.V, a.ld, a.ws_records,
+                       a.current_version, a.clip_eps, a.prox_mode, hdr, row_queue_of(a.ws_header), out);
+    return hipGetLastError();
+}
+
+template <typename DT, bool ENT, bool EDGE>
+static hipError_t launch_register_rows(const LossArgs &a, int sweeps, unsigned grid, hipStream_t s)
+{
     const RowOutputs out = {a.logp_out, a.prox_out, a.ws_obj, a.ws_iw, a.ent_out, a.ws_flags};
     const WsHeader *hdr = reinterpret_cast<const WsHeader *>(a.ws_header);
     unsigned int *queue = row_queue_of(a.ws_header);
     switch (sweeps) {
 #define A3PO_SWEEP_CASE(N) \
     case N: \
-        if (a.ent_out) \
-            hipLaunchKernelGGL((loss_rows_kernel<DT, N, true>), dim3(row_grid), dim3(kRowThreads), 0, s, a.z, a.dz, a.T, \
-                               a.V, a.ld, a.ws_records, a.current_version, a.clip_eps, a.prox_mode, hdr, queue, out); \
-        else \
-            hipLaunchKernelGGL((loss_rows_kernel<DT, N, false>), dim3(row_grid), dim3(kRowThreads), 0, s, a.z, a.dz, a.T, \
-                               a.V, a.ld, a.ws_records, a.current_version, a.clip_eps, a.prox_mode, hdr, queue, out); \
+        hipLaunchKernelGGL((loss_rows_kernel<DT, N, ENT, EDGE>), dim3(grid), dim3(kRowThreads), 0, s, a.z, a.dz, a.T, a.V, \
+                           a.ld, a.ws_records, a.current_version, a.clip_eps, a.prox_mode, hdr, queue, out); \
         break;
         A3PO_SWEEP_CASE(1) A3PO_SWEEP_CASE(2) A3PO_SWEEP_CASE(3) A3PO_SWEEP_CASE(4) A3PO_SWEEP_CASE(5)
         A3PO_SWEEP_CASE(6) A3PO_SWEEP_CASE(7) A3PO_SWEEP_CASE(8) A3PO_SWEEP_CASE(9) A3PO_SWEEP_CASE(10)
@@ -805,6 +911,27 @@ static hipError_t launch_loss_rows_t(const LossArgs &a, hipStream_t s)
     return hipGetLastError();
 }
 
+template <typename DT>
+static hipError_t launch_loss_rows_t(const LossArgs &a, hipStream_t s)
+{
+    const int cus = device_cu_count();
+    const RowPlan plan = plan_rows<DT>(a);
+    const int64_t resident = (int64_t)cus * (plan.kind == RowPlan::kElements ||
+                                             (plan.kind == RowPlan::kRegisters && plan.sweeps <= kTwoRowSweeps) ? 2 : 1);
+    const unsigned grid = (unsigned)(a.T < resident ? a.T : resident);
+    if (plan.kind == RowPlan::kElements) {
+        hipLaunchKernelGGL((loss_rows_generic_kernel<DT>), dim3(grid), dim3(kRowThreads), 0, s, a);
+        return hipGetLastError();
+    }
+    if (plan.kind == RowPlan::kLong)
+        return plan.edge ? launch_long_rows<DT, true>(a, grid, s) : launch_long_rows<DT, false>(a, grid, s);
+    if (a.ent_out)
+        return plan.edge ? launch_register_rows<DT, true, true>(a, plan.sweeps, grid, s)
+                         : launch_register_rows<DT, true, false>(a, plan.sweeps, grid, s);
+    return plan.edge ? launch_register_rows<DT, false, true>(a, plan.sweeps, grid, s)
+                     : launch_register_rows<DT, false, false>(a, plan.sweeps, grid, s);
+}
+
 hipError_t launch_loss_rows(const LossArgs &a, hipStream_t s)
 {
     if (a.T == 0) return hipSuccess;
@@ -813,27 +940,24 @@ hipError_t launch_loss_rows(const LossArgs &a, hipStream_t s)
 
 template <typename DT>
 static void launch_logprob_rows_t(unsigned grid, hipStream_t s, const void *z, int64_t T, int64_t V, int64_t ld,
-                                  const int32_t *chosen, float *logp, float *lse, void *chosen_logit, float *ent,
-                                  int vec)
+                                  const int32_t *chosen, float *logp, float *lse, void *chosen_logit, float *ent)
 {
     if (ent)
         hipLaunchKernelGGL((logprob_rows_kernel<DT, true>), dim3(grid), dim3(kFwdThreads), 0, s, z, T, V, ld, chosen,
-                           logp, lse, chosen_logit, ent, vec);
+                           logp, lse, chosen_logit, ent);
     else
         hipLaunchKernelGGL((logprob_rows_kernel<DT, false>), dim3(grid), dim3(kFwdThreads), 0, s, z, T, V, ld, chosen,
-                           logp, lse, chosen_logit, ent, vec);
+                           logp, lse, chosen_logit, ent);
 }
 
 hipError_t launch_token_logprobs(const void *z, int dt, int64_t T, int64_t V, int64_t ld, const int32_t *chosen,
                                  float *logp, float *lse, void *chosen_logit, float *ent, hipStream_t s)
 {
     if (T == 0) return hipSuccess;
-    const int64_t esz = dt == A3PO_F32 ? 4 : 2;
-    const int vec = aligned16(z) && (ld * esz) % 16 == 0;
     const int64_t want = (int64_t)device_cu_count() * 8;
     const unsigned grid = (unsigned)(T < want ? T : want);
-    if (dt == A3PO_F32) launch_logprob_rows_t<F32>(grid, s, z, T, V, ld, chosen, logp, lse, chosen_logit, ent, vec);
-    else launch_logprob_rows_t<Bf16>(grid, s, z, T, V, ld, chosen, logp, lse, chosen_logit, ent, vec);
+    if (dt == A3PO_F32) launch_logprob_rows_t<F32>(grid, s, z, T, V, ld, chosen, logp, lse, chosen_logit, ent);
+    else launch_logprob_rows_t<Bf16>(grid, s, z, T, V, ld, chosen, logp, lse, chosen_logit, ent);
     return hipGetLastError();
 }
 

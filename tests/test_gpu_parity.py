@@ -187,8 +187,8 @@ def test_bf16_full_vocabulary_rows_every_element(a3po):
 def test_ragged_vocabularies_and_strides(a3po, dtype, V, pad):
     # covers: single partial sweep, exact sweep multiples, ragged tail vectors, padded strides
     # (padding columns hold a 1e30 sentinel and must be neither read nor written), strides
-    # whose byte size is not a multiple of 16 (element-wise multi-pass kernel), and rows too long for the
-    # registers (100,000 float32 / 170,000 bfloat16: registers plus LDS; 100,001: element-wise).
+    # whose byte size is not a multiple of 16 (rows cut at the lines of the gradient), and rows too long for the
+    # registers (100,000 and 100,001 float32 / 170,000 bfloat16: registers plus LDS).
     w = synth.WORKLOADS["tiny"].scaled(V=V, dtype=dtype, S=4, L=6, len_lo=3, len_hi=6, sigma=3.0,
                                        boost=6.0, boost_prob=0.5, noise_std=0.15, stale_max=6)
     c = make_case(w, ld=V + pad)
@@ -196,6 +196,46 @@ def test_ragged_vocabularies_and_strides(a3po, dtype, V, pad):
     check_against_oracle(a3po, c, out)
     if pad:
         assert (out["dlogits"][:, V:].float() == 7.0).all(), "padding columns were written"
+
+
+@pytest.mark.parametrize("dtype,V,pad,z_off,dz_off", [
+    ("bf16", 40, 1, 0, 0), ("bf16", 71, 0, 3, 3),       # rows shorter than a line; no whole vector in some
+    ("bf16", 8254, 1, 0, 0), ("bf16", 8255, 0, 5, 5),   # one full sweep: surplus vectors in the tail; a second sweep
+    ("f32", 4126, 1, 2, 2), ("f32", 4127, 0, 0, 0),     # the same in fp32
+    ("bf16", 50001, 0, 1, 0), ("f32", 32001, 0, 0, 3),  # logits aligned differently from the gradient
+    ("bf16", 131135, 0, 0, 0), ("bf16", 151937, 3, 7, 7),  # the entropy's LDS stash; the longest register rows
+    ("bf16", 163902, 1, 0, 0), ("bf16", 163903, 0, 1, 1),  # last length of the registers, first beyond
+    ("f32", 100001, 0, 1, 1), ("f32", 100001, 0, 1, 0),    # beyond the registers, alike and not (element-wise)
+])
+@pytest.mark.parametrize("entropy", [False, True])
+def test_rows_at_any_address(a3po, dtype, V, pad, z_off, dz_off, entropy):
+    # rows that start anywhere inside a line, logits and gradient at their own element offsets: every element against
+    # the oracle, and nothing beside the rows is written
+    w = synth.WORKLOADS["tiny"].scaled(V=V, dtype=dtype, S=4, L=10, len_lo=6, len_hi=10, sigma=3.0,
+                                       boost=6.0, boost_prob=0.5, noise_std=0.15, stale_max=6)
+    c = make_case(w, ld=V + pad)
+    T, ld = c["T"], V + pad
+    z_d = dev_logits(c["z"])
+
+    def place(off):
+        flat = torch.full((T * ld + off + 64,), 7.0, dtype=z_d.dtype, device="cuda")
+        return flat, flat[off:off + T * ld].view(T, ld)
+
+    _, z_at = place(z_off)
+    z_at.copy_(z_d)
+    flat, dz_at = place(dz_off)
+    dev = lambda k: torch.from_numpy(c[k]).cuda()
+    out = a3po.loss_fwd_bwd(z_at, dev("chosen"), dev("lb"), dev("versions"), CUR, dev("adv"), dev("mask"), w.clip_eps,
+                            V=V, dlogits=dz_at, want_entropy=entropy)
+    torch.cuda.synchronize()
+    check_against_oracle(a3po, c, out)
+    if pad:
+        assert (dz_at[:, V:].float() == 7.0).all(), "padding columns were written"
+    assert (flat[:dz_off].float() == 7.0).all() and (flat[dz_off + T * ld:].float() == 7.0).all()
+    if entropy:
+        ent = np.where(c["mask"] != 0, oracle.entropy(c["z"], V=V), 0.0)
+        err = np.abs(out["entropy"].cpu().numpy().astype(np.float64) - ent)
+        assert (err <= 1e-5 * np.abs(ent) + 2e-5 * (1 + np.abs(c["fwd"]["lse"]))).all()
 
 
 @pytest.mark.parametrize("dtype,V,pad", [
