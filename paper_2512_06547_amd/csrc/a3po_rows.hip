@@ -22,14 +22,16 @@ constexpr int kMaxVec = 20;  // 16-byte vectors per thread the fused kernel can 
 // ---------------------------------------------------------------------------------------
 // Fused forward+backward, register-resident rows.
 //
-// NSWEEP is the exact number of 1024-lane sweeps of 16-byte vectors a row needs:
-// (NSWEEP-1)*1024 < ceil(V / elements-per-vector) <= NSWEEP*1024.  Sweeps 0..NSWEEP-2 are
-// full and carry no predicate at all; only the last sweep is predicated (and holds the
+// A workgroup of NT threads (1024; 512 or 256 for short rows, see plan_rows) owns a row.  NSWEEP is the number of
+// NT-lane sweeps of 16-byte vectors a row needs: (NSWEEP-1)*NT < ceil(V / elements-per-vector) <= NSWEEP*NT.
+// Sweeps 0..NSWEEP-2 are full and carry no predicate at all; only the last sweep is predicated (and holds the
 // ragged tail when V is not a multiple of the vector width).
-// Requires: 16-byte aligned bases, (ld * element size) % 16 == 0, blockDim.x == 1024.
-// Rows are claimed from a device-wide queue (one atomic add per row): workgroup b starts with
-// row b and then takes whatever row is next, so masked rows (cheap) and slower compute units
-// balance out by themselves.  The queue counter is zeroed by the prep kernel.
+// Requires (EDGE aside): 16-byte aligned bases, (ld * element size) % 16 == 0.
+// Rows are claimed from a device-wide queue (one atomic add per item): workgroup b starts with
+// item b and then takes whatever item is next, so masked rows (cheap) and slower compute units
+// balance out by themselves.  The queue counter is zeroed by the prep kernel.  With 1024 threads an item is one row.
+// Claims on the one counter are served about every 13 ns whatever the number of workgroups (measured: 8,192 rows of
+// 2,048 bfloat16 took 115 us, 32,768 rows 397 us), so short rows are claimed `batch` at a time (now 35 and 90 us).
 // Loads and stores of logit rows are non-temporal: every byte is touched exactly once.
 constexpr uint32_t kSweepBytes = kRowThreads * 16;
 
@@ -120,24 +122,35 @@ __device__ __forceinline__ uint4 row_load(const char *p)
 // ENT variant parks the first STASH vectors it consumes in LDS between the forward and the backward
 // pass and issues the last STASH loads of the row only then, into the registers just freed
 // (a load pipeline of depth NSWEEP - STASH instead of NSWEEP).
-// Rows of at most kTwoRowSweeps sweeps (64 KiB) run as two workgroups per compute unit (64 registers each): one
-// such row is too short a burst to keep the memory system busy between a workgroup's barrier, queue claim and
-// per-token arithmetic (+12 % at 32,000 bfloat16 columns, +26 % at 16,000; with longer rows two workgroups are slower).
-constexpr int kTwoRowSweeps = 4;
-template <typename DT, int NSWEEP, bool ENT, bool EDGE>
-__global__ __launch_bounds__(kRowThreads, NSWEEP <= kTwoRowSweeps ? 8 : 4) void loss_rows_kernel(
+//
+// Workgroups per compute unit.  Rows of 4 sweeps of 1024 threads (64 KiB) run as two workgroups per compute unit (64
+// registers each): one such row is too short a burst to keep the memory system busy between a workgroup's barrier,
+// queue claim and per-token arithmetic (+12 % at 32,000 bfloat16 columns; with longer rows two workgroups are slower).
+// Smaller workgroups take as many wavefronts per SIMD as the registers of a row and its temporaries leave room for.
+constexpr int row_waves_per_simd(int threads, int sweeps, bool ent)
+{
+    if (threads == kRowThreads) return sweeps <= 4 ? 8 : 4;
+    const int regs = (4 * sweeps + (ent ? 64 : 48) + 7) / 8 * 8;
+    const int waves = 512 / regs < 8 ? 512 / regs : 8, per_group = threads / 256;
+    return waves < per_group ? per_group : waves / per_group * per_group;
+}
+template <typename DT, int NT, int NSWEEP, bool ENT, bool EDGE>
+__global__ __launch_bounds__(NT, row_waves_per_simd(NT, NSWEEP, ENT)) void loss_rows_kernel(
     const void *z, void *dz, int64_t T, int64_t V, int64_t ld, const TokenRecord *__restrict__ records,
     int32_t current_version, float clip_eps, int prox_mode, const WsHeader *__restrict__ hdr,
-    unsigned int *row_queue, RowOutputs out)
+    unsigned int *row_queue, int batch, RowOutputs out)
 {
     constexpr int EPV = DT::kPerVec;
     constexpr int LAST = NSWEEP - 1;
-    constexpr int STASH = (ENT && NSWEEP >= 16) ? 2 : 0;  // consumed first: v[LAST], v[0]; loaded late: v[LAST-2], v[LAST-1]
-    __shared__ float red_m[2][kRowWaves];
-    __shared__ float red_s[2][kRowWaves];
-    __shared__ float ent_part[2][kRowWaves];
+    constexpr int NW = NT / kWave;
+    constexpr bool BATCHED = NT < kRowThreads;  // items of several rows
+    constexpr uint32_t kSweep = NT * 16;  // bytes
+    constexpr int STASH = (ENT && NT == 1024 && NSWEEP >= 16) ? (EDGE ? 4 : 2) : 0;  // consumed first: v[LAST], v[0]; loaded late: v[LAST-2], v[LAST-1]
+    __shared__ float red_m[2][NW];
+    __shared__ float red_s[2][NW];
+    __shared__ float ent_part[2][NW];
     __shared__ unsigned int next_row[2];
-    __shared__ uint4 stash[STASH ? STASH : 1][STASH ? kRowThreads : 1];
+    __shared__ uint4 stash[STASH ? STASH : 1][STASH ? NT : 1];
 
     const int tid = threadIdx.x;
     const int lane = tid & (kWave - 1), wave = tid / kWave;
@@ -145,7 +158,7 @@ __global__ __launch_bounds__(kRowThreads, NSWEEP <= kTwoRowSweeps ? 8 : 4) void 
     const int nfull = (int)(V / EPV);             // complete vectors in a row
     const int rem = EDGE ? 0 : (int)(V % EPV);    // elements in the ragged tail vector (0 = none)
     // this thread's vector of the last sweep, relative to the row's end (EDGE: set per row)
-    const int last_idx = LAST * kRowThreads + tid;
+    const int last_idx = LAST * NT + tid;
     bool last_full = last_idx < nfull;                     // a complete vector
     const bool last_tail = rem != 0 && last_idx == nfull;  // the ragged tail vector
     bool last_any = last_full || last_tail;
@@ -160,7 +173,7 @@ __global__ __launch_bounds__(kRowThreads, NSWEEP <= kTwoRowSweeps ? 8 : 4) void 
         if (pend_row >= 0 && tid == 0) {
             float sum = 0.0f;
 #pragma unroll
-            for (int w = 0; w < kRowWaves; ++w) sum += ent_part[pend_par][w];
+            for (int w = 0; w < NW; ++w) sum += ent_part[pend_par][w];
             out.ent[pend_row] = pend_lse - sum;
         }
         pend_row = -1;
@@ -168,7 +181,9 @@ __global__ __launch_bounds__(kRowThreads, NSWEEP <= kTwoRowSweeps ? 8 : 4) void 
 
     // Per-token inputs are uniform over the workgroup and come from the packed records the
     // prep kernel wrote (one 16-byte scalar load per row, fetched as soon as the row is known).
-    int64_t row = blockIdx.x;
+    int64_t row = (int64_t)blockIdx.x * (BATCHED ? batch : 1);
+    int64_t item_end = row + batch;  // rows [row, item_end) are this workgroup's already
+    const bool queued = (int64_t)gridDim.x * batch < T;  // else there is nothing left to claim
     TokenRecord nxt = {-1, 0, 0.0f, 0.0f};
     if (row < T) nxt = records[row];
 
@@ -178,14 +193,16 @@ __global__ __launch_bounds__(kRowThreads, NSWEEP <= kTwoRowSweeps ? 8 : 4) void 
         const bool live = y >= 0;  // the prep kernel stores y = -1 for masked or invalid tokens
         // thread 0 claims this workgroup's next row; the answer is shared at the row's barrier
         unsigned int claimed = 0;
-        if (tid == 0) claimed = atomicAdd(row_queue, 1u);
+        // (uniform) the last row of an item claims the next item
+        const bool claims = !BATCHED || (queued && row + 1 == item_end);
+        if (claims && tid == 0) claimed = atomicAdd(row_queue, 1u);
         __builtin_amdgcn_sched_barrier(0);
         // (EDGE: these point at the row's first body vector, `head` elements into the row)
         char *out_row = reinterpret_cast<char *>(dz) + (size_t)row * row_bytes;
         const char *in_row = reinterpret_cast<const char *>(z) + (size_t)row * row_bytes;
         EdgeSpan span = {0, 0, 0};
         if constexpr (EDGE) {
-            span = edge_span<DT>(out_row, (int)V, NSWEEP * kRowThreads);
+            span = edge_span<DT>(out_row, (int)V, NSWEEP * NT);
             out_row += span.head * DT::kBytes;
             in_row += span.head * DT::kBytes;
             last_full = last_any = last_idx < span.nbody;
@@ -207,11 +224,11 @@ __global__ __launch_bounds__(kRowThreads, NSWEEP <= kTwoRowSweeps ? 8 : 4) void 
                 if (has_edge) edge_bits = load_raw<DT>(in_row, edge_at());
             __builtin_amdgcn_sched_barrier(0);
             v[LAST] = neg_inf_vec<DT>();
-            if (last_any) v[LAST] = row_load<EDGE>(in_row + (size_t)LAST * kSweepBytes + voff);
+            if (last_any) v[LAST] = row_load<EDGE>(in_row + (size_t)LAST * kSweep + voff);
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
             for (int k = 0; k < LAST - STASH; ++k) {
-                v[k] = row_load<EDGE>(in_row + (size_t)k * kSweepBytes + voff);
+                v[k] = row_load<EDGE>(in_row + (size_t)k * kSweep + voff);
                 __builtin_amdgcn_sched_barrier(0);
             }
 
@@ -224,7 +241,7 @@ __global__ __launch_bounds__(kRowThreads, NSWEEP <= kTwoRowSweeps ? 8 : 4) void 
                 fold<EPV>(acc, f);
                 if constexpr (STASH > 0) {
                     stash[0][tid] = v[LAST];
-                    v[LAST - STASH] = row_load<EDGE>(in_row + (size_t)(LAST - STASH) * kSweepBytes + voff);
+                    v[LAST - STASH] = row_load<EDGE>(in_row + (size_t)(LAST - STASH) * kSweep + voff);
                 }
             }
             if (tid == 0) next_row[parity] = claimed;  // the claim was issued before the row's loads
@@ -238,7 +255,7 @@ __global__ __launch_bounds__(kRowThreads, NSWEEP <= kTwoRowSweeps ? 8 : 4) void 
                     if (k + 1 < STASH) {
                         stash[k + 1][tid] = v[k];
                         v[LAST - STASH + k + 1] =
-                            row_load<EDGE>(in_row + (size_t)(LAST - STASH + k + 1) * kSweepBytes + voff);
+                            row_load<EDGE>(in_row + (size_t)(LAST - STASH + k + 1) * kSweep + voff);
                     }
                 }
                 __builtin_amdgcn_sched_barrier(0);
@@ -258,8 +275,9 @@ __global__ __launch_bounds__(kRowThreads, NSWEEP <= kTwoRowSweeps ? 8 : 4) void 
             __syncthreads();
             MaxSum tot = {red_m[parity][0], red_s[parity][0]};
 #pragma unroll
-            for (int w = 1; w < kRowWaves; ++w) tot = combine(tot, MaxSum{red_m[parity][w], red_s[parity][w]});
-            const int64_t upcoming = (int64_t)gridDim.x + (int64_t)__builtin_amdgcn_readfirstlane(next_row[parity]);
+            for (int w = 1; w < NW; ++w) tot = combine(tot, MaxSum{red_m[parity][w], red_s[parity][w]});
+            int64_t upcoming = row + 1 < item_end ? row + 1 : T;
+            if (claims) upcoming = ((int64_t)gridDim.x + (int64_t)__builtin_amdgcn_readfirstlane(next_row[parity])) * (BATCHED ? batch : 1);
             parity ^= 1;
             if (upcoming < T) nxt = records[upcoming];  // scalar load, lands during the backward pass
             if constexpr (ENT) finish_pending_entropy();
@@ -292,20 +310,23 @@ __global__ __launch_bounds__(kRowThreads, NSWEEP <= kTwoRowSweeps ? 8 : 4) void 
                 out.flags[row] = 0;
             }
             __syncthreads();
-            next = (int64_t)gridDim.x + (int64_t)__builtin_amdgcn_readfirstlane(next_row[parity]);
+            next = row + 1 < item_end ? row + 1 : T;
+            if (claims) next = ((int64_t)gridDim.x + (int64_t)__builtin_amdgcn_readfirstlane(next_row[parity])) * (BATCHED ? batch : 1);
             parity ^= 1;
             if (next < T) nxt = records[next];
             if constexpr (ENT) finish_pending_entropy();
         }
+
+        if (BATCHED && claims) item_end = next + batch;
 
         const bool want_p = ENT ? live : g != 0.0f;  // the entropy needs every p_j of a counted row
         if (!want_p) {
             // masked, invalid id, clipped, zero advantage or empty batch: the gradient row is zero
             const uint4 zero = make_uint4(0u, 0u, 0u, 0u);
 #pragma unroll
-            for (int k = 0; k < LAST; ++k) stream_store(out_row + (size_t)k * kSweepBytes + voff, zero);
+            for (int k = 0; k < LAST; ++k) stream_store(out_row + (size_t)k * kSweep + voff, zero);
             if (last_full) {
-                stream_store(out_row + (size_t)LAST * kSweepBytes + voff, zero);
+                stream_store(out_row + (size_t)LAST * kSweep + voff, zero);
             } else if (last_tail) {
                 for (int e = 0; e < rem; ++e) store_elem<DT>(out_row, (int64_t)nfull * EPV + e, 0.0f);
             }
@@ -325,7 +346,7 @@ __global__ __launch_bounds__(kRowThreads, NSWEEP <= kTwoRowSweeps ? 8 : 4) void 
             float f[EPV];
             unpack<DT>(v[k], f);
             backward_vec<EPV, ENT>(f, neg_g, row_max, nls2, pz);
-            stream_store(out_row + (size_t)k * kSweepBytes + voff, pack<DT>(f));
+            stream_store(out_row + (size_t)k * kSweep + voff, pack<DT>(f));
             if constexpr (ENT) __builtin_amdgcn_sched_barrier(0);  // one vector's temporaries at a time
         }
         if constexpr (STASH > 1) {  // the vectors parked in LDS come last, into registers that are free by now
@@ -334,7 +355,7 @@ __global__ __launch_bounds__(kRowThreads, NSWEEP <= kTwoRowSweeps ? 8 : 4) void 
                 float f[EPV];
                 unpack<DT>(stash[k + 1][tid], f);
                 backward_vec<EPV, ENT>(f, neg_g, row_max, nls2, pz);
-                stream_store(out_row + (size_t)k * kSweepBytes + voff, pack<DT>(f));
+                stream_store(out_row + (size_t)k * kSweep + voff, pack<DT>(f));
             }
         }
         if (last_any) {
@@ -343,7 +364,7 @@ __global__ __launch_bounds__(kRowThreads, NSWEEP <= kTwoRowSweeps ? 8 : 4) void 
             else unpack<DT>(v[LAST], f);
             backward_vec<EPV, ENT>(f, neg_g, row_max, nls2, pz);
             if (last_full) {
-                stream_store(out_row + (size_t)LAST * kSweepBytes + voff, pack<DT>(f));
+                stream_store(out_row + (size_t)LAST * kSweep + voff, pack<DT>(f));
             } else {
 #pragma unroll
                 for (int e = 0; e < EPV; ++e)
@@ -362,7 +383,7 @@ __global__ __launch_bounds__(kRowThreads, NSWEEP <= kTwoRowSweeps ? 8 : 4) void 
                 store_elem<DT>(out_row, edge_at(), edge_at() == yb ? f[0] + g : f[0]);
             }
         }
-        if (g != 0.0f && y_in_body && tid == ((yb / EPV) & (kRowThreads - 1)))
+        if (g != 0.0f && y_in_body && tid == ((yb / EPV) & (NT - 1)))
             store_elem<DT>(out_row, yb, neg_g * exp2_hw(fmaf(zy - row_max, kLog2e, nls2)) + g);
         if constexpr (ENT) {
 #pragma unroll
@@ -851,27 +872,36 @@ static bool aligned16(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 
 struct RowPlan {
     enum Kind { kRegisters, kLong, kElements } kind;
     bool edge;   // cut rows at the lines of the gradient (see EdgeSpan)
-    int sweeps;  // kRegisters: template argument NSWEEP
+    int threads, sweeps;  // kRegisters: template arguments NT and NSWEEP
 };
 
-// Rows whose base and stride are multiples of 16 bytes are taken whole; others are cut at lines.  A row whose body
-// needs more than kMaxVec sweeps goes through the long kernel, whose direct loads into LDS want 16-byte addresses:
-// logits and gradient must then have the same alignment within 16 bytes.  What is left (a long row of which they do
-// not) is taken element by element.
+// Rows whose bases are multiples of 16 bytes and whose stride is a multiple of 128 are taken whole; others are cut at
+// the lines of the gradient.  (A stride of whole vectors could be taken whole too, but the cut makes every store cover
+// whole lines: 8,192 rows of bfloat16 x 32,008 / 100,360 / 151,944 210 / 621 / 988 us whole, 199 / 564 / 875 us cut.)
+//
+// Threads per row.  Short rows need more of them in flight per compute unit than two workgroups of 1024: 256 threads
+// up to 16 KiB, 512 up to 48 KiB (8,192 rows of bfloat16 x 8,192 / 16,000 / 24,000: 119 / 140 / 166 us with 1024
+// threads, 66 / 112 / 159 us so); at 64 KiB (32,000 columns) 512 threads and 1024 are alike (203 / 200 us).  With the
+// entropy, whose temporaries do not fit beside a row in the 64 registers of two workgroups of 1024, 512 threads are
+// better up to 104 KiB (32,000 columns 250 -> 197 us, 50,264: 336 -> 308) and equal at 128 KiB.
+//
+// A row whose body needs more than kMaxVec sweeps goes through the long kernel, whose direct loads into LDS want
+// 16-byte addresses: logits and gradient must then have the same alignment within 16 bytes.  What is left (a long row
+// of which they do not) is taken element by element.
 template <typename DT>
 static RowPlan plan_rows(const LossArgs &a)
 {
     constexpr int64_t EPV = DT::kPerVec;
-    const bool whole = aligned16(a.z) && aligned16(a.dz) && (a.ld * DT::kBytes) % 16 == 0;
-    if (whole) {
-        const int64_t sweeps = ((a.V + EPV - 1) / EPV + kRowThreads - 1) / kRowThreads;
-        return sweeps <= kMaxVec ? RowPlan{RowPlan::kRegisters, false, (int)sweeps} : RowPlan{RowPlan::kLong, false, 0};
-    }
+    const bool edge = !(aligned16(a.z) && aligned16(a.dz) && (a.ld * DT::kBytes) % kLineBytes == 0);
     const int64_t head_max = kLineBytes / DT::kBytes - 1;
-    const int64_t sweeps = (a.V > head_max ? a.V - head_max : 0) / EPV / kRowThreads + 1;
-    if (sweeps <= kMaxVec) return {RowPlan::kRegisters, true, (int)sweeps};
+    const int64_t least = (a.V > head_max ? a.V - head_max : 0) / EPV;  // body vectors of the row with the fewest
+    const int64_t nvec = (a.V + EPV - 1) / EPV;
+    auto sweeps = [&](int64_t nt) { return edge ? least / nt + 1 : (nvec + nt - 1) / nt; };
+    if (sweeps(256) <= 4) return {RowPlan::kRegisters, edge, 256, (int)sweeps(256)};
+    if (sweeps(512) <= (a.ent_out ? 13 : 6)) return {RowPlan::kRegisters, edge, 512, (int)sweeps(512)};
+    if (sweeps(kRowThreads) <= kMaxVec) return {RowPlan::kRegisters, edge, kRowThreads, (int)sweeps(kRowThreads)};
     const bool same = ((reinterpret_cast<uintptr_t>(a.z) ^ reinterpret_cast<uintptr_t>(a.dz)) & 15u) == 0;
-    return {same ? RowPlan::kLong : RowPlan::kElements, true, 0};
+    return {same ? RowPlan::kLong : RowPlan::kElements, edge, kRowThreads, 0};
 }
 
 template <typename DT, bool EDGE>
@@ -889,26 +919,51 @@ static hipError_t launch_long_rows(const LossArgs &a, unsigned grid, hipStream_t
     return hipGetLastError();
 }
 
-template <typename DT, bool ENT, bool EDGE>
-static hipError_t launch_register_rows(const LossArgs &a, int sweeps, unsigned grid, hipStream_t s)
+template <typename DT, int NT, int NSWEEP, bool ENT, bool EDGE>
+static hipError_t launch_register_rows(const LossArgs &a, int cus, hipStream_t s)
 {
     const RowOutputs out = {a.logp_out, a.prox_out, a.ws_obj, a.ws_iw, a.ent_out, a.ws_flags};
-    const WsHeader *hdr = reinterpret_cast<const WsHeader *>(a.ws_header);
-    unsigned int *queue = row_queue_of(a.ws_header);
-    switch (sweeps) {
-#define A3PO_SWEEP_CASE(N) \
-    case N: \
-        hipLaunchKernelGGL((loss_rows_kernel<DT, N, ENT, EDGE>), dim3(grid), dim3(kRowThreads), 0, s, a.z, a.dz, a.T, a.V, \
-                           a.ld, a.ws_records, a.current_version, a.clip_eps, a.prox_mode, hdr, queue, out); \
-        break;
-        A3PO_SWEEP_CASE(1) A3PO_SWEEP_CASE(2) A3PO_SWEEP_CASE(3) A3PO_SWEEP_CASE(4) A3PO_SWEEP_CASE(5)
-        A3PO_SWEEP_CASE(6) A3PO_SWEEP_CASE(7) A3PO_SWEEP_CASE(8) A3PO_SWEEP_CASE(9) A3PO_SWEEP_CASE(10)
-        A3PO_SWEEP_CASE(11) A3PO_SWEEP_CASE(12) A3PO_SWEEP_CASE(13) A3PO_SWEEP_CASE(14) A3PO_SWEEP_CASE(15)
-        A3PO_SWEEP_CASE(16) A3PO_SWEEP_CASE(17) A3PO_SWEEP_CASE(18) A3PO_SWEEP_CASE(19) A3PO_SWEEP_CASE(20)
-#undef A3PO_SWEEP_CASE
-        default: return hipErrorInvalidValue;
-    }
+    const int64_t resident = (int64_t)cus * (row_waves_per_simd(NT, NSWEEP, ENT) * 4 * kWave / NT);
+    // rows per claim: items of at least 48 KiB (larger ones even out the tail less: 64 KiB rows two at a time 5 %
+    // slower), but no more than an equal share of the rows, which then needs no claim at all
+    constexpr int64_t kItemBytes = 48 * 1024;
+    const int64_t row_bytes = a.V * DT::kBytes, share = (a.T + resident - 1) / resident;
+    int64_t batch = NT < kRowThreads ? (kItemBytes + row_bytes - 1) / row_bytes : 1;
+    if (batch > share) batch = share;
+    const int64_t items = (a.T + batch - 1) / batch;
+    const unsigned grid = (unsigned)(items < resident ? items : resident);
+    hipLaunchKernelGGL((loss_rows_kernel<DT, NT, NSWEEP, ENT, EDGE>), dim3(grid), dim3(NT), 0, s, a.z, a.dz, a.T, a.V, a.ld,
+                       a.ws_records, a.current_version, a.clip_eps, a.prox_mode,
+                       reinterpret_cast<const WsHeader *>(a.ws_header), row_queue_of(a.ws_header), (int)batch, out);
     return hipGetLastError();
+}
+
+template <typename DT, bool ENT, bool EDGE>
+static hipError_t dispatch_register_rows(const LossArgs &a, const RowPlan &plan, int cus, hipStream_t s)
+{
+    // (the instances that plan_rows can ask for; with the entropy, 512 threads take the rows of 7 to 13 of their sweeps
+    // that 1024 threads take in 4 to 6 of theirs without)
+    constexpr bool E = ENT;
+    switch (plan.threads * 100 + plan.sweeps) {
+#define A3PO_ROWS(NT, N) \
+    case NT * 100 + N: return launch_register_rows<DT, NT, N, ENT, EDGE>(a, cus, s);
+#define A3PO_ROWS_IF(COND, NT, N) \
+    case NT * 100 + N: \
+        if constexpr (COND) return launch_register_rows<DT, NT, N, ENT, EDGE>(a, cus, s); \
+        break;
+        A3PO_ROWS(256, 1) A3PO_ROWS(256, 2) A3PO_ROWS(256, 3) A3PO_ROWS(256, 4)
+        A3PO_ROWS(512, 3) A3PO_ROWS(512, 4) A3PO_ROWS(512, 5) A3PO_ROWS(512, 6)
+        A3PO_ROWS_IF(E, 512, 7) A3PO_ROWS_IF(E, 512, 8) A3PO_ROWS_IF(E, 512, 9) A3PO_ROWS_IF(E, 512, 10)
+        A3PO_ROWS_IF(E, 512, 11) A3PO_ROWS_IF(E, 512, 12) A3PO_ROWS_IF(E, 512, 13)
+        A3PO_ROWS_IF(!E, 1024, 4) A3PO_ROWS_IF(!E, 1024, 5) A3PO_ROWS_IF(!E, 1024, 6)
+        A3PO_ROWS(1024, 7) A3PO_ROWS(1024, 8) A3PO_ROWS(1024, 9) A3PO_ROWS(1024, 10) A3PO_ROWS(1024, 11)
+        A3PO_ROWS(1024, 12) A3PO_ROWS(1024, 13) A3PO_ROWS(1024, 14) A3PO_ROWS(1024, 15) A3PO_ROWS(1024, 16)
+        A3PO_ROWS(1024, 17) A3PO_ROWS(1024, 18) A3PO_ROWS(1024, 19) A3PO_ROWS(1024, 20)
+#undef A3PO_ROWS_IF
+#undef A3PO_ROWS
+        default: break;
+    }
+    return hipErrorInvalidValue;
 }
 
 template <typename DT>
@@ -916,20 +971,21 @@ static hipError_t launch_loss_rows_t(const LossArgs &a, hipStream_t s)
 {
     const int cus = device_cu_count();
     const RowPlan plan = plan_rows<DT>(a);
-    const int64_t resident = (int64_t)cus * (plan.kind == RowPlan::kElements ||
-                                             (plan.kind == RowPlan::kRegisters && plan.sweeps <= kTwoRowSweeps) ? 2 : 1);
-    const unsigned grid = (unsigned)(a.T < resident ? a.T : resident);
     if (plan.kind == RowPlan::kElements) {
-        hipLaunchKernelGGL((loss_rows_generic_kernel<DT>), dim3(grid), dim3(kRowThreads), 0, s, a);
+        const int64_t resident = (int64_t)cus * 2;
+        hipLaunchKernelGGL((loss_rows_generic_kernel<DT>), dim3((unsigned)(a.T < resident ? a.T : resident)),
+                           dim3(kRowThreads), 0, s, a);
         return hipGetLastError();
     }
-    if (plan.kind == RowPlan::kLong)
+    if (plan.kind == RowPlan::kLong) {
+        const unsigned grid = (unsigned)(a.T < cus ? a.T : cus);
         return plan.edge ? launch_long_rows<DT, true>(a, grid, s) : launch_long_rows<DT, false>(a, grid, s);
+    }
     if (a.ent_out)
-        return plan.edge ? launch_register_rows<DT, true, true>(a, plan.sweeps, grid, s)
-                         : launch_register_rows<DT, true, false>(a, plan.sweeps, grid, s);
-    return plan.edge ? launch_register_rows<DT, false, true>(a, plan.sweeps, grid, s)
-                     : launch_register_rows<DT, false, false>(a, plan.sweeps, grid, s);
+        return plan.edge ? dispatch_register_rows<DT, true, true>(a, plan, cus, s)
+                         : dispatch_register_rows<DT, true, false>(a, plan, cus, s);
+    return plan.edge ? dispatch_register_rows<DT, false, true>(a, plan, cus, s)
+                     : dispatch_register_rows<DT, false, false>(a, plan, cus, s);
 }
 
 hipError_t launch_loss_rows(const LossArgs &a, hipStream_t s)

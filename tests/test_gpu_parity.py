@@ -277,6 +277,24 @@ def test_many_short_rows(a3po, dtype, V, L):
     assert 0 < st["n_tokens"] < c["T"]
 
 
+@pytest.mark.parametrize("dtype,V,L,entropy", [
+    ("bf16", 304, 12500, False), ("f32", 301, 12500, True),    # tens of rows per claim
+    ("bf16", 8192, 601, False), ("bf16", 8193, 601, True),     # 256 / 512 threads per row; odd remainder of an item
+    ("f32", 12288, 300, False), ("f32", 12292, 300, False),    # 512 / 1024 threads
+    ("bf16", 53248, 40, True), ("bf16", 53249, 40, True),      # the same with the entropy
+])
+def test_rows_claimed_in_items(a3po, dtype, V, L, entropy):
+    # short rows are claimed several at a time; the last item of the queue holds fewer
+    w = synth.WORKLOADS["tiny"].scaled(V=V, dtype=dtype, S=8, L=L, G=8, len_lo=L // 4, len_hi=L, sigma=3.0, boost=6.0,
+                                       boost_prob=0.5, noise_std=0.15, stale_max=6)
+    c = make_case(w)
+    dev = lambda k: torch.from_numpy(c[k]).cuda()
+    out = a3po.loss_fwd_bwd(dev_logits(c["z"]), dev("chosen"), dev("lb"), dev("versions"), CUR, dev("adv"), dev("mask"),
+                            w.clip_eps, V=V, want_entropy=entropy)
+    torch.cuda.synchronize()
+    check_against_oracle(a3po, c, out)
+
+
 @pytest.mark.parametrize("dtype,V", [("f32", 32000), ("bf16", 151936), ("bf16", 4099), ("f32", 1001)])
 def test_in_place_gradient(a3po, dtype, V):
     w = synth.WORKLOADS["tiny"].scaled(V=V, dtype=dtype, S=4, L=8, len_lo=4, len_hi=8, noise_std=0.1)
