@@ -31,9 +31,9 @@
 // next tile's first stages, so a tile's epilogue overlaps with their arrival.
 //
 // Tile order.  One persistent workgroup per compute unit; the workgroups of an XCD (dispatch order deals
-// workgroups round-robin over the XCDs) form a block of ml_count x 4 tiles that share ml_count tiles of A and 4
-// tiles of B through that XCD's L2.  The tile grid is cut into such blocks ("pairs" of a 4-tile column group and an
-// ml_count-tile row round); pair p = group * rounds + round, and each XCD takes a contiguous range of pairs, i.e.
+// workgroups round-robin over the XCDs) form a block of ml x ncol tiles (8 x 4 in the usual case, GemmShape) that
+// share ml tiles of A and ncol tiles of B through that XCD's L2.  The tile grid is cut into such blocks ("pairs" of a
+// column group and a row round); pair p = group * rounds + round, and each XCD takes a contiguous range of pairs, i.e.
 // it sweeps down the rows of one column group before it moves to the next.  With kEpiLse* a workgroup therefore
 // keeps its running (max, sum) in registers over a whole sweep and writes one partial per column per sweep.
 //
@@ -48,10 +48,8 @@
 
 namespace a3po {
 
-constexpr int kGemmTile = 256;  // tile edge, both sides
 constexpr int kGemmThreads = 512;
 constexpr int kGemmWaves = kGemmThreads / kWave;
-constexpr int kGemmColTiles = 4;  // tiles of B (columns) side by side in an XCD's block
 
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 typedef float f32x4_t __attribute__((ext_vector_type(4)));
@@ -249,16 +247,21 @@ __device__ __forceinline__ void store_tile_wide(const f32x4_t (&acc)[8][4], void
 // the ring depth (all LDS addresses are constants) and the refill cursor moves once per kDmaStages stages.
 // Otherwise the loop is unrolled by two (the column fragments alternate; the number of stages is even) and slot
 // and cursor are tracked per stage.
+//
+// kEpiSplitBf16 (QUAD only).  The work items are slices of tiles: item u of slices * tiles is slice u / tiles of a tile,
+// tiles taken in super-rows of 8 tile rows (column by column inside), and round j of the grid deals each XCD 32
+// consecutive items, which share their operand tiles as a block of 8 x 4 does.  With one slice the launch is an
+// ordinary product in the order of the other epilogues.
 template <int EPI, bool QUAD>
 __global__ __launch_bounds__(kGemmThreads) void gemm_nt_kernel(const GemmArgs g)
 {
     extern __shared__ __align__(16) char lds[];
-    constexpr bool LSE = EPI == kEpiLse || EPI == kEpiLseStore;
+    constexpr bool LSE = EPI == kEpiLse || EPI == kEpiLseStore, SPLIT = EPI == kEpiSplitBf16;
+    static_assert(!SPLIT || QUAD, "slices are whole groups of ring stages");
     constexpr int kLoads = 4;  // direct loads per wavefront and stage: two 16-row blocks of A, two of B
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int wm = wave & 1, wn = wave >> 1;  // row half (128 rows), column quarter (64 columns) of the tile
     const int xcd = (int)(blockIdx.x % (unsigned)g.nxcd), slot = (int)(blockIdx.x / (unsigned)g.nxcd);
-    const int nl = slot & (kGemmColTiles - 1), ml = slot / kGemmColTiles;
     int64_t M = g.M, N = g.N, K = g.K;
     if (g.dyn_dim != kDynNone) {  // an extent that only the device knows (uniform: one scalar load)
         const int64_t v = dyn_extent(g.dyn, 0);
@@ -267,22 +270,53 @@ __global__ __launch_bounds__(kGemmThreads) void gemm_nt_kernel(const GemmArgs g)
         else K = (v + 127) / 128 * 128;
         if (v <= 0) return;
     }
-    const int mtiles = (int)((M + kGemmTile - 1) / kGemmTile), ntiles = (int)((N + kGemmTile - 1) / kGemmTile);
-    const int groups = (ntiles + kGemmColTiles - 1) / kGemmColTiles;
-    const int rounds = (mtiles + g.ml_count - 1) / g.ml_count;
-    const int64_t pairs = (int64_t)groups * rounds;
-    const int64_t p_end = (int64_t)(xcd + 1) * pairs / g.nxcd;
+    const GemmShape shp = gemm_shape(M, N, g.nxcd, g.per_xcd);
+    const int rounds = shp.rounds;
+    const int nl = slot % shp.ncol, ml = slot / shp.ncol;  // (ml >= shp.ml: no place in the block)
+    const int64_t tiles = (int64_t)shp.mtiles * shp.ntiles;
+    const int slices = SPLIT ? gemm_slices(tiles, K / (kDmaK * kDmaStages), g.nxcd * g.per_xcd, g.split_max) : 1;
+    const bool flat = SPLIT && slices > 1;
+    const int64_t pairs = (int64_t)shp.groups * rounds;
+    const int64_t p_end = flat ? tiles * slices : ml < shp.ml ? (int64_t)(xcd + 1) * pairs / g.nxcd : 0;
     const int nstages = (int)(K / kDmaK);
     const int wave_s = __builtin_amdgcn_readfirstlane(wave);  // the wavefront number in a scalar register
     const uint32_t lda2 = (uint32_t)g.lda * 2u, ldb2 = (uint32_t)g.ldb * 2u;  // row strides in bytes
 
-    // the first pair >= p in this XCD's range whose tile exists for this workgroup's place in the block (else p_end)
+    // the first work item at or after p for this workgroup (p_end if there is none): the next pair in this XCD's range
+    // whose tile exists for this workgroup's place in the block, or (flat) p itself
     auto next_tile = [&](int64_t p) {
+        if (flat) return p < p_end ? p : p_end;
         for (; p < p_end; ++p) {
             const int grp = (int)(p / rounds), rnd = (int)(p % rounds);
-            if (rnd * g.ml_count + ml < mtiles && grp * kGemmColTiles + nl < ntiles) break;
+            if (rnd * shp.ml + ml < shp.mtiles && grp * shp.ncol + nl < shp.ntiles) break;
         }
         return p;
+    };
+    const int64_t p_step = flat ? (int64_t)g.nxcd * g.per_xcd : 1;
+    // tile coordinates and stage range of a work item
+    struct Item {
+        int mt, nt, slice, s0, s1;
+    };
+    auto locate = [&](int64_t p) {
+        Item it;
+        it.slice = 0;
+        it.s0 = 0;
+        it.s1 = nstages;
+        if (flat) {
+            const int quads = nstages / kDmaStages;
+            it.slice = (int)(p / tiles);
+            it.s0 = (int)((int64_t)it.slice * quads / slices) * kDmaStages;
+            it.s1 = (int)((int64_t)(it.slice + 1) * quads / slices) * kDmaStages;
+            const int64_t tile = p % tiles;
+            const int srow = (int)(tile / (8 * (int64_t)shp.ntiles)), in = (int)(tile % (8 * (int64_t)shp.ntiles));
+            const int h = min(8, shp.mtiles - srow * 8);
+            it.mt = srow * 8 + in % h;
+            it.nt = in / h;
+        } else {
+            it.mt = (int)(p % rounds) * shp.ml + ml;
+            it.nt = (int)(p / rounds) * shp.ncol + nl;
+        }
+        return it;
     };
 
     // direct loads: instruction j of an operand covers tile rows (8 j + wave) 16 .. + 15; lane -> row lane >> 2,
@@ -295,7 +329,7 @@ __global__ __launch_bounds__(kGemmThreads) void gemm_nt_kernel(const GemmArgs g)
     const uint32_t fa_base = (uint32_t)(wm * 8) * 1024u + fr;
     const uint32_t fb_base = kDmaOperandBytes + (uint32_t)(wn * 4) * 1024u + fr;
 
-    int64_t p_cur = next_tile((int64_t)xcd * pairs / g.nxcd);
+    int64_t p_cur = next_tile(flat ? (int64_t)xcd * g.per_xcd + slot : (int64_t)xcd * pairs / g.nxcd);
     if (p_cur >= p_end) return;  // uniform over the workgroup
 
     // The refill cursor names the tile (r_p) and stage (r_k; QUAD: the first of a group of kDmaStages stages) that
@@ -303,11 +337,14 @@ __global__ __launch_bounds__(kGemmThreads) void gemm_nt_kernel(const GemmArgs g)
     // bytes that are already there, which keep the number of loads per stage, and with it the s_waitcnt
     // arithmetic, constant.  Rows past the end of an operand are clamped (computed, never written).
     int64_t r_p = p_cur;
-    int r_k = 0;
+    int r_k = 0, r_end = 0;
     const char *r_a = nullptr, *r_b = nullptr;
     uint32_t aoff[2], boff[2];
     auto set_tile = [&](int64_t p) {
-        const int mt = (int)(p % rounds) * g.ml_count + ml, nt = (int)(p / rounds) * kGemmColTiles + nl;
+        const Item it = locate(p);
+        const int mt = it.mt, nt = it.nt;
+        r_k = it.s0;
+        r_end = it.s1;
         r_a = reinterpret_cast<const char *>(g.A + (int64_t)mt * kGemmTile * g.lda);  // (a 256-row band of panels is as long)
         r_b = reinterpret_cast<const char *>(g.B + (int64_t)nt * kGemmTile * g.ldb);
         const int m_last = (int)(M - 1 - (int64_t)mt * kGemmTile), n_last = (int)(N - 1 - (int64_t)nt * kGemmTile);
@@ -330,13 +367,12 @@ __global__ __launch_bounds__(kGemmThreads) void gemm_nt_kernel(const GemmArgs g)
         else dma16(r_b + (g.b_panel ? poff : koff) + boff[q], dst + kDmaOperandBytes);
     };
     auto advance = [&](int step) {
-        if (r_k + step < nstages) {
+        if (r_k + step < r_end) {
             r_k += step;
         } else {
-            const int64_t np = next_tile(r_p + 1);
+            const int64_t np = next_tile(r_p + p_step);
             if (np < p_end) {
                 r_p = np;
-                r_k = 0;
                 set_tile(np);
             }
         }
@@ -370,9 +406,8 @@ __global__ __launch_bounds__(kGemmThreads) void gemm_nt_kernel(const GemmArgs g)
     }
 
     while (p_cur < p_end) {
-        const int grp = (int)(p_cur / rounds);
-        const int64_t m0 = ((int64_t)(p_cur % rounds) * g.ml_count + ml) * kGemmTile;
-        const int64_t n0 = ((int64_t)grp * kGemmColTiles + nl) * kGemmTile;
+        const Item cur = locate(p_cur);
+        const int64_t m0 = (int64_t)cur.mt * kGemmTile, n0 = (int64_t)cur.nt * kGemmTile;
         f32x4_t acc[8][4];
 #pragma unroll
         for (int a = 0; a < 8; ++a)
@@ -412,7 +447,7 @@ __global__ __launch_bounds__(kGemmThreads) void gemm_nt_kernel(const GemmArgs g)
         if (QUAD) {
             static_assert(kDmaStages == 4, "the unrolled loop names the four ring slots");
 #pragma unroll 1
-            for (int i = 0; i < nstages; i += kDmaStages) {
+            for (int i = cur.s0; i < cur.s1; i += kDmaStages) {
                 stage(0, 0, 0);
                 stage(1, 1, 1);
                 stage(2, 2, 0);
@@ -432,13 +467,21 @@ __global__ __launch_bounds__(kGemmThreads) void gemm_nt_kernel(const GemmArgs g)
         }
 
         // ---- the tile's epilogue, while the next tile's first stages arrive ----
-        const int64_t p_next = next_tile(p_cur + 1);
+        const int64_t p_next = next_tile(p_cur + p_step);
         const bool edge = m0 + kGemmTile > M || n0 + kGemmTile > N;  // uniform
         if constexpr (EPI != kEpiLse) {
             // tiles inside C leave with 16-byte stores (the launcher checks that rows of C start on 16 bytes);
             // only sums into C go element by element, through the memory side's adders
             float *stage_tile = reinterpret_cast<float *>(lds + kDmaRingBytes + kGemmRedBytes + wave_s * kStageBytes);
-            if (EPI == kEpiStoreBf16 && g.transposed != 0) {
+            if (SPLIT && flat) {
+                // this slice's fp32 contribution, added up by gemm_split_reduce_kernel
+                float *part = g.split + (int64_t)cur.slice * M * N;
+                if (edge) store_tile<kEpiAccumF32, true>(acc, part, N, m0, n0, M, N, wm, wn, lane, false);
+                else store_tile_wide<kEpiAccumF32>(acc, part, N, m0, n0, wm, wn, lane, stage_tile);
+            } else if constexpr (SPLIT) {
+                if (edge) store_tile<kEpiStoreBf16, true>(acc, g.C, g.ldc, m0, n0, M, N, wm, wn, lane, false);
+                else store_tile_wide<kEpiStoreBf16>(acc, g.C, g.ldc, m0, n0, wm, wn, lane, stage_tile);
+            } else if (EPI == kEpiStoreBf16 && g.transposed != 0) {
                 uint16_t *ct = reinterpret_cast<uint16_t *>(g.C);
                 if (edge) store_tile_transposed_bf16<true>(acc, ct, g.ldc, m0, n0, M, N, wm, wn, lane);
                 else store_tile_transposed_bf16<false>(acc, ct, g.ldc, m0, n0, M, N, wm, wn, lane);
@@ -467,7 +510,7 @@ __global__ __launch_bounds__(kGemmThreads) void gemm_nt_kernel(const GemmArgs g)
             }
             // end of this column group's sweep: merge the four lane groups, then the two row halves, and write the
             // workgroup's partial of its 256 columns (the reduction has LDS of its own: the ring keeps running)
-            if (p_next >= p_end || (int)(p_next / rounds) != grp) {
+            if (p_next >= p_end || p_next / rounds != p_cur / rounds) {
                 float2 *red = reinterpret_cast<float2 *>(lds + kDmaRingBytes);  // [2][256]
 #pragma unroll
                 for (int b = 0; b < 4; ++b) {
@@ -490,7 +533,7 @@ __global__ __launch_bounds__(kGemmThreads) void gemm_nt_kernel(const GemmArgs g)
                     const float2 q0 = red[tid], q1 = red[kGemmTile + tid];
                     const MaxSum tot = combine(MaxSum{q0.x, q0.y}, MaxSum{q1.x, q1.y});
                     if (n0 + tid < N)
-                        g.partial[(int64_t)(xcd * g.ml_count + ml) * g.partial_stride + n0 + tid] = make_float2(tot.m, tot.s);
+                        g.partial[(int64_t)(xcd * shp.ml + ml) * N + n0 + tid] = make_float2(tot.m, tot.s);
                 }
                 asm volatile("" ::: "memory");
                 __builtin_amdgcn_s_waitcnt(waitcnt_imm(kNoVmWait, 0));  // red is read before anyone writes it again
@@ -505,12 +548,27 @@ __global__ __launch_bounds__(kGemmThreads) void gemm_nt_kernel(const GemmArgs g)
     __builtin_amdgcn_s_barrier();
 }
 
-// Sets every (max, sum) partial to the neutral element, so that slots no workgroup writes (an XCD that did not
-// touch a column group) drop out of the merge.
-__global__ void gemm_partials_init_kernel(float2 *partial, int64_t n)
+// C (bfloat16) = the slices of a kEpiSplitBf16 launch, added in ascending order; nothing when the launch did not slice.
+// Memory bound: 8 elements per thread and step, 2 x 16 bytes per slice.
+__global__ __launch_bounds__(256) void gemm_split_reduce_kernel(const GemmArgs g)
 {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) partial[i] = make_float2(kNegFloor, 0.0f);
+    const int64_t M = g.dyn_dim == kDynM ? dyn_extent(g.dyn, 0) : g.M, N = g.N;
+    if (M <= 0) return;
+    const int64_t tiles = ((M + kGemmTile - 1) / kGemmTile) * ((N + kGemmTile - 1) / kGemmTile);
+    const int slices = gemm_slices(tiles, g.K / (kDmaK * kDmaStages), g.nxcd * g.per_xcd, g.split_max);
+    if (slices <= 1) return;
+    const int64_t step = (int64_t)gridDim.x * blockDim.x * 8;
+    for (int64_t i = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) * 8; i < M * N; i += step) {  // N % 8 == 0
+        float f[8];
+        for (int q = 0; q < slices; ++q) {
+            const float4 *src = reinterpret_cast<const float4 *>(g.split + (int64_t)q * M * N + i);
+            const float4 a = src[0], b = src[1];
+            const float v[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
+#pragma unroll
+            for (int e = 0; e < 8; ++e) f[e] = q ? f[e] + v[e] : v[e];
+        }
+        *reinterpret_cast<uint4 *>(reinterpret_cast<uint16_t *>(g.C) + (i / N) * g.ldc + i % N) = pack<Bf16>(f);
+    }
 }
 
 // ---------------------------------------------------------------------------------------
@@ -523,41 +581,37 @@ GemmGrid gemm_grid()
     int dev = 0, cus = 0;
     if (hipGetDevice(&dev) != hipSuccess ||
         hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0)
-        cus = 256;
+        cus = kGemmMaxBlocks;
+    if (cus > kGemmMaxBlocks) cus = kGemmMaxBlocks;
     GemmGrid gg;
     gg.nxcd = (cus >= 64 && cus % 8 == 0) ? 8 : 1;
-    gg.ml_count = cus / gg.nxcd / kGemmColTiles;
-    if (gg.ml_count < 1) gg.ml_count = 1;
-    if (gg.nxcd * gg.ml_count > kGemmMaxPartialSlots) gg.ml_count = kGemmMaxPartialSlots / gg.nxcd;
-    gg.blocks = gg.nxcd * gg.ml_count * kGemmColTiles;
+    gg.per_xcd = cus / gg.nxcd;
     return gg;
 }
 
-size_t gemm_partial_slots() { const GemmGrid gg = gemm_grid(); return (size_t)gg.nxcd * gg.ml_count; }
-
-template <int EPI>
-static hipError_t launch_gemm_t(GemmArgs g, hipStream_t s)
+template <int EPI, bool QUAD>
+static hipError_t launch_gemm_t(const GemmArgs &g, hipStream_t s)
 {
-    const GemmGrid gg = gemm_grid();
-    g.nxcd = gg.nxcd;
-    g.ml_count = gg.ml_count;
-    const bool quad = g.K % (kDmaK * kDmaStages) == 0;
-    auto *kernel = quad ? gemm_nt_kernel<EPI, true> : gemm_nt_kernel<EPI, false>;
-    static LdsLimitState lds_limit[2];  // (one per variant of this epilogue)
-    const hipError_t attr_err = ensure_lds_limit(reinterpret_cast<const void *>(kernel), kGemmLdsBytes, lds_limit[quad]);
+    static LdsLimitState lds_limit;
+    auto *kernel = gemm_nt_kernel<EPI, QUAD>;
+    const hipError_t attr_err = ensure_lds_limit(reinterpret_cast<const void *>(kernel), kGemmLdsBytes, lds_limit);
     if (attr_err != hipSuccess) return attr_err;
-    if (EPI == kEpiLse || EPI == kEpiLseStore) {
-        const int64_t n = (int64_t)gg.nxcd * gg.ml_count * g.partial_stride;
-        hipLaunchKernelGGL(gemm_partials_init_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, g.partial, n);
-        const hipError_t e = hipGetLastError();
-        if (e != hipSuccess) return e;
-    }
-    hipLaunchKernelGGL(kernel, dim3(gg.blocks), dim3(kGemmThreads), kGemmLdsBytes, s, g);
+    hipLaunchKernelGGL(kernel, dim3(g.nxcd * g.per_xcd), dim3(kGemmThreads), kGemmLdsBytes, s, g);
     return hipGetLastError();
 }
 
-hipError_t launch_gemm_nt(const GemmArgs &g, int epilogue, hipStream_t s)
+template <int EPI>
+static hipError_t launch_gemm_t(const GemmArgs &g, hipStream_t s)
 {
+    return g.K % (kDmaK * kDmaStages) == 0 ? launch_gemm_t<EPI, true>(g, s) : launch_gemm_t<EPI, false>(g, s);
+}
+
+hipError_t launch_gemm_nt(const GemmArgs &args, int epilogue, hipStream_t s)
+{
+    GemmArgs g = args;
+    const GemmGrid gg = gemm_grid();
+    g.nxcd = gg.nxcd;
+    g.per_xcd = gg.per_xcd;
     // what the kernel's 32-bit offsets and its stage arithmetic assume
     if (g.M <= 0 || g.N <= 0 || g.K <= 0 || g.K % 64 != 0 || g.lda % 8 != 0 || g.ldb % 8 != 0 || g.lda < g.K ||
         g.ldb < g.K || g.lda > (1 << 22) || g.ldb > (1 << 22))
@@ -571,6 +625,15 @@ hipError_t launch_gemm_nt(const GemmArgs &g, int epilogue, hipStream_t s)
         case kEpiLseStore: return launch_gemm_t<kEpiLseStore>(g, s);
         case kEpiStoreBf16: return launch_gemm_t<kEpiStoreBf16>(g, s);
         case kEpiAccumF32: return launch_gemm_t<kEpiAccumF32>(g, s);
+        case kEpiSplitBf16: {
+            if (g.K % (kDmaK * kDmaStages) != 0 || g.dyn_dim == kDynK || g.dyn_dim == kDynN || g.N % 8 != 0 ||
+                (g.split_max > 1 && !g.split))
+                return hipErrorInvalidValue;
+            const hipError_t e = launch_gemm_t<kEpiSplitBf16, true>(g, s);
+            if (e != hipSuccess || g.split_max <= 1) return e;
+            hipLaunchKernelGGL(gemm_split_reduce_kernel, dim3(4 * g.nxcd * g.per_xcd), dim3(256), 0, s, g);
+            return hipGetLastError();
+        }
         default: return hipErrorInvalidValue;
     }
 }

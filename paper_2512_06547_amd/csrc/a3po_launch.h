@@ -116,7 +116,8 @@ enum GemmEpilogue {
     kEpiLse = 0,        // running (max, sum) per column n over the rows m -> partial; C untouched
     kEpiLseStore = 1,   // the same, and C (float) = the product
     kEpiStoreBf16 = 2,  // C (bfloat16) = the product
-    kEpiAccumF32 = 3    // C (float) = the product, or += when accumulate is set
+    kEpiAccumF32 = 3,   // C (float) = the product, or += when accumulate is set
+    kEpiSplitBf16 = 4   // C (bfloat16) = the product; few tiles: the contraction is cut into slices (see GemmSplit)
 };
 
 // An extent that is only known on the device when the launch is queued (the number of tokens that enter the loss):
@@ -142,8 +143,10 @@ struct GemmArgs {
     int64_t M, N, K;    // K a multiple of 64 (operands that need it are zero-padded by the caller)
     void *C;            // [M, N] row-major, row stride ldc elements
     int64_t ldc;
-    float2 *partial;    // kEpiLse*: [gemm_partial_slots()][partial_stride] (max, sum) per column, merged by the caller
-    int64_t partial_stride;
+    float2 *partial;    // kEpiLse*: [slots][N] (max, sum) per column (see GemmShape), merged by the caller; room for
+                        // gemm_partial_entries(N) entries
+    float *split;       // kEpiSplitBf16: room for split_max slices of M x N floats (overwritten)
+    int split_max;
     int a_panel, b_panel;  // the operand is stored in panels instead of rows (see panel_offset): lda / ldb is then the
                            // K extent of the buffer (a multiple of 64), rows are padded to a multiple of 256
     int accumulate;     // kEpiAccumF32
@@ -151,8 +154,65 @@ struct GemmArgs {
                         // ldc): a lane's four accumulator values are then 16 contiguous bytes.  Needs M % 4 == 0.
     int dyn_dim;        // GemmDynDim: which of M, N, K is replaced by dyn_extent(dyn, .) on the device (K: rounded up
     DynCount dyn;       // to 128; the host's M, N, K are then upper bounds).  A zero extent makes the launch a no-op.
-    int nxcd, ml_count; // filled in by the launcher from the device
+    int nxcd, per_xcd;  // filled in by the launcher from the device: the persistent grid (nxcd x per_xcd workgroups)
 };
+
+// How the workgroups of an XCD (per_xcd of them) share the tile grid: a block of ml rows x ncol columns of tiles, whose
+// operand tiles they share through that XCD's L2; the tile grid is cut into `groups` column groups of ncol tiles and
+// `rounds` of ml tile rows.  Four columns where there are enough of them (8 x 4 tiles on 32 compute units); fewer
+// columns, or fewer rows, than a block holds are spread evenly over as many blocks as they need, and the other side of
+// the block takes the workgroups that this frees.  A launch with the log-sum-exp epilogue leaves one partial per column
+// in each of nxcd * ml slots (slot = xcd * ml + row of the block) that had a tile of that column.
+// (A fixed 8 x 4 block left three workgroups in four idle for a single column of tiles: log-probs of 200 tokens x
+// 4,096 x 151,936 925 us so, 333 us with blocks of 32 x 1; weight gradient with 6 tile rows 500 against 424 us.)
+struct GemmShape {
+    int mtiles, ntiles, ncol, ml, groups, rounds;
+};
+constexpr int kGemmTile = 256;  // tile edge, both sides
+constexpr int kGemmColTiles = 4;
+__host__ __device__ inline GemmShape gemm_shape(int64_t M, int64_t N, int nxcd, int per_xcd)
+{
+    GemmShape s;
+    s.mtiles = (int)((M + kGemmTile - 1) / kGemmTile);
+    s.ntiles = (int)((N + kGemmTile - 1) / kGemmTile);
+    s.groups = (s.ntiles + kGemmColTiles - 1) / kGemmColTiles;
+    s.ncol = (s.ntiles + s.groups - 1) / s.groups;
+    s.ml = per_xcd / s.ncol > 0 ? per_xcd / s.ncol : 1;
+    s.rounds = (s.mtiles + s.ml - 1) / s.ml;
+    if (s.groups * s.rounds < nxcd) s.rounds = (nxcd + s.groups - 1) / s.groups;  // a block for every XCD
+    s.ml = (s.mtiles + s.rounds - 1) / s.rounds;
+    s.rounds = (s.mtiles + s.ml - 1) / s.ml;
+    s.ncol = per_xcd / s.ml < s.ntiles ? per_xcd / s.ml : s.ntiles;
+    s.groups = (s.ntiles + s.ncol - 1) / s.ncol;
+    return s;
+}
+
+// Slices of a kEpiSplitBf16 launch.  A product with fewer tiles than compute units (or a last round of tiles that fills
+// few of them) leaves the chip idle for its whole contracted length, so the contraction is cut into slices that are
+// work items of their own; their fp32 results are added in a fixed order by a second kernel.  The number of slices is
+// the one with the least predicted time among those that fill one to four rounds of the grid, in units of 0.1 us:
+// 3.2 us per 128 contracted elements and round, 4 us of epilogue per round, and 0.13 us of memory traffic per slice of
+// a tile (256 KiB written and read back at 4 TB/s).  (560 x 1,536 over 151,936: 18 tiles, 2.4 ms in one piece, 0.30 +
+// 0.014 ms as 14 slices; 512 tiles, two full rounds, stay whole: a second slice would only add its traffic.)
+__host__ __device__ inline int gemm_slices(int64_t tiles, int64_t quads, int workgroups, int split_max)
+{
+    auto cost = [&](int64_t n) {
+        const int64_t rounds = (tiles * n + workgroups - 1) / workgroups;
+        return rounds * ((quads + n - 1) / n * 32 + 40) + (n > 1 ? n * tiles * 13 / 10 : 0);
+    };
+    int best = 1;
+    int64_t least = cost(1);
+    for (int k = 1; k <= 4; ++k) {
+        int64_t n = (int64_t)k * workgroups / tiles;
+        n = n < split_max ? n : split_max;
+        n = n < quads ? n : quads;
+        if (n > 1 && cost(n) < least) {
+            least = cost(n);
+            best = (int)n;
+        }
+    }
+    return best;
+}
 
 // Panel layout of a bfloat16 operand of the contraction kernel: the matrix is cut into blocks of 256 rows x 32
 // contracted elements - what one stage of the kernel consumes -, each stored as 256 rows x 64 bytes = 16 KiB
@@ -188,11 +248,19 @@ inline hipError_t ensure_lds_limit(const void *kernel, int bytes, LdsLimitState 
 }
 
 struct GemmGrid {
-    int nxcd, ml_count, blocks;
+    int nxcd, per_xcd;
 };
+constexpr int kGemmMaxBlocks = 256;
 GemmGrid gemm_grid();
-constexpr int kGemmMaxPartialSlots = 64;  // workspaces are sized for this many; gemm_partial_slots() never exceeds it
-size_t gemm_partial_slots();
+// (max, sum) partials of up to N columns: nxcd * ml slots of N entries, at most 256 / ncol slots, and blocks of fewer
+// than four columns exist only up to 256 (one), 512 (two) and 2,304 columns (three: 3, 5, 6 or 9 tiles)
+inline size_t gemm_partial_entries(int64_t N)
+{
+    auto upto = [&](int64_t slots, int64_t most) { return (size_t)(slots * (N < most ? N : most)); };
+    size_t e = upto(kGemmMaxBlocks / 4, N);
+    for (size_t o : {upto(kGemmMaxBlocks, 256), upto(kGemmMaxBlocks / 2, 512), upto(kGemmMaxBlocks / 3, 2304)}) e = o > e ? o : e;
+    return e;
+}
 hipError_t launch_gemm_nt(const GemmArgs &g, int epilogue, hipStream_t s);
 
 size_t lmhead_workspace_bytes(int64_t T);
@@ -202,7 +270,7 @@ hipError_t launch_fused_lmhead_logprob(const void *hidden, const void *weight, i
 // merges the (max, sum) partials of a token, adds the chosen logit (a dot product) and writes lse and log pi
 // (T is an upper bound when `count` names a device-side token count)
 hipError_t launch_lmhead_lse_finish(const void *hidden, const void *weight, int64_t T, int64_t H, int64_t V,
-                                    const int32_t *chosen, const float2 *partial, int64_t partial_stride, float *logp,
+                                    const int32_t *chosen, const float2 *partial, float *logp,
                                     float *lse, hipStream_t s, DynCount count = DynCount());
 
 size_t lmhead_bwd_workspace_bytes(int64_t T, int64_t V, int64_t H);

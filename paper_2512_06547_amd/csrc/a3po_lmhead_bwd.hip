@@ -67,7 +67,7 @@ static LmBwdLayout lmhead_bwd_layout(int64_t T, int64_t V, int64_t H)
     l.pos = l.index + up(t * sizeof(int32_t));
     l.counts = l.pos + up(t * sizeof(int32_t));
     l.partial = l.counts + up(((t + kCompactBlock - 1) / kCompactBlock + 1) * sizeof(int32_t));
-    l.zt = l.partial + up((size_t)kGemmMaxPartialSlots * (size_t)l.chunk * sizeof(float2));
+    l.zt = l.partial + up(gemm_partial_entries(l.chunk) * sizeof(float2));
     l.dzt = l.zt + up((size_t)l.chunk * (size_t)l.ldv * sizeof(float));
     // the four operands that this file's own kernels write are kept in the contraction kernel's panel layout
     l.dz = l.dzt + up(panel_elements(V, l.ldg) * 2);
@@ -479,13 +479,11 @@ extern "C" int a3po_fused_lmhead_loss_fwd_bwd(const void *hidden, const void *we
         fw.ldc = lay.ldv;
         fw.transposed = 1;
         fw.partial = partial;
-        fw.partial_stride = lay.chunk;
         fw.dyn_dim = kDynN;
         fw.dyn = cnt;
         if (launch_gemm_nt(fw, kEpiLseStore, s) != hipSuccess) return A3PO_E_LAUNCH;
         // 2. log pi_theta and the per-token terms
-        if (launch_lmhead_lse_finish(hc + c0 * H, W, nmax, H, V, ysel + c0, partial, lay.chunk, logp_c + c0, lse + c0, s,
-                                     cnt) != hipSuccess)
+        if (launch_lmhead_lse_finish(hc + c0 * H, W, nmax, H, V, ysel + c0, partial, logp_c + c0, lse + c0, s, cnt) != hipSuccess)
             return A3PO_E_LAUNCH;
         hipLaunchKernelGGL(lmhead_token_terms_kernel, dim3((unsigned)((nmax + 255) / 256)), dim3(256), 0, s,
                            a.ws_records, index + c0, cnt, current_version, clip_eps, hdr, logp_c + c0, logp_out,
@@ -512,7 +510,10 @@ extern "C" int a3po_fused_lmhead_loss_fwd_bwd(const void *hidden, const void *we
         bh.ldc = H;
         bh.dyn_dim = kDynM;
         bh.dyn = cnt;
-        if (launch_gemm_nt(bh, kEpiStoreBf16, s) != hipSuccess) return A3PO_E_LAUNCH;
+        // (few tokens: slices of the contraction, in the chunk's logits, which nobody needs any more)
+        bh.split = zt;
+        bh.split_max = (int)(lay.ldv / H < 256 ? lay.ldv / H : 256);
+        if (launch_gemm_nt(bh, kEpiSplitBf16, s) != hipSuccess) return A3PO_E_LAUNCH;
         // 5. at the end of a group of chunks: dW [V, H] += (dz^T [V, group] (h^T [H, group])^T): h^T on the row side
         //    of the tiles, stored transposed; fp32 accumulator across groups
         const bool group_ends = c0 + lay.chunk >= T || (c0 + lay.chunk) % (kLmDwGroup * lay.chunk) == 0;

@@ -34,11 +34,13 @@ def close(gpu, ref, what):
 
 
 @pytest.mark.parametrize("T,H,V", [(1, 64, 1), (5, 64, 7), (256, 128, 256), (300, 192, 1000), (257, 64, 2049),
-                                   (1100, 256, 4500), (2048, 128, 2304), (9000, 64, 300), (700, 320, 20000)])
+                                   (1100, 256, 4500), (2048, 128, 2304), (9000, 64, 300), (700, 320, 20000),
+                                   (200, 128, 17000), (512, 64, 16900), (1500, 64, 9000), (2304, 64, 2561)])
 def test_fused_lmhead_logprob_small(a3po, T, H, V):
     # spans: single partial tile, exact tile multiples, ragged token and vocabulary tiles, hidden sizes that are and
     # are not a multiple of the ring depth, more token-tile groups than XCDs (several sweeps per workgroup), more
-    # vocabulary tiles than one round of an XCD's workgroups, XCDs that share a token group
+    # vocabulary tiles than one round of an XCD's workgroups, XCDs that share a token group, one to nine token tiles
+    # (blocks of one, two, three and four columns)
     r = np.random.default_rng(T * 131 + V)
     h = bf16_bits(r.standard_normal((T, H)))
     W = bf16_bits(r.standard_normal((V, H)) * 0.3)
@@ -193,12 +195,14 @@ def _check_backward(gpu, ref, ref_abs, what):
 
 
 @pytest.mark.parametrize("T,H,V,p_mask", [(300, 64, 1000, 0.8), (1, 64, 8, 1.0), (8192 + 300, 64, 512, 0.8),
-                                          (467, 192, 1344, 0.8), (16384, 256, 4096, 1.0),
+                                          (467, 192, 1344, 0.8), (560, 1536, 4000, 1.0), (2500, 832, 1336, 0.9),
+                                          (16384, 256, 4096, 1.0),
                                           (65536 + 700, 64, 512, 1.0)])
 def test_fused_lmhead_loss_fwd_bwd(a3po, T, H, V, p_mask):
     """Whole path from hidden states against the un-rounded fp64 oracle.  The cases span one and several token
     chunks (8,192 tokens each), ragged tiles on every side, hidden sizes that are and are not a multiple of the
-    ring depth; the last but one has every token counted with a non-zero advantage over two full chunks, the last
+    ring depth, hidden gradients contracted whole and in slices (bounded by the groups of stages, by the room for
+    their results, or by the number that fills the chip); the last but one has every token counted with a non-zero advantage over two full chunks, the last
     one nine chunks, i.e. more than the 65,536 tokens one weight-gradient contraction takes, so the second
     contraction adds onto the result of the first."""
     r = np.random.default_rng(T + 7 * V)
