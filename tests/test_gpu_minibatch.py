@@ -104,3 +104,17 @@ def test_microbatches_add_up_to_the_minibatch(a3po, dtype, V, budget, n_mb, L):
         assert_close_dz(host_rows(dz[sl])[ok], ref["dz"][ok], ref["g"][ok], dtype, f"dlogits of mini-batch {k}")
         assert not host_rows(dz[sl])[(ref["g"] == 0) & ok].any()
     assert not (dz.float() == 9.0).any(), "every row of the packed stream was written by some micro-batch"
+
+
+@pytest.mark.parametrize("T", [1, 3, 4, 4097, 65536 + 4 * 1024 + 5, 200003])
+@pytest.mark.parametrize("off", [0, 1, 3])
+def test_count_tokens_of_views(a3po, T, off):
+    # groups of four tokens, full and partial strides of the workgroup, arrays at any element alignment; ids at both
+    # ends of the valid range and beyond them, mask bytes other than 0 and 1
+    r = np.random.default_rng(T + off)
+    V = 1000
+    ids = r.choice(np.array([-1, 0, 5, V - 1, V, 2 ** 31 - 1, -2 ** 31], dtype=np.int64), T + off).astype(np.int32)
+    mask = r.choice(np.array([0, 1, 2, 255], dtype=np.uint8), T + off)
+    want = int(((mask != 0) & (ids >= 0) & (ids < V))[off:].sum())
+    denom, count = a3po.count_tokens(torch.from_numpy(ids).cuda()[off:], torch.from_numpy(mask).cuda()[off:], V, want_count=True)
+    assert int(count.cpu()[0]) == want and float(denom.cpu()[0]) == float(want)
