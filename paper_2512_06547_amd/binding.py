@@ -114,6 +114,11 @@ def _torch():
 
 
 def _stream() -> int:
+    # the raw handle of the current device's current stream.  torch.cuda.current_stream() builds a Stream object for it,
+    # 3.0 us of the 10 us a short call takes on the host; asked for directly the handle costs 0.2 us
+    c = _torch()._C
+    if hasattr(c, "_cuda_getCurrentRawStream"):
+        return c._cuda_getCurrentRawStream(c._cuda_getDevice())
     return _torch().cuda.current_stream().cuda_stream
 
 
