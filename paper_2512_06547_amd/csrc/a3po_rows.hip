@@ -783,21 +783,19 @@ __global__ __launch_bounds__(kRowThreads) void loss_rows_generic_kernel(const Lo
 }
 
 // ---------------------------------------------------------------------------------------
-// Forward only: log-sum-exp and chosen-token gather, one 256-thread workgroup per row,
+// Forward only: log-sum-exp and chosen-token gather, one workgroup of NT threads per row,
 // rows dealt round-robin.  A row is read as whole 16-byte vectors from its first 16-byte boundary on; the elements
 // before (rows of a stride or base that is no multiple of 16 bytes) and after the vectors are read singly.
-constexpr int kFwdThreads = 256;
-constexpr int kFwdWaves = kFwdThreads / kWave;
 constexpr int kFwdUnroll = 8;  // 16-byte vectors in flight per thread
 
-template <typename DT, bool ENT>
-__global__ __launch_bounds__(kFwdThreads) void logprob_rows_kernel(const void *z, int64_t T, int64_t V, int64_t ld,
+template <typename DT, bool ENT, int NT>
+__global__ __launch_bounds__(NT) void logprob_rows_kernel(const void *z, int64_t T, int64_t V, int64_t ld,
                                                                     const int32_t *chosen, float *logp, float *lse_out,
                                                                     void *chosen_logit, float *ent_out)
 {
-    constexpr int EPV = DT::kPerVec;
+    constexpr int EPV = DT::kPerVec, NW = NT / kWave;
     using Acc = typename RowAcc<ENT>::type;
-    __shared__ float red[3 * kFwdWaves];
+    __shared__ float red[3 * NW];
     const int tid = threadIdx.x;
     const size_t row_bytes = (size_t)ld * DT::kBytes;
 
@@ -808,48 +806,56 @@ __global__ __launch_bounds__(kFwdThreads) void logprob_rows_kernel(const void *z
         const int head = (int)min(V, (int64_t)((0u - (uint32_t)reinterpret_cast<uintptr_t>(in_row)) & 15u) / DT::kBytes);
         const int nfull = (int)(V - head) / EPV;
         const char *body = in_row + head * DT::kBytes;
+        // asked for first, so that their latency hides behind the row's loads: the chosen id and its logit (thread 0
+        // alone uses them), and the single elements (the head's on the first threads, the tail's on the next ones)
+        const int32_t y = chosen[row];
+        const bool ok = y >= 0 && (int64_t)y < V;
+        const uint32_t zy_bits = ok ? load_raw<DT>(in_row, y) : 0u;
+        const int64_t ecol = tid < head ? tid : nfull * EPV + (int64_t)tid;  // < 2 EPV elements in all
+        const bool edge = ecol < V;
+        const uint32_t edge_bits = edge ? load_raw<DT>(in_row, ecol) : 0u;
         int idx = tid;
-        for (; idx + (kFwdUnroll - 1) * kFwdThreads < nfull; idx += kFwdUnroll * kFwdThreads) {
+        for (; idx - tid + kFwdUnroll * NT <= nfull; idx += kFwdUnroll * NT) {
             uint4 v[kFwdUnroll];
 #pragma unroll
-            for (int u = 0; u < kFwdUnroll; ++u) v[u] = stream_load(body + (size_t)(idx + u * kFwdThreads) * 16);
+            for (int u = 0; u < kFwdUnroll; ++u) v[u] = stream_load(body + (size_t)(idx + u * NT) * 16);
 #pragma unroll
             for (int u = 0; u < kFwdUnroll; ++u) {
                 float f[EPV];
                 unpack<DT>(v[u], f);
                 fold<EPV>(acc, f);
+                __builtin_amdgcn_sched_barrier(0);  // one vector's temporaries at a time
             }
         }
-        for (; idx < nfull; idx += kFwdThreads) {
-            float f[EPV];
-            unpack<DT>(stream_load(body + (size_t)idx * 16), f);
-            fold<EPV>(acc, f);
+        if (idx - tid < nfull) {  // the ragged last pass (uniform): its loads are in flight together as well
+            uint4 v[kFwdUnroll];
+#pragma unroll
+            for (int u = 0; u < kFwdUnroll; ++u)
+                if (idx + u * NT < nfull) v[u] = stream_load(body + (size_t)(idx + u * NT) * 16);
+#pragma unroll
+            for (int u = 0; u < kFwdUnroll; ++u) {
+                if (idx + u * NT < nfull) {
+                    float f[EPV];
+                    unpack<DT>(v[u], f);
+                    fold<EPV>(acc, f);
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            }
         }
-        if (tid < head) {
-            float f[1] = {load_elem<DT>(in_row, tid)};
+        if (edge) {
+            float f[1] = {raw_to_float<DT>(edge_bits)};
             fold<1>(acc, f);
         }
-        for (int64_t j = head + (int64_t)nfull * EPV + tid; j < V; j += kFwdThreads) {
-            float f[1] = {load_elem<DT>(in_row, j)};
-            fold<1>(acc, f);
-        }
-        const Acc tot = block_allreduce<kFwdWaves>(acc, red);
+        const Acc tot = block_allreduce<NW>(acc, red);
         if (tid == 0) {
             const float log_s = logf(tot.s);
             const float lse = tot.m + log_s;
-            const int32_t y = chosen[row];
-            const bool ok = y >= 0 && (int64_t)y < V;
             if (lse_out) lse_out[row] = lse;
             if constexpr (ENT) ent_out[row] = entropy_of(tot, lse);
-            logp[row] = ok ? (load_elem<DT>(in_row, y) - tot.m) - log_s : 0.0f;
+            logp[row] = ok ? (raw_to_float<DT>(zy_bits) - tot.m) - log_s : 0.0f;
             if (chosen_logit) {
-                if constexpr (DT::kBytes == 4) {
-                    reinterpret_cast<uint32_t *>(chosen_logit)[row] =
-                        ok ? reinterpret_cast<const uint32_t *>(in_row)[y] : 0u;
-                } else {
-                    reinterpret_cast<uint16_t *>(chosen_logit)[row] =
-                        ok ? reinterpret_cast<const uint16_t *>(in_row)[y] : (uint16_t)0;
-                }
+                if constexpr (DT::kBytes == 4) reinterpret_cast<uint32_t *>(chosen_logit)[row] = zy_bits;
+                else reinterpret_cast<uint16_t *>(chosen_logit)[row] = (uint16_t)zy_bits;
             }
         }
     }
@@ -994,26 +1000,34 @@ hipError_t launch_loss_rows(const LossArgs &a, hipStream_t s)
     return a.dt == A3PO_F32 ? launch_loss_rows_t<F32>(a, s) : launch_loss_rows_t<Bf16>(a, s);
 }
 
-template <typename DT>
+template <typename DT, int NT>
 static void launch_logprob_rows_t(unsigned grid, hipStream_t s, const void *z, int64_t T, int64_t V, int64_t ld,
                                   const int32_t *chosen, float *logp, float *lse, void *chosen_logit, float *ent)
 {
-    if (ent)
-        hipLaunchKernelGGL((logprob_rows_kernel<DT, true>), dim3(grid), dim3(kFwdThreads), 0, s, z, T, V, ld, chosen,
-                           logp, lse, chosen_logit, ent);
-    else
-        hipLaunchKernelGGL((logprob_rows_kernel<DT, false>), dim3(grid), dim3(kFwdThreads), 0, s, z, T, V, ld, chosen,
-                           logp, lse, chosen_logit, ent);
+    auto *kernel = ent ? logprob_rows_kernel<DT, true, NT> : logprob_rows_kernel<DT, false, NT>;
+    hipLaunchKernelGGL(kernel, dim3(grid), dim3(NT), 0, s, z, T, V, ld, chosen, logp, lse, chosen_logit, ent);
 }
 
 hipError_t launch_token_logprobs(const void *z, int dt, int64_t T, int64_t V, int64_t ld, const int32_t *chosen,
                                  float *logp, float *lse, void *chosen_logit, float *ent, hipStream_t s)
 {
     if (T == 0) return hipSuccess;
-    const int64_t want = (int64_t)device_cu_count() * 8;
+    const int64_t cus = device_cu_count(), want = cus * 8;
     const unsigned grid = (unsigned)(T < want ? T : want);
-    if (dt == A3PO_F32) launch_logprob_rows_t<F32>(grid, s, z, T, V, ld, chosen, logp, lse, chosen_logit, ent);
-    else launch_logprob_rows_t<Bf16>(grid, s, z, T, V, ld, chosen, logp, lse, chosen_logit, ent);
+#define A3PO_FWD(DT, NT) launch_logprob_rows_t<DT, NT>(grid, s, z, T, V, ld, chosen, logp, lse, chosen_logit, ent)
+#define A3PO_FWD_DT(NT) \
+    do { \
+        if (dt == A3PO_F32) A3PO_FWD(F32, NT); \
+        else A3PO_FWD(Bf16, NT); \
+    } while (0)
+    // 512 threads per row for up to two rows per compute unit (a lone row is bound by what one compute unit can have in
+    // flight: 64 / 256 rows of 151,936 bfloat16 17.5 / 20.8 us with 256 threads, 13.3 / 16.5 with 512), and for long
+    // rows without the entropy (10,240 rows: 484 -> 470 us); 256 for many shorter ones (16,000 columns, 10,240 rows:
+    // 61 against 78 us).  At 100 KiB the two are alike.
+    if (T <= 2 * cus || (!ent && V * (dt == A3PO_F32 ? 4 : 2) >= 112 * 1024)) A3PO_FWD_DT(512);
+    else A3PO_FWD_DT(256);
+#undef A3PO_FWD_DT
+#undef A3PO_FWD
     return hipGetLastError();
 }
 

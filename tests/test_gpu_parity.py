@@ -388,6 +388,35 @@ def test_token_logprobs(a3po, dtype, V, pad):
     assert logp[1] == 0 and logp[2] == 0
 
 
+@pytest.mark.parametrize("dtype,V,T,off", [
+    ("bf16", 5, 700, 1), ("bf16", 15, 40, 3), ("f32", 6, 700, 3),               # shorter than a vector after the head
+    ("bf16", 16384, 700, 0), ("bf16", 16399, 700, 5), ("bf16", 32769, 40, 7),   # whole passes of 256 and 512 threads
+    ("f32", 28673, 1040, 1), ("f32", 28668, 1040, 2),                           # the row length from which 512 are used
+])
+def test_token_logprobs_at_any_address(a3po, dtype, V, T, off):
+    r = np.random.default_rng(V + T)
+    z = (r.standard_normal((T, V)) * 3).astype(np.float32)
+    flat = torch.zeros(T * V + off, dtype=torch.float32 if dtype == "f32" else torch.bfloat16, device="cuda")
+    z_d = flat[off:].view(T, V)
+    z_d.copy_(torch.from_numpy(z))
+    z = z_d.cpu().numpy() if dtype == "f32" else z_d.cpu().view(torch.uint16).numpy()
+    y = r.integers(0, V, T).astype(np.int32)
+    y[:2] = 0, V - 1
+    y[2:4] = -1, V
+    ref = oracle.token_logprobs(z, y)
+    ok = (y >= 0) & (y < V)
+    for want_entropy in (False, True):
+        out = a3po.token_logprobs(z_d, torch.from_numpy(y).cuda(), want_entropy=want_entropy)
+        assert_close_logp(out[1].cpu().numpy(), ref["lse"], "lse")
+        assert_close_logp(out[0].cpu().numpy()[ok], ref["logp"][ok], "logp")
+        assert (out[0].cpu().numpy()[~ok] == 0).all()
+        want = torch.where(torch.from_numpy(ok).cuda(), z_d.gather(1, torch.from_numpy(np.where(ok, y, 0)).cuda().long()[:, None])[:, 0], torch.zeros_like(z_d[:, 0]))
+        assert torch.equal(out[2], want)
+        if want_entropy:
+            ent = oracle.entropy(z)
+            assert (np.abs(out[3].cpu().numpy() - ent) <= 1e-5 * np.abs(ent) + 2e-5 * (1 + np.abs(ref["lse"]))).all()
+
+
 def test_fused_logp_equals_standalone_logp_closely(a3po):
     c = make_case(synth.WORKLOADS["tiny"], T=256)
     out = run_gpu(a3po, c)
