@@ -21,11 +21,12 @@
  *    a3po_loss_fwd_bwd_noalloc uses in place of a workspace.)
  *  - Logits are row-major [T, V] with a row stride of `ld` elements (ld >= V), float32
  *    or bfloat16.  Row t pairs with chosen[t]; any next-token shift is the caller's.
- *    Base pointers of logits / dlogits must be aligned to their element size.  Rows whose base
- *    and byte stride are multiples of 16 take the vectorised kernels: each row is read once and written
- *    once when it fits the registers (V <= 163,840 bfloat16 / 81,920 float32); a longer row stays on chip as
- *    far as registers and LDS hold it (448 KiB) and only its remainder is read a second time.  Everything
- *    else takes slower element-wise multi-pass kernels.  Results are identical up to rounding order.
+ *    Base pointers of logits / dlogits must be aligned to their element size.  Each row
+ *    is read once and written once when it fits the registers (V <= 163,840 bfloat16 / 81,920 float32); a longer
+ *    row stays on chip as far as registers and LDS hold it (448 KiB) and only its remainder is read a second time.
+ *    Rows that do not start on 128-byte lines are cut at the lines of the gradient, at nearly the same speed; only
+ *    rows too long for the registers whose logits and gradient differ in alignment within 16 bytes, and gradients of
+ *    unaligned vocabulary shards, take slower element-wise kernels.  Results are identical up to rounding order.
  */
 #ifndef A3PO_H
 #define A3PO_H
@@ -368,8 +369,8 @@ int a3po_fused_lmhead_logprob(const void *hidden, const void *weight, int64_t T,
  * hidden, dhidden [T, H]; weight, dweight [V, H]: row-major, contiguous, bfloat16, 16-byte
  * aligned; H a positive multiple of 64, at most 2^20; V a multiple of 8 below 2^21; T below 2^22
  * (A3PO_E_SIZE otherwise).  Per-token arguments and outputs as in a3po_loss_fwd_bwd.
- * workspace: a3po_workspace_bytes(A3PO_WS_FUSED_LMHEAD_LOSS, T, V, H) bytes, 256-byte aligned: W^T, the gathered
- * hidden rows and their transpose, a chunk of logits (fp32) and of its gradient, the vocabulary-major gradient of
+ * workspace: a3po_workspace_bytes(A3PO_WS_FUSED_LMHEAD_LOSS, T, V, H) bytes, 256-byte aligned: W^T (from 16,384
+ * tokens on), the gathered hidden rows and their transpose, a chunk of logits (fp32) and of its gradient, the vocabulary-major gradient of
  * up to 65,536 tokens, and beyond that many tokens an fp32 accumulator of dweight - about 2 V H + 6 T H +
  * 6 * 8192 V + 2 V min(T, 65536) (+ 4 V H) bytes, 30 GB at T = 65,536, H = 4,096, V = 151,936.
  */

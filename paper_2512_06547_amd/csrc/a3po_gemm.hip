@@ -1,12 +1,13 @@
-// bfloat16 contraction on the matrix cores for the LM-head path:  C[M, N] = A[M, K] B[N, K]^T, both operands
-// row-major with the contracted index contiguous, fp32 accumulation (v_mfma_f32_16x16x32_bf16), and one of four
-// epilogues applied to each 256 x 256 tile as it leaves the accumulators:
-//   kEpiLse        fold the tile into a running (max, sum) per column n over the rows m (the online log-sum-exp
-//                  of the vocabulary when A is the LM-head weight and B the hidden states); C is not written
-//   kEpiLseStore   the same, and the tile is also stored as fp32 (the logits of a token chunk, kept for the
-//                  backward pass)
-//   kEpiStoreBf16  the tile is stored as bfloat16 (the gradient of the hidden states)
-//   kEpiAccumF32   the tile is stored as fp32, or added to what C holds (the weight gradient, summed over chunks)
+// bfloat16 contraction on the matrix cores for the LM-head path:  C(m, n) = sum_k A(m, k) B(n, k), fp32 accumulation
+// (v_mfma_f32_16x16x32_bf16).  The products that exist (GemmProduct) differ in the layouts of their operands and in
+// what happens to each 256 x 256 tile as it leaves the accumulators:
+//   kGemmLse        folded into a running (max, sum) per column n over the rows m (the online log-sum-exp of the
+//                   vocabulary when A is the LM-head weight and B the hidden states); C is not written
+//   kGemmLseStore   the same, and the tile is also stored as fp32 (the logits of a token chunk, kept for the
+//                   backward pass)
+//   kGemmSplit*     stored as bfloat16 (the gradient of the hidden states), or as fp32 slices to be added up
+//   kGemmPanelsBf16 stored as bfloat16 (the weight gradient of a batch whose tokens fit one contraction)
+//   kGemmPanelsF32  stored as fp32, or added to what C holds (the weight gradient, summed over groups of tokens)
 //
 // Tiling.  A workgroup of 512 threads (8 wavefronts, two per SIMD) computes a 256 x 256 tile, each wavefront a
 // 128 x 64 part = 8 x 4 MFMA tiles of 16 x 16 = 128 accumulator registers.  Two wavefronts per SIMD: while one
@@ -18,9 +19,7 @@
 //
 // K is walked in stages of 32 (one MFMA deep) through a ring of LDS buffers that direct global -> LDS loads
 // (global_load_lds_dwordx4: lane l of a wavefront lands at lds_base + 16 l; no staging registers, no LDS write
-// instructions) fill a few stages ahead.  LDS layout of one operand stage: 256 rows x 64 bytes, unpadded; the
-// 16-byte piece p of row r sits at physical piece p ^ ((r >> 2) & 3) - the permutation is applied on the global
-// side of the load - so a fragment read (16 consecutive rows, same logical piece) touches 16 distinct bank groups.
+// instructions) fill a few stages ahead.  Operand layouts and their LDS images: see Operand below.
 //
 // Schedule of stage i (32 MFMAs per wavefront).  At the top a wavefront waits for its own loads of stage i+1 and
 // its own fragment reads, and all wavefronts meet at one barrier: stage i+1 is now visible and the slot of stage i
@@ -34,13 +33,11 @@
 // workgroups round-robin over the XCDs) form a block of ml x ncol tiles (8 x 4 in the usual case, GemmShape) that
 // share ml tiles of A and ncol tiles of B through that XCD's L2.  The tile grid is cut into such blocks ("pairs" of a
 // column group and a row round); pair p = group * rounds + round, and each XCD takes a contiguous range of pairs, i.e.
-// it sweeps down the rows of one column group before it moves to the next.  With kEpiLse* a workgroup therefore
+// it sweeps down the rows of one column group before it moves to the next.  With kGemmLse* a workgroup therefore
 // keeps its running (max, sum) in registers over a whole sweep and writes one partial per column per sweep.
 //
-// Operand and result layouts.  An operand is either row-major (row stride lda / ldb) or in panels of 256 rows x 32
-// contracted elements (a3po_launch.h), in which the 16 rows x 64 bytes of a direct load are 1 KiB of contiguous
-// memory.  The fp32 epilogues can store the tile transposed (element (m, n) at C[n ldc + m]): a lane's four
-// accumulator values of one MFMA tile are four consecutive m of one n, i.e. one 16-byte store without staging.
+// Results.  The logits and the weight gradient are stored transposed (element (m, n) at C[n ldc + m]): a lane's four
+// accumulator values of one MFMA tile are four consecutive m of one n, i.e. one 16- or 8-byte store without staging.
 // One of M, N, K may be known only on the device (DynCount): the launch is sized for the host's upper bound and
 // every workgroup reads the extent first; beyond it there is nothing to do and it returns.
 #include "a3po_common.h"
@@ -115,13 +112,11 @@ __device__ __forceinline__ void fold_column(const f32x4_t (&acc)[8][4], int b, i
     run_s = s;
 }
 
-// Element-wise store of a wavefront's part of the tile: one accumulator register covers 4 rows x 16 consecutive
-// columns.  EDGE: the tile reaches past M or N; rows / columns beyond are skipped.  Used for tiles on the edge and
-// for sums into C, which go through the memory side's adders (every element has one owner per launch and launches
-// are ordered on the stream, so the sum is deterministic; nobody waits for its result).
-template <int EPI, bool EDGE>
-__device__ __forceinline__ void store_tile(const f32x4_t (&acc)[8][4], void *C, int64_t ldc, int64_t m0, int64_t n0,
-                                           int64_t M, int64_t N, int wm, int wn, int lane, bool add)
+// Element-wise store of a wavefront's part of a tile that reaches past M or N (rows / columns beyond are skipped): one
+// accumulator register covers 4 rows x 16 consecutive columns.
+template <typename DT>
+__device__ __forceinline__ void store_tile_edge(const f32x4_t (&acc)[8][4], void *C, int64_t ldc, int64_t m0, int64_t n0,
+                                                int64_t M, int64_t N, int wm, int wn, int lane)
 {
     const int col0 = wn * 64 + (lane & 15);
     const int row0 = wm * 128 + 4 * (lane >> 4);
@@ -132,22 +127,10 @@ __device__ __forceinline__ void store_tile(const f32x4_t (&acc)[8][4], void *C, 
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             const int row = row0 + a * 16 + i;
-            if (EDGE && row >= rows_left) continue;
-            const int64_t at = (m0 + row) * ldc + n0 + col0;
+            if (row >= rows_left) continue;
 #pragma unroll
-            for (int b = 0; b < 4; ++b) {
-                if (EDGE && col0 + b * 16 >= cols_left) continue;
-                const float v = acc[a][b][i];
-                if constexpr (EPI == kEpiStoreBf16) {
-                    reinterpret_cast<uint16_t *>(C)[at + b * 16] = (uint16_t)(pack_bf16x2(v, 0.0f) & 0xFFFFu);
-                } else if constexpr (EPI == kEpiAccumF32) {
-                    float *p = reinterpret_cast<float *>(C) + at + b * 16;
-                    if (add) unsafeAtomicAdd(p, v);
-                    else *p = v;
-                } else {
-                    reinterpret_cast<float *>(C)[at + b * 16] = v;
-                }
-            }
+            for (int b = 0; b < 4; ++b)
+                if (col0 + b * 16 < cols_left) store_elem<DT>(C, (m0 + row) * ldc + n0 + col0 + b * 16, acc[a][b][i]);
         }
         __builtin_amdgcn_sched_barrier(0);
     }
@@ -206,15 +189,14 @@ __device__ __forceinline__ void store_tile_transposed_bf16(const f32x4_t (&acc)[
     }
 }
 
-// The same for a tile that lies inside C, with 16-byte stores: 16 rows x 32 columns at a time go through a staging
+// Plain store of a tile that lies inside C, with 16-byte stores: 16 rows x 32 columns at a time go through a staging
 // tile in LDS that belongs to this wavefront alone (LDS instructions of one wavefront execute in order, so no waits
 // or barriers are needed between its writes and its reads) and leave as 8 rows x 128 bytes (fp32) or 8 rows x 64
 // bytes (bfloat16) per store instruction.
-template <int EPI>
+template <typename DT>
 __device__ __forceinline__ void store_tile_wide(const f32x4_t (&acc)[8][4], void *C, int64_t ldc, int64_t m0, int64_t n0,
                                                 int wm, int wn, int lane, float *stage)
 {
-    static_assert(EPI == kEpiStoreBf16 || EPI == kEpiLseStore || EPI == kEpiAccumF32, "plain stores only");
     const int wcol = lane & 15, wrow = 4 * (lane >> 4);  // where this lane's accumulator registers sit in a 16 x 16 tile
     const int rrow = lane >> 3, rcol = (lane & 7) * 4;   // what it reads back: 4 consecutive columns of row rrow + 8 pass
 #pragma unroll
@@ -230,7 +212,7 @@ __device__ __forceinline__ void store_tile_wide(const f32x4_t (&acc)[8][4], void
 #pragma unroll
             for (int pass = 0; pass < 2; ++pass) {
                 const float4 v = *reinterpret_cast<const float4 *>(stage + (rrow + 8 * pass) * kStageLd + rcol);
-                if constexpr (EPI == kEpiStoreBf16) {
+                if constexpr (DT::kBytes == 2) {
                     *reinterpret_cast<uint2 *>(reinterpret_cast<uint16_t *>(C) + at + (int64_t)pass * 8 * ldc) =
                         make_uint2(pack_bf16x2(v.x, v.y), pack_bf16x2(v.z, v.w));
                 } else {
@@ -243,22 +225,122 @@ __device__ __forceinline__ void store_tile_wide(const f32x4_t (&acc)[8][4], void
     }
 }
 
+// ---- operands -----------------------------------------------------------------------------------------------
+// One stage of an operand is 256 rows (m or n) x 32 contracted elements = 16 KiB of LDS, brought in by 16 direct loads
+// of 1 KiB, two per wavefront (load j of wavefront w is number 8 j + w); a fragment is the 16 rows x 32 elements that
+// one MFMA takes, lane l holding row l & 15 and elements 8 (l >> 4) .. + 7.
+//
+// Contracted index fast (kRows, kPanels): a load covers 16 rows x 64 bytes; LDS row r is 64 bytes, its four 16-byte
+// pieces permuted by (r >> 2) & 3 on the global side of the load, and a fragment is one 16-byte read per lane (16
+// consecutive rows, same logical piece: 16 distinct bank groups).
+//
+// Contracted index slow (kSlowRows): LDS holds the stage as it lies in memory, contracted elements as rows, and
+// ds_read_b64_tr_b16 transposes on the way out: within a group of 16 lanes, lane i receives as value j the element i % 4
+// of the 8 bytes addressed by lane i / 4 + 4 j.  With lane s of group q pointing at row 8 q + s / 4 (+ 4 for the second
+// read), columns 4 (s % 4) .., two reads give each lane 8 contracted elements of column lane & 15.  A load covers 8 rows x
+// 128 bytes (whole lines); LDS is 4 blocks of [32 rows][128 bytes], the four 32-byte granules of row r permuted by
+// (r >> 1) & 3, so that the 4 rows x 32 bytes of a lane group fall into distinct banks.
+enum OperandLayout { kRows, kPanels, kSlowRows };
+
+typedef __bf16 bf16x4_t __attribute__((ext_vector_type(4)));
+typedef __attribute__((address_space(3))) bf16x4_t *lds_tr_ptr_t;
+
+// (the __restrict__ parameters put the read into an alias scope of its own once this is inlined: without one the
+// compiler waits for every direct load in flight, vmcnt(0), before each transposing read; the stage's own wait and
+// barrier are what orders the two)
+__device__ __forceinline__ bf16x4_t tr_half(lds_tr_ptr_t __restrict__ p) { return __builtin_amdgcn_ds_read_tr16_b64_v4bf16(p); }
+__device__ __forceinline__ bf16x8_t tr_read(char *lo, char *hi)
+{
+    const bf16x4_t a = tr_half((lds_tr_ptr_t)lo), b = tr_half((lds_tr_ptr_t)hi);
+    return __builtin_shufflevector(a, b, 0, 1, 2, 3, 4, 5, 6, 7);
+}
+
+template <int L>
+struct Operand {
+    static constexpr bool kSlow = L == kSlowRows;
+    const char *base;    // of the operand
+    int64_t ld;          // elements
+    int64_t extent;      // rows of the result on this operand's side
+    uint32_t k_last;     // kSlowRows: last row that exists
+    int wave, lane;
+    const char *tile;    // of the current tile
+    uint32_t off[2];     // this lane's byte offsets of its two loads
+
+    __device__ __forceinline__ void init(const uint16_t *p, int64_t ld_, int64_t extent_, int64_t k_rows, int wave_, int lane_)
+    {
+        base = reinterpret_cast<const char *>(p);
+        ld = ld_;
+        extent = extent_;
+        k_last = (uint32_t)(k_rows - 1);
+        wave = wave_;
+        lane = lane_;
+    }
+    // rows or columns past the end of the operand are clamped (computed, never written); rows of panels exist (padding)
+    __device__ __forceinline__ void set_tile(int t)
+    {
+        // (a 256-row band of panels is as long as 256 rows)
+        tile = base + (int64_t)t * kGemmTile * 2 * (kSlow ? 1 : ld);
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            const int i = 8 * j + wave;
+            if constexpr (!kSlow) {
+                const int r = i * 16 + (lane >> 2), last = (int)(extent - 1 - (int64_t)t * kGemmTile);
+                const uint32_t piece = (uint32_t)((lane & 3) ^ ((lane >> 4) & 3)) * 16u;
+                off[j] = L == kPanels ? (uint32_t)r * 64u + piece : (uint32_t)min(r, last) * ((uint32_t)ld * 2u) + piece;
+            } else {
+                const int block = min((i >> 2) * 64, (int)(extent - 64 - (int64_t)t * kGemmTile));
+                const uint32_t granule = (uint32_t)(((lane & 7) >> 1) ^ ((lane >> 4) & 3));  // row = 8 (i & 3) + (lane >> 3)
+                off[j] = (uint32_t)block * 2u + granule * 32u + (uint32_t)(lane & 1) * 16u;
+            }
+        }
+    }
+    // load j of stage st into the operand's 16 KiB at dst
+    __device__ __forceinline__ void refill(char *dst, int j, uint32_t st) const
+    {
+        const char *src;
+        if constexpr (!kSlow) {
+            src = tile + st * (L == kPanels ? 16384u : (uint32_t)kDmaRowBytes) + off[j];
+        } else {
+            const uint32_t row = min(st * (uint32_t)kDmaK + 8u * (wave & 3) + (uint32_t)(lane >> 3), k_last);
+            src = tile + (uint64_t)row * ((uint32_t)ld * 2u) + off[j];
+        }
+        dma16(src, dst + (8 * j + wave) * 1024);
+    }
+    // this lane's part of a fragment's address, for the fragments of a wavefront whose part of the stage begins at 16-row
+    // block t0 (a multiple of 4), and fragment t from there in the stage at p
+    __device__ __forceinline__ uint32_t lane_base(int t0) const
+    {
+        if constexpr (!kSlow) return t0 * 1024u + (uint32_t)(lane & 15) * kDmaRowBytes + (uint32_t)(((lane >> 4) ^ ((lane >> 2) & 3)) * 16);
+        const int row = 8 * (lane >> 4) + ((lane & 15) >> 2);
+        return t0 * 1024u + row * 128u + (lane & 3) * 8u + ((lane >> 3) & 1) * 32u;
+    }
+    static __device__ __forceinline__ bf16x8_t fragment(char *p, uint32_t lane0, int t)
+    {
+        if constexpr (!kSlow) return *reinterpret_cast<const bf16x8_t *>(p + lane0 + t * 1024);
+        // granule t & 3 of rows 8 q + s / 4 is stored at granule (t & 3) ^ (s >> 3), of the rows 4 further at
+        // that ^ 2: lane0 holds the place of granule 0, and an odd granule lies 32 bytes up or down from the even one
+        char *q = p + (t >> 2) * 4096 + ((t & 1) ? lane0 ^ 32u : lane0);
+        return tr_read(q + (t & 2) * 32, q + ((t & 2) ^ 2) * 32 + 512);
+    }
+};
+
 // QUAD: K is a multiple of kDmaStages stages.  Then every tile starts in ring slot 0, the K loop is unrolled by
 // the ring depth (all LDS addresses are constants) and the refill cursor moves once per kDmaStages stages.
 // Otherwise the loop is unrolled by two (the column fragments alternate; the number of stages is even) and slot
 // and cursor are tracked per stage.
 //
-// kEpiSplitBf16 (QUAD only).  The work items are slices of tiles: item u of slices * tiles is slice u / tiles of a tile,
+// kGemmSplit* (QUAD only).  The work items are slices of tiles: item u of slices * tiles is slice u / tiles of a tile,
 // tiles taken in super-rows of 8 tile rows (column by column inside), and round j of the grid deals each XCD 32
 // consecutive items, which share their operand tiles as a block of 8 x 4 does.  With one slice the launch is an
-// ordinary product in the order of the other epilogues.
-template <int EPI, bool QUAD>
-__global__ __launch_bounds__(kGemmThreads) void gemm_nt_kernel(const GemmArgs g)
+// ordinary product in the order of the others.
+template <int PRODUCT, bool QUAD>
+__global__ __launch_bounds__(kGemmThreads) void gemm_kernel(const GemmArgs g)
 {
     extern __shared__ __align__(16) char lds[];
-    constexpr bool LSE = EPI == kEpiLse || EPI == kEpiLseStore, SPLIT = EPI == kEpiSplitBf16;
-    static_assert(!SPLIT || QUAD, "slices are whole groups of ring stages");
-    constexpr int kLoads = 4;  // direct loads per wavefront and stage: two 16-row blocks of A, two of B
+    constexpr bool LSE = PRODUCT == kGemmLse || PRODUCT == kGemmLseStore, SPLIT = PRODUCT == kGemmSplitRows || PRODUCT == kGemmSplitPanels;
+    constexpr bool PANELS = PRODUCT == kGemmPanelsBf16 || PRODUCT == kGemmPanelsF32;
+    static_assert(LSE || QUAD, "slices are whole groups of ring stages");
+    constexpr int kLoads = 4;  // direct loads per wavefront and stage: two of A, two of B
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int wm = wave & 1, wn = wave >> 1;  // row half (128 rows), column quarter (64 columns) of the tile
     const int xcd = (int)(blockIdx.x % (unsigned)g.nxcd), slot = (int)(blockIdx.x / (unsigned)g.nxcd);
@@ -280,7 +362,6 @@ __global__ __launch_bounds__(kGemmThreads) void gemm_nt_kernel(const GemmArgs g)
     const int64_t p_end = flat ? tiles * slices : ml < shp.ml ? (int64_t)(xcd + 1) * pairs / g.nxcd : 0;
     const int nstages = (int)(K / kDmaK);
     const int wave_s = __builtin_amdgcn_readfirstlane(wave);  // the wavefront number in a scalar register
-    const uint32_t lda2 = (uint32_t)g.lda * 2u, ldb2 = (uint32_t)g.ldb * 2u;  // row strides in bytes
 
     // the first work item at or after p for this workgroup (p_end if there is none): the next pair in this XCD's range
     // whose tile exists for this workgroup's place in the block, or (flat) p itself
@@ -302,16 +383,15 @@ __global__ __launch_bounds__(kGemmThreads) void gemm_nt_kernel(const GemmArgs g)
         it.slice = 0;
         it.s0 = 0;
         it.s1 = nstages;
-        if (flat) {
-            const int quads = nstages / kDmaStages;
-            it.slice = (int)(p / tiles);
-            it.s0 = (int)((int64_t)it.slice * quads / slices) * kDmaStages;
-            it.s1 = (int)((int64_t)(it.slice + 1) * quads / slices) * kDmaStages;
-            const int64_t tile = p % tiles;
-            const int srow = (int)(tile / (8 * (int64_t)shp.ntiles)), in = (int)(tile % (8 * (int64_t)shp.ntiles));
-            const int h = min(8, shp.mtiles - srow * 8);
-            it.mt = srow * 8 + in % h;
-            it.nt = in / h;
+        if (flat) {  // (few items: 32-bit arithmetic)
+            const uint32_t u = (uint32_t)p, nt = (uint32_t)tiles, quads = (uint32_t)nstages / kDmaStages;
+            const uint32_t slice = u / nt, tile = u % nt, super = 8u * (uint32_t)shp.ntiles;
+            it.slice = (int)slice;
+            it.s0 = (int)(slice * quads / (uint32_t)slices) * kDmaStages;
+            it.s1 = (int)((slice + 1) * quads / (uint32_t)slices) * kDmaStages;
+            const uint32_t srow = tile / super, in = tile % super, h = min(8u, (uint32_t)shp.mtiles - srow * 8u);
+            it.mt = (int)(srow * 8u + in % h);
+            it.nt = (int)(in / h);
         } else {
             it.mt = (int)(p % rounds) * shp.ml + ml;
             it.nt = (int)(p / rounds) * shp.ncol + nl;
@@ -319,15 +399,13 @@ __global__ __launch_bounds__(kGemmThreads) void gemm_nt_kernel(const GemmArgs g)
         return it;
     };
 
-    // direct loads: instruction j of an operand covers tile rows (8 j + wave) 16 .. + 15; lane -> row lane >> 2,
-    // physical piece lane & 3, which holds logical piece (lane & 3) ^ ((row >> 2) & 3) = (lane & 3) ^ ((lane >> 4) & 3)
-    const int drow = lane >> 2;
-    const uint32_t dpiece = (uint32_t)((lane & 3) ^ ((lane >> 4) & 3)) * 16u;
-    // fragment reads: row lane & 15 of a 16-row block, k quarter lane >> 4 = logical piece, physical piece
-    // that ^ ((row >> 2) & 3) = that ^ ((lane >> 2) & 3); block t of an operand starts at t * 1024 bytes
-    const uint32_t fr = (uint32_t)(lane & 15) * kDmaRowBytes + (uint32_t)(((lane >> 4) ^ ((lane >> 2) & 3)) * 16);
-    const uint32_t fa_base = (uint32_t)(wm * 8) * 1024u + fr;
-    const uint32_t fb_base = kDmaOperandBytes + (uint32_t)(wn * 4) * 1024u + fr;
+    Operand<LSE ? kRows : kPanels> opa;
+    Operand<LSE ? kRows : PRODUCT == kGemmSplitRows ? kSlowRows : kPanels> opb;
+    opa.init(g.A, g.lda, M, g.k_rows, wave_s, lane);
+    opb.init(g.B, g.ldb, N, g.k_rows, wave_s, lane);
+    const uint32_t fa_base = opa.lane_base(wm * 8), fb_base = kDmaOperandBytes + opb.lane_base(wn * 4);
+    auto frag_a = [&](char *stage, int t) { return opa.fragment(stage, fa_base, t); };
+    auto frag_b = [&](char *stage, int t) { return opb.fragment(stage, fb_base, t); };
 
     int64_t p_cur = next_tile(flat ? (int64_t)xcd * g.per_xcd + slot : (int64_t)xcd * pairs / g.nxcd);
     if (p_cur >= p_end) return;  // uniform over the workgroup
@@ -338,33 +416,19 @@ __global__ __launch_bounds__(kGemmThreads) void gemm_nt_kernel(const GemmArgs g)
     // arithmetic, constant.  Rows past the end of an operand are clamped (computed, never written).
     int64_t r_p = p_cur;
     int r_k = 0, r_end = 0;
-    const char *r_a = nullptr, *r_b = nullptr;
-    uint32_t aoff[2], boff[2];
     auto set_tile = [&](int64_t p) {
         const Item it = locate(p);
-        const int mt = it.mt, nt = it.nt;
         r_k = it.s0;
         r_end = it.s1;
-        r_a = reinterpret_cast<const char *>(g.A + (int64_t)mt * kGemmTile * g.lda);  // (a 256-row band of panels is as long)
-        r_b = reinterpret_cast<const char *>(g.B + (int64_t)nt * kGemmTile * g.ldb);
-        const int m_last = (int)(M - 1 - (int64_t)mt * kGemmTile), n_last = (int)(N - 1 - (int64_t)nt * kGemmTile);
-#pragma unroll
-        for (int j = 0; j < 2; ++j) {
-            const int r = (8 * j + wave) * 16 + drow;
-            // panels: every row of the band exists (padding), rows are 64 bytes apart
-            aoff[j] = g.a_panel ? (uint32_t)r * 64u + dpiece : (uint32_t)min(r, m_last) * lda2 + dpiece;
-            boff[j] = g.b_panel ? (uint32_t)r * 64u + dpiece : (uint32_t)min(r, n_last) * ldb2 + dpiece;
-        }
+        opa.set_tile(it.mt);
+        opb.set_tile(it.nt);
     };
     set_tile(r_p);
-    // direct load number q of one operand (0: A rows, 1: B rows) of stage r_k + u into ring slot sl
+    // direct load number q of one operand (0: A, 1: B) of stage r_k + u into ring slot sl
     auto refill = [&](int sl, int q, int u, int operand) {
-        const uint32_t st = (uint32_t)(r_k + u);
-        const uint32_t koff = st * (uint32_t)kDmaRowBytes;                 // rows: 64 bytes further along the row
-        const uint32_t poff = st * 16384u;                                 // panels: the next block
-        char *dst = lds + sl * kDmaStageBytes + wave_s * 1024 + q * 8192;
-        if (operand == 0) dma16(r_a + (g.a_panel ? poff : koff) + aoff[q], dst);
-        else dma16(r_b + (g.b_panel ? poff : koff) + boff[q], dst + kDmaOperandBytes);
+        char *dst = lds + sl * kDmaStageBytes;
+        if (operand == 0) opa.refill(dst, q, (uint32_t)(r_k + u));
+        else opb.refill(dst + kDmaOperandBytes, q, (uint32_t)(r_k + u));
     };
     auto advance = [&](int step) {
         if (r_k + step < r_end) {
@@ -393,12 +457,12 @@ __global__ __launch_bounds__(kGemmThreads) void gemm_nt_kernel(const GemmArgs g)
     __builtin_amdgcn_s_barrier();  // bare, as in the K loop: the rest of the ring stays in flight
     bf16x8_t fa[8], fb[2][4];
 #pragma unroll
-    for (int a = 0; a < 8; ++a) fa[a] = *reinterpret_cast<const bf16x8_t *>(lds + fa_base + a * 1024);
+    for (int a = 0; a < 8; ++a) fa[a] = frag_a(lds, a);
 #pragma unroll
-    for (int b = 0; b < 4; ++b) fb[0][b] = *reinterpret_cast<const bf16x8_t *>(lds + fb_base + b * 1024);
+    for (int b = 0; b < 4; ++b) fb[0][b] = frag_b(lds, b);
     int sl_dyn = 0;  // ring slot of the stage being computed (tracked only when !QUAD)
 
-    float run_m[4], run_s[4];  // kEpiLse*: this lane's four columns over the sweep
+    float run_m[4], run_s[4];  // kGemmLse*: this lane's four columns over the sweep
 #pragma unroll
     for (int b = 0; b < 4; ++b) {
         run_m[b] = kNegFloor;
@@ -420,7 +484,7 @@ __global__ __launch_bounds__(kGemmThreads) void gemm_nt_kernel(const GemmArgs g)
         // stage before); u: the stage's position in the cursor's group (0 when !QUAD).
         auto stage = [&](const int sl, const int u, const int p) __attribute__((always_inline)) {
             const int nsl = sl + 1 == kDmaStages ? 0 : sl + 1;
-            const char *nxt = lds + nsl * kDmaStageBytes;
+            char *nxt = lds + nsl * kDmaStageBytes;
             __builtin_amdgcn_sched_barrier(0);
             // The next stage has landed (own loads: the kDmaStages - 2 stages after it may still be in flight) and
             // this stage is in registers (own reads, lgkmcnt(0)): meet.  A bare barrier: the fence that
@@ -432,7 +496,7 @@ __global__ __launch_bounds__(kGemmThreads) void gemm_nt_kernel(const GemmArgs g)
 #pragma unroll
             for (int a = 0; a < 8; ++a) {
                 // a column fragment of the next stage, a direct load into the slot this stage came from ...
-                if (a < 4) fb[p ^ 1][a] = *reinterpret_cast<const bf16x8_t *>(nxt + fb_base + a * 1024);
+                if (a < 4) fb[p ^ 1][a] = frag_b(nxt, a);
                 if ((a & 1) == 0) refill(sl, a >> 2, u, (a >> 1) & 1);
                 // ... four MFMAs ...
 #pragma unroll
@@ -440,7 +504,7 @@ __global__ __launch_bounds__(kGemmThreads) void gemm_nt_kernel(const GemmArgs g)
                     acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[a], fb[p][b], acc[a][b], 0, 0, 0);
                 __builtin_amdgcn_sched_barrier(0);
                 // ... and this row fragment's successor, into the registers those MFMAs have just read
-                fa[a] = *reinterpret_cast<const bf16x8_t *>(nxt + fa_base + a * 1024);
+                fa[a] = frag_a(nxt, a);
                 __builtin_amdgcn_sched_barrier(0);
             }
         };
@@ -469,35 +533,25 @@ __global__ __launch_bounds__(kGemmThreads) void gemm_nt_kernel(const GemmArgs g)
         // ---- the tile's epilogue, while the next tile's first stages arrive ----
         const int64_t p_next = next_tile(p_cur + p_step);
         const bool edge = m0 + kGemmTile > M || n0 + kGemmTile > N;  // uniform
-        if constexpr (EPI != kEpiLse) {
-            // tiles inside C leave with 16-byte stores (the launcher checks that rows of C start on 16 bytes);
-            // only sums into C go element by element, through the memory side's adders
+        if constexpr (SPLIT) {
             float *stage_tile = reinterpret_cast<float *>(lds + kDmaRingBytes + kGemmRedBytes + wave_s * kStageBytes);
-            if (SPLIT && flat) {
-                // this slice's fp32 contribution, added up by gemm_split_reduce_kernel
+            if (flat) {  // this slice's fp32 contribution, added up by gemm_split_reduce_kernel
                 float *part = g.split + (int64_t)cur.slice * M * N;
-                if (edge) store_tile<kEpiAccumF32, true>(acc, part, N, m0, n0, M, N, wm, wn, lane, false);
-                else store_tile_wide<kEpiAccumF32>(acc, part, N, m0, n0, wm, wn, lane, stage_tile);
-            } else if constexpr (SPLIT) {
-                if (edge) store_tile<kEpiStoreBf16, true>(acc, g.C, g.ldc, m0, n0, M, N, wm, wn, lane, false);
-                else store_tile_wide<kEpiStoreBf16>(acc, g.C, g.ldc, m0, n0, wm, wn, lane, stage_tile);
-            } else if (EPI == kEpiStoreBf16 && g.transposed != 0) {
-                uint16_t *ct = reinterpret_cast<uint16_t *>(g.C);
-                if (edge) store_tile_transposed_bf16<true>(acc, ct, g.ldc, m0, n0, M, N, wm, wn, lane);
-                else store_tile_transposed_bf16<false>(acc, ct, g.ldc, m0, n0, M, N, wm, wn, lane);
-            } else if (g.transposed != 0) {
-                float *ct = reinterpret_cast<float *>(g.C);
-                const bool add = EPI == kEpiAccumF32 && g.accumulate != 0;
-                if (edge) store_tile_transposed<true>(acc, ct, g.ldc, m0, n0, M, N, wm, wn, lane, add);
-                else store_tile_transposed<false>(acc, ct, g.ldc, m0, n0, M, N, wm, wn, lane, add);
-            } else if (edge) {
-                store_tile<EPI, true>(acc, g.C, g.ldc, m0, n0, M, N, wm, wn, lane, g.accumulate != 0);
-            } else if constexpr (EPI == kEpiAccumF32) {
-                if (g.accumulate != 0) store_tile<EPI, false>(acc, g.C, g.ldc, m0, n0, M, N, wm, wn, lane, true);
-                else store_tile_wide<EPI>(acc, g.C, g.ldc, m0, n0, wm, wn, lane, stage_tile);
+                if (edge) store_tile_edge<F32>(acc, part, N, m0, n0, M, N, wm, wn, lane);
+                else store_tile_wide<F32>(acc, part, N, m0, n0, wm, wn, lane, stage_tile);
             } else {
-                store_tile_wide<EPI>(acc, g.C, g.ldc, m0, n0, wm, wn, lane, stage_tile);
+                if (edge) store_tile_edge<Bf16>(acc, g.C, g.ldc, m0, n0, M, N, wm, wn, lane);
+                else store_tile_wide<Bf16>(acc, g.C, g.ldc, m0, n0, wm, wn, lane, stage_tile);
             }
+        } else if constexpr (PRODUCT == kGemmPanelsBf16) {
+            uint16_t *ct = reinterpret_cast<uint16_t *>(g.C);
+            if (edge) store_tile_transposed_bf16<true>(acc, ct, g.ldc, m0, n0, M, N, wm, wn, lane);
+            else store_tile_transposed_bf16<false>(acc, ct, g.ldc, m0, n0, M, N, wm, wn, lane);
+        } else if constexpr (PRODUCT != kGemmLse) {
+            float *ct = reinterpret_cast<float *>(g.C);
+            const bool add = PANELS && g.accumulate != 0;
+            if (edge) store_tile_transposed<true>(acc, ct, g.ldc, m0, n0, M, N, wm, wn, lane, add);
+            else store_tile_transposed<false>(acc, ct, g.ldc, m0, n0, M, N, wm, wn, lane, add);
         }
         if constexpr (LSE) {
             const bool ragged = m0 + kGemmTile > M;
@@ -548,7 +602,7 @@ __global__ __launch_bounds__(kGemmThreads) void gemm_nt_kernel(const GemmArgs g)
     __builtin_amdgcn_s_barrier();
 }
 
-// C (bfloat16) = the slices of a kEpiSplitBf16 launch, added in ascending order; nothing when the launch did not slice.
+// C (bfloat16) = the slices of a kGemmSplit* launch, added in ascending order; nothing when the launch did not slice.
 // Memory bound: 8 elements per thread and step, 2 x 16 bytes per slice.
 __global__ __launch_bounds__(256) void gemm_split_reduce_kernel(const GemmArgs g)
 {
@@ -589,53 +643,51 @@ GemmGrid gemm_grid()
     return gg;
 }
 
-template <int EPI, bool QUAD>
+template <int PRODUCT, bool QUAD>
 static hipError_t launch_gemm_t(const GemmArgs &g, hipStream_t s)
 {
     static LdsLimitState lds_limit;
-    auto *kernel = gemm_nt_kernel<EPI, QUAD>;
+    auto *kernel = gemm_kernel<PRODUCT, QUAD>;
     const hipError_t attr_err = ensure_lds_limit(reinterpret_cast<const void *>(kernel), kGemmLdsBytes, lds_limit);
     if (attr_err != hipSuccess) return attr_err;
     hipLaunchKernelGGL(kernel, dim3(g.nxcd * g.per_xcd), dim3(kGemmThreads), kGemmLdsBytes, s, g);
     return hipGetLastError();
 }
 
-template <int EPI>
-static hipError_t launch_gemm_t(const GemmArgs &g, hipStream_t s)
-{
-    return g.K % (kDmaK * kDmaStages) == 0 ? launch_gemm_t<EPI, true>(g, s) : launch_gemm_t<EPI, false>(g, s);
-}
-
-hipError_t launch_gemm_nt(const GemmArgs &args, int epilogue, hipStream_t s)
+hipError_t launch_gemm(const GemmArgs &args, int product, hipStream_t s)
 {
     GemmArgs g = args;
     const GemmGrid gg = gemm_grid();
     g.nxcd = gg.nxcd;
     g.per_xcd = gg.per_xcd;
+    const bool lse = product == kGemmLse || product == kGemmLseStore, quad = g.K % (kDmaK * kDmaStages) == 0;
+    const bool panels = product == kGemmPanelsBf16 || product == kGemmPanelsF32;
     // what the kernel's 32-bit offsets and its stage arithmetic assume
-    if (g.M <= 0 || g.N <= 0 || g.K <= 0 || g.K % 64 != 0 || g.lda % 8 != 0 || g.ldb % 8 != 0 || g.lda < g.K ||
-        g.ldb < g.K || g.lda > (1 << 22) || g.ldb > (1 << 22))
+    if (g.M <= 0 || g.N <= 0 || g.K <= 0 || g.K % 64 != 0 || g.lda % 8 != 0 || g.ldb % 8 != 0 || g.lda > (1 << 22) ||
+        g.ldb > (1 << 22))
         return hipErrorInvalidValue;
-    if (g.dyn_dim != kDynNone && (!g.dyn.n || (g.dyn_dim == kDynK && g.K % 128 != 0))) return hipErrorInvalidValue;
-    if ((g.a_panel && g.lda % 64 != 0) || (g.b_panel && g.ldb % 64 != 0)) return hipErrorInvalidValue;
-    if (g.transposed != 0 && (g.M % 4 != 0 || g.dyn_dim == kDynM || epilogue == kEpiLse)) return hipErrorInvalidValue;
-    if (epilogue != kEpiLse && (g.ldc % 8 != 0 || (reinterpret_cast<uintptr_t>(g.C) & 15) != 0)) return hipErrorInvalidValue;
-    switch (epilogue) {
-        case kEpiLse: return launch_gemm_t<kEpiLse>(g, s);
-        case kEpiLseStore: return launch_gemm_t<kEpiLseStore>(g, s);
-        case kEpiStoreBf16: return launch_gemm_t<kEpiStoreBf16>(g, s);
-        case kEpiAccumF32: return launch_gemm_t<kEpiAccumF32>(g, s);
-        case kEpiSplitBf16: {
-            if (g.K % (kDmaK * kDmaStages) != 0 || g.dyn_dim == kDynK || g.dyn_dim == kDynN || g.N % 8 != 0 ||
-                (g.split_max > 1 && !g.split))
-                return hipErrorInvalidValue;
-            const hipError_t e = launch_gemm_t<kEpiSplitBf16, true>(g, s);
-            if (e != hipSuccess || g.split_max <= 1) return e;
-            hipLaunchKernelGGL(gemm_split_reduce_kernel, dim3(4 * g.nxcd * g.per_xcd), dim3(256), 0, s, g);
-            return hipGetLastError();
-        }
-        default: return hipErrorInvalidValue;
+    if (g.dyn_dim != kDynNone && !g.dyn.n) return hipErrorInvalidValue;
+    if (g.dyn_dim == kDynK && !panels) return hipErrorInvalidValue;
+    if (product != kGemmLse && (g.ldc % 8 != 0 || (reinterpret_cast<uintptr_t>(g.C) & 15) != 0)) return hipErrorInvalidValue;
+    // C^T: groups of four rows
+    if ((product == kGemmLseStore || panels) && (g.M % 4 != 0 || g.dyn_dim == kDynM)) return hipErrorInvalidValue;
+    if (lse) {
+        if (g.lda < g.K || g.ldb < g.K) return hipErrorInvalidValue;
+        if (product == kGemmLse) return quad ? launch_gemm_t<kGemmLse, true>(g, s) : launch_gemm_t<kGemmLse, false>(g, s);
+        return quad ? launch_gemm_t<kGemmLseStore, true>(g, s) : launch_gemm_t<kGemmLseStore, false>(g, s);
     }
+    if (!quad || g.lda % 64 != 0 || g.lda < g.K) return hipErrorInvalidValue;
+    if (panels) {
+        if (g.ldb % 64 != 0 || g.ldb < g.K) return hipErrorInvalidValue;
+        return product == kGemmPanelsBf16 ? launch_gemm_t<kGemmPanelsBf16, true>(g, s) : launch_gemm_t<kGemmPanelsF32, true>(g, s);
+    }
+    if (g.N % 64 != 0 || g.dyn_dim == kDynN || (g.split_max > 1 && !g.split)) return hipErrorInvalidValue;
+    hipError_t e = hipErrorInvalidValue;
+    if (product == kGemmSplitRows && g.k_rows > 0 && g.ldb >= g.N) e = launch_gemm_t<kGemmSplitRows, true>(g, s);
+    else if (product == kGemmSplitPanels && g.ldb % 64 == 0 && g.ldb >= g.K) e = launch_gemm_t<kGemmSplitPanels, true>(g, s);
+    if (e != hipSuccess || g.split_max <= 1) return e;
+    hipLaunchKernelGGL(gemm_split_reduce_kernel, dim3(4 * g.nxcd * g.per_xcd), dim3(256), 0, s, g);
+    return hipGetLastError();
 }
 
 }  // namespace a3po

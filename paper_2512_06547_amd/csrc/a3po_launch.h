@@ -111,13 +111,16 @@ int64_t shard_bwd_queue_items(int dt, int64_t T, int64_t Vs);  // bursts launch_
 // a.V is the shard width here; a.ws_records must come from a prep launch made with the full vocabulary size
 hipError_t launch_shard_bwd_rows(const LossArgs &a, int64_t v0, const float *logp_theta, const float *lse, hipStream_t s);
 
-// ---- bfloat16 contraction on the matrix cores (a3po_gemm.hip): C[M, N] = A[M, K] B[N, K]^T ------------------
-enum GemmEpilogue {
-    kEpiLse = 0,        // running (max, sum) per column n over the rows m -> partial; C untouched
-    kEpiLseStore = 1,   // the same, and C (float) = the product
-    kEpiStoreBf16 = 2,  // C (bfloat16) = the product
-    kEpiAccumF32 = 3,   // C (float) = the product, or += when accumulate is set
-    kEpiSplitBf16 = 4   // C (bfloat16) = the product; few tiles: the contraction is cut into slices (see GemmSplit)
+// ---- bfloat16 contraction on the matrix cores (a3po_gemm.hip): C[m, n] = sum_k A(m, k) B(n, k) ---------------
+// The products that exist, each with the layouts of its operands (see GemmArgs) and its epilogue:
+enum GemmProduct {
+    kGemmLse = 0,        // A rows, B rows: running (max, sum) per column n over the rows m -> partial; C untouched
+    kGemmLseStore = 1,   // the same, and C^T (float) = the product
+    kGemmSplitRows = 2,    // A panels, B slow rows: C (bfloat16) = the product; few tiles: the contraction is cut into
+                           // slices (see gemm_slices)
+    kGemmSplitPanels = 3,  // the same with B panels
+    kGemmPanelsBf16 = 4,   // A panels, B panels: C^T (bfloat16) = the product
+    kGemmPanelsF32 = 5     // the same in float, or += when accumulate is set
 };
 
 // An extent that is only known on the device when the launch is queued (the number of tokens that enter the loss):
@@ -135,23 +138,26 @@ __host__ __device__ inline int64_t dyn_extent(const DynCount &d, int64_t host_va
 
 enum GemmDynDim { kDynNone = 0, kDynM = 1, kDynN = 2, kDynK = 3 };
 
+// Operand layouts (bfloat16, 16-byte aligned base, ld in elements):
+//   rows         [M, K] row-major, row stride ld: the contracted index is the fast one
+//   panels       panel layout (panel_offset) of [M, K]; ld = K extent of the buffer, rows padded to a multiple of 256
+//   slow rows    [K, M] row-major, row stride ld (M a multiple of 64): the contracted index is the slow one
+// Contracted positions beyond those that exist must hold zeros in a panel operand; beyond the last row of a slow-rows
+// operand its last row is read again.
 struct GemmArgs {
-    const uint16_t *A;  // [M, K] bfloat16, row-major, row stride lda elements (a multiple of 8; 16-byte aligned base)
+    const uint16_t *A;
     int64_t lda;
-    const uint16_t *B;  // [N, K] likewise
+    const uint16_t *B;
     int64_t ldb;
-    int64_t M, N, K;    // K a multiple of 64 (operands that need it are zero-padded by the caller)
-    void *C;            // [M, N] row-major, row stride ldc elements
-    int64_t ldc;
-    float2 *partial;    // kEpiLse*: [slots][N] (max, sum) per column (see GemmShape), merged by the caller; room for
+    int64_t M, N, K;    // K a multiple of 64 (the others than kGemmLse*: of 128)
+    int64_t k_rows;     // kGemmSplitRows: rows that B has
+    void *C;            // row stride ldc elements; C^T: element (m, n) at C[n * ldc + m], M a multiple of 4 (a lane's four
+    int64_t ldc;        // accumulator values are then contiguous)
+    float2 *partial;    // kGemmLse*: [slots][N] (max, sum) per column (see GemmShape), merged by the caller; room for
                         // gemm_partial_entries(N) entries
-    float *split;       // kEpiSplitBf16: room for split_max slices of M x N floats (overwritten)
+    float *split;       // kGemmSplit*: room for split_max slices of M x N floats (overwritten)
     int split_max;
-    int a_panel, b_panel;  // the operand is stored in panels instead of rows (see panel_offset): lda / ldb is then the
-                           // K extent of the buffer (a multiple of 64), rows are padded to a multiple of 256
-    int accumulate;     // kEpiAccumF32
-    int transposed;     // kEpiLseStore / kEpiAccumF32: element (m, n) goes to C[n * ldc + m] (C^T row-major, row stride
-                        // ldc): a lane's four accumulator values are then 16 contiguous bytes.  Needs M % 4 == 0.
+    int accumulate;     // kGemmPanelsF32
     int dyn_dim;        // GemmDynDim: which of M, N, K is replaced by dyn_extent(dyn, .) on the device (K: rounded up
     DynCount dyn;       // to 128; the host's M, N, K are then upper bounds).  A zero extent makes the launch a no-op.
     int nxcd, per_xcd;  // filled in by the launcher from the device: the persistent grid (nxcd x per_xcd workgroups)
@@ -187,7 +193,7 @@ __host__ __device__ inline GemmShape gemm_shape(int64_t M, int64_t N, int nxcd, 
     return s;
 }
 
-// Slices of a kEpiSplitBf16 launch.  A product with fewer tiles than compute units (or a last round of tiles that fills
+// Slices of a kGemmSplit* launch.  A product with fewer tiles than compute units (or a last round of tiles that fills
 // few of them) leaves the chip idle for its whole contracted length, so the contraction is cut into slices that are
 // work items of their own; their fp32 results are added in a fixed order by a second kernel.  The number of slices is
 // the one with the least predicted time among those that fill one to four rounds of the grid, in units of 0.1 us:
@@ -196,19 +202,21 @@ __host__ __device__ inline GemmShape gemm_shape(int64_t M, int64_t N, int nxcd, 
 // 0.014 ms as 14 slices; 512 tiles, two full rounds, stay whole: a second slice would only add its traffic.)
 __host__ __device__ inline int gemm_slices(int64_t tiles, int64_t quads, int workgroups, int split_max)
 {
-    auto cost = [&](int64_t n) {
-        const int64_t rounds = (tiles * n + workgroups - 1) / workgroups;
-        return rounds * ((quads + n - 1) / n * 32 + 40) + (n > 1 ? n * tiles * 13 / 10 : 0);
+    if (tiles > 2 * workgroups) return 1;  // (two slices would need more than four rounds)
+    const int t = (int)tiles, q = (int)quads;
+    auto cost = [&](int n) {
+        const int rounds = (t * n + workgroups - 1) / workgroups;
+        return rounds * ((q + n - 1) / n * 32 + 40) + (n > 1 ? n * t * 13 / 10 : 0);
     };
-    int best = 1;
-    int64_t least = cost(1);
+    int best = 1, least = cost(1);
     for (int k = 1; k <= 4; ++k) {
-        int64_t n = (int64_t)k * workgroups / tiles;
+        int n = k * workgroups / t;
         n = n < split_max ? n : split_max;
-        n = n < quads ? n : quads;
-        if (n > 1 && cost(n) < least) {
-            least = cost(n);
-            best = (int)n;
+        n = n < q ? n : q;
+        const int c = n > 1 ? cost(n) : least;
+        if (c < least) {
+            least = c;
+            best = n;
         }
     }
     return best;
@@ -261,7 +269,7 @@ inline size_t gemm_partial_entries(int64_t N)
     for (size_t o : {upto(kGemmMaxBlocks, 256), upto(kGemmMaxBlocks / 2, 512), upto(kGemmMaxBlocks / 3, 2304)}) e = o > e ? o : e;
     return e;
 }
-hipError_t launch_gemm_nt(const GemmArgs &g, int epilogue, hipStream_t s);
+hipError_t launch_gemm(const GemmArgs &args, int product, hipStream_t s);
 
 size_t lmhead_workspace_bytes(int64_t T);
 hipError_t launch_fused_lmhead_logprob(const void *hidden, const void *weight, int64_t T, int64_t H, int64_t V,

@@ -104,7 +104,7 @@ hipError_t launch_fused_lmhead_logprob(const void *hidden, const void *weight, i
     g.N = T;
     g.K = H;
     g.partial = reinterpret_cast<float2 *>(workspace);
-    hipError_t e = launch_gemm_nt(g, kEpiLse, s);
+    hipError_t e = launch_gemm(g, kGemmLse, s);
     if (e != hipSuccess) return e;
     return launch_lmhead_lse_finish(hidden, weight, T, H, V, chosen, g.partial, logp, lse, s);
 }

@@ -19,7 +19,7 @@
 //      bfloat16 straight from the accumulators when one group holds every token, else summed in an fp32
 //      accumulator across groups and rounded to bfloat16 once at the end).
 // All three contractions are the kernel of a3po_gemm.hip, which wants the contracted index contiguous in both
-// operands; W^T and h^T are therefore written once per call.  6 N V H flops per step for N counted tokens: the
+// operands; h^T, and for long batches W^T, are therefore written once per call (short ones take W as it lies).  6 N V H flops per step for N counted tokens: the
 // logits of a chunk are kept (4 bytes each, 5 GB for 8,192 tokens at V = 151,936) rather than recomputed, which
 // would be a fourth contraction.  Finally the rows of dh are scattered back to their tokens.
 #include "a3po_common.h"
@@ -36,6 +36,11 @@ constexpr int64_t kLmBwdChunk = A3PO_LM_BWD_CHUNK;  // tokens whose logits live 
 // whole group in memory (20 GB for 65,536 tokens at V = 151,936; batches up to that size need a single contraction and no
 // accumulation pass at all).
 constexpr int64_t kLmDwGroup = 8;
+// The hidden-state gradient takes W as it lies in batches of fewer tokens than this (its contracted index, the vocabulary,
+// is then the slow one: transposing reads from LDS, 6 % slower than plain ones, 30.2 against 28.5 ms for 36,000 counted
+// tokens x 4,096), and a transposed copy of W from here on, where the copy (0.45 ms at 151,936 x 4,096, 0.17 at 1,536)
+// pays for itself.
+constexpr int64_t kLmTransposeMin = 16384;
 constexpr int64_t kPadK = 128;                      // contracted extents are zero-padded to this
 
 struct LmBwdLayout {
@@ -72,7 +77,7 @@ static LmBwdLayout lmhead_bwd_layout(int64_t T, int64_t V, int64_t H)
     // the four operands that this file's own kernels write are kept in the contraction kernel's panel layout
     l.dz = l.dzt + up(panel_elements(V, l.ldg) * 2);
     l.wt = l.dz + up(panel_elements(l.chunk, l.ldv) * 2);
-    l.hc = l.wt + up(panel_elements(H, l.ldv) * 2);
+    l.hc = l.wt + (T >= kLmTransposeMin ? up(panel_elements(H, l.ldv) * 2) : 0);
     l.ht = l.hc + up(t * h * 2);
     l.dhc = l.ht + up(panel_elements(H, l.ldt) * 2);
     l.dwacc = l.dhc + up(t * h * 2);
@@ -447,7 +452,8 @@ extern "C" int a3po_fused_lmhead_loss_fwd_bwd(const void *hidden, const void *we
                        logp_out, logp_prox_out, a.ws_obj, a.ws_iw, a.ws_flags);
     hipLaunchKernelGGL(gather_rows_kernel, dim3((unsigned)((T + 3) / 4)), dim3(256), 0, s, h, hc, index, n_counted, H);
     if (hipGetLastError() != hipSuccess) return A3PO_E_LAUNCH;
-    if (launch_transpose_pad(W, wt, V, H, lay.ldv, nullptr, s) != hipSuccess) return A3PO_E_LAUNCH;
+    const bool transposed_w = T >= kLmTransposeMin;
+    if (transposed_w && launch_transpose_pad(W, wt, V, H, lay.ldv, nullptr, s) != hipSuccess) return A3PO_E_LAUNCH;
     if (launch_transpose_pad(hc, ht, T, H, lay.ldt, n_counted, s) != hipSuccess) return A3PO_E_LAUNCH;
     if (lay.ldv > V) {  // padding of the contracted index in the token-major gradient chunk: never written below
         const int64_t rows = (lay.chunk + 255) / 256 * 256, cells = rows * (lay.ldv - V);
@@ -477,11 +483,10 @@ extern "C" int a3po_fused_lmhead_loss_fwd_bwd(const void *hidden, const void *we
         fw.K = H;
         fw.C = zt;
         fw.ldc = lay.ldv;
-        fw.transposed = 1;
         fw.partial = partial;
         fw.dyn_dim = kDynN;
         fw.dyn = cnt;
-        if (launch_gemm_nt(fw, kEpiLseStore, s) != hipSuccess) return A3PO_E_LAUNCH;
+        if (launch_gemm(fw, kGemmLseStore, s) != hipSuccess) return A3PO_E_LAUNCH;
         // 2. log pi_theta and the per-token terms
         if (launch_lmhead_lse_finish(hc + c0 * H, W, nmax, H, V, ysel + c0, partial, logp_c + c0, lse + c0, s, cnt) != hipSuccess)
             return A3PO_E_LAUNCH;
@@ -495,14 +500,13 @@ extern "C" int a3po_fused_lmhead_loss_fwd_bwd(const void *hidden, const void *we
         hipLaunchKernelGGL(lmhead_dz_kernel, dz_grid, dim3(256), 0, s, zt, V, cnt, lay.ldv, lse + c0, gtok + c0,
                            ysel + c0, dz, dzt, lay.ldg, c0 - g0);
         if (hipGetLastError() != hipSuccess) return A3PO_E_LAUNCH;
-        // 4. dh_chunk [n, H] = dz [n, V] (W^T [H, V])^T
+        // 4. dh_chunk [n, H] = dz [n, V] W [V, H]
         GemmArgs bh = {};
         bh.A = dz;
         bh.lda = lay.ldv;
-        bh.a_panel = 1;
-        bh.B = wt;
-        bh.ldb = lay.ldv;
-        bh.b_panel = 1;
+        bh.B = transposed_w ? wt : W;
+        bh.ldb = transposed_w ? lay.ldv : H;
+        bh.k_rows = V;
         bh.M = nmax;
         bh.N = H;
         bh.K = lay.ldv;
@@ -513,7 +517,7 @@ extern "C" int a3po_fused_lmhead_loss_fwd_bwd(const void *hidden, const void *we
         // (few tokens: slices of the contraction, in the chunk's logits, which nobody needs any more)
         bh.split = zt;
         bh.split_max = (int)(lay.ldv / H < 256 ? lay.ldv / H : 256);
-        if (launch_gemm_nt(bh, kEpiSplitBf16, s) != hipSuccess) return A3PO_E_LAUNCH;
+        if (launch_gemm(bh, transposed_w ? kGemmSplitPanels : kGemmSplitRows, s) != hipSuccess) return A3PO_E_LAUNCH;
         // 5. at the end of a group of chunks: dW [V, H] += (dz^T [V, group] (h^T [H, group])^T): h^T on the row side
         //    of the tiles, stored transposed; fp32 accumulator across groups
         const bool group_ends = c0 + lay.chunk >= T || (c0 + lay.chunk) % (kLmDwGroup * lay.chunk) == 0;
@@ -526,20 +530,17 @@ extern "C" int a3po_fused_lmhead_loss_fwd_bwd(const void *hidden, const void *we
             GemmArgs bw = {};
             bw.A = ht + panel_offset(0, g0, lay.ldt);
             bw.lda = lay.ldt;
-            bw.a_panel = 1;
             bw.B = dzt;
             bw.ldb = lay.ldg;
-            bw.b_panel = 1;
             bw.M = H;
             bw.N = V;
             bw.K = (gmax + kPadK - 1) / kPadK * kPadK;
             bw.C = single_group ? dweight : static_cast<void *>(dwacc);
             bw.ldc = H;
-            bw.transposed = 1;
             bw.accumulate = g0 > 0;
             bw.dyn_dim = kDynK;
             bw.dyn = gcnt;
-            if (launch_gemm_nt(bw, single_group ? kEpiStoreBf16 : kEpiAccumF32, s) != hipSuccess) return A3PO_E_LAUNCH;
+            if (launch_gemm(bw, single_group ? kGemmPanelsBf16 : kGemmPanelsF32, s) != hipSuccess) return A3PO_E_LAUNCH;
         }
     }
     if (launch_loss_finish(a, s) != hipSuccess) return A3PO_E_LAUNCH;
