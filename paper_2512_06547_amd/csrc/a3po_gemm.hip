@@ -42,15 +42,12 @@
 // every workgroup reads the extent first; beyond it there is nothing to do and it returns.
 #include "a3po_common.h"
 #include "a3po_launch.h"
+#include "a3po_direct.h"
 
 namespace a3po {
 
 constexpr int kGemmThreads = 512;
 constexpr int kGemmWaves = kGemmThreads / kWave;
-
-typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
-typedef float f32x4_t __attribute__((ext_vector_type(4)));
-typedef uint32_t gemm_u32x4_t __attribute__((ext_vector_type(4)));
 
 constexpr int kDmaStages = 4;
 constexpr int kDmaK = 32;                                  // K elements per stage
@@ -63,20 +60,6 @@ constexpr int kGemmRedBytes = 2 * kGemmTile * (int)sizeof(float2);  // column pa
 constexpr int kStageLd = 36;
 constexpr int kStageBytes = 16 * kStageLd * (int)sizeof(float);  // 2,304
 constexpr int kGemmLdsBytes = kDmaRingBytes + kGemmRedBytes + kGemmWaves * kStageBytes;  // 153,600 of 163,840
-
-typedef __attribute__((address_space(3))) void *lds_ptr_t;
-
-__device__ __forceinline__ void dma16(const char *g, char *l)
-{
-    __builtin_amdgcn_global_load_lds(reinterpret_cast<const gemm_u32x4_t *>(g), (lds_ptr_t)l, 16, 0, 0);
-}
-
-// s_waitcnt with the given vector-memory and LDS counts (the export count is left alone)
-__device__ __forceinline__ constexpr int waitcnt_imm(int vmcnt, int lgkmcnt)
-{
-    return 0x0070 | (vmcnt & 15) | ((vmcnt >> 4) << 14) | ((lgkmcnt & 15) << 8);
-}
-constexpr int kNoVmWait = 63, kNoLgkmWait = 15;
 
 // Accumulator layout of a wavefront: acc[a][b][i] is row a 16 + 4 (lane >> 4) + i, column b 16 + (lane & 15) of its
 // 128 x 64 part of the tile.

@@ -276,10 +276,11 @@ hipError_t launch_fused_lmhead_logprob(const void *hidden, const void *weight, i
                                        const int32_t *chosen, float *logp, float *lse, void *workspace, hipStream_t s);
 
 // merges the (max, sum) partials of a token, adds the chosen logit (a dot product) and writes lse and log pi
-// (T is an upper bound when `count` names a device-side token count)
+// (T is an upper bound when `count` names a device-side token count; slots > 0: that many partials per token, all of
+// them written, instead of those of a contraction)
 hipError_t launch_lmhead_lse_finish(const void *hidden, const void *weight, int64_t T, int64_t H, int64_t V,
                                     const int32_t *chosen, const float2 *partial, float *logp,
-                                    float *lse, hipStream_t s, DynCount count = DynCount());
+                                    float *lse, hipStream_t s, DynCount count = DynCount(), int slots = 0);
 
 size_t lmhead_bwd_workspace_bytes(int64_t T, int64_t V, int64_t H);
 

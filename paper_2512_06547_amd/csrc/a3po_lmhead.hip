@@ -5,8 +5,180 @@
 // token, adds the chosen logit (a separate dot product) and writes log pi.
 #include "a3po_common.h"
 #include "a3po_launch.h"
+#include "a3po_direct.h"
 
 namespace a3po {
+
+// ---- few tokens -------------------------------------------------------------------------------------------------
+// Up to 256 tokens the projection is bound by reading the weight, and the contraction kernel, whose ring holds three
+// stages of 16 KiB of it ahead, reads 3.6 TB/s.  Here the weight does not pass through LDS at all: a wavefront owns 32
+// vocabulary entries and loads their rows straight into MFMA operands (lane l: row l & 15, 16 bytes at quarter l >> 4;
+// the two loads of a row block and chunk complete each 128-byte line), four chunks of 64 hidden elements ahead: 128 KiB
+// in flight per compute unit.  The workgroups start at different chunks: all of them at the same offset of rows 8 KiB
+// apart would meet on a few memory channels (16 tokens x 4,096 x 151,936: 309 us so, 253 us apart = 4.9 TB/s; non-temporal
+// loads, which let go of a line after its first half, are slower).  The hidden rows, which all wavefronts share, come
+// through a ring of four chunks in LDS by
+// direct loads; 16-byte piece p of row r sits at piece p ^ ((r >> 1) & 7), so that 16 consecutive rows of one piece fall
+// into distinct banks.  32 rows per wavefront, because every operand read from LDS then feeds two MFMAs (with 16 rows and
+// 256 tokens LDS would be the bound); kAhead of those reads are on the way (two, the compiler's choice: 376 instead of
+// 340 us for 200 tokens).  One workgroup per compute unit, static tiles of 256 vocabulary entries.
+//
+// NB: 16-token column blocks.  H is a multiple of 256 (the loop is unrolled by the ring).  Operations in flight are
+// counted by hand as in the contraction kernel: per chunk NB / 4 direct loads, then 4 operand loads, in this order.
+constexpr int kFewThreads = 512;
+constexpr int kFewWaves = kFewThreads / kWave;
+constexpr int kFewRows = 32 * kFewWaves;  // vocabulary entries per tile
+constexpr int kFewRing = 4;
+constexpr int kAhead = 4;
+constexpr int kFewMaxTokens = 256;
+template <int NB> constexpr int kFewLdsBytes = kFewRing * NB * 16 * 128 + kFewWaves * NB * 16 * (int)sizeof(float2);
+
+template <int NB>
+__global__ __launch_bounds__(kFewThreads) void lmhead_few_tokens_kernel(const uint16_t *__restrict__ W,
+                                                                        const uint16_t *__restrict__ h, int T, int H,
+                                                                        int V, float2 *__restrict__ partial)
+{
+    constexpr int kSlot = NB * 16 * 128;  // bytes of one chunk of the hidden rows
+    constexpr int kDma = NB / 4;          // direct loads per wavefront and chunk
+    static_assert(NB % 4 == 0, "the loads of a chunk are dealt evenly");
+    extern __shared__ __align__(16) char lds[];
+    float2 *red = reinterpret_cast<float2 *>(lds + kFewRing * kSlot);  // [kFewWaves][NB * 16]
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int nch = H / 64, ntiles = (V + kFewRows - 1) / kFewRows;
+    const int64_t row_bytes = (int64_t)H * 2;
+    const int rot = (int)(blockIdx.x % (unsigned)nch);
+    auto chunk_at = [&](int i) { return i + rot < nch ? i + rot : i + rot - nch; };  // the i-th chunk this workgroup takes
+    float2 *my_red = red + wave * (NB * 16);
+    for (int c = lane; c < NB * 16; c += kWave) my_red[c] = make_float2(kNegFloor, 0.0f);
+
+    // hidden rows: load i of a chunk covers rows 8 i .. 8 i + 7, this wavefront's are i = wave * kDma + j
+    const __amdgpu_buffer_rsrc_t hbuf = dma_buffer(h, (uint32_t)(T * row_bytes));  // (at most 256 rows of 2 MiB)
+    uint32_t hoff[kDma];
+#pragma unroll
+    for (int j = 0; j < kDma; ++j) {
+        const int r = (wave * kDma + j) * 8 + (lane >> 3);
+        hoff[j] = (uint32_t)(min(r, T - 1) * row_bytes) + (uint32_t)(((lane & 7) ^ ((r >> 1) & 7)) * 16);
+    }
+    auto load_hidden = [&](int slot, int chunk) {
+#pragma unroll
+        for (int j = 0; j < kDma; ++j) dma16(hbuf, hoff[j], (uint32_t)chunk_at(chunk) * 128u, lds + slot * kSlot + (wave * kDma + j) * 1024);
+    };
+    // weight rows of a tile: this lane's two row blocks (rows past the vocabulary are clamped and masked below)
+    const char *wcur[2], *wnext[2];
+    auto rows_of = [&](int tile, const char **p) {
+#pragma unroll
+        for (int r = 0; r < 2; ++r) {
+            const int v = tile * kFewRows + wave * 32 + r * 16 + (lane & 15);
+            p[r] = reinterpret_cast<const char *>(W) + min(v, V - 1) * row_bytes + (lane >> 4) * 16;
+        }
+    };
+    bf16x8_t a[kFewRing][2][2];  // [chunk mod ring][row block][half of the chunk]
+    auto load_weight = [&](int j, const char *const *p, int i) {
+        const int chunk = chunk_at(i);
+#pragma unroll
+        for (int r = 0; r < 2; ++r)
+#pragma unroll
+            for (int k = 0; k < 2; ++k)
+                a[j][r][k] = __builtin_bit_cast(
+                    bf16x8_t, *reinterpret_cast<const u32x4_t *>(p[r] + chunk * 128 + k * 64));
+    };
+    // a hidden-row operand: row lane & 15 of block b, piece 4 k + (lane >> 4)
+    const uint32_t brow = (uint32_t)(lane & 15) * 128u, bswz = (uint32_t)((lane >> 1) & 7);
+    const uint32_t bpiece[2] = {brow + (((uint32_t)(lane >> 4)) ^ bswz) * 16u, brow + ((4u + (uint32_t)(lane >> 4)) ^ bswz) * 16u};
+
+    int tile = blockIdx.x;
+    rows_of(tile, wcur);
+#pragma unroll
+    for (int j = 0; j < kFewRing; ++j) {
+        load_weight(j, wcur, j);
+        asm volatile("" ::: "memory");  // (keeps the two kinds of loads in the order that is counted on)
+        __builtin_amdgcn_sched_barrier(0);
+        if (j < kFewRing - 1) load_hidden(j, j);
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    for (; tile < ntiles; tile += gridDim.x) {
+        rows_of(tile + (int)gridDim.x < ntiles ? tile + (int)gridDim.x : tile, wnext);  // (past the end: read again, unused)
+        f32x4_t acc[2][NB];
+#pragma unroll
+        for (int r = 0; r < 2; ++r)
+#pragma unroll
+            for (int b = 0; b < NB; ++b)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) acc[r][b][i] = 0.0f;
+#pragma unroll 1
+        for (int c = 0; c < nch; c += kFewRing) {
+            const bool last = c + kFewRing >= nch;
+#pragma unroll
+            for (int j = 0; j < kFewRing; ++j) {
+                __builtin_amdgcn_sched_barrier(0);
+                // this chunk's hidden rows have landed (own loads: everything issued after them may still fly) and the
+                // reads of the chunk before are done: meet, then refill the slot of the chunk before
+                __builtin_amdgcn_s_waitcnt(waitcnt_imm(12 + 2 * kDma, 0));
+                __builtin_amdgcn_s_barrier();
+                __builtin_amdgcn_sched_barrier(0);
+                const int ahead = c + j + kFewRing - 1;
+                load_hidden((j + kFewRing - 1) % kFewRing, ahead < nch ? ahead : ahead - nch);
+                __builtin_amdgcn_sched_barrier(0);
+                const char *stage = lds + j * kSlot;
+                // 2 NB operands of hidden rows, kAhead of them on the way while one is used
+                bf16x8_t fb[kAhead + 1];
+                auto read = [&](int i) {
+                    fb[i % (kAhead + 1)] = *reinterpret_cast<const bf16x8_t *>(stage + (i % NB) * 2048 + bpiece[i / NB]);
+                };
+#pragma unroll
+                for (int i = 0; i < kAhead; ++i) read(i);
+#pragma unroll
+                for (int i = 0; i < 2 * NB; ++i) {
+                    if (i + kAhead < 2 * NB) read(i + kAhead);
+#pragma unroll
+                    for (int r = 0; r < 2; ++r)
+                        acc[r][i % NB] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[j][r][i / NB], fb[i % (kAhead + 1)],
+                                                                                 acc[r][i % NB], 0, 0, 0);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+                __builtin_amdgcn_sched_barrier(0);
+                load_weight(j, last ? wnext : wcur, last ? c + j + kFewRing - nch : c + j + kFewRing);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+        // fold the tile: accumulator (r, b, i) is entry r 16 + 4 (lane >> 4) + i of this wavefront's 32, token b 16 + (lane & 15)
+        const int left = V - tile * kFewRows - wave * 32 - 4 * (lane >> 4);
+#pragma unroll
+        for (int b = 0; b < NB; ++b) {
+            float f[8];
+#pragma unroll
+            for (int r = 0; r < 2; ++r)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) f[r * 4 + i] = r * 16 + i < left ? acc[r][b][i] : -INFINITY;
+            MaxSum mine = {kNegFloor, 0.0f};
+            fold<8>(mine, f);
+#pragma unroll
+            for (int off = 16; off <= 32; off <<= 1) {
+                const MaxSum other = {__shfl_xor(mine.m, off, kWave), __shfl_xor(mine.s, off, kWave)};
+                mine = combine(mine, other);
+            }
+            if (lane < 16) {  // (this wavefront's own row of red)
+                const float2 q = my_red[b * 16 + lane];
+                mine = combine(MaxSum{q.x, q.y}, mine);
+                my_red[b * 16 + lane] = make_float2(mine.m, mine.s);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+#pragma unroll
+        for (int r = 0; r < 2; ++r) wcur[r] = wnext[r];
+    }
+    __syncthreads();  // (also drains the loads past the last tile)
+    if (tid < NB * 16 && tid < T) {
+        MaxSum tot = {kNegFloor, 0.0f};
+        for (int w = 0; w < kFewWaves; ++w) {
+            const float2 q = red[w * (NB * 16) + tid];
+            tot = combine(tot, MaxSum{q.x, q.y});
+        }
+        partial[(int64_t)blockIdx.x * T + tid] = make_float2(tot.m, tot.s);
+    }
+    __builtin_amdgcn_s_waitcnt(waitcnt_imm(0, 0));
+}
 
 // z[t, y_t] = h[t, :] . W[y_t, :] in fp32, one wavefront per token; then
 // lse_t from the partials of the workgroups that swept this token and log pi = z_y - lse.
@@ -17,7 +189,7 @@ __global__ __launch_bounds__(256) void lmhead_finish_kernel(const uint16_t *__re
                                                             const uint16_t *__restrict__ h, int64_t T, int64_t H,
                                                             int64_t V, const int32_t *__restrict__ chosen,
                                                             const float2 *__restrict__ partial, int nxcd, int per_xcd,
-                                                            float *logp, float *lse_out, DynCount count)
+                                                            int slots, float *logp, float *lse_out, DynCount count)
 {
     const int lane = threadIdx.x & 63;
     const int64_t t = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
@@ -30,7 +202,12 @@ __global__ __launch_bounds__(256) void lmhead_finish_kernel(const uint16_t *__re
     const GemmShape shp = gemm_shape(V, N, nxcd, per_xcd);
     const int64_t pairs = (int64_t)shp.groups * shp.rounds, g0 = (t / kGemmTile / shp.ncol) * shp.rounds;
     MaxSum tot = {kNegFloor, 0.0f};
-    for (int p = lane; p < nxcd * shp.ml; p += kWave) {
+    // (slots > 0: that many partials, all of them written)
+    for (int p = lane; p < slots; p += kWave) {
+        const float2 q = partial[(int64_t)p * N + t];
+        tot = combine(tot, MaxSum{q.x, q.y});
+    }
+    for (int p = lane; slots == 0 && p < nxcd * shp.ml; p += kWave) {
         const int xcd = p / shp.ml, m = p % shp.ml;
         const int64_t lo = max((int64_t)xcd * pairs / nxcd, g0), hi = min((int64_t)(xcd + 1) * pairs / nxcd, g0 + shp.rounds);
         if (lo < hi && (lo - g0) * shp.ml + m < shp.mtiles) {
@@ -81,13 +258,26 @@ size_t lmhead_workspace_bytes(int64_t T)
 
 hipError_t launch_lmhead_lse_finish(const void *hidden, const void *weight, int64_t T, int64_t H, int64_t V,
                                     const int32_t *chosen, const float2 *partial, float *logp,
-                                    float *lse, hipStream_t s, DynCount count)
+                                    float *lse, hipStream_t s, DynCount count, int slots)
 {
     const unsigned grid = (unsigned)((T + 3) / 4);
     const GemmGrid gg = gemm_grid();
     hipLaunchKernelGGL(lmhead_finish_kernel, dim3(grid), dim3(256), 0, s, reinterpret_cast<const uint16_t *>(weight),
-                       reinterpret_cast<const uint16_t *>(hidden), T, H, V, chosen, partial, gg.nxcd, gg.per_xcd, logp,
-                       lse, count);
+                       reinterpret_cast<const uint16_t *>(hidden), T, H, V, chosen, partial, gg.nxcd, gg.per_xcd, slots,
+                       logp, lse, count);
+    return hipGetLastError();
+}
+
+template <int NB>
+static hipError_t launch_few_tokens(const void *hidden, const void *weight, int64_t T, int64_t H, int64_t V, float2 *partial,
+                                    int slots, hipStream_t s)
+{
+    static LdsLimitState lds_limit;
+    auto *kernel = lmhead_few_tokens_kernel<NB>;
+    const hipError_t e = ensure_lds_limit(reinterpret_cast<const void *>(kernel), kFewLdsBytes<NB>, lds_limit);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(kernel, dim3(slots), dim3(kFewThreads), kFewLdsBytes<NB>, s, reinterpret_cast<const uint16_t *>(weight),
+                       reinterpret_cast<const uint16_t *>(hidden), (int)T, (int)H, (int)V, partial);
     return hipGetLastError();
 }
 
@@ -95,6 +285,22 @@ hipError_t launch_fused_lmhead_logprob(const void *hidden, const void *weight, i
                                        const int32_t *chosen, float *logp, float *lse, void *workspace, hipStream_t s)
 {
     if (T == 0) return hipSuccess;
+    float2 *partial = reinterpret_cast<float2 *>(workspace);
+    // Few tokens: the kernel for them up to 128; from 129 to 256 where its tiles occupy most compute units (65,536 x 2
+    // bytes of hidden rows per tile then weigh as much as the weight).  Contraction kernel / this one, us:
+    // 16 / 128 / 200 tokens x 4,096 x 151,936 347 / 334 / 346 and 253 / 271 / 336; 250 x 2,048 x 128,256 156 and 145,
+    // 250 x 1,536 x 50,264 (197 tiles) 58 and 57, 200 x 2,048 x 32,000 (125 tiles) 53 and 57.
+    const GemmGrid gg = gemm_grid();
+    const int64_t tiles = (V + kFewRows - 1) / kFewRows, cus = (int64_t)gg.nxcd * gg.per_xcd;
+    const bool few = T <= 128 || (T <= kFewMaxTokens && tiles >= cus * 3 / 4);
+    if (few && H % 256 == 0 && V <= 0x7FFFFFFF - 256 * kFewRows) {
+        const int slots = (int)(tiles < cus ? tiles : cus);  // at most 256: gemm_partial_entries(T) is 256 T here
+        const hipError_t e = T <= 64    ? launch_few_tokens<4>(hidden, weight, T, H, V, partial, slots, s)
+                             : T <= 128 ? launch_few_tokens<8>(hidden, weight, T, H, V, partial, slots, s)
+                                        : launch_few_tokens<16>(hidden, weight, T, H, V, partial, slots, s);
+        if (e != hipSuccess) return e;
+        return launch_lmhead_lse_finish(hidden, weight, T, H, V, chosen, partial, logp, lse, s, DynCount(), slots);
+    }
     GemmArgs g = {};
     g.A = reinterpret_cast<const uint16_t *>(weight);
     g.lda = H;
@@ -103,7 +309,7 @@ hipError_t launch_fused_lmhead_logprob(const void *hidden, const void *weight, i
     g.M = V;
     g.N = T;
     g.K = H;
-    g.partial = reinterpret_cast<float2 *>(workspace);
+    g.partial = partial;
     hipError_t e = launch_gemm(g, kGemmLse, s);
     if (e != hipSuccess) return e;
     return launch_lmhead_lse_finish(hidden, weight, T, H, V, chosen, g.partial, logp, lse, s);

@@ -35,12 +35,15 @@ def close(gpu, ref, what):
 
 @pytest.mark.parametrize("T,H,V", [(1, 64, 1), (5, 64, 7), (256, 128, 256), (300, 192, 1000), (257, 64, 2049),
                                    (1100, 256, 4500), (2048, 128, 2304), (9000, 64, 300), (700, 320, 20000),
-                                   (200, 128, 17000), (512, 64, 16900), (1500, 64, 9000), (2304, 64, 2561)])
+                                   (200, 128, 17000), (512, 64, 16900), (1500, 64, 9000), (2304, 64, 2561),
+                                   (1, 256, 1), (17, 512, 255), (64, 256, 66000), (65, 768, 2817), (128, 256, 131500),
+                                   (129, 1024, 257), (255, 256, 66049), (256, 512, 70000), (257, 256, 512)])
 def test_fused_lmhead_logprob_small(a3po, T, H, V):
     # spans: single partial tile, exact tile multiples, ragged token and vocabulary tiles, hidden sizes that are and
     # are not a multiple of the ring depth, more token-tile groups than XCDs (several sweeps per workgroup), more
     # vocabulary tiles than one round of an XCD's workgroups, XCDs that share a token group, one to nine token tiles
-    # (blocks of one, two, three and four columns)
+    # (blocks of one, two, three and four columns), and up to 256 tokens with a hidden size that is a multiple of 256 (the
+    # weight straight to the matrix cores): 64, 128 and 256 token columns, fewer tiles than workgroups and several each
     r = np.random.default_rng(T * 131 + V)
     h = bf16_bits(r.standard_normal((T, H)))
     W = bf16_bits(r.standard_normal((V, H)) * 0.3)
