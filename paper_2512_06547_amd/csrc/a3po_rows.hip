@@ -12,6 +12,7 @@
 // gradient of each vector is stored while the next is being computed.
 #include "a3po_common.h"
 #include "a3po_launch.h"
+#include "a3po_direct.h"
 
 namespace a3po {
 
@@ -408,7 +409,11 @@ __global__ __launch_bounds__(NT, row_waves_per_simd(NT, NSWEEP, ENT)) void loss_
 //   sweeps 0 .. kLongReg-1            in vector registers, as in the kernel above;
 //   the next up to kLongLds sweeps    in LDS, brought there by direct global -> LDS loads (no registers, no LDS
 //                                     write instructions; lane l of a wavefront lands at base + 16 l, so a thread
-//                                     reads back exactly the 16 bytes its own load wrote and no barrier is needed);
+//                                     reads back exactly the 16 bytes its own load wrote and no barrier is needed;
+//                                     in the buffer form, behind which the folds of the register sweeps start as
+//                                     these arrive - with the global form they waited for the whole burst: 4,096 rows
+//                                     of fp32 x 90,000 / bf16 x 180,000 496 / 518 us, now 478 / 498; fp32 x 151,936,
+//                                     whose tail decides, 894 and 892);
 //   the rest ("tail")                 streamed: read once for the forward reduction, last of all, and read again
 //                                     at the end of the backward pass, latest sweeps first.
 // Registers plus LDS hold 28 sweeps = 448 KiB, three quarters of an fp32 row of 151,936 (594 KiB): at most 2.25
@@ -421,8 +426,6 @@ constexpr int kLongLds = 9;
 constexpr int kLongTailUnroll = 4;  // tail vectors in flight per thread
 constexpr int kLongStashBytes = kLongLds * (int)kSweepBytes;
 constexpr int kLongLdsBytes = kLongStashBytes + (6 * kRowWaves + 2) * (int)sizeof(float);
-
-typedef __attribute__((address_space(3))) void *rows_lds_ptr_t;
 
 __device__ __forceinline__ uint4 cached_load(const char *p) { return *reinterpret_cast<const uint4 *>(p); }
 
@@ -512,14 +515,14 @@ __global__ __launch_bounds__(kRowThreads) void loss_rows_long_kernel(
                 v[k] = stream_load(in_row + (size_t)k * kSweepBytes + voff);
                 __builtin_amdgcn_sched_barrier(0);
             }
-            // LDS sweeps; a lane past the row's end fetches the row's last vector instead (its data is never used)
+            // LDS sweeps; a lane past the row's end fetches the row's last vector instead (its data is never used).
+            // Always kLongLds of them, also where the row has fewer: the compiler then knows how many loads are in flight
+            // behind each register sweep.
+            const __amdgpu_buffer_rsrc_t row_buf = dma_buffer(in_row, (uint32_t)min(nvec, 1 << 20) * 16u);
 #pragma unroll
             for (int j = 0; j < kLongLds; ++j) {
-                if (j < lds_sweeps) {
-                    const uint32_t idx = (uint32_t)min((NREG + j) * kRowThreads + tid_r, nvec - 1);
-                    __builtin_amdgcn_global_load_lds(reinterpret_cast<const u32x4_t *>(in_row + (size_t)(idx * 16u)),
-                                                     (rows_lds_ptr_t)(smem + j * (int)kSweepBytes + wave_s * 1024), 16, 0, 0);
-                }
+                const uint32_t idx = (uint32_t)min((NREG + j) * kRowThreads + tid_r, nvec - 1);
+                dma16(row_buf, idx * 16u, 0u, smem + j * (int)kSweepBytes + wave_s * 1024);
                 __builtin_amdgcn_sched_barrier(0);
             }
 
@@ -532,8 +535,8 @@ __global__ __launch_bounds__(kRowThreads) void loss_rows_long_kernel(
                 fold<EPV>(acc, f);
                 __builtin_amdgcn_sched_barrier(0);
             }
-            // the direct loads are invisible to the compiler's dependency tracking: wait for them by hand
-            __builtin_amdgcn_s_waitcnt(0x0070 | (15 << 8));  // vmcnt(0), LDS count untouched
+            // the direct loads are waited for by hand, all at once (sweep by sweep is no faster)
+            __builtin_amdgcn_s_waitcnt(waitcnt_imm(0, kNoLgkmWait));
             __builtin_amdgcn_sched_barrier(0);
             for (int j = 0; j < lds_sweeps; ++j) {
                 const int idx = (NREG + j) * kRowThreads + tid;
