@@ -13,7 +13,7 @@ namespace a3po {
 // Up to 256 tokens the projection is bound by reading the weight, and the contraction kernel, whose ring holds three
 // stages of 16 KiB of it ahead, reads 3.6 TB/s.  Here the weight does not pass through LDS at all: a wavefront owns 32
 // vocabulary entries and loads their rows straight into MFMA operands (lane l: row l & 15, 16 bytes at quarter l >> 4;
-// the two loads of a row block and chunk complete each 128-byte line), four chunks of 64 hidden elements ahead: 128 KiB
+// the two loads of a row block and chunk complete each 128-byte line), four chunks of 64 hidden elements ahead: 96 to 128 KiB
 // in flight per compute unit.  The workgroups start at different chunks: all of them at the same offset of rows 8 KiB
 // apart would meet on a few memory channels (16 tokens x 4,096 x 151,936: 309 us so, 253 us apart = 4.9 TB/s; non-temporal
 // loads, which let go of a line after its first half, are slower).  The hidden rows, which all wavefronts share, come
@@ -24,7 +24,8 @@ namespace a3po {
 // 340 us for 200 tokens).  One workgroup per compute unit, static tiles of 256 vocabulary entries.
 //
 // NB: 16-token column blocks.  H is a multiple of 256 (the loop is unrolled by the ring).  Operations in flight are
-// counted by hand as in the contraction kernel: per chunk NB / 4 direct loads, then 4 operand loads, in this order.
+// counted by hand as in the contraction kernel: per chunk NB / 4 direct loads, then 4 operand loads, in this order (held to
+// in the source by in_order; tests/test_schedule.py reads it off the compiled kernel).
 constexpr int kFewThreads = 512;
 constexpr int kFewWaves = kFewThreads / kWave;
 constexpr int kFewRows = 32 * kFewWaves;  // vocabulary entries per tile
@@ -34,7 +35,7 @@ constexpr int kFewMaxTokens = 256;
 template <int NB> constexpr int kFewLdsBytes = kFewRing * NB * 16 * 128 + kFewWaves * NB * 16 * (int)sizeof(float2);
 
 template <int NB>
-__global__ __launch_bounds__(kFewThreads) void lmhead_few_tokens_kernel(const uint16_t *__restrict__ W,
+__global__ __launch_bounds__(kFewThreads) void lmhead_few_tokens_kernel(const uint16_t *W,
                                                                         const uint16_t *__restrict__ h, int T, int H,
                                                                         int V, float2 *__restrict__ partial)
 {
@@ -86,18 +87,24 @@ __global__ __launch_bounds__(kFewThreads) void lmhead_few_tokens_kernel(const ui
     const uint32_t brow = (uint32_t)(lane & 15) * 128u, bswz = (uint32_t)((lane >> 1) & 7);
     const uint32_t bpiece[2] = {brow + (((uint32_t)(lane >> 4)) ^ bswz) * 16u, brow + ((4u + (uint32_t)(lane >> 4)) ^ bswz) * 16u};
 
-    int tile = blockIdx.x;
+    // Keeps the two kinds of loads in the order that is counted on: the compiler moves no load across the memory clobber
+    // (W is no __restrict__ pointer, through which it would) and no instruction across the scheduling barrier.
+    auto in_order = [&]() {
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_sched_barrier(0);
+    };
+
+    int tile = blockIdx.x;  // (the grid has no more workgroups than there are tiles)
     rows_of(tile, wcur);
 #pragma unroll
     for (int j = 0; j < kFewRing; ++j) {
         load_weight(j, wcur, j);
-        asm volatile("" ::: "memory");  // (keeps the two kinds of loads in the order that is counted on)
-        __builtin_amdgcn_sched_barrier(0);
+        in_order();
         if (j < kFewRing - 1) load_hidden(j, j);
-        asm volatile("" ::: "memory");
-        __builtin_amdgcn_sched_barrier(0);
+        in_order();
     }
-    for (; tile < ntiles; tile += gridDim.x) {
+    // (no test before the first tile: the loads above would be moved behind it)
+    do {
         rows_of(tile + (int)gridDim.x < ntiles ? tile + (int)gridDim.x : tile, wnext);  // (past the end: read again, unused)
         f32x4_t acc[2][NB];
 #pragma unroll
@@ -119,7 +126,7 @@ __global__ __launch_bounds__(kFewThreads) void lmhead_few_tokens_kernel(const ui
                 __builtin_amdgcn_sched_barrier(0);
                 const int ahead = c + j + kFewRing - 1;
                 load_hidden((j + kFewRing - 1) % kFewRing, ahead < nch ? ahead : ahead - nch);
-                __builtin_amdgcn_sched_barrier(0);
+                in_order();
                 const char *stage = lds + j * kSlot;
                 // 2 NB operands of hidden rows, kAhead of them on the way while one is used
                 bf16x8_t fb[kAhead + 1];
@@ -137,9 +144,9 @@ __global__ __launch_bounds__(kFewThreads) void lmhead_few_tokens_kernel(const ui
                                                                                  acc[r][i % NB], 0, 0, 0);
                     __builtin_amdgcn_sched_barrier(0);
                 }
-                __builtin_amdgcn_sched_barrier(0);
+                in_order();
                 load_weight(j, last ? wnext : wcur, last ? c + j + kFewRing - nch : c + j + kFewRing);
-                __builtin_amdgcn_sched_barrier(0);
+                in_order();
             }
         }
         // fold the tile: accumulator (r, b, i) is entry r 16 + 4 (lane >> 4) + i of this wavefront's 32, token b 16 + (lane & 15)
@@ -167,7 +174,8 @@ __global__ __launch_bounds__(kFewThreads) void lmhead_few_tokens_kernel(const ui
         }
 #pragma unroll
         for (int r = 0; r < 2; ++r) wcur[r] = wnext[r];
-    }
+        tile += (int)gridDim.x;
+    } while (tile < ntiles);
     __syncthreads();  // (also drains the loads past the last tile)
     if (tid < NB * 16 && tid < T) {
         MaxSum tot = {kNegFloor, 0.0f};

@@ -1,0 +1,62 @@
+"""Properties of the compiled kernels that their sources rely on and no run can show: read from the assembly that the
+compiler writes for this library's own files (no GPU needed)."""
+import os
+import re
+import subprocess
+
+import pytest
+
+from paper_2512_06547_amd import build
+
+
+@pytest.fixture(scope="module")
+def assembly(tmp_path_factory):
+    done = {}
+
+    def of(name):
+        if name not in done:
+            out = str(tmp_path_factory.mktemp("asm") / (name + ".s"))
+            subprocess.check_call([build.HIPCC, *build.FLAGS, "--offload-device-only", "-S", os.path.join(build.CSRC, name),
+                                   "-o", out], stderr=subprocess.DEVNULL)
+            with open(out) as f:
+                done[name] = f.read()
+        return done[name]
+
+    return of
+
+
+def kernels(text, name):
+    """{mangled name: body} of the kernels whose name holds `name`."""
+    found = {m.group(1): m.group(2) for m in
+             re.finditer(r"^(_ZN4a3po\w*" + name + r"\w*):[^\n]*\n(.*?)\n\s*s_endpgm", text, re.S | re.M)}
+    assert found, f"no kernel {name}"
+    return found
+
+
+def memory_events(body):
+    """The vector memory operations, waits on them and barriers of a kernel, in program order."""
+    events = []
+    for line in body.splitlines():
+        line = line.split(";")[0].strip()
+        op = line.split(" ")[0] if line else ""
+        if re.match(r"(global|buffer|flat|scratch)_(load|store)", op):
+            events.append("direct" if line.endswith(" lds") else op)
+        elif op == "s_barrier":
+            events.append("barrier")
+        elif op == "s_waitcnt" and "vmcnt" in line:
+            events.append(int(re.search(r"vmcnt\((\d+)\)", line).group(1)))
+    return events
+
+
+@pytest.mark.parametrize("blocks", [4, 8, 16])
+def test_few_token_kernel_issues_loads_in_the_counted_order(assembly, blocks):
+    """lmhead_few_tokens_kernel waits for its hidden rows by a number of operations that may still be in flight, which
+    holds for one order of issue: weight and hidden rows of a chunk in turn before the loop (no hidden rows for the
+    fourth chunk), then per chunk the hidden rows three chunks ahead and the weight four ahead.  No wait in the loop may
+    ask for more than that number either: it would drain the weight's loads."""
+    body, = kernels(assembly("a3po_lmhead.hip"), f"lmhead_few_tokens_kernelILi{blocks}E").values()
+    events, direct, load = memory_events(body), ["direct"] * (blocks // 4), ["global_load_dwordx4"] * 4
+    wait = [12 + 2 * (blocks // 4), "barrier"]
+    steady = (load + direct) * 3 + load + (wait + direct + load) * 4
+    first = events.index("barrier")
+    assert events[:len(steady)] == steady, events[:max(first + 1, len(steady))]
