@@ -176,6 +176,9 @@ __device__ __forceinline__ void store_tile_transposed_bf16(const f32x4_t (&acc)[
 // tile in LDS that belongs to this wavefront alone (LDS instructions of one wavefront execute in order, so no waits
 // or barriers are needed between its writes and its reads) and leave as 8 rows x 128 bytes (fp32) or 8 rows x 64
 // bytes (bfloat16) per store instruction.
+// (__restrict__: the read then has an alias scope of its own.  Without one the compiler takes the staging tile for a part
+// of the ring and waits for every direct load in flight before the first read of each tile.)
+__device__ __forceinline__ float4 staged(const float *__restrict__ p) { return *reinterpret_cast<const float4 *>(p); }
 template <typename DT>
 __device__ __forceinline__ void store_tile_wide(const f32x4_t (&acc)[8][4], void *C, int64_t ldc, int64_t m0, int64_t n0,
                                                 int wm, int wn, int lane, float *stage)
@@ -194,7 +197,7 @@ __device__ __forceinline__ void store_tile_wide(const f32x4_t (&acc)[8][4], void
             const int64_t at = (m0 + wm * 128 + a * 16 + rrow) * ldc + n0 + wn * 64 + bp * 32 + rcol;
 #pragma unroll
             for (int pass = 0; pass < 2; ++pass) {
-                const float4 v = *reinterpret_cast<const float4 *>(stage + (rrow + 8 * pass) * kStageLd + rcol);
+                const float4 v = staged(stage + (rrow + 8 * pass) * kStageLd + rcol);
                 if constexpr (DT::kBytes == 2) {
                     *reinterpret_cast<uint2 *>(reinterpret_cast<uint16_t *>(C) + at + (int64_t)pass * 8 * ldc) =
                         make_uint2(pack_bf16x2(v.x, v.y), pack_bf16x2(v.z, v.w));
@@ -518,13 +521,17 @@ __global__ __launch_bounds__(kGemmThreads) void gemm_kernel(const GemmArgs g)
         const bool edge = m0 + kGemmTile > M || n0 + kGemmTile > N;  // uniform
         if constexpr (SPLIT) {
             float *stage_tile = reinterpret_cast<float *>(lds + kDmaRingBytes + kGemmRedBytes + wave_s * kStageBytes);
+            // (a copy of the lane number that the compiler cannot see through: the four stores' addresses are computed
+            // here instead of being kept, and spilled, across the K loop)
+            int lane_e = lane;
+            asm volatile("" : "+v"(lane_e));
             if (flat) {  // this slice's fp32 contribution, added up by gemm_split_reduce_kernel
                 float *part = g.split + (int64_t)cur.slice * M * N;
-                if (edge) store_tile_edge<F32>(acc, part, N, m0, n0, M, N, wm, wn, lane);
-                else store_tile_wide<F32>(acc, part, N, m0, n0, wm, wn, lane, stage_tile);
+                if (edge) store_tile_edge<F32>(acc, part, N, m0, n0, M, N, wm, wn, lane_e);
+                else store_tile_wide<F32>(acc, part, N, m0, n0, wm, wn, lane_e, stage_tile);
             } else {
-                if (edge) store_tile_edge<Bf16>(acc, g.C, g.ldc, m0, n0, M, N, wm, wn, lane);
-                else store_tile_wide<Bf16>(acc, g.C, g.ldc, m0, n0, wm, wn, lane, stage_tile);
+                if (edge) store_tile_edge<Bf16>(acc, g.C, g.ldc, m0, n0, M, N, wm, wn, lane_e);
+                else store_tile_wide<Bf16>(acc, g.C, g.ldc, m0, n0, wm, wn, lane_e, stage_tile);
             }
         } else if constexpr (PRODUCT == kGemmPanelsBf16) {
             uint16_t *ct = reinterpret_cast<uint16_t *>(g.C);

@@ -28,7 +28,7 @@ def assembly(tmp_path_factory):
 def kernels(text, name):
     """{mangled name: body} of the kernels whose name holds `name`."""
     found = {m.group(1): m.group(2) for m in
-             re.finditer(r"^(_ZN4a3po\w*" + name + r"\w*):[^\n]*\n(.*?)\n\s*s_endpgm", text, re.S | re.M)}
+             re.finditer(r"^(_ZN4a3po\w*" + name + r"\w*):[^\n]*\n(.*?)\n\.Lfunc_end", text, re.S | re.M)}
     assert found, f"no kernel {name}"
     return found
 
@@ -60,3 +60,17 @@ def test_few_token_kernel_issues_loads_in_the_counted_order(assembly, blocks):
     steady = (load + direct) * 3 + load + (wait + direct + load) * 4
     first = events.index("barrier")
     assert events[:len(steady)] == steady, events[:max(first + 1, len(steady))]
+
+
+@pytest.mark.parametrize("product", ["SplitRows", "SplitPanels", "PanelsBf16", "PanelsF32"])
+def test_contraction_epilogue_leaves_the_ring_in_flight(assembly, product):
+    """gemm_kernel writes a tile out while the direct loads of the next one arrive: between the waits that are counted by
+    hand (12 operations in flight before the loop, 8 per stage) and the one at the kernel's end it waits for no vector
+    memory operation - which a spilled register, or a read of the staging tile that the compiler holds for a read of
+    the ring, would bring."""
+    number = {"SplitRows": 2, "SplitPanels": 3, "PanelsBf16": 4, "PanelsF32": 5}[product]
+    text = assembly("a3po_gemm.hip")
+    (name, body), = kernels(text, f"gemm_kernelILi{number}E").items()
+    events = memory_events(body)
+    assert not [e for e in events if str(e).startswith("scratch")]
+    assert [e for e in events if isinstance(e, int)] == [12, 8, 8, 8, 8, 0]
