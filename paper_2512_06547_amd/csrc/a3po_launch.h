@@ -165,10 +165,13 @@ struct GemmArgs {
 
 // How the workgroups of an XCD (per_xcd of them) share the tile grid: a block of ml rows x ncol columns of tiles, whose
 // operand tiles they share through that XCD's L2; the tile grid is cut into `groups` column groups of ncol tiles and
-// `rounds` of ml tile rows.  Four columns where there are enough of them (8 x 4 tiles on 32 compute units); fewer
-// columns, or fewer rows, than a block holds are spread evenly over as many blocks as they need, and the other side of
-// the block takes the workgroups that this frees.  A launch with the log-sum-exp epilogue leaves one partial per column
-// in each of nxcd * ml slots (slot = xcd * ml + row of the block) that had a tile of that column.
+// `rounds` of ml tile rows.  Four columns where there are enough of them (8 x 4 tiles on 32 compute units); up to three,
+// or five, six or nine, go as blocks of one to three columns, whose rows take the workgroups that this frees, and rows that
+// would leave XCDs without a block are cut into more rounds, whose columns then take them.  (Thirteen columns are
+// still 4 + 4 + 4 + 1.)  More blocks than XCDs for that would be a second round for some of them: 16 x 12 tiles as 9
+// blocks of 6 x 5 took two rounds for the one of 6 blocks of 8 x 4 (3,000 tokens x 4,096 x 4,000: 160 us, now 110).  A
+// launch with the log-sum-exp epilogue leaves one partial per column in each of nxcd * ml slots (slot = xcd * ml + row of
+// the block) that had a tile of that column.
 // (A fixed 8 x 4 block left three workgroups in four idle for a single column of tiles: log-probs of 200 tokens x
 // 4,096 x 151,936 925 us so, 333 us with blocks of 32 x 1; weight gradient with 6 tile rows 500 against 424 us.)
 struct GemmShape {
@@ -185,7 +188,7 @@ __host__ __device__ inline GemmShape gemm_shape(int64_t M, int64_t N, int nxcd, 
     s.ncol = (s.ntiles + s.groups - 1) / s.groups;
     s.ml = per_xcd / s.ncol > 0 ? per_xcd / s.ncol : 1;
     s.rounds = (s.mtiles + s.ml - 1) / s.ml;
-    if (s.groups * s.rounds < nxcd) s.rounds = (nxcd + s.groups - 1) / s.groups;  // a block for every XCD
+    if (nxcd / s.groups > s.rounds) s.rounds = nxcd / s.groups;  // fewer blocks than XCDs: as many as do not exceed them
     s.ml = (s.mtiles + s.rounds - 1) / s.rounds;
     s.rounds = (s.mtiles + s.ml - 1) / s.ml;
     s.ncol = per_xcd / s.ml < s.ntiles ? per_xcd / s.ml : s.ntiles;
