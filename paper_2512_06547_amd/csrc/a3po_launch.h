@@ -1,6 +1,7 @@
 // Host-side launch interface between the C ABI (a3po_api.hip) and the kernel files.
 #pragma once
 
+#include <cmath>
 #include <mutex>
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -86,6 +87,18 @@ hipError_t launch_loss_rows(const LossArgs &a, hipStream_t s);
 hipError_t launch_loss_finish(const LossArgs &a, hipStream_t s);
 hipError_t launch_count_tokens(const int32_t *chosen, const uint8_t *mask, int64_t T, int64_t V, float *denom_out,
                                int64_t *count_out, hipStream_t s);
+// Workgroups of the histogram kernel.  Each adds its occupied slots to the one result when it is done, one atomic at a
+// time and all workgroups in turn (some 12 ns each), so their number is bounded by what that costs against the values
+// they count: one value per thread up to 192 workgroups, from some 280,000 values on 0.36 sqrt(T) of them.  64 bins,
+// 192 / 512 / 1,024 / 2,048 workgroups: 131,072 values 10.8 / 14.4 / 14.4 / - us, 1,000,000: 20.0 / 18.9 / 27.8 / 48.2
+// (360: 18.1), 4,000,000: 59 / 35 / 36 / 54 (768: 34), 16,000,000: 271 / 114 / 78 / 78, 64,000,000: 1,263 / 493 / 271 / 180.
+constexpr int kHistThreads = 256;
+inline int64_t histogram_blocks(int64_t T)
+{
+    const int64_t want = (T + kHistThreads - 1) / kHistThreads, root = (int64_t)(0.36 * std::sqrt((double)T));
+    const int64_t most = root > 192 ? root : 192;
+    return want < most ? want : most;
+}
 hipError_t launch_histogram(const float *values, const uint8_t *select, int64_t T, const float *edges, int nbins,
                             bool accumulate, int64_t *counts, hipStream_t s);
 hipError_t launch_reset_row_queue(void *ws_header, hipStream_t s);  // before re-running the row kernel on one header

@@ -345,9 +345,7 @@ __global__ __launch_bounds__(kTokThreads) void count_tokens_kernel(const int32_t
 // Histogram over explicit edges: slot k of a value = number of edges <= it (0: below the first edge,
 // nbins + 1: at or above the last), slot nbins + 2 for NaN.  Edges and per-workgroup counts live in LDS;
 // integer atomics only, so the result does not depend on the order of arrival.  A workgroup's counts are 32-bit (its
-// share is about 2,048 values); each thread has kHistUnroll of them in flight.
-constexpr int kHistThreads = 256;
-constexpr int kHistMaxBlocks = 192;
+// share of T values is 2.8 sqrt(T) or fewer, see histogram_blocks); each thread has kHistUnroll values in flight.
 constexpr int kHistUnroll = 4;
 
 __global__ void histogram_clear_kernel(int64_t *counts, int n)
@@ -402,12 +400,7 @@ hipError_t launch_histogram(const float *values, const uint8_t *select, int64_t 
         if (e != hipSuccess) return e;
     }
     if (T == 0) return hipSuccess;
-    // one value per thread up to kHistMaxBlocks workgroups (every workgroup adds its occupied slots to the result one
-    // atomic at a time, which bounds their number: 131,072 values 7.5 / 6.0 / 5.7 / 6.5 us with 64 / 128 / 192 / 256),
-    // beyond 8 values per thread more of them again (1,000,000 values: 17.1 us with 192, 14.1 with 488)
-    const int64_t want = (T + kHistThreads - 1) / kHistThreads, many = T / (8 * kHistThreads);
-    const int64_t most = many > kHistMaxBlocks ? many : kHistMaxBlocks;
-    const unsigned grid = (unsigned)(want < most ? want : most);
+    const unsigned grid = (unsigned)histogram_blocks(T);
     hipLaunchKernelGGL(histogram_kernel, dim3(grid), dim3(kHistThreads), 0, s, values, select, T, edges, nbins,
                        reinterpret_cast<unsigned long long *>(counts));
     return hipGetLastError();

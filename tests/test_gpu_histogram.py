@@ -44,6 +44,26 @@ def test_counts_equal_the_oracle_bit_for_bit(a3po, T, nbins):
         assert int(got.sum()) == (T if s is None else int(s.sum()))
 
 
+@pytest.mark.parametrize("T,nbins", [(3001, 20), (279999, 64), (1000003, 64), (4194304, 1000), (20000001, 16)])
+def test_counts_of_many_values(a3po, T, nbins):
+    # beyond some 280,000 values the number of workgroups grows with the root of the number of values; the counts are
+    # those of a binary search (which the smallest case holds against the oracle)
+    edges = np.geomspace(0.3, 3.0, nbins + 1).astype(np.float32)
+    v = values_with_special_cases(T, edges, seed=T + nbins)
+    sel = (np.random.default_rng(T).random(T) < 0.6).astype(np.uint8)
+
+    def counts(w):
+        slot = np.searchsorted(edges, w[~np.isnan(w)], side="right")
+        return np.append(np.bincount(slot, minlength=nbins + 2), np.isnan(w).sum())
+
+    if T < 10000:
+        assert np.array_equal(counts(v[sel != 0]), oracle.histogram(v, edges, sel))
+    for s in (None, sel):
+        got = a3po.histogram(cu(v), cu(edges), select=None if s is None else cu(s))
+        torch.cuda.synchronize()
+        assert np.array_equal(got.cpu().numpy(), counts(v if s is None else v[s != 0])), (T, nbins, s is not None)
+
+
 def test_repeated_edges_accumulation_and_empty_input(a3po):
     edges = np.array([0.5, 1.0, 1.0, 1.0, 2.0], dtype=np.float32)
     v = np.array([1.0, 0.25, 1.5, 2.0, 0.5, 1.0, np.nan], dtype=np.float32)

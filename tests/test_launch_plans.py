@@ -1,0 +1,42 @@
+"""The sharing-out of work that the launchers do, walked on the host (no GPU needed)."""
+import os
+import subprocess
+
+from paper_2512_06547_amd import build
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+
+
+def run_on_host(source, tmp_path):
+    exe = str(tmp_path / "plan")
+    subprocess.check_call([build.HIPCC, "-x", "hip", "--offload-arch=gfx950", "--offload-host-only", "-O2", "-std=c++17",
+                           "-I", os.path.join(build.ROOT, "include"), "-I", build.CSRC, source, "-o", exe],
+                          stderr=subprocess.DEVNULL)
+    done = subprocess.run([exe], capture_output=True, text=True, timeout=120)
+    assert done.returncode == 0, done.stdout
+    return done.stdout
+
+
+def test_every_tile_has_one_place_and_no_unit_more_than_its_share(tmp_path):
+    assert run_on_host(os.path.join(HERE, "gemm_plan_driver.cpp"), tmp_path) == "ok\n"
+
+
+def test_histogram_workgroups_are_bounded_by_what_their_merge_costs(tmp_path):
+    """Workgroups merge one after the other, some 12 ns each: the merge stays below 4 us plus the time that a fifth of
+    the memory's rate takes for the values (4 bytes and a selection byte each, 1.2 TB/s), and there are never fewer
+    workgroups than for a smaller input."""
+    source = tmp_path / "hist.cpp"
+    source.write_text('''#include <cstdio>
+#include "a3po_common.h"
+#include "a3po_launch.h"
+int main()
+{
+    for (int64_t T = 1; T < ((int64_t)1 << 36); T += 1 + T / 7)
+        std::printf("%lld %lld\\n", (long long)T, (long long)a3po::histogram_blocks(T));
+}
+''')
+    plan = [tuple(map(int, line.split())) for line in run_on_host(str(source), tmp_path).splitlines()]
+    assert plan[0] == (1, 1) and all(a[1] <= b[1] for a, b in zip(plan, plan[1:]))
+    for T, blocks in plan:
+        assert blocks * 12e-9 <= 4e-6 + 5 * T / 1.2e12, (T, blocks)
+        assert (T + blocks - 1) // blocks < 2 ** 32, "a workgroup counts in 32 bits"
