@@ -1,0 +1,70 @@
+// Which kernel of a3po_rows.hip takes the rows of a loss call (host code only: no kernel here, so that the rule can be
+// walked by a program of its own).
+#pragma once
+
+#include "a3po_common.h"
+#include "a3po_launch.h"
+
+namespace a3po {
+
+constexpr int kRowThreads = 1024;
+constexpr int kMaxVec = 20;        // 16-byte vectors per thread that the fused kernel can hold
+constexpr int kLineBytes = 128;
+constexpr int kEdgeTail0 = kWave;  // first thread of a cut row's tail (see EdgeSpan)
+
+inline bool aligned16(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
+
+// How the rows of a call are handled.
+struct RowPlan {
+    enum Kind { kRegisters, kLong, kElements } kind;
+    bool edge;   // cut rows at the lines of the gradient (see EdgeSpan)
+    int threads, sweeps;  // kRegisters: template arguments NT and NSWEEP
+};
+
+// Rows whose bases are multiples of 16 bytes and whose stride is a multiple of 128 are taken whole; others are cut at
+// the lines of the gradient.  (A stride of whole vectors could be taken whole too, but the cut makes every store cover
+// whole lines: 8,192 rows of bfloat16 x 32,008 / 100,360 / 151,944 210 / 621 / 988 us whole, 199 / 564 / 875 us cut.)
+//
+// Threads per row.  Short rows need more of them in flight per compute unit than one or two workgroups of 1024: 256
+// threads up to 16 KiB (8,192 rows of bfloat16 x 8,192: 119 us with 1024 threads, 67 so), then 512.  Where 512 ends was
+// measured on rows that all count and on rows of which 9 in 16 do (the others are only written), whose times cross at
+// different lengths; it is set where neither is more than 1 % slower than with 1024 threads (8,192 rows, 512 / 1024
+// threads, all counted and 9 in 16 counted, us):
+//   bfloat16                    42 KiB  0.91 and 0.98 of the time      48 KiB (24,576)  160 / 167 and 139 / 135
+//   fp32                        40 KiB  132 / 133 and 113 / 122        48 KiB (12,288)  157 / 151 and 135 / 131
+//   bfloat16, entropy           68 KiB  0.82 and 1.00                  80 KiB (40,960)  251 / 290 and 214 / 203
+//   fp32, entropy               64 KiB  193 / 243 and 170 / 192        80 KiB (20,480)  245 / 245 and 212 / 195
+// (with the entropy the temporaries do not fit beside a row in the 64 registers of two workgroups of 1024, which rows
+// of up to four of their sweeps run as: those keep 512 threads).
+//
+// A row whose body needs more than kMaxVec sweeps goes through the long kernel, whose direct loads into LDS want
+// 16-byte addresses: logits and gradient must then have the same alignment within 16 bytes.  What is left (a long row
+// of which they do not) is taken element by element.
+template <typename DT>
+inline RowPlan plan_rows(const LossArgs &a)
+{
+    constexpr int64_t EPV = DT::kPerVec;
+    const bool edge = !(aligned16(a.z) && aligned16(a.dz) && (a.ld * DT::kBytes) % kLineBytes == 0);
+    const int64_t head_max = kLineBytes / DT::kBytes - 1;
+    const int64_t least = (a.V > head_max ? a.V - head_max : 0) / EPV;  // body vectors of the row with the fewest
+    const int64_t nvec = (a.V + EPV - 1) / EPV;
+    auto sweeps = [&](int64_t nt) { return edge ? least / nt + 1 : (nvec + nt - 1) / nt; };
+    if (sweeps(256) <= 4) return {RowPlan::kRegisters, edge, 256, (int)sweeps(256)};
+    constexpr bool kF32 = DT::kBytes == 4;
+    const int64_t most = (a.ent_out ? (kF32 ? 64 : 68) : (kF32 ? 40 : 42)) * 1024;
+    if (a.V * DT::kBytes <= most || (a.ent_out && sweeps(kRowThreads) <= 4))
+        return {RowPlan::kRegisters, edge, 512, (int)sweeps(512)};
+    if (sweeps(kRowThreads) <= kMaxVec) return {RowPlan::kRegisters, edge, kRowThreads, (int)sweeps(kRowThreads)};
+    const bool same = ((reinterpret_cast<uintptr_t>(a.z) ^ reinterpret_cast<uintptr_t>(a.dz)) & 15u) == 0;
+    return {same ? RowPlan::kLong : RowPlan::kElements, edge, kRowThreads, 0};
+}
+
+// the instances that plan_rows can ask for: threads, sweeps, without / with the entropy
+#define A3PO_ROW_INSTANCES(X) \
+    X(256, 1, 1, 1) X(256, 2, 1, 1) X(256, 3, 1, 1) X(256, 4, 1, 1) \
+    X(512, 3, 1, 1) X(512, 4, 1, 1) X(512, 5, 1, 1) X(512, 6, 1, 1) X(512, 7, 0, 1) X(512, 8, 0, 1) X(512, 9, 0, 1) \
+    X(1024, 3, 1, 0) X(1024, 4, 1, 0) X(1024, 5, 1, 1) X(1024, 6, 1, 1) X(1024, 7, 1, 1) X(1024, 8, 1, 1) \
+    X(1024, 9, 1, 1) X(1024, 10, 1, 1) X(1024, 11, 1, 1) X(1024, 12, 1, 1) X(1024, 13, 1, 1) X(1024, 14, 1, 1) \
+    X(1024, 15, 1, 1) X(1024, 16, 1, 1) X(1024, 17, 1, 1) X(1024, 18, 1, 1) X(1024, 19, 1, 1) X(1024, 20, 1, 1)
+
+}  // namespace a3po

@@ -13,12 +13,11 @@
 #include "a3po_common.h"
 #include "a3po_launch.h"
 #include "a3po_direct.h"
+#include "a3po_row_plan.h"
 
 namespace a3po {
 
-constexpr int kRowThreads = 1024;
 constexpr int kRowWaves = kRowThreads / kWave;
-constexpr int kMaxVec = 20;  // 16-byte vectors per thread the fused kernel can hold
 
 // ---------------------------------------------------------------------------------------
 // Fused forward+backward, register-resident rows.
@@ -78,9 +77,6 @@ __device__ __forceinline__ void mask_tail(uint4 &v, int rem)
 // The cut differs from row to row: the number of body vectors by up to 8 over all rows of a matrix.  NSWEEP is
 // (fewest body vectors) / 1024 + 1, so sweeps 0 .. NSWEEP-2 are full in every row; a row with more vectors than
 // NSWEEP sweeps hold leaves the surplus in its tail (at most 64 + 7 elements).
-constexpr int kLineBytes = 128;
-constexpr int kEdgeTail0 = kWave;      // first thread of the tail
-
 struct EdgeSpan {
     int head, nbody, tail;  // elements, vectors, elements
 };
@@ -875,44 +871,6 @@ static int device_cu_count()
     return n;
 }
 
-static bool aligned16(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
-
-// How the rows of a call are handled.
-struct RowPlan {
-    enum Kind { kRegisters, kLong, kElements } kind;
-    bool edge;   // cut rows at the lines of the gradient (see EdgeSpan)
-    int threads, sweeps;  // kRegisters: template arguments NT and NSWEEP
-};
-
-// Rows whose bases are multiples of 16 bytes and whose stride is a multiple of 128 are taken whole; others are cut at
-// the lines of the gradient.  (A stride of whole vectors could be taken whole too, but the cut makes every store cover
-// whole lines: 8,192 rows of bfloat16 x 32,008 / 100,360 / 151,944 210 / 621 / 988 us whole, 199 / 564 / 875 us cut.)
-//
-// Threads per row.  Short rows need more of them in flight per compute unit than two workgroups of 1024: 256 threads
-// up to 16 KiB, 512 up to 48 KiB (8,192 rows of bfloat16 x 8,192 / 16,000 / 24,000: 119 / 140 / 166 us with 1024
-// threads, 66 / 112 / 159 us so); at 64 KiB (32,000 columns) 512 threads and 1024 are alike (203 / 200 us).  With the
-// entropy, whose temporaries do not fit beside a row in the 64 registers of two workgroups of 1024, 512 threads are
-// better up to 104 KiB (32,000 columns 250 -> 197 us, 50,264: 336 -> 308) and equal at 128 KiB.
-//
-// A row whose body needs more than kMaxVec sweeps goes through the long kernel, whose direct loads into LDS want
-// 16-byte addresses: logits and gradient must then have the same alignment within 16 bytes.  What is left (a long row
-// of which they do not) is taken element by element.
-template <typename DT>
-static RowPlan plan_rows(const LossArgs &a)
-{
-    constexpr int64_t EPV = DT::kPerVec;
-    const bool edge = !(aligned16(a.z) && aligned16(a.dz) && (a.ld * DT::kBytes) % kLineBytes == 0);
-    const int64_t head_max = kLineBytes / DT::kBytes - 1;
-    const int64_t least = (a.V > head_max ? a.V - head_max : 0) / EPV;  // body vectors of the row with the fewest
-    const int64_t nvec = (a.V + EPV - 1) / EPV;
-    auto sweeps = [&](int64_t nt) { return edge ? least / nt + 1 : (nvec + nt - 1) / nt; };
-    if (sweeps(256) <= 4) return {RowPlan::kRegisters, edge, 256, (int)sweeps(256)};
-    if (sweeps(512) <= (a.ent_out ? 13 : 6)) return {RowPlan::kRegisters, edge, 512, (int)sweeps(512)};
-    if (sweeps(kRowThreads) <= kMaxVec) return {RowPlan::kRegisters, edge, kRowThreads, (int)sweeps(kRowThreads)};
-    const bool same = ((reinterpret_cast<uintptr_t>(a.z) ^ reinterpret_cast<uintptr_t>(a.dz)) & 15u) == 0;
-    return {same ? RowPlan::kLong : RowPlan::kElements, edge, kRowThreads, 0};
-}
-
 template <typename DT, bool EDGE>
 static hipError_t launch_long_rows(const LossArgs &a, unsigned grid, hipStream_t s)
 {
@@ -950,25 +908,12 @@ static hipError_t launch_register_rows(const LossArgs &a, int cus, hipStream_t s
 template <typename DT, bool ENT, bool EDGE>
 static hipError_t dispatch_register_rows(const LossArgs &a, const RowPlan &plan, int cus, hipStream_t s)
 {
-    // (the instances that plan_rows can ask for; with the entropy, 512 threads take the rows of 7 to 13 of their sweeps
-    // that 1024 threads take in 4 to 6 of theirs without)
-    constexpr bool E = ENT;
     switch (plan.threads * 100 + plan.sweeps) {
-#define A3PO_ROWS(NT, N) \
-    case NT * 100 + N: return launch_register_rows<DT, NT, N, ENT, EDGE>(a, cus, s);
-#define A3PO_ROWS_IF(COND, NT, N) \
+#define A3PO_ROWS(NT, N, PLAIN, WITH_ENT) \
     case NT * 100 + N: \
-        if constexpr (COND) return launch_register_rows<DT, NT, N, ENT, EDGE>(a, cus, s); \
+        if constexpr (ENT ? WITH_ENT : PLAIN) return launch_register_rows<DT, NT, N, ENT, EDGE>(a, cus, s); \
         break;
-        A3PO_ROWS(256, 1) A3PO_ROWS(256, 2) A3PO_ROWS(256, 3) A3PO_ROWS(256, 4)
-        A3PO_ROWS(512, 3) A3PO_ROWS(512, 4) A3PO_ROWS(512, 5) A3PO_ROWS(512, 6)
-        A3PO_ROWS_IF(E, 512, 7) A3PO_ROWS_IF(E, 512, 8) A3PO_ROWS_IF(E, 512, 9) A3PO_ROWS_IF(E, 512, 10)
-        A3PO_ROWS_IF(E, 512, 11) A3PO_ROWS_IF(E, 512, 12) A3PO_ROWS_IF(E, 512, 13)
-        A3PO_ROWS_IF(!E, 1024, 4) A3PO_ROWS_IF(!E, 1024, 5) A3PO_ROWS_IF(!E, 1024, 6)
-        A3PO_ROWS(1024, 7) A3PO_ROWS(1024, 8) A3PO_ROWS(1024, 9) A3PO_ROWS(1024, 10) A3PO_ROWS(1024, 11)
-        A3PO_ROWS(1024, 12) A3PO_ROWS(1024, 13) A3PO_ROWS(1024, 14) A3PO_ROWS(1024, 15) A3PO_ROWS(1024, 16)
-        A3PO_ROWS(1024, 17) A3PO_ROWS(1024, 18) A3PO_ROWS(1024, 19) A3PO_ROWS(1024, 20)
-#undef A3PO_ROWS_IF
+        A3PO_ROW_INSTANCES(A3PO_ROWS)
 #undef A3PO_ROWS
         default: break;
     }

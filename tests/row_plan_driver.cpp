@@ -1,0 +1,69 @@
+// How loss rows are dispatched (plan_rows), walked on the host over every row length up to beyond the registers:
+//  - a kernel instance exists for the plan;
+//  - all but its last sweep are full in every row, and what its sweeps do not hold fits the tail of single elements;
+//  - rows of whole lines take as many threads as they were measured to be fastest with.
+#include <cstdio>
+#include <cstdlib>
+
+#include "a3po_row_plan.h"
+
+using namespace a3po;
+
+static bool exists(int threads, int sweeps, bool ent)
+{
+#define A3PO_HAS(NT, N, PLAIN, WITH_ENT) \
+    if (threads == NT && sweeps == N) return ent ? WITH_ENT : PLAIN;
+    A3PO_ROW_INSTANCES(A3PO_HAS)
+#undef A3PO_HAS
+    return false;
+}
+
+template <typename DT>
+static void walk(bool ent, bool edge)
+{
+    constexpr int64_t EPV = DT::kPerVec, E = DT::kBytes;
+    float dummy;
+    for (int64_t V = 1; V <= 190000; ++V) {
+        LossArgs a = {};
+        a.z = reinterpret_cast<const void *>((uintptr_t)(4096 + (edge ? E : 0)));
+        a.dz = reinterpret_cast<void *>((uintptr_t)(8192 + (edge ? E : 0)));
+        a.V = V;
+        a.ld = (V * E + 127) / 128 * 128 / E;
+        a.T = 100;
+        a.ent_out = ent ? &dummy : nullptr;
+        const RowPlan p = plan_rows<DT>(a);
+        auto fail = [&](const char *what) {
+            std::printf("%s: V %lld, %d bytes, entropy %d, edge %d: %d threads, %d sweeps\n", what, (long long)V,
+                        DT::kBytes, ent, edge, p.threads, p.sweeps);
+            std::exit(1);
+        };
+        if (p.edge != edge) fail("cut or not");
+        if (p.kind == RowPlan::kLong) {
+            if (V <= kMaxVec * 1024 * EPV) fail("a row that fits the registers taken as a long one");
+            continue;
+        }
+        if (p.kind != RowPlan::kRegisters || !exists(p.threads, p.sweeps, ent)) fail("no such kernel");
+        const int64_t full = (int64_t)(p.sweeps - 1) * p.threads, room = (int64_t)p.sweeps * p.threads;
+        if (!edge) {
+            const int64_t nvec = (V + EPV - 1) / EPV;
+            if (!(full < nvec && nvec <= room)) fail("sweeps");
+        }
+        for (int64_t head = 0; edge && head < kLineBytes / E; ++head) {
+            const int64_t h = head < V ? head : V, body = (V - h) / EPV, held = body < room ? body : room;
+            if (held < full) fail("a sweep that is not full");
+            if (V - h - held * EPV > p.threads - kEdgeTail0) fail("a tail that is too long");
+        }
+        const int64_t most = (ent ? (E == 4 ? 64 : 68) : (E == 4 ? 40 : 42)) * 1024;
+        if (!edge && p.threads != (V * E <= 16384 ? 256 : V * E <= most ? 512 : 1024)) fail("threads");
+    }
+}
+
+int main()
+{
+    for (bool ent : {false, true})
+        for (bool edge : {false, true}) {
+            walk<F32>(ent, edge);
+            walk<Bf16>(ent, edge);
+        }
+    std::puts("ok");
+}

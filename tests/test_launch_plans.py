@@ -21,6 +21,10 @@ def test_every_tile_has_one_place_and_no_unit_more_than_its_share(tmp_path):
     assert run_on_host(os.path.join(HERE, "gemm_plan_driver.cpp"), tmp_path) == "ok\n"
 
 
+def test_every_row_length_has_a_kernel_and_the_threads_it_is_fastest_with(tmp_path):
+    assert run_on_host(os.path.join(HERE, "row_plan_driver.cpp"), tmp_path) == "ok\n"
+
+
 def test_histogram_workgroups_are_bounded_by_what_their_merge_costs(tmp_path):
     """Workgroups merge one after the other, some 12 ns each: the merge stays below 4 us plus the time that a fifth of
     the memory's rate takes for the values (4 bytes and a selection byte each, 1.2 TB/s), and there are never fewer
