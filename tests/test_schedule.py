@@ -74,3 +74,12 @@ def test_contraction_epilogue_leaves_the_ring_in_flight(assembly, product):
     events = memory_events(body)
     assert not [e for e in events if str(e).startswith("scratch")]
     assert [e for e in events if isinstance(e, int)] == [12, 8, 8, 8, 8, 0]
+
+
+def test_row_kernels_keep_their_rows_in_registers(assembly):
+    """The register-resident rows are only that if the compiler does not spill them: a handful of addresses may go to
+    scratch memory (15 registers at most), rows may not."""
+    text = assembly("a3po_rows.hip")
+    spills = re.findall(r"\.name:\s+(_ZN4a3po\w+)\n(?:(?!\.name:).)*?\.vgpr_spill_count:\s+(\d+)", text, re.S)
+    assert len(spills) > 100
+    assert not [(name, n) for name, n in spills if int(n) > 15]
