@@ -67,4 +67,22 @@ inline RowPlan plan_rows(const LossArgs &a)
     X(1024, 9, 1, 1) X(1024, 10, 1, 1) X(1024, 11, 1, 1) X(1024, 12, 1, 1) X(1024, 13, 1, 1) X(1024, 14, 1, 1) \
     X(1024, 15, 1, 1) X(1024, 16, 1, 1) X(1024, 17, 1, 1) X(1024, 18, 1, 1) X(1024, 19, 1, 1) X(1024, 20, 1, 1)
 
+// Threads per row of the forward-only kernel, five wavefronts per SIMD either way.  512
+//  - where a row has a compute unit to itself, since it is bound by what that can have in flight (64 / 256 rows of 151,936
+//    bfloat16 17.5 / 20.8 us with 256 threads, 13.3 / 16.5 with 512), and up to two rows per compute unit (300 rows of 150 to
+//    600 KiB 0.92 to 1.02 of the time);
+//  - for many long rows without the entropy (10,240 rows of 151,936 bfloat16 484 -> 470 us; 3,000 rows of 125 to 600 KiB
+//    0.95 to 1.02 of the time, 1,800 and 2,048 up to 1.04);
+//  - for long rows of which six fall to a compute unit that holds five of 256 threads at a time (1,536 rows of 125 to 600
+//    KiB 0.91 to 1.00 of the time).
+// 256 for all others: 513 to 1,280 rows of 100 to 600 KiB take up to 1.16 times as long with 512, many short ones 1.6;
+// rows a multiple of 256 KiB apart, which meet on the same memory channels, 1.02 to 1.09 in the last three of these cases.
+inline int logprob_row_threads(int64_t T, int64_t row_bytes, int64_t stride_bytes, bool entropy, int64_t cus)
+{
+    if (T <= cus) return 512;
+    const bool is_long = row_bytes >= 112 * 1024, two = T <= 2 * cus, six = is_long && T > 5 * cus && T <= 6 * cus;
+    const bool many = is_long && !entropy && T >= 11 * cus;
+    return (two || six || many) && stride_bytes % (256 * 1024) != 0 ? 512 : 256;
+}
+
 }  // namespace a3po

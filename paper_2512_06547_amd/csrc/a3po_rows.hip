@@ -970,11 +970,8 @@ hipError_t launch_token_logprobs(const void *z, int dt, int64_t T, int64_t V, in
         if (dt == A3PO_F32) A3PO_FWD(F32, NT); \
         else A3PO_FWD(Bf16, NT); \
     } while (0)
-    // 512 threads per row for up to two rows per compute unit (a lone row is bound by what one compute unit can have in
-    // flight: 64 / 256 rows of 151,936 bfloat16 17.5 / 20.8 us with 256 threads, 13.3 / 16.5 with 512), and for long
-    // rows without the entropy (10,240 rows: 484 -> 470 us); 256 for many shorter ones (16,000 columns, 10,240 rows:
-    // 61 against 78 us).  At 100 KiB the two are alike.
-    if (T <= 2 * cus || (!ent && V * (dt == A3PO_F32 ? 4 : 2) >= 112 * 1024)) A3PO_FWD_DT(512);
+    const int64_t esz = dt == A3PO_F32 ? 4 : 2;
+    if (logprob_row_threads(T, V * esz, ld * esz, ent != nullptr, cus) == 512) A3PO_FWD_DT(512);
     else A3PO_FWD_DT(256);
 #undef A3PO_FWD_DT
 #undef A3PO_FWD

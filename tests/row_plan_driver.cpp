@@ -58,8 +58,33 @@ static void walk(bool ent, bool edge)
     }
 }
 
+// Forward-only rows, 256 compute units: counts between two and five rows per unit, rows a multiple of 256 KiB apart and
+// short rows were measured slower with 512 threads (up to 1.16 and 1.6 times as long).
+static void forward_rows()
+{
+    const struct {
+        int64_t T, row, stride;
+        bool ent;
+        int want;
+    } rows[] = {
+        {1, 300 * 1024, 300 * 1024, false, 512},      {256, 16 * 1024, 16 * 1024, true, 512},
+        {300, 297 * 1024, 297 * 1024, true, 512},     {400, 256 * 1024, 256 * 1024, false, 256},
+        {513, 200 * 1024, 200 * 1024, false, 256},    {768, 600 * 1024, 600 * 1024, false, 256},
+        {1280, 600 * 1024, 600 * 1024, false, 256},   {1536, 297 * 1024, 297 * 1024, true, 512},
+        {1536, 64 * 1024, 64 * 1024, false, 256},     {2048, 297 * 1024, 297 * 1024, false, 256},
+        {10240, 297 * 1024, 297 * 1024, false, 512},  {10240, 297 * 1024, 297 * 1024, true, 256},
+        {10240, 256 * 1024, 256 * 1024, false, 256},  {10240, 32 * 1024, 32 * 1024, false, 256},
+    };
+    for (const auto &r : rows)
+        if (logprob_row_threads(r.T, r.row, r.stride, r.ent, 256) != r.want) {
+            std::printf("forward rows: %lld of %lld bytes, entropy %d\n", (long long)r.T, (long long)r.row, r.ent);
+            std::exit(1);
+        }
+}
+
 int main()
 {
+    forward_rows();
     for (bool ent : {false, true})
         for (bool edge : {false, true}) {
             walk<F32>(ent, edge);
