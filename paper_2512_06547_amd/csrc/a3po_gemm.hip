@@ -273,6 +273,9 @@ struct Operand {
                 const int r = i * 16 + (lane >> 2), last = (int)(extent - 1 - (int64_t)t * kGemmTile);
                 const uint32_t piece = (uint32_t)((lane & 3) ^ ((lane >> 4) & 3)) * 16u;
                 off[j] = L == kPanels ? (uint32_t)r * 64u + piece : (uint32_t)min(r, last) * ((uint32_t)ld * 2u) + piece;
+                // (known to the compiler, a panel offset would be added to the tile's base once, in vector registers, and
+                // every load would need a 64-bit vector addition instead of a scalar base and this offset)
+                if constexpr (L == kPanels) asm volatile("" : "+v"(off[j]));
             } else {
                 const int block = min((i >> 2) * 64, (int)(extent - 64 - (int64_t)t * kGemmTile));
                 const uint32_t granule = (uint32_t)(((lane & 7) >> 1) ^ ((lane >> 4) & 3));  // row = 8 (i & 3) + (lane >> 3)
@@ -280,15 +283,15 @@ struct Operand {
             }
         }
     }
-    // load j of stage st into the operand's 16 KiB at dst
+    // load j of stage st into the operand's 16 KiB at dst: a base that is the same for the wavefront, a 32-bit lane offset
     __device__ __forceinline__ void refill(char *dst, int j, uint32_t st) const
     {
         const char *src;
         if constexpr (!kSlow) {
             src = tile + st * (L == kPanels ? 16384u : (uint32_t)kDmaRowBytes) + off[j];
         } else {
-            const uint32_t row = min(st * (uint32_t)kDmaK + 8u * (wave & 3) + (uint32_t)(lane >> 3), k_last);
-            src = tile + (uint64_t)row * ((uint32_t)ld * 2u) + off[j];
+            const uint32_t row0 = min(st * (uint32_t)kDmaK, k_last), row = min(8u * (wave & 3) + (uint32_t)(lane >> 3), k_last - row0);
+            src = tile + (uint64_t)row0 * ((uint32_t)ld * 2u) + (row * ((uint32_t)ld * 2u) + off[j]);
         }
         dma16(src, dst + (8 * j + wave) * 1024);
     }
@@ -381,6 +384,13 @@ __global__ __launch_bounds__(kGemmThreads) void gemm_kernel(const GemmArgs g)
         } else {
             it.mt = (int)(p % rounds) * shp.ml + ml;
             it.nt = (int)(p / rounds) * shp.ncol + nl;
+        }
+        if constexpr (SPLIT) {  // (the divisions are done in vector registers: back to scalar ones, as what they are for)
+            it.mt = __builtin_amdgcn_readfirstlane(it.mt);
+            it.nt = __builtin_amdgcn_readfirstlane(it.nt);
+            it.slice = __builtin_amdgcn_readfirstlane(it.slice);
+            it.s0 = __builtin_amdgcn_readfirstlane(it.s0);
+            it.s1 = __builtin_amdgcn_readfirstlane(it.s1);
         }
         return it;
     };

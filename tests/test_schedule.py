@@ -76,6 +76,16 @@ def test_contraction_epilogue_leaves_the_ring_in_flight(assembly, product):
     assert [e for e in events if isinstance(e, int)] == [12, 8, 8, 8, 8, 0]
 
 
+@pytest.mark.parametrize("number", range(6))
+def test_contraction_loop_computes_addresses_in_scalar_registers(assembly, number):
+    """Every direct load of gemm_kernel's K loop takes a scalar base and a 32-bit lane offset; 64-bit vector additions
+    between the matrix instructions cost the products of panel operands 2 to 5 %."""
+    (name, body), = [(n, b) for n, b in kernels(assembly("a3po_gemm.hip"), f"gemm_kernelILi{number}ELb1E").items()]
+    loop = max(re.split(r"\n\.?LBB\w+:", body), key=lambda block: block.count("v_mfma"))
+    assert loop.count("v_mfma") == 4 * 32 and loop.count("global_load_lds_dwordx4") == 4 * 4
+    assert not re.findall(r"v_lshl_add_u64|v_mad_[ui]64|v_add_co|v_readfirstlane", loop)
+
+
 def test_row_kernels_keep_their_rows_in_registers(assembly):
     """The register-resident rows are only that if the compiler does not spill them: a handful of addresses may go to
     scratch memory (15 registers at most), rows may not."""
