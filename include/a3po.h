@@ -369,7 +369,7 @@ int a3po_fused_lmhead_logprob(const void *hidden, const void *weight, int64_t T,
  * hidden, dhidden [T, H]; weight, dweight [V, H]: row-major, contiguous, bfloat16, 16-byte
  * aligned; H a positive multiple of 64, at most 2^20; V a multiple of 8 below 2^21; T below 2^22
  * (A3PO_E_SIZE otherwise).  Per-token arguments and outputs as in a3po_loss_fwd_bwd.
- * workspace: a3po_workspace_bytes(A3PO_WS_FUSED_LMHEAD_LOSS, T, V, H) bytes, 256-byte aligned: W^T (from 16,384
+ * workspace: a3po_workspace_bytes(A3PO_WS_FUSED_LMHEAD_LOSS, T, V, H) bytes, 256-byte aligned: W^T (from 12,288
  * tokens on), the gathered hidden rows and their transpose, a chunk of logits (fp32) and of its gradient, the vocabulary-major gradient of
  * up to 65,536 tokens, and beyond that many tokens an fp32 accumulator of dweight - about 2 V H + 6 T H +
  * 6 * 8192 V + 2 V min(T, 65536) (+ 4 V H) bytes, 30 GB at T = 65,536, H = 4,096, V = 151,936.

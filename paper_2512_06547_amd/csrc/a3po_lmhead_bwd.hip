@@ -37,10 +37,11 @@ constexpr int64_t kLmBwdChunk = A3PO_LM_BWD_CHUNK;  // tokens whose logits live 
 // accumulation pass at all).
 constexpr int64_t kLmDwGroup = 8;
 // The hidden-state gradient takes W as it lies in batches of fewer tokens than this (its contracted index, the vocabulary,
-// is then the slow one: transposing reads from LDS, 6 % slower than plain ones, 30.2 against 28.5 ms for 36,000 counted
-// tokens x 4,096), and a transposed copy of W from here on, where the copy (0.45 ms at 151,936 x 4,096, 0.17 at 1,536)
-// pays for itself.
-constexpr int64_t kLmTransposeMin = 16384;
+// is then the slow one: transposing reads from LDS), and a transposed copy of W from here on.  The copy costs 0.45 ms at
+// 151,936 x 4,096 (0.17 at 1,536) and is worth it from some 10,000 counted tokens on: whole steps with the copy / without,
+// every token counted, 151,936 x 4,096: 2,048 tokens 6.85 / 6.41 ms, 6,000: 18.7 / 18.5, 10,000: 29.9 / 30.0, 16,384:
+// 48.2 / 48.9; 9 in 16 counted: 6,000 tokens 11.5 / 11.1, 12,000: 22.0 / 21.9, 16,384: 27.7 / 27.7.
+constexpr int64_t kLmTransposeMin = 12288;
 constexpr int64_t kPadK = 128;                      // contracted extents are zero-padded to this
 
 struct LmBwdLayout {

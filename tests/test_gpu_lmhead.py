@@ -199,6 +199,7 @@ def _check_backward(gpu, ref, ref_abs, what):
 
 @pytest.mark.parametrize("T,H,V,p_mask", [(300, 64, 1000, 0.8), (1, 64, 8, 1.0), (8192 + 300, 64, 512, 0.8),
                                           (467, 192, 1344, 0.8), (560, 1536, 4000, 1.0), (2500, 832, 1336, 0.9),
+                                          (12287, 64, 264, 1.0), (12288, 64, 264, 1.0),  # the weight as it lies, W^T
                                           (16384, 256, 4096, 1.0),
                                           (65536 + 700, 64, 512, 1.0)])
 def test_fused_lmhead_loss_fwd_bwd(a3po, T, H, V, p_mask):
