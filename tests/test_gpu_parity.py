@@ -206,6 +206,7 @@ def test_ragged_vocabularies_and_strides(a3po, dtype, V, pad):
     ("bf16", 131135, 0, 0, 0), ("bf16", 151937, 3, 7, 7),  # the entropy's LDS stash; the longest register rows
     ("bf16", 163902, 1, 0, 0), ("bf16", 163903, 0, 1, 1),  # last length of the registers, first beyond
     ("f32", 100001, 0, 1, 1), ("f32", 100001, 0, 1, 0),    # beyond the registers, alike and not (element-wise)
+    ("bf16", 170001, 0, 1, 0), ("bf16", 170001, 3, 8, 1),  # the same element-wise kernel in bfloat16
 ])
 @pytest.mark.parametrize("entropy", [False, True])
 def test_rows_at_any_address(a3po, dtype, V, pad, z_off, dz_off, entropy):
@@ -241,16 +242,16 @@ def test_rows_at_any_address(a3po, dtype, V, pad, z_off, dz_off, entropy):
 @pytest.mark.parametrize("dtype,V,pad", [
     ("f32", 151936, 0),    # the full vocabulary in fp32: 19 sweeps in registers, 9 in LDS, 9.1 streamed twice
     ("f32", 114688, 0),    # exactly 28 sweeps: nothing streamed, the last LDS sweep full
-    ("f32", 114690, 2),    # the ragged vector is the first one of the streamed part
-    ("f32", 130001, 3),    # ragged end inside the streamed part, two batches
-    ("f32", 86017, 3),     # 21 sweeps and one ragged vector, which lives in LDS
+    ("f32", 114690, 2),    # rows cut at the lines of the gradient: a streamed part of a few vectors or none
+    ("f32", 130001, 3),    # cut rows, two streamed batches
+    ("f32", 86017, 3),     # cut rows, the last vectors in LDS
     ("f32", 500000, 0),    # 122 sweeps: 24 batches of streamed vectors
     ("bf16", 163848, 0),   # one vector more than the register-resident kernel holds
     ("bf16", 256000, 0),   # 31.25 sweeps
-    ("bf16", 300005, 3),   # 36.6 sweeps, ragged end in the last streamed batch
+    ("bf16", 300005, 3),   # cut rows of 36.6 sweeps
 ])
 def test_rows_beyond_the_registers(a3po, dtype, V, pad):
-    # 16-byte aligned rows of more than 20 sweeps of 1024 vectors: kept in registers and LDS as far as they fit, the
+    # rows of more than 20 sweeps of 1024 vectors, whole (those without padding) and cut at lines: kept in registers and LDS as far as they fit, the
     # rest read twice; every element against the oracle, padding untouched, and the in-place form bit-identical
     w = synth.WORKLOADS["tiny"].scaled(V=V, dtype=dtype, S=4, L=6, len_lo=3, len_hi=6, sigma=3.0,
                                        boost=6.0, boost_prob=0.5, noise_std=0.15, stale_max=6)
@@ -263,6 +264,99 @@ def test_rows_beyond_the_registers(a3po, dtype, V, pad):
     assert torch.equal(out["dlogits"][:, :V].contiguous().view(torch.uint8),
                        inp["dlogits"][:, :V].contiguous().view(torch.uint8))
     assert torch.equal(out["logp"], inp["logp"]) and torch.equal(out["loss"], inp["loss"])
+
+
+@pytest.mark.parametrize("dtype,V,ld", [
+    ("bf16", 5, 64), ("f32", 3, 32), ("bf16", 1001, 1024), ("f32", 1001, 1024),  # 256 threads: one sweep, the ragged one
+    ("bf16", 8191, 8192), ("f32", 4093, 4096),       # the last element of their last sweep's last vector is missing
+    ("bf16", 12289, 12352), ("f32", 6145, 6176),     # 512 threads: a ragged vector alone in the last sweep
+    ("bf16", 16385, 16448), ("f32", 10239, 10240),
+    ("bf16", 21503, 21504), ("bf16", 21505, 21568),  # where 512 threads end (1,024 from there), without the entropy
+    ("bf16", 34815, 34816), ("f32", 16383, 16384), ("f32", 16385, 16416),  # and with it
+    ("bf16", 30001, 30016), ("f32", 65537, 65568),   # 1,024 threads
+    ("bf16", 151665, 151936),                        # a vocabulary in rows padded to a common width
+    ("bf16", 155653, 155712), ("bf16", 163833, 163840), ("f32", 81917, 81920),  # 20 sweeps: four vectors parked
+    ("f32", 86017, 86048),     # beyond the registers: the ragged vector in LDS
+    ("f32", 114690, 114720),   # the ragged vector is the first and only one of the streamed part
+    ("f32", 130001, 130016),   # ragged end inside the streamed part, two batches
+    ("bf16", 163841, 163904), ("bf16", 300005, 300032),  # ragged vector in LDS, in the last streamed batch
+])
+@pytest.mark.parametrize("entropy", [False, True])
+def test_whole_rows_with_a_ragged_end(a3po, dtype, V, ld, entropy):
+    # rows that start on lines are taken whole, their last vector in part when the vocabulary is no multiple of a vector:
+    # every element against the oracle, the padding neither read nor written, and the in-place form bit-identical
+    size, per_vec = (4, 4) if dtype == "f32" else (2, 8)
+    assert ld * size % 128 == 0 and V % per_vec != 0
+    w = synth.WORKLOADS["tiny"].scaled(V=V, dtype=dtype, S=4, L=10, len_lo=6, len_hi=10, sigma=3.0,
+                                       boost=6.0, boost_prob=0.5, noise_std=0.15, stale_max=6)
+    c = make_case(w, ld=ld)
+    c["chosen"][:2] = V - 1, V - 1  # the chosen entry in the ragged vector
+    c["mask"][:2] = 1
+    dev = lambda k: torch.from_numpy(c[k]).cuda()
+    outs = []
+    for inplace in (False, True):
+        z_d = dev_logits(c["z"])
+        dl = z_d if inplace else torch.full_like(z_d, 7.0)
+        outs.append(a3po.loss_fwd_bwd(z_d, dev("chosen"), dev("lb"), dev("versions"), CUR, dev("adv"), dev("mask"),
+                                      w.clip_eps, V=V, dlogits=dl, want_entropy=entropy))
+        torch.cuda.synchronize()
+    out, inp = outs
+    check_against_oracle(a3po, c, out)
+    assert (out["dlogits"][:, V:].float() == 7.0).all(), "padding columns were written"
+    assert torch.equal(out["dlogits"][:, :V].contiguous().view(torch.uint8),
+                       inp["dlogits"][:, :V].contiguous().view(torch.uint8))
+    assert torch.equal(out["logp"], inp["logp"]) and torch.equal(out["loss"], inp["loss"])
+    if entropy:
+        ent = np.where(c["mask"] != 0, oracle.entropy(c["z"], V=V), 0.0)
+        err = np.abs(out["entropy"].cpu().numpy().astype(np.float64) - ent)
+        assert (err <= 1e-5 * np.abs(ent) + 2e-5 * (1 + np.abs(c["fwd"]["lse"]))).all()
+
+
+@pytest.mark.parametrize("dtype,V,off", [("bf16", 301, 1), ("f32", 1000, 0), ("bf16", 20001, 3), ("f32", 12288, 0),
+                                         ("bf16", 50001, 1), ("bf16", 50048, 0), ("f32", 81921, 1), ("f32", 100001, 1),
+                                         ("f32", 100000, 0), ("bf16", 170001, 5)])
+@pytest.mark.parametrize("entropy", [False, True])
+def test_rows_with_nan_and_infinite_logits(a3po, dtype, V, off, entropy):
+    # a NaN or +inf anywhere in a counted row (its first elements, its body, its last ones) makes that row's log-prob
+    # and gradient NaN; a masked row is not looked at, and no other row changes by a bit
+    w = synth.WORKLOADS["tiny"].scaled(V=V, dtype=dtype, S=4, L=6, len_lo=6, len_hi=6, sigma=3.0, noise_std=0.15)
+    c = make_case(w)
+    c["mask"][:] = 1
+    c["mask"][7] = 0
+    dev = lambda k: torch.from_numpy(c[k]).cuda()
+
+    def run(poison):
+        z_d = dev_logits(c["z"])
+        for row, col, value in poison:
+            z_d[row, col] = value
+        flat = torch.zeros(z_d.numel() + off, dtype=z_d.dtype, device="cuda")
+        z_at = flat[off:].view(z_d.shape)
+        z_at.copy_(z_d)
+        dz_at = torch.full_like(flat, 7.0)[off:].view(z_d.shape)
+        out = a3po.loss_fwd_bwd(z_at, dev("chosen"), dev("lb"), dev("versions"), CUR, dev("adv"), dev("mask"), w.clip_eps,
+                                dlogits=dz_at, want_entropy=entropy)
+        lp = a3po.token_logprobs(z_at, dev("chosen"), want_entropy=entropy)
+        torch.cuda.synchronize()
+        return out, lp
+
+    nan, inf = float("nan"), float("inf")
+    poison = [(1, 0, nan), (2, V // 2, nan), (3, V - 1, nan), (4, 0, inf), (5, V // 2, inf), (6, V - 1, inf),
+              (7, 3, nan), (9, 1, nan), (9, V - 2, inf)]
+    (clean, clean_lp), (out, lp) = run([]), run(poison)
+    bad = torch.zeros(c["T"], dtype=torch.bool, device="cuda")
+    bad[[1, 2, 3, 4, 5, 6, 9]] = True
+    assert out["logp"][bad].isnan().all() and out["dlogits"][bad].isnan().all() and out["loss"].isnan().all()
+    assert (out["dlogits"][7] == 0).all() and out["logp"][7] == 0
+    assert torch.equal(out["logp"][~bad], clean["logp"][~bad])
+    assert torch.equal(out["dlogits"][~bad].view(torch.uint8), clean["dlogits"][~bad].view(torch.uint8))
+    looked_at = bad.clone()
+    looked_at[7] = True  # (log-probs take no mask)
+    for a, b in zip(lp, clean_lp):
+        assert torch.equal(a[~looked_at], b[~looked_at])
+    assert lp[0][looked_at].isnan().all() and lp[1][looked_at].isnan().all()
+    if entropy:
+        assert out["entropy"][bad].isnan().all() and lp[3][looked_at].isnan().all()
+        assert torch.equal(out["entropy"][~bad], clean["entropy"][~bad])
 
 
 @pytest.mark.parametrize("dtype,V,L", [("bf16", 8000, 2000), ("bf16", 32000, 1500), ("f32", 16000, 1500)])

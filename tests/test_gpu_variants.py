@@ -45,13 +45,13 @@ def assert_close_entropy(gpu, ref, lse_ref, what):
 ENTROPY_CASES = [
     ("f32", 32000, 0),      # 8 sweeps, everything in registers
     ("bf16", 151936, 0),    # 19 sweeps: two vectors parked in LDS, two loads issued late
-    ("f32", 65537, 3),      # 17 sweeps with a ragged tail vector, padded stride
+    ("f32", 65537, 3),      # 17 sweeps of cut rows, padded stride: four vectors parked
     ("bf16", 131072, 0),    # exactly 16 full sweeps
-    ("bf16", 4099, 5),      # stride not a multiple of 16 bytes: multi-pass kernel
+    ("bf16", 4099, 5),      # rows cut at the lines of the gradient
     ("f32", 7, 1),
     ("f32", 100000, 0),     # too long for the registers: registers plus LDS
     ("f32", 151936, 0),     # registers, LDS and a remainder that is read twice
-    ("bf16", 300005, 3),    # the same in bfloat16 with a ragged end
+    ("bf16", 300005, 3),    # the same in bfloat16, rows cut at lines
 ]
 
 
