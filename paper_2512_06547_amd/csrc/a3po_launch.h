@@ -101,7 +101,6 @@ inline int64_t histogram_blocks(int64_t T)
 }
 hipError_t launch_histogram(const float *values, const uint8_t *select, int64_t T, const float *edges, int nbins,
                             bool accumulate, int64_t *counts, hipStream_t s);
-hipError_t launch_reset_row_queue(void *ws_header, hipStream_t s);  // before re-running the row kernel on one header
 
 hipError_t launch_token_logprobs(const void *z, int dt, int64_t T, int64_t V, int64_t ld, const int32_t *chosen,
                                  float *logp, float *lse, void *chosen_logit, float *ent, hipStream_t s);

@@ -488,14 +488,6 @@ hipError_t launch_count_tokens(const int32_t *chosen, const uint8_t *mask, int64
     return hipGetLastError();
 }
 
-__global__ void reset_row_queue_kernel(void *ws_header) { *row_queue_of(ws_header) = 0u; }
-
-hipError_t launch_reset_row_queue(void *ws_header, hipStream_t s)
-{
-    hipLaunchKernelGGL(reset_row_queue_kernel, dim3(1), dim3(1), 0, s, ws_header);
-    return hipGetLastError();
-}
-
 hipError_t launch_loss_finish(const LossArgs &a, hipStream_t s)
 {
     const WsHeader *hdr = reinterpret_cast<const WsHeader *>(a.ws_header);
