@@ -28,7 +28,7 @@ int check_logits(const void *logits, int dt, int64_t T, int64_t V, int64_t ld)
     // (the bounds on T and ld keep every byte offset T * ld * 4 far inside 64 bits)
     if (T < 0 || V <= 0 || ld < V || V > (int64_t)0x7FFFFFFF || T > kMaxRows || ld > kMaxStride) return A3PO_E_SIZE;
     if (T > 0 && !logits) return A3PO_E_NULL;
-    if (!aligned(logits, dt == A3PO_F32 ? 4 : 2)) return A3PO_E_ALIGN;  // element alignment; 16 bytes selects the fast kernels
+    if (!aligned(logits, dt == A3PO_F32 ? 4 : 2)) return A3PO_E_ALIGN;  // (of an element: rows may start anywhere in a line)
     return A3PO_OK;
 }
 

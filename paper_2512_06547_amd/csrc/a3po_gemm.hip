@@ -27,7 +27,8 @@
 // use in stage i; the 4 column fragments, which every MFMA group of the stage needs, alternate between two sets.
 // The 4 direct loads of stage i + kDmaStages go into the freed slot, spread over the stage.  The ring runs through
 // a workgroup's whole sequence of tiles without a break: the refills of a tile's last stages already bring the
-// next tile's first stages, so a tile's epilogue overlaps with their arrival.
+// next tile's first stages, so a tile's epilogue overlaps with their arrival (but for the reduction at the end of a sweep of
+// kGemmLse*: the compiler holds its LDS for a part of the ring and waits for the direct loads in flight).
 //
 // Tile order.  One persistent workgroup per compute unit; the workgroups of an XCD (dispatch order deals
 // workgroups round-robin over the XCDs) form a block of ml x ncol tiles (8 x 4 in the usual case, GemmShape) that

@@ -15,7 +15,7 @@ namespace a3po {
 // vocabulary entries and loads their rows straight into MFMA operands (lane l: row l & 15, 16 bytes at quarter l >> 4;
 // the two loads of a row block and chunk complete each 128-byte line), four chunks of 64 hidden elements ahead: 96 to 128 KiB
 // in flight per compute unit.  The workgroups start at different chunks: all of them at the same offset of rows 8 KiB
-// apart would meet on a few memory channels (16 tokens x 4,096 x 151,936: 309 us so, 253 us apart = 4.9 TB/s; non-temporal
+// apart would meet on a few memory channels (16 tokens x 4,096 x 151,936: 309 us so, 247 us apart = 5.0 TB/s; non-temporal
 // loads, which let go of a line after its first half, are slower).  The hidden rows, which all wavefronts share, come
 // through a ring of four chunks in LDS by
 // direct loads; 16-byte piece p of row r sits at piece p ^ ((r >> 1) & 7), so that 16 consecutive rows of one piece fall
@@ -294,9 +294,10 @@ hipError_t launch_fused_lmhead_logprob(const void *hidden, const void *weight, i
 {
     if (T == 0) return hipSuccess;
     float2 *partial = reinterpret_cast<float2 *>(workspace);
-    // Few tokens: the kernel for them up to 128; from 129 to 256 where its tiles occupy most compute units (65,536 x 2
-    // bytes of hidden rows per tile then weigh as much as the weight).  Contraction kernel / this one, us:
-    // 16 / 128 / 200 tokens x 4,096 x 151,936 347 / 334 / 346 and 253 / 271 / 336; 250 x 2,048 x 128,256 156 and 145,
+    // Few tokens: the kernel for them up to 128; from 129 to 256 where its tiles occupy most compute units (every tile
+    // reads the T x H x 2 bytes of hidden rows, which at 256 tokens weigh as much as its 256 x H x 2 bytes of weight).
+    // Contraction kernel / this one, us:
+    // 16 / 128 / 200 tokens x 4,096 x 151,936 347 / 334 / 346 and 247 / 272 / 342; 250 x 2,048 x 128,256 156 and 145,
     // 250 x 1,536 x 50,264 (197 tiles) 58 and 57, 200 x 2,048 x 32,000 (125 tiles) 53 and 57.
     const GemmGrid gg = gemm_grid();
     const int64_t tiles = (V + kFewRows - 1) / kFewRows, cus = (int64_t)gg.nxcd * gg.per_xcd;

@@ -26,7 +26,7 @@ constexpr int kRowWaves = kRowThreads / kWave;
 // NT-lane sweeps of 16-byte vectors a row needs: (NSWEEP-1)*NT < ceil(V / elements-per-vector) <= NSWEEP*NT.
 // Sweeps 0..NSWEEP-2 are full and carry no predicate at all; only the last sweep is predicated (and holds the
 // ragged tail when V is not a multiple of the vector width).
-// Requires (EDGE aside): 16-byte aligned bases, (ld * element size) % 16 == 0.
+// Requires (EDGE aside): 16-byte aligned bases, rows whole lines of 128 bytes apart.
 // Rows are claimed from a device-wide queue (one atomic add per item): workgroup b starts with
 // item b and then takes whatever item is next, so masked rows (cheap) and slower compute units
 // balance out by themselves.  The queue counter is zeroed by the prep kernel.  With 1024 threads an item is one row.
@@ -75,7 +75,7 @@ __device__ __forceinline__ void mask_tail(uint4 &v, int rem)
 // covers whole lines.  The cut follows the gradient's address, because stores that straddle lines cost more than
 // loads that do; the logits may sit at any other element alignment (the loads then straddle, nothing else changes).
 // The cut differs from row to row: the number of body vectors by up to 8 over all rows of a matrix.  NSWEEP is
-// (fewest body vectors) / 1024 + 1, so sweeps 0 .. NSWEEP-2 are full in every row; a row with more vectors than
+// (fewest body vectors) / NT + 1, so sweeps 0 .. NSWEEP-2 are full in every row; a row with more vectors than
 // NSWEEP sweeps hold leaves the surplus in its tail (at most 64 + 7 elements).
 struct EdgeSpan {
     int head, nbody, tail;  // elements, vectors, elements
