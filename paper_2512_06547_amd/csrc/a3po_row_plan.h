@@ -26,14 +26,17 @@ struct RowPlan {
 // whole lines: 8,192 rows of bfloat16 x 32,008 / 100,360 / 151,944 210 / 621 / 988 us whole, 199 / 564 / 875 us cut.)
 //
 // Threads per row.  Short rows need more of them in flight per compute unit than one or two workgroups of 1024: 256
-// threads up to 16 KiB (8,192 rows of bfloat16 x 8,192: 119 us with 1024 threads, 67 so), then 512.  Where 512 ends was
-// measured on rows that all count and on rows of which 9 in 16 do (the others are only written), whose times cross at
-// different lengths; it is set where neither is more than 1 % slower than with 1024 threads (8,192 rows, 512 / 1024
-// threads, all counted and 9 in 16 counted, us):
-//   bfloat16                    42 KiB  0.91 and 0.98 of the time      48 KiB (24,576)  160 / 167 and 139 / 135
-//   fp32                        40 KiB  132 / 133 and 113 / 122        48 KiB (12,288)  157 / 151 and 135 / 131
-//   bfloat16, entropy           68 KiB  0.82 and 1.00                  80 KiB (40,960)  251 / 290 and 214 / 203
-//   fp32, entropy               64 KiB  193 / 243 and 170 / 192        80 KiB (20,480)  245 / 245 and 212 / 195
+// threads up to 16 KiB (8,192 rows of bfloat16 x 8,192: 119 us with 1024 threads, 67 so), then 512.  Where 512 ends depends
+// on how many rows there are.  With no more than two (without the entropy three) per compute unit each is on its own, and
+// 512 threads, of which a unit takes several at once, are faster at any length (250 / 400 / 512 rows of 41 to 104 KiB: 0.84 /
+// 0.79 / 0.78 of the time with 1024; used up to 48 KiB, with the entropy 104).  With more of them the two cross, at
+// different lengths for batches that all count, batches masked in runs (tails of sequences) and here and there; the line
+// lies where none is more than 3 % slower (8,192 rows, time with 512 threads over that with 1024):
+//                        all count / in runs / here and there
+//   bfloat16             42 KiB 0.91 0.96 0.97    47 KiB  0.97 1.03 1.03
+//   fp32                 40 KiB 0.99 0.96 0.93    44 KiB  1.04 1.00 1.01    47 KiB  1.04 1.05 1.04
+//   bfloat16, entropy    72 KiB 0.83 0.96 1.03    80 KiB  0.87 1.00 1.06    98 KiB  0.93 1.04 1.09
+//   fp32, entropy        65 KiB 0.90 0.98 1.03    72 KiB  0.94 1.02 1.07    98 KiB  1.05 1.07 1.11
 // (with the entropy the temporaries do not fit beside a row in the 64 registers of two workgroups of 1024, which rows
 // of up to four of their sweeps run as: those keep 512 threads).
 //
@@ -41,7 +44,7 @@ struct RowPlan {
 // 16-byte addresses: logits and gradient must then have the same alignment within 16 bytes.  What is left (a long row
 // of which they do not) is taken element by element.
 template <typename DT>
-inline RowPlan plan_rows(const LossArgs &a)
+inline RowPlan plan_rows(const LossArgs &a, int cus)
 {
     constexpr int64_t EPV = DT::kPerVec;
     const bool edge = !(aligned16(a.z) && aligned16(a.dz) && (a.ld * DT::kBytes) % kLineBytes == 0);
@@ -51,7 +54,8 @@ inline RowPlan plan_rows(const LossArgs &a)
     auto sweeps = [&](int64_t nt) { return edge ? least / nt + 1 : (nvec + nt - 1) / nt; };
     if (sweeps(256) <= 4) return {RowPlan::kRegisters, edge, 256, (int)sweeps(256)};
     constexpr bool kF32 = DT::kBytes == 4;
-    const int64_t most = (a.ent_out ? (kF32 ? 64 : 68) : (kF32 ? 40 : 42)) * 1024;
+    const bool few = a.T <= (a.ent_out ? 2 : 3) * (int64_t)cus;
+    const int64_t most = 1024 * (a.ent_out ? (few ? 104 : kF32 ? 65 : 72) : (few ? 48 : kF32 ? 40 : 42));
     if (a.V * DT::kBytes <= most || (a.ent_out && sweeps(kRowThreads) <= 4))
         return {RowPlan::kRegisters, edge, 512, (int)sweeps(512)};
     if (sweeps(kRowThreads) <= kMaxVec) return {RowPlan::kRegisters, edge, kRowThreads, (int)sweeps(kRowThreads)};
@@ -63,6 +67,7 @@ inline RowPlan plan_rows(const LossArgs &a)
 #define A3PO_ROW_INSTANCES(X) \
     X(256, 1, 1, 1) X(256, 2, 1, 1) X(256, 3, 1, 1) X(256, 4, 1, 1) \
     X(512, 3, 1, 1) X(512, 4, 1, 1) X(512, 5, 1, 1) X(512, 6, 1, 1) X(512, 7, 0, 1) X(512, 8, 0, 1) X(512, 9, 0, 1) \
+    X(512, 10, 0, 1) X(512, 11, 0, 1) X(512, 12, 0, 1) X(512, 13, 0, 1) \
     X(1024, 3, 1, 0) X(1024, 4, 1, 0) X(1024, 5, 1, 1) X(1024, 6, 1, 1) X(1024, 7, 1, 1) X(1024, 8, 1, 1) \
     X(1024, 9, 1, 1) X(1024, 10, 1, 1) X(1024, 11, 1, 1) X(1024, 12, 1, 1) X(1024, 13, 1, 1) X(1024, 14, 1, 1) \
     X(1024, 15, 1, 1) X(1024, 16, 1, 1) X(1024, 17, 1, 1) X(1024, 18, 1, 1) X(1024, 19, 1, 1) X(1024, 20, 1, 1)

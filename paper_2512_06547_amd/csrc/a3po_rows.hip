@@ -926,7 +926,7 @@ template <typename DT>
 static hipError_t launch_loss_rows_t(const LossArgs &a, hipStream_t s)
 {
     const int cus = device_cu_count();
-    const RowPlan plan = plan_rows<DT>(a);
+    const RowPlan plan = plan_rows<DT>(a, cus);
     if (plan.kind == RowPlan::kElements) {
         const int64_t resident = (int64_t)cus * 2;
         hipLaunchKernelGGL((loss_rows_generic_kernel<DT>), dim3((unsigned)(a.T < resident ? a.T : resident)),

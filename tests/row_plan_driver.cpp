@@ -19,7 +19,7 @@ static bool exists(int threads, int sweeps, bool ent)
 }
 
 template <typename DT>
-static void walk(bool ent, bool edge)
+static void walk(bool ent, bool edge, int64_t T)
 {
     constexpr int64_t EPV = DT::kPerVec, E = DT::kBytes;
     float dummy;
@@ -29,9 +29,9 @@ static void walk(bool ent, bool edge)
         a.dz = reinterpret_cast<void *>((uintptr_t)(8192 + (edge ? E : 0)));
         a.V = V;
         a.ld = (V * E + 127) / 128 * 128 / E;
-        a.T = 100;
+        a.T = T;
         a.ent_out = ent ? &dummy : nullptr;
-        const RowPlan p = plan_rows<DT>(a);
+        const RowPlan p = plan_rows<DT>(a, 256);
         auto fail = [&](const char *what) {
             std::printf("%s: V %lld, %d bytes, entropy %d, edge %d: %d threads, %d sweeps\n", what, (long long)V,
                         DT::kBytes, ent, edge, p.threads, p.sweeps);
@@ -53,7 +53,8 @@ static void walk(bool ent, bool edge)
             if (held < full) fail("a sweep that is not full");
             if (V - h - held * EPV > p.threads - kEdgeTail0) fail("a tail that is too long");
         }
-        const int64_t most = (ent ? (E == 4 ? 64 : 68) : (E == 4 ? 40 : 42)) * 1024;
+        const bool few = T <= (ent ? 512 : 768);
+        const int64_t most = 1024 * (ent ? (few ? 104 : E == 4 ? 65 : 72) : (few ? 48 : E == 4 ? 40 : 42));
         if (!edge && p.threads != (V * E <= 16384 ? 256 : V * E <= most ? 512 : 1024)) fail("threads");
     }
 }
@@ -86,9 +87,10 @@ int main()
 {
     forward_rows();
     for (bool ent : {false, true})
-        for (bool edge : {false, true}) {
-            walk<F32>(ent, edge);
-            walk<Bf16>(ent, edge);
-        }
+        for (bool edge : {false, true})
+            for (int64_t T : {1, 512, 768, 769, 100000}) {
+                walk<F32>(ent, edge, T);
+                walk<Bf16>(ent, edge, T);
+            }
     std::puts("ok");
 }
