@@ -38,12 +38,14 @@
 // keeps its running (max, sum) in registers over a whole sweep and writes one partial per column per sweep.
 //
 // Results.  The logits and the weight gradient are stored transposed (element (m, n) at C[n ldc + m]): a lane's four
-// accumulator values of one MFMA tile are four consecutive m of one n, i.e. one 16- or 8-byte store without staging.
+// accumulator values of one MFMA tile are four consecutive m of one n, which a staging tile in LDS puts together to whole
+// lines (store_tile_lines).
 // One of M, N, K may be known only on the device (DynCount): the launch is sized for the host's upper bound and
 // every workgroup reads the extent first; beyond it there is nothing to do and it returns.
 #include "a3po_common.h"
 #include "a3po_launch.h"
 #include "a3po_direct.h"
+#include <type_traits>
 
 namespace a3po {
 
@@ -96,6 +98,14 @@ __device__ __forceinline__ void fold_column(const f32x4_t (&acc)[8][4], int b, i
     run_s = s;
 }
 
+// Accesses to the LDS behind the ring (staging tiles, column partials).  The __restrict__ parameters put each into an alias
+// scope of its own; without one the compiler takes that LDS for a part of the ring and waits for every direct load in flight.
+typedef float f32x2_t __attribute__((ext_vector_type(2)));
+template <typename T>
+__device__ __forceinline__ void stage_put(char *__restrict__ p, T v) { *reinterpret_cast<T *>(p) = v; }
+template <typename T>
+__device__ __forceinline__ T stage_get(const char *__restrict__ p) { return *reinterpret_cast<const T *>(p); }
+
 // Element-wise store of a wavefront's part of a tile that reaches past M or N (rows / columns beyond are skipped): one
 // accumulator register covers 4 rows x 16 consecutive columns.
 template <typename DT>
@@ -120,13 +130,9 @@ __device__ __forceinline__ void store_tile_edge(const f32x4_t (&acc)[8][4], void
     }
 }
 
-// fp32 store of C^T (element (m, n) at C[n * ldc + m]): the four values of an accumulator register are four
-// consecutive m of one column n, i.e. 16 contiguous bytes, so every register leaves with one 16-byte store and no
-// staging; a wavefront's instruction covers 16 columns x 64 contiguous bytes.  M is a multiple of 4, so a group of
-// four rows lies inside or outside as a whole.  `add`: sums into C through the memory side's adders.
-template <bool EDGE>
-__device__ __forceinline__ void store_tile_transposed(const f32x4_t (&acc)[8][4], float *C, int64_t ldc, int64_t m0,
-                                                      int64_t n0, int64_t M, int64_t N, int wm, int wn, int lane, bool add)
+// Adds a tile to C^T (fp32; element (m, n) at C[n * ldc + m]) through the memory side's adders.  M is a multiple of 4.
+__device__ __forceinline__ void add_tile_transposed(const f32x4_t (&acc)[8][4], float *C, int64_t ldc, int64_t m0, int64_t n0,
+                                                    int64_t M, int64_t N, int wm, int wn, int lane)
 {
     const int col0 = wn * 64 + (lane & 15);
     const int row0 = wm * 128 + 4 * (lane >> 4);
@@ -134,42 +140,63 @@ __device__ __forceinline__ void store_tile_transposed(const f32x4_t (&acc)[8][4]
     const int cols_left = (int)(N - n0 < kGemmTile ? N - n0 : kGemmTile);
 #pragma unroll
     for (int b = 0; b < 4; ++b) {
-        if (EDGE && col0 + b * 16 >= cols_left) continue;
+        if (col0 + b * 16 >= cols_left) continue;
         float *col = C + (n0 + col0 + b * 16) * ldc + m0 + row0;
 #pragma unroll
         for (int a = 0; a < 8; ++a) {
-            if (EDGE && row0 + a * 16 >= rows_left) continue;
-            if (add) {
+            if (row0 + a * 16 >= rows_left) continue;
 #pragma unroll
-                for (int i = 0; i < 4; ++i) unsafeAtomicAdd(col + a * 16 + i, acc[a][b][i]);
-            } else {
-                *reinterpret_cast<float4 *>(col + a * 16) = make_float4(acc[a][b][0], acc[a][b][1], acc[a][b][2], acc[a][b][3]);
-            }
+            for (int i = 0; i < 4; ++i) unsafeAtomicAdd(col + a * 16 + i, acc[a][b][i]);
         }
         __builtin_amdgcn_sched_barrier(0);
     }
 }
 
-// The transposed store in bfloat16: the four values of a register are rounded and leave as one 8-byte store.
-template <bool EDGE>
-__device__ __forceinline__ void store_tile_transposed_bf16(const f32x4_t (&acc)[8][4], uint16_t *C, int64_t ldc, int64_t m0,
-                                                           int64_t n0, int64_t M, int64_t N, int wm, int wn, int lane)
+// Store of C^T in whole 128-byte lines: 16 columns x 32 rows (fp32; bfloat16: 64) at a time go through this wavefront's
+// staging tile in LDS, into which a lane's four values of an MFMA tile, consecutive m of one column, go as one write, and
+// leave as 8 columns x 128 bytes per store instruction.  (LDS instructions of one wavefront execute in order: no waits or
+// barriers between its writes and its reads.)
+// Straight from the registers a store instruction covers 16 columns x 64 (bfloat16: 32) bytes, and the memory takes such
+// pieces of lines far more slowly than whole ones: the weight gradient of 53 / 654 / 2,557 tokens (1,536 x 151,936, whose
+// 467 MB of stores bound it) 193 / 385 / 950 us so, 163 / 335 / 905 with pieces of 64 bytes, 140 / 335 / 890 with lines.
+// Non-temporal: nothing in this call reads the weight gradient again, and what it would displace from the caches is the
+// weight (119 us at 53 tokens, and the next projection 137 instead of 167; no gain from 654 tokens on); the logits (a few GB per chunk) do
+// not fit any cache (projection with stores of 2,557 tokens x 896 x 50,264 / 1,536 x 151,936 375 / 1,605 us before, 340 / 1,540
+// with lines that are not, 310 / 1,500 so).
+// EDGE: the tile reaches past M or N; M is a multiple of the elements in 16 bytes.
+template <typename DT, bool EDGE>
+__device__ __forceinline__ void store_tile_lines(const f32x4_t (&acc)[8][4], void *C, int64_t ldc, int64_t m0, int64_t n0,
+                                                 int64_t M, int64_t N, int wm, int wn, int lane, char *stage)
 {
-    const int col0 = wn * 64 + (lane & 15);
-    const int row0 = wm * 128 + 4 * (lane >> 4);
+    constexpr int kTiles = 8 / DT::kBytes;  // MFMA tiles along m that make up a line
+    constexpr int kPitch = kStageLd * (int)sizeof(float);
+    char *put = stage + (lane & 15) * kPitch + (lane >> 4) * 4 * DT::kBytes;  // column lane & 15, rows 4 (lane >> 4) ..
+    const char *get = stage + (lane >> 3) * kPitch + (lane & 7) * 16;         // column lane >> 3 (+ 8), 16 bytes of its line
+    const int col0 = wn * 64 + (lane >> 3), row0 = wm * 128 + (lane & 7) * DT::kPerVec;
+    char *out = reinterpret_cast<char *>(C) + ((n0 + col0) * ldc + m0 + row0) * DT::kBytes;
+    const int64_t eight = 8 * ldc * DT::kBytes;
     const int rows_left = (int)(M - m0 < kGemmTile ? M - m0 : kGemmTile);
     const int cols_left = (int)(N - n0 < kGemmTile ? N - n0 : kGemmTile);
 #pragma unroll
     for (int b = 0; b < 4; ++b) {
-        if (EDGE && col0 + b * 16 >= cols_left) continue;
-        uint16_t *col = C + (n0 + col0 + b * 16) * ldc + m0 + row0;
 #pragma unroll
-        for (int a = 0; a < 8; ++a) {
-            if (EDGE && row0 + a * 16 >= rows_left) continue;
-            *reinterpret_cast<uint2 *>(col + a * 16) =
-                make_uint2(pack_bf16x2(acc[a][b][0], acc[a][b][1]), pack_bf16x2(acc[a][b][2], acc[a][b][3]));
+        for (int a = 0; a < 8; a += kTiles) {
+#pragma unroll
+            for (int u = 0; u < kTiles; ++u) {
+                const f32x4_t v = acc[a + u][b];
+                if constexpr (DT::kBytes == 4) stage_put(put + u * 64, v);
+                else stage_put(put + u * 32, f32x2_t{__uint_as_float(pack_bf16x2(v[0], v[1])), __uint_as_float(pack_bf16x2(v[2], v[3]))});
+            }
+            asm volatile("" ::: "memory");
+#pragma unroll
+            for (int pass = 0; pass < 2; ++pass) {
+                const f32x4_t v = stage_get<f32x4_t>(get + pass * 8 * kPitch);
+                if (!EDGE || (col0 + 16 * b + 8 * pass < cols_left && row0 + 16 * a < rows_left))
+                    __builtin_nontemporal_store(v, reinterpret_cast<f32x4_t *>(out + (2 * b + pass) * eight + a * 16 * DT::kBytes));
+            }
+            asm volatile("" ::: "memory");
+            __builtin_amdgcn_sched_barrier(0);
         }
-        __builtin_amdgcn_sched_barrier(0);
     }
 }
 
@@ -177,9 +204,6 @@ __device__ __forceinline__ void store_tile_transposed_bf16(const f32x4_t (&acc)[
 // tile in LDS that belongs to this wavefront alone (LDS instructions of one wavefront execute in order, so no waits
 // or barriers are needed between its writes and its reads) and leave as 8 rows x 128 bytes (fp32) or 8 rows x 64
 // bytes (bfloat16) per store instruction.
-// (__restrict__: the read then has an alias scope of its own.  Without one the compiler takes the staging tile for a part
-// of the ring and waits for every direct load in flight before the first read of each tile.)
-__device__ __forceinline__ float4 staged(const float *__restrict__ p) { return *reinterpret_cast<const float4 *>(p); }
 template <typename DT>
 __device__ __forceinline__ void store_tile_wide(const f32x4_t (&acc)[8][4], void *C, int64_t ldc, int64_t m0, int64_t n0,
                                                 int wm, int wn, int lane, float *stage)
@@ -198,7 +222,7 @@ __device__ __forceinline__ void store_tile_wide(const f32x4_t (&acc)[8][4], void
             const int64_t at = (m0 + wm * 128 + a * 16 + rrow) * ldc + n0 + wn * 64 + bp * 32 + rcol;
 #pragma unroll
             for (int pass = 0; pass < 2; ++pass) {
-                const float4 v = staged(stage + (rrow + 8 * pass) * kStageLd + rcol);
+                const float4 v = stage_get<float4>(reinterpret_cast<const char *>(stage + (rrow + 8 * pass) * kStageLd + rcol));
                 if constexpr (DT::kBytes == 2) {
                     *reinterpret_cast<uint2 *>(reinterpret_cast<uint16_t *>(C) + at + (int64_t)pass * 8 * ldc) =
                         make_uint2(pack_bf16x2(v.x, v.y), pack_bf16x2(v.z, v.w));
@@ -328,7 +352,6 @@ __global__ __launch_bounds__(kGemmThreads) void gemm_kernel(const GemmArgs g)
 {
     extern __shared__ __align__(16) char lds[];
     constexpr bool LSE = PRODUCT == kGemmLse || PRODUCT == kGemmLseStore, SPLIT = PRODUCT == kGemmSplitRows || PRODUCT == kGemmSplitPanels;
-    constexpr bool PANELS = PRODUCT == kGemmPanelsBf16 || PRODUCT == kGemmPanelsF32;
     static_assert(LSE || QUAD, "slices are whole groups of ring stages");
     constexpr int kLoads = 4;  // direct loads per wavefront and stage: two of A, two of B
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -544,15 +567,15 @@ __global__ __launch_bounds__(kGemmThreads) void gemm_kernel(const GemmArgs g)
                 if (edge) store_tile_edge<Bf16>(acc, g.C, g.ldc, m0, n0, M, N, wm, wn, lane_e);
                 else store_tile_wide<Bf16>(acc, g.C, g.ldc, m0, n0, wm, wn, lane_e, stage_tile);
             }
-        } else if constexpr (PRODUCT == kGemmPanelsBf16) {
-            uint16_t *ct = reinterpret_cast<uint16_t *>(g.C);
-            if (edge) store_tile_transposed_bf16<true>(acc, ct, g.ldc, m0, n0, M, N, wm, wn, lane);
-            else store_tile_transposed_bf16<false>(acc, ct, g.ldc, m0, n0, M, N, wm, wn, lane);
         } else if constexpr (PRODUCT != kGemmLse) {
-            float *ct = reinterpret_cast<float *>(g.C);
-            const bool add = PANELS && g.accumulate != 0;
-            if (edge) store_tile_transposed<true>(acc, ct, g.ldc, m0, n0, M, N, wm, wn, lane, add);
-            else store_tile_transposed<false>(acc, ct, g.ldc, m0, n0, M, N, wm, wn, lane, add);
+            char *stage_tile = lds + kDmaRingBytes + kGemmRedBytes + wave_s * kStageBytes;
+            int lane_e = lane;  // (as above)
+            asm volatile("" : "+v"(lane_e));
+            using DT = typename std::conditional<PRODUCT == kGemmPanelsBf16, Bf16, F32>::type;
+            if (PRODUCT == kGemmPanelsF32 && g.accumulate != 0)
+                add_tile_transposed(acc, reinterpret_cast<float *>(g.C), g.ldc, m0, n0, M, N, wm, wn, lane_e);
+            else if (edge) store_tile_lines<DT, true>(acc, g.C, g.ldc, m0, n0, M, N, wm, wn, lane_e, stage_tile);
+            else store_tile_lines<DT, false>(acc, g.C, g.ldc, m0, n0, M, N, wm, wn, lane_e, stage_tile);
         }
         if constexpr (LSE) {
             const bool ragged = m0 + kGemmTile > M;
@@ -575,7 +598,7 @@ __global__ __launch_bounds__(kGemmThreads) void gemm_kernel(const GemmArgs g)
                         const MaxSum other = {__shfl_xor(mine.m, off, kWave), __shfl_xor(mine.s, off, kWave)};
                         mine = combine(mine, other);
                     }
-                    if (lane < 16) red[wm * kGemmTile + wn * 64 + b * 16 + lane] = make_float2(mine.m, mine.s);
+                    if (lane < 16) stage_put(reinterpret_cast<char *>(red + wm * kGemmTile + wn * 64 + b * 16 + lane), f32x2_t{mine.m, mine.s});
                     run_m[b] = kNegFloor;
                     run_s[b] = 0.0f;
                 }
@@ -585,8 +608,9 @@ __global__ __launch_bounds__(kGemmThreads) void gemm_kernel(const GemmArgs g)
                 __builtin_amdgcn_s_barrier();
                 asm volatile("" ::: "memory");
                 if (tid < kGemmTile) {
-                    const float2 q0 = red[tid], q1 = red[kGemmTile + tid];
-                    const MaxSum tot = combine(MaxSum{q0.x, q0.y}, MaxSum{q1.x, q1.y});
+                    const f32x2_t q0 = stage_get<f32x2_t>(reinterpret_cast<const char *>(red + tid));
+                    const f32x2_t q1 = stage_get<f32x2_t>(reinterpret_cast<const char *>(red + kGemmTile + tid));
+                    const MaxSum tot = combine(MaxSum{q0[0], q0[1]}, MaxSum{q1[0], q1[1]});
                     if (n0 + tid < N)
                         g.partial[(int64_t)(xcd * shp.ml + ml) * N + n0 + tid] = make_float2(tot.m, tot.s);
                 }
@@ -670,8 +694,9 @@ hipError_t launch_gemm(const GemmArgs &args, int product, hipStream_t s)
     if (g.dyn_dim != kDynNone && !g.dyn.n) return hipErrorInvalidValue;
     if (g.dyn_dim == kDynK && !panels) return hipErrorInvalidValue;
     if (product != kGemmLse && (g.ldc % 8 != 0 || (reinterpret_cast<uintptr_t>(g.C) & 15) != 0)) return hipErrorInvalidValue;
-    // C^T: groups of four rows
-    if ((product == kGemmLseStore || panels) && (g.M % 4 != 0 || g.dyn_dim == kDynM)) return hipErrorInvalidValue;
+    // C^T: 16-byte stores along M
+    if ((product == kGemmLseStore || panels) && (g.M % (product == kGemmPanelsBf16 ? 8 : 4) != 0 || g.dyn_dim == kDynM))
+        return hipErrorInvalidValue;
     if (lse) {
         if (g.lda < g.K || g.ldb < g.K) return hipErrorInvalidValue;
         if (product == kGemmLse) return quad ? launch_gemm_t<kGemmLse, true>(g, s) : launch_gemm_t<kGemmLse, false>(g, s);

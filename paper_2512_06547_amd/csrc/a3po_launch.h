@@ -163,8 +163,8 @@ struct GemmArgs {
     int64_t ldb;
     int64_t M, N, K;    // K a multiple of 64 (the others than kGemmLse*: of 128)
     int64_t k_rows;     // kGemmSplitRows: rows that B has
-    void *C;            // row stride ldc elements; C^T: element (m, n) at C[n * ldc + m], M a multiple of 4 (a lane's four
-    int64_t ldc;        // accumulator values are then contiguous)
+    void *C;            // row stride ldc elements; C^T: element (m, n) at C[n * ldc + m], M a multiple of the
+    int64_t ldc;        // elements in 16 bytes
     float2 *partial;    // kGemmLse*: [slots][N] (max, sum) per column (see GemmShape), merged by the caller; room for
                         // gemm_partial_entries(N) entries
     float *split;       // kGemmSplit*: room for split_max slices of M x N floats (overwritten)

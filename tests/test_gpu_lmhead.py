@@ -257,6 +257,13 @@ def test_fused_lmhead_loss_fwd_bwd(a3po, T, H, V, p_mask):
           f"{st['n_clipped']} clipped of {st['n_tokens']}")
 
 
+@pytest.mark.parametrize("T,H,V", [(256, 256, 512), (257, 320, 520), (265, 192, 264), (520, 448, 776)])
+def test_fused_lmhead_loss_tiles_that_end_inside_a_line(a3po, T, H, V):
+    """Logits and weight gradient leave as whole lines, eight columns at a time: tiles that are whole, that end one and nine
+    columns into a group of eight, and whose rows end inside a wavefront's half and inside a line."""
+    test_fused_lmhead_loss_fwd_bwd(a3po, T, H, V, 1.0)
+
+
 def test_fused_lmhead_loss_matches_forward_only_entry_point(a3po):
     """Both entry points keep fp32 logits on chip for the log-sum-exp: their log-probs agree to rounding order."""
     r = np.random.default_rng(5)
