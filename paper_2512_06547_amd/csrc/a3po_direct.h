@@ -8,6 +8,7 @@ namespace a3po {
 
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 typedef float f32x4_t __attribute__((ext_vector_type(4)));
+typedef float f32x2_t __attribute__((ext_vector_type(2)));
 typedef uint32_t dma_u32x4_t __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) void *lds_ptr_t;
 
@@ -29,6 +30,14 @@ __device__ __forceinline__ void dma16(__amdgpu_buffer_rsrc_t buffer, uint32_t of
 {
     __builtin_amdgcn_raw_ptr_buffer_load_lds(buffer, (lds_ptr_t)l, 16, (int)off, (int)at, 0, 0);
 }
+
+// Accesses to LDS beside a ring that direct loads fill (staging tiles, partial results).  The __restrict__ parameter puts each
+// into an alias scope of its own; without one the compiler takes that LDS for a part of the ring and waits for the direct
+// loads in flight.  (Such accesses keep their order among themselves: neither is said to be free of the other's scope.)
+template <typename T>
+__device__ __forceinline__ void lds_put(void *__restrict__ p, T v) { *reinterpret_cast<T *>(p) = v; }
+template <typename T>
+__device__ __forceinline__ T lds_get(const void *__restrict__ p) { return *reinterpret_cast<const T *>(p); }
 
 // s_waitcnt with the given vector-memory and LDS counts (the export count is left alone)
 __device__ __forceinline__ constexpr int waitcnt_imm(int vmcnt, int lgkmcnt)

@@ -98,14 +98,6 @@ __device__ __forceinline__ void fold_column(const f32x4_t (&acc)[8][4], int b, i
     run_s = s;
 }
 
-// Accesses to the LDS behind the ring (staging tiles, column partials).  The __restrict__ parameters put each into an alias
-// scope of its own; without one the compiler takes that LDS for a part of the ring and waits for every direct load in flight.
-typedef float f32x2_t __attribute__((ext_vector_type(2)));
-template <typename T>
-__device__ __forceinline__ void stage_put(char *__restrict__ p, T v) { *reinterpret_cast<T *>(p) = v; }
-template <typename T>
-__device__ __forceinline__ T stage_get(const char *__restrict__ p) { return *reinterpret_cast<const T *>(p); }
-
 // Element-wise store of a wavefront's part of a tile that reaches past M or N (rows / columns beyond are skipped): one
 // accumulator register covers 4 rows x 16 consecutive columns.
 template <typename DT>
@@ -184,13 +176,13 @@ __device__ __forceinline__ void store_tile_lines(const f32x4_t (&acc)[8][4], voi
 #pragma unroll
             for (int u = 0; u < kTiles; ++u) {
                 const f32x4_t v = acc[a + u][b];
-                if constexpr (DT::kBytes == 4) stage_put(put + u * 64, v);
-                else stage_put(put + u * 32, f32x2_t{__uint_as_float(pack_bf16x2(v[0], v[1])), __uint_as_float(pack_bf16x2(v[2], v[3]))});
+                if constexpr (DT::kBytes == 4) lds_put(put + u * 64, v);
+                else lds_put(put + u * 32, f32x2_t{__uint_as_float(pack_bf16x2(v[0], v[1])), __uint_as_float(pack_bf16x2(v[2], v[3]))});
             }
             asm volatile("" ::: "memory");
 #pragma unroll
             for (int pass = 0; pass < 2; ++pass) {
-                const f32x4_t v = stage_get<f32x4_t>(get + pass * 8 * kPitch);
+                const f32x4_t v = lds_get<f32x4_t>(get + pass * 8 * kPitch);
                 if (!EDGE || (col0 + 16 * b + 8 * pass < cols_left && row0 + 16 * a < rows_left))
                     __builtin_nontemporal_store(v, reinterpret_cast<f32x4_t *>(out + (2 * b + pass) * eight + a * 16 * DT::kBytes));
             }
@@ -222,7 +214,7 @@ __device__ __forceinline__ void store_tile_wide(const f32x4_t (&acc)[8][4], void
             const int64_t at = (m0 + wm * 128 + a * 16 + rrow) * ldc + n0 + wn * 64 + bp * 32 + rcol;
 #pragma unroll
             for (int pass = 0; pass < 2; ++pass) {
-                const float4 v = stage_get<float4>(reinterpret_cast<const char *>(stage + (rrow + 8 * pass) * kStageLd + rcol));
+                const float4 v = lds_get<float4>(stage + (rrow + 8 * pass) * kStageLd + rcol);
                 if constexpr (DT::kBytes == 2) {
                     *reinterpret_cast<uint2 *>(reinterpret_cast<uint16_t *>(C) + at + (int64_t)pass * 8 * ldc) =
                         make_uint2(pack_bf16x2(v.x, v.y), pack_bf16x2(v.z, v.w));
@@ -598,7 +590,7 @@ __global__ __launch_bounds__(kGemmThreads) void gemm_kernel(const GemmArgs g)
                         const MaxSum other = {__shfl_xor(mine.m, off, kWave), __shfl_xor(mine.s, off, kWave)};
                         mine = combine(mine, other);
                     }
-                    if (lane < 16) stage_put(reinterpret_cast<char *>(red + wm * kGemmTile + wn * 64 + b * 16 + lane), f32x2_t{mine.m, mine.s});
+                    if (lane < 16) lds_put(red + wm * kGemmTile + wn * 64 + b * 16 + lane, f32x2_t{mine.m, mine.s});
                     run_m[b] = kNegFloor;
                     run_s[b] = 0.0f;
                 }
@@ -608,8 +600,8 @@ __global__ __launch_bounds__(kGemmThreads) void gemm_kernel(const GemmArgs g)
                 __builtin_amdgcn_s_barrier();
                 asm volatile("" ::: "memory");
                 if (tid < kGemmTile) {
-                    const f32x2_t q0 = stage_get<f32x2_t>(reinterpret_cast<const char *>(red + tid));
-                    const f32x2_t q1 = stage_get<f32x2_t>(reinterpret_cast<const char *>(red + kGemmTile + tid));
+                    const f32x2_t q0 = lds_get<f32x2_t>(red + tid);
+                    const f32x2_t q1 = lds_get<f32x2_t>(red + kGemmTile + tid);
                     const MaxSum tot = combine(MaxSum{q0[0], q0[1]}, MaxSum{q1[0], q1[1]});
                     if (n0 + tid < N)
                         g.partial[(int64_t)(xcd * shp.ml + ml) * N + n0 + tid] = make_float2(tot.m, tot.s);

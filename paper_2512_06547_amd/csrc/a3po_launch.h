@@ -286,6 +286,24 @@ inline size_t gemm_partial_entries(int64_t N)
 }
 hipError_t launch_gemm(const GemmArgs &args, int product, hipStream_t s);
 
+// Tiles of the few-token kernel: nfull whole tiles of kFewRows vocabulary entries, one for each compute unit and round, then
+// those of the last round, each of last_blocks row blocks of 16 (16 for a whole tile).
+constexpr int kFewWaves = 8;
+constexpr int kFewRows = 32 * kFewWaves;
+struct FewTiles {
+    int nfull, ntiles, last_blocks, slots;
+};
+inline FewTiles few_tiles(int64_t V, int64_t cus)
+{
+    const int64_t blocks = (V + 15) / 16, rounds = (blocks - 1) / (2 * kFewWaves * cus), left = blocks - rounds * 2 * kFewWaves * cus;
+    FewTiles f;
+    f.last_blocks = (int)((left + cus - 1) / cus);
+    f.nfull = (int)(rounds * cus);
+    f.ntiles = f.nfull + (int)((left + f.last_blocks - 1) / f.last_blocks);
+    f.slots = (int)(f.ntiles < cus ? f.ntiles : cus);
+    return f;
+}
+
 size_t lmhead_workspace_bytes(int64_t T);
 hipError_t launch_fused_lmhead_logprob(const void *hidden, const void *weight, int64_t T, int64_t H, int64_t V,
                                        const int32_t *chosen, float *logp, float *lse, void *workspace, hipStream_t s);

@@ -6,16 +6,17 @@
 #include "a3po_common.h"
 #include "a3po_launch.h"
 #include "a3po_direct.h"
+#include <type_traits>
 
 namespace a3po {
 
 // ---- few tokens -------------------------------------------------------------------------------------------------
-// Up to 256 tokens the projection is bound by reading the weight, and the contraction kernel, whose ring holds three
-// stages of 16 KiB of it ahead, reads 3.6 TB/s.  Here the weight does not pass through LDS at all: a wavefront owns 32
-// vocabulary entries and loads their rows straight into MFMA operands (lane l: row l & 15, 16 bytes at quarter l >> 4;
+// Up to 256 tokens the projection is bound by reading the weight (at 256 by the products as much), and the contraction kernel, whose ring holds three
+// stages of 16 KiB of it ahead, reads 3.6 TB/s.  Here the weight does not pass through LDS at all: a wavefront owns two
+// blocks of 16 vocabulary entries and loads their rows straight into MFMA operands (lane l: row l & 15, 16 bytes at quarter l >> 4;
 // the two loads of a row block and chunk complete each 128-byte line), four chunks of 64 hidden elements ahead: 96 to 128 KiB
 // in flight per compute unit.  The workgroups start at different chunks: all of them at the same offset of rows 8 KiB
-// apart would meet on a few memory channels (16 tokens x 4,096 x 151,936: 309 us so, 247 us apart = 5.0 TB/s; non-temporal
+// apart would meet on a few memory channels (16 tokens x 4,096 x 151,936: 309 us so, 247 us apart, before the last round was spread; non-temporal
 // loads, which let go of a line after its first half, are slower).  The hidden rows, which all wavefronts share, come
 // through a ring of four chunks in LDS by
 // direct loads; 16-byte piece p of row r sits at piece p ^ ((r >> 1) & 7), so that 16 consecutive rows of one piece fall
@@ -24,11 +25,18 @@ namespace a3po {
 // 340 us for 200 tokens).  One workgroup per compute unit, static tiles of 256 vocabulary entries.
 //
 // NB: 16-token column blocks.  H is a multiple of 256 (the loop is unrolled by the ring).  Operations in flight are
-// counted by hand as in the contraction kernel: per chunk NB / 4 direct loads, then 4 operand loads, in this order (held to
-// in the source by in_order; tests/test_schedule.py reads it off the compiled kernel).
-constexpr int kFewThreads = 512;
-constexpr int kFewWaves = kFewThreads / kWave;
-constexpr int kFewRows = 32 * kFewWaves;  // vocabulary entries per tile
+// counted by hand as in the contraction kernel: per chunk NB / 4 direct loads, then 4 operand loads (2 in the loop with one
+// row block, whose first chunks thus wait for a little more than they need), in this order (held to in the source by in_order; tests/test_schedule.py reads it off the compiled kernel).
+//
+// A tile is 16 row blocks of 16, two per wavefront, but the tiles of the last round have only as many (last_blocks) as spread
+// its rows over all compute units (FewTiles): a wavefront without a first or second block multiplies the tile's first row,
+// whose lines all its lanes share, and leaves the products out of the fold.  A compute unit streams the weight at its own pace
+// whatever the others do, so a third round of 82 whole tiles took as long as the two full ones before it (16 tokens x 4,096 x
+// 151,936 247 us, now 220; x 2,048 x 32,000, 125 tiles on 256 units, 39 and 30; reading the rows of another block instead of
+// one row gains nothing: lines that two loads ask for at a time are fetched twice).  From 129 tokens on the products count
+// too: where no wavefront has a second block, the last round is a loop without it (192 tokens x 4,096 x 151,936 310 -> 286
+// us, 256: 345 -> 329; a branch inside the one loop spills the accumulators).
+constexpr int kFewThreads = kFewWaves * kWave;
 constexpr int kFewRing = 4;
 constexpr int kAhead = 4;
 constexpr int kFewMaxTokens = 256;
@@ -37,7 +45,8 @@ template <int NB> constexpr int kFewLdsBytes = kFewRing * NB * 16 * 128 + kFewWa
 template <int NB>
 __global__ __launch_bounds__(kFewThreads) void lmhead_few_tokens_kernel(const uint16_t *W,
                                                                         const uint16_t *__restrict__ h, int T, int H,
-                                                                        int V, float2 *__restrict__ partial)
+                                                                        int V, int nfull, int ntiles, int last_blocks,
+                                                                        float2 *__restrict__ partial)
 {
     constexpr int kSlot = NB * 16 * 128;  // bytes of one chunk of the hidden rows
     constexpr int kDma = NB / 4;          // direct loads per wavefront and chunk
@@ -45,7 +54,7 @@ __global__ __launch_bounds__(kFewThreads) void lmhead_few_tokens_kernel(const ui
     extern __shared__ __align__(16) char lds[];
     float2 *red = reinterpret_cast<float2 *>(lds + kFewRing * kSlot);  // [kFewWaves][NB * 16]
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int nch = H / 64, ntiles = (V + kFewRows - 1) / kFewRows;
+    const int nch = H / 64;
     const int64_t row_bytes = (int64_t)H * 2;
     const int rot = (int)(blockIdx.x % (unsigned)nch);
     auto chunk_at = [&](int i) { return i + rot < nch ? i + rot : i + rot - nch; };  // the i-th chunk this workgroup takes
@@ -66,18 +75,20 @@ __global__ __launch_bounds__(kFewThreads) void lmhead_few_tokens_kernel(const ui
     };
     // weight rows of a tile: this lane's two row blocks (rows past the vocabulary are clamped and masked below)
     const char *wcur[2], *wnext[2];
+    auto base_of = [&](int tile) { return tile < nfull ? tile * kFewRows : nfull * kFewRows + (tile - nfull) * last_blocks * 16; };
+    auto has = [&](int tile, int r) { return tile < nfull || r * kFewWaves + wave < last_blocks; };
     auto rows_of = [&](int tile, const char **p) {
 #pragma unroll
         for (int r = 0; r < 2; ++r) {
-            const int v = tile * kFewRows + wave * 32 + r * 16 + (lane & 15);
+            const int v = has(tile, r) ? base_of(tile) + (r * kFewWaves + wave) * 16 + (lane & 15) : base_of(tile);
             p[r] = reinterpret_cast<const char *>(W) + min(v, V - 1) * row_bytes + (lane >> 4) * 16;
         }
     };
     bf16x8_t a[kFewRing][2][2];  // [chunk mod ring][row block][half of the chunk]
-    auto load_weight = [&](int j, const char *const *p, int i) {
+    auto load_weight = [&](int j, const char *const *p, int i, int rows = 2) {
         const int chunk = chunk_at(i);
 #pragma unroll
-        for (int r = 0; r < 2; ++r)
+        for (int r = 0; r < rows; ++r)
 #pragma unroll
             for (int k = 0; k < 2; ++k)
                 a[j][r][k] = __builtin_bit_cast(
@@ -103,12 +114,13 @@ __global__ __launch_bounds__(kFewThreads) void lmhead_few_tokens_kernel(const ui
         if (j < kFewRing - 1) load_hidden(j, j);
         in_order();
     }
-    // (no test before the first tile: the loads above would be moved behind it)
-    do {
+    // one tile, of whose row blocks this wavefront has the first `rows`
+    auto take_tile = [&](auto rows) __attribute__((always_inline)) {
+        constexpr int kRows = decltype(rows)::value;
         rows_of(tile + (int)gridDim.x < ntiles ? tile + (int)gridDim.x : tile, wnext);  // (past the end: read again, unused)
-        f32x4_t acc[2][NB];
+        f32x4_t acc[kRows][NB];
 #pragma unroll
-        for (int r = 0; r < 2; ++r)
+        for (int r = 0; r < kRows; ++r)
 #pragma unroll
             for (int b = 0; b < NB; ++b)
 #pragma unroll
@@ -121,7 +133,7 @@ __global__ __launch_bounds__(kFewThreads) void lmhead_few_tokens_kernel(const ui
                 __builtin_amdgcn_sched_barrier(0);
                 // this chunk's hidden rows have landed (own loads: everything issued after them may still fly) and the
                 // reads of the chunk before are done: meet, then refill the slot of the chunk before
-                __builtin_amdgcn_s_waitcnt(waitcnt_imm(12 + 2 * kDma, 0));
+                __builtin_amdgcn_s_waitcnt(waitcnt_imm(3 * 2 * kRows + 2 * kDma, 0));
                 __builtin_amdgcn_s_barrier();
                 __builtin_amdgcn_sched_barrier(0);
                 const int ahead = c + j + kFewRing - 1;
@@ -139,43 +151,52 @@ __global__ __launch_bounds__(kFewThreads) void lmhead_few_tokens_kernel(const ui
                 for (int i = 0; i < 2 * NB; ++i) {
                     if (i + kAhead < 2 * NB) read(i + kAhead);
 #pragma unroll
-                    for (int r = 0; r < 2; ++r)
+                    for (int r = 0; r < kRows; ++r)
                         acc[r][i % NB] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[j][r][i / NB], fb[i % (kAhead + 1)],
                                                                                  acc[r][i % NB], 0, 0, 0);
                     __builtin_amdgcn_sched_barrier(0);
                 }
                 in_order();
-                load_weight(j, last ? wnext : wcur, last ? c + j + kFewRing - nch : c + j + kFewRing);
+                load_weight(j, last ? wnext : wcur, last ? c + j + kFewRing - nch : c + j + kFewRing, kRows);
                 in_order();
             }
         }
-        // fold the tile: accumulator (r, b, i) is entry r 16 + 4 (lane >> 4) + i of this wavefront's 32, token b 16 + (lane & 15)
-        const int left = V - tile * kFewRows - wave * 32 - 4 * (lane >> 4);
+        // fold the tile: accumulator (r, b, i) is entry 4 (lane >> 4) + i of this wavefront's row block r, token b 16 + (lane & 15)
+        int left[kRows];
+#pragma unroll
+        for (int r = 0; r < kRows; ++r) left[r] = has(tile, r) ? V - base_of(tile) - (r * kFewWaves + wave) * 16 - 4 * (lane >> 4) : 0;
 #pragma unroll
         for (int b = 0; b < NB; ++b) {
-            float f[8];
+            float f[4 * kRows];
 #pragma unroll
-            for (int r = 0; r < 2; ++r)
+            for (int r = 0; r < kRows; ++r)
 #pragma unroll
-                for (int i = 0; i < 4; ++i) f[r * 4 + i] = r * 16 + i < left ? acc[r][b][i] : -INFINITY;
+                for (int i = 0; i < 4; ++i) f[r * 4 + i] = i < left[r] ? acc[r][b][i] : -INFINITY;
             MaxSum mine = {kNegFloor, 0.0f};
-            fold<8>(mine, f);
+            fold<4 * kRows>(mine, f);
 #pragma unroll
             for (int off = 16; off <= 32; off <<= 1) {
                 const MaxSum other = {__shfl_xor(mine.m, off, kWave), __shfl_xor(mine.s, off, kWave)};
                 mine = combine(mine, other);
             }
             if (lane < 16) {  // (this wavefront's own row of red)
-                const float2 q = my_red[b * 16 + lane];
-                mine = combine(MaxSum{q.x, q.y}, mine);
-                my_red[b * 16 + lane] = make_float2(mine.m, mine.s);
+                const f32x2_t q = lds_get<f32x2_t>(my_red + b * 16 + lane);
+                mine = combine(MaxSum{q[0], q[1]}, mine);
+                lds_put(my_red + b * 16 + lane, f32x2_t{mine.m, mine.s});
             }
             __builtin_amdgcn_sched_barrier(0);
         }
 #pragma unroll
         for (int r = 0; r < 2; ++r) wcur[r] = wnext[r];
         tile += (int)gridDim.x;
-    } while (tile < ntiles);
+    };
+    // (no test before the first tile: the loads above would be moved behind it)
+    const int nloop = NB >= 12 && nfull > 0 && last_blocks <= kFewWaves ? nfull : ntiles;
+    do {
+        take_tile(std::integral_constant<int, 2>());
+    } while (tile < nloop);
+    if constexpr (NB >= 12)
+        if (tile < ntiles) take_tile(std::integral_constant<int, 1>());
     __syncthreads();  // (also drains the loads past the last tile)
     if (tid < NB * 16 && tid < T) {
         MaxSum tot = {kNegFloor, 0.0f};
@@ -278,14 +299,15 @@ hipError_t launch_lmhead_lse_finish(const void *hidden, const void *weight, int6
 
 template <int NB>
 static hipError_t launch_few_tokens(const void *hidden, const void *weight, int64_t T, int64_t H, int64_t V, float2 *partial,
-                                    int slots, hipStream_t s)
+                                    const FewTiles &ft, hipStream_t s)
 {
     static LdsLimitState lds_limit;
     auto *kernel = lmhead_few_tokens_kernel<NB>;
     const hipError_t e = ensure_lds_limit(reinterpret_cast<const void *>(kernel), kFewLdsBytes<NB>, lds_limit);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(kernel, dim3(slots), dim3(kFewThreads), kFewLdsBytes<NB>, s, reinterpret_cast<const uint16_t *>(weight),
-                       reinterpret_cast<const uint16_t *>(hidden), (int)T, (int)H, (int)V, partial);
+    hipLaunchKernelGGL(kernel, dim3(ft.slots), dim3(kFewThreads), kFewLdsBytes<NB>, s, reinterpret_cast<const uint16_t *>(weight),
+                       reinterpret_cast<const uint16_t *>(hidden), (int)T, (int)H, (int)V, ft.nfull, ft.ntiles, ft.last_blocks,
+                       partial);
     return hipGetLastError();
 }
 
@@ -294,21 +316,23 @@ hipError_t launch_fused_lmhead_logprob(const void *hidden, const void *weight, i
 {
     if (T == 0) return hipSuccess;
     float2 *partial = reinterpret_cast<float2 *>(workspace);
-    // Few tokens: the kernel for them up to 128; from 129 to 256 where its tiles occupy most compute units (every tile
+    // Few tokens: the kernel for them up to 192; from 193 to 256 where its tiles occupy most compute units (every tile
     // reads the T x H x 2 bytes of hidden rows, which at 256 tokens weigh as much as its 256 x H x 2 bytes of weight).
     // Contraction kernel / this one, us:
-    // 16 / 128 / 200 tokens x 4,096 x 151,936 347 / 334 / 346 and 247 / 272 / 342; 250 x 2,048 x 128,256 156 and 145,
-    // 250 x 1,536 x 50,264 (197 tiles) 58 and 57, 200 x 2,048 x 32,000 (125 tiles) 53 and 57.
+    // 16 / 128 / 192 / 200 tokens x 4,096 x 151,936 347 / 334 / 346 / 346 and 220 / 255 / 286 / 318; 192 x 4,096 x 16,000 / 40,000
+    // 79 / 113 and 73 / 94, 192 x 896 x 32,000 28.1 and 28.4; 250 x 2,048 x 128,256 156 and 139, 250 x 1,536 x 50,264 (197
+    // tiles) 58 and 57, 200 x 2,048 x 32,000 (125 tiles) 47 and 56.
     const GemmGrid gg = gemm_grid();
     const int64_t tiles = (V + kFewRows - 1) / kFewRows, cus = (int64_t)gg.nxcd * gg.per_xcd;
-    const bool few = T <= 128 || (T <= kFewMaxTokens && tiles >= cus * 3 / 4);
+    const bool few = T <= 192 || (T <= kFewMaxTokens && tiles >= cus * 3 / 4);
     if (few && H % 256 == 0 && V <= 0x7FFFFFFF - 256 * kFewRows) {
-        const int slots = (int)(tiles < cus ? tiles : cus);  // at most 256: gemm_partial_entries(T) is 256 T here
-        const hipError_t e = T <= 64    ? launch_few_tokens<4>(hidden, weight, T, H, V, partial, slots, s)
-                             : T <= 128 ? launch_few_tokens<8>(hidden, weight, T, H, V, partial, slots, s)
-                                        : launch_few_tokens<16>(hidden, weight, T, H, V, partial, slots, s);
+        const FewTiles ft = few_tiles(V, cus);  // at most 256 slots: gemm_partial_entries(T) is 256 T here
+        const hipError_t e = T <= 64    ? launch_few_tokens<4>(hidden, weight, T, H, V, partial, ft, s)
+                             : T <= 128 ? launch_few_tokens<8>(hidden, weight, T, H, V, partial, ft, s)
+                             : T <= 192 ? launch_few_tokens<12>(hidden, weight, T, H, V, partial, ft, s)
+                                        : launch_few_tokens<16>(hidden, weight, T, H, V, partial, ft, s);
         if (e != hipSuccess) return e;
-        return launch_lmhead_lse_finish(hidden, weight, T, H, V, chosen, partial, logp, lse, s, DynCount(), slots);
+        return launch_lmhead_lse_finish(hidden, weight, T, H, V, chosen, partial, logp, lse, s, DynCount(), ft.slots);
     }
     GemmArgs g = {};
     g.A = reinterpret_cast<const uint16_t *>(weight);

@@ -62,6 +62,15 @@ def test_fused_lmhead_logprob_small(a3po, T, H, V):
         assert logp[1] == 0 and logp[2] == 0
 
 
+@pytest.mark.parametrize("T,H,V", [(40, 256, 65536 + 16), (100, 256, 65536 + 4096 * 6 + 1), (129, 256, 65536), (150, 256, 65536 + 17),
+                                   (192, 512, 65536 + 4096 * 8), (170, 256, 65536 + 4096 * 8 + 1), (250, 512, 131072 + 4096 * 3 + 5),
+                                   (192, 256, 15), (192, 1024, 4097)])
+def test_fused_lmhead_logprob_last_round(a3po, T, H, V):
+    """Up to 256 tokens: last rounds of one, two, three, seven, eight, nine and sixteen row blocks a tile, after whole tiles and alone,
+    with one and two blocks a wavefront, and a ragged last block."""
+    test_fused_lmhead_logprob_small(a3po, T, H, V)
+
+
 def test_fused_lmhead_matches_materialised_path(a3po):
     # same inputs through a bf16-materialised logits matrix + a3po_token_logprobs: differs only by
     # the bf16 rounding of the logits the fused path never performs

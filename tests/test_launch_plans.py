@@ -44,3 +44,28 @@ int main()
     for T, blocks in plan:
         assert blocks * 12e-9 <= 4e-6 + 5 * T / 1.2e12, (T, blocks)
         assert (T + blocks - 1) // blocks < 2 ** 32, "a workgroup counts in 32 bits"
+
+
+def test_few_token_tiles_cover_the_vocabulary_evenly(tmp_path):
+    """Every row block of 16 vocabulary entries lies in one tile, no compute unit has more of them than an even share
+    rounded up, and there are no more tiles in a round than compute units."""
+    source = tmp_path / "few.cpp"
+    source.write_text('''#include <cstdio>
+#include "a3po_common.h"
+#include "a3po_launch.h"
+using namespace a3po;
+int main()
+{
+    for (int64_t cus : {256, 64, 38})
+        for (int64_t V = 1; V < 700000; V += V < 9000 ? 1 : 97) {
+            const FewTiles f = few_tiles(V, cus);
+            const int64_t blocks = (V + 15) / 16, held = f.nfull * 16ll + (int64_t)(f.ntiles - f.nfull) * f.last_blocks;
+            const int64_t rounds = f.nfull / cus, share = (blocks + cus - 1) / cus;
+            const bool ok = f.nfull % cus == 0 && f.ntiles > f.nfull && f.ntiles - f.nfull <= cus && f.last_blocks >= 1 &&
+                            f.last_blocks <= 16 && held >= blocks && held - blocks < f.last_blocks &&
+                            rounds * 16 + f.last_blocks <= share && f.slots == (f.ntiles < cus ? f.ntiles : cus);
+            if (!ok) return std::printf("V %lld on %lld\\\\n", (long long)V, (long long)cus), 1;
+        }
+}
+''')
+    assert run_on_host(str(source), tmp_path) == ""

@@ -93,3 +93,14 @@ def test_row_kernels_keep_their_rows_in_registers(assembly):
     spills = re.findall(r"\.name:\s+(_ZN4a3po\w+)\n(?:(?!\.name:).)*?\.vgpr_spill_count:\s+(\d+)", text, re.S)
     assert len(spills) > 100
     assert not [(name, n) for name, n in spills if int(n) > 15]
+
+
+@pytest.mark.parametrize("blocks", [12, 16])
+def test_few_token_kernel_with_one_row_block_waits_for_its_own_count(assembly, blocks):
+    """The last round's loop without second row blocks has two weight loads per chunk, and its waits allow for no more: what
+    may be in flight behind a chunk's hidden rows is three chunks' weight and two chunks' hidden rows."""
+    body, = kernels(assembly("a3po_lmhead.hip"), f"lmhead_few_tokens_kernelILi{blocks}E").values()
+    events, direct, load = memory_events(body), ["direct"] * (blocks // 4), ["global_load_dwordx4"]
+    wait = [6 + 2 * (blocks // 4), "barrier"]
+    first = events.index(wait[0])
+    assert events[first:first + 4 * (2 + len(direct) + 2)] == (wait + direct + load * 2) * 4, events[first:]
