@@ -33,8 +33,8 @@
 // Tile order.  One persistent workgroup per compute unit; the workgroups of an XCD (dispatch order deals
 // workgroups round-robin over the XCDs) form a block of ml x ncol tiles (8 x 4 in the usual case, GemmShape) that
 // share ml tiles of A and ncol tiles of B through that XCD's L2.  The tile grid is cut into such blocks ("pairs" of a
-// column group and a row round); pair p = group * rounds + round, and each XCD takes a contiguous range of pairs, i.e.
-// it sweeps down the rows of one column group before it moves to the next.  With kGemmLse* a workgroup therefore
+// column group and a row round); pair p = group * rounds + round, counted on through the groups of both widths where there are two (GemmCut), and each XCD
+// takes a contiguous range of pairs, i.e. it sweeps down the rows of one column group before it moves to the next.  With kGemmLse* a workgroup therefore
 // keeps its running (max, sum) in registers over a whole sweep and writes one partial per column per sweep.
 //
 // Results.  The logits and the weight gradient are stored transposed (element (m, n) at C[n ldc + m]): a lane's four
@@ -330,6 +330,13 @@ struct Operand {
     }
 };
 
+// a value that is the same for the wavefront, in scalar registers (64-bit divisions leave theirs in vector registers)
+__device__ __forceinline__ int64_t uniform64(int64_t v)
+{
+    return (int64_t)(((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(v >> 32)) << 32) |
+                     (uint32_t)__builtin_amdgcn_readfirstlane((int)v));
+}
+
 // QUAD: K is a multiple of kDmaStages stages.  Then every tile starts in ring slot 0, the K loop is unrolled by
 // the ring depth (all LDS addresses are constants) and the refill cursor moves once per kDmaStages stages.
 // Otherwise the loop is unrolled by two (the column fragments alternate; the number of stages is even) and slot
@@ -357,49 +364,92 @@ __global__ __launch_bounds__(kGemmThreads) void gemm_kernel(const GemmArgs g)
         else K = (v + 127) / 128 * 128;
         if (v <= 0) return;
     }
-    const GemmShape shp = gemm_shape(M, N, g.nxcd, g.per_xcd);
-    const int rounds = shp.rounds;
-    const int nl = slot % shp.ncol, ml = slot / shp.ncol;  // (ml >= shp.ml: no place in the block)
-    const int64_t tiles = (int64_t)shp.mtiles * shp.ntiles;
+    GemmCut cut;  // (part 1: LSE only)
+    if constexpr (LSE) {  // (the search costs some 3 us here: done on the host where N is known there)
+        if (g.dyn_dim == kDynNone) cut = g.cut;
+        else cut = gemm_cut(M, N, g.nxcd, g.per_xcd, g.room);
+    } else cut = gemm_plain_cut(gemm_shape(M, N, g.nxcd, g.per_xcd));
+    const int ntiles = LSE ? cut.tiles0 + cut.part[1].ntiles : cut.tiles0, mtiles = cut.part[0].mtiles;
+    const int nl0 = slot % cut.part[0].ncol, ml0 = slot / cut.part[0].ncol;  // (ml >= the part's ml: no place in its blocks)
+    const int nl1 = LSE ? slot % cut.part[1].ncol : 0, ml1 = LSE ? slot / cut.part[1].ncol : 0;
+    const int64_t tiles = (int64_t)mtiles * ntiles;
     const int slices = SPLIT ? gemm_slices(tiles, K / (kDmaK * kDmaStages), g.nxcd * g.per_xcd, g.split_max) : 1;
     const bool flat = SPLIT && slices > 1;
-    const int64_t pairs = (int64_t)shp.groups * rounds;
-    const int64_t p_end = flat ? tiles * slices : ml < shp.ml ? (int64_t)(xcd + 1) * pairs / g.nxcd : 0;
+    const bool placed = ml0 < cut.part[0].ml || (LSE && ml1 < cut.part[1].ml);
+    const int64_t p_end = uniform64(flat ? tiles * slices : placed ? (int64_t)(xcd + 1) * cut.pairs / g.nxcd : 0);
     const int nstages = (int)(K / kDmaK);
     const int wave_s = __builtin_amdgcn_readfirstlane(wave);  // the wavefront number in a scalar register
 
-    // the first work item at or after p for this workgroup (p_end if there is none): the next pair in this XCD's range
-    // whose tile exists for this workgroup's place in the block, or (flat) p itself
-    auto next_tile = [&](int64_t p) {
-        if (flat) return p < p_end ? p : p_end;
-        for (; p < p_end; ++p) {
-            const int grp = (int)(p / rounds), rnd = (int)(p % rounds);
-            if (rnd * shp.ml + ml < shp.mtiles && grp * shp.ncol + nl < shp.ntiles) break;
-        }
-        return p;
+    // A work item: number p, and for a pair its column group, round and part (counted on, not divided out of p).
+    struct Work {
+        int64_t p;
+        int grp, rnd;
+        bool two;
     };
-    const int64_t p_step = flat ? (int64_t)g.nxcd * g.per_xcd : 1;
+    // this workgroup's tile of a pair (its place in the block may have none: past the end of the grid or of the part)
+    auto row_tile = [&](const Work &w) { return w.rnd * (LSE && w.two ? cut.part[1].ml : cut.part[0].ml) + (LSE && w.two ? ml1 : ml0); };
+    auto column_tile = [&](const Work &w) {
+        return LSE && w.two ? cut.tiles0 + w.grp * cut.part[1].ncol + nl1 : w.grp * cut.part[0].ncol + nl0;
+    };
+    auto exists = [&](const Work &w) {
+        const bool two = LSE && w.two;
+        return (two ? ml1 < cut.part[1].ml : ml0 < cut.part[0].ml) && row_tile(w) < mtiles && column_tile(w) < (two ? ntiles : cut.tiles0);
+    };
+    auto step = [&](Work &w) {
+        ++w.p;
+        if (++w.rnd < (LSE && w.two ? cut.part[1].rounds : cut.part[0].rounds)) return;
+        w.rnd = 0;
+        ++w.grp;
+        if (LSE && w.p == cut.pairs0) {
+            w.two = true;
+            w.grp = 0;
+        }
+    };
+    // the first work item from w on for this workgroup (p >= p_end if there is none): the next pair in this XCD's range whose
+    // tile exists, or (flat) w itself
+    auto seek = [&](Work w) {
+        while (!flat && w.p < p_end && !exists(w)) step(w);
+        return w;
+    };
+    auto start = [&](int64_t p) {
+        Work w;
+        w.p = p;
+        w.two = LSE && p >= cut.pairs0;
+        const int64_t q = w.two ? p - cut.pairs0 : p;
+        const int rounds = w.two ? cut.part[1].rounds : cut.part[0].rounds;
+        w.grp = __builtin_amdgcn_readfirstlane((int)(q / rounds));
+        w.rnd = __builtin_amdgcn_readfirstlane((int)(q % rounds));
+        return seek(w);
+    };
+    auto next_item = [&](Work w) {
+        if (flat) {
+            w.p += (int64_t)g.nxcd * g.per_xcd;
+            return seek(w);
+        }
+        step(w);
+        return seek(w);
+    };
     // tile coordinates and stage range of a work item
     struct Item {
         int mt, nt, slice, s0, s1;
     };
-    auto locate = [&](int64_t p) {
+    auto locate = [&](const Work &w) {
         Item it;
         it.slice = 0;
         it.s0 = 0;
         it.s1 = nstages;
         if (flat) {  // (few items: 32-bit arithmetic)
-            const uint32_t u = (uint32_t)p, nt = (uint32_t)tiles, quads = (uint32_t)nstages / kDmaStages;
-            const uint32_t slice = u / nt, tile = u % nt, super = 8u * (uint32_t)shp.ntiles;
+            const uint32_t u = (uint32_t)w.p, nt = (uint32_t)tiles, quads = (uint32_t)nstages / kDmaStages;
+            const uint32_t slice = u / nt, tile = u % nt, super = 8u * (uint32_t)ntiles;
             it.slice = (int)slice;
             it.s0 = (int)(slice * quads / (uint32_t)slices) * kDmaStages;
             it.s1 = (int)((slice + 1) * quads / (uint32_t)slices) * kDmaStages;
-            const uint32_t srow = tile / super, in = tile % super, h = min(8u, (uint32_t)shp.mtiles - srow * 8u);
+            const uint32_t srow = tile / super, in = tile % super, h = min(8u, (uint32_t)mtiles - srow * 8u);
             it.mt = (int)(srow * 8u + in % h);
             it.nt = (int)(in / h);
         } else {
-            it.mt = (int)(p % rounds) * shp.ml + ml;
-            it.nt = (int)(p / rounds) * shp.ncol + nl;
+            it.mt = row_tile(w);
+            it.nt = column_tile(w);
         }
         if constexpr (SPLIT) {  // (the divisions are done in vector registers: back to scalar ones, as what they are for)
             it.mt = __builtin_amdgcn_readfirstlane(it.mt);
@@ -419,23 +469,23 @@ __global__ __launch_bounds__(kGemmThreads) void gemm_kernel(const GemmArgs g)
     auto frag_a = [&](char *stage, int t) { return opa.fragment(stage, fa_base, t); };
     auto frag_b = [&](char *stage, int t) { return opb.fragment(stage, fb_base, t); };
 
-    int64_t p_cur = next_tile(flat ? (int64_t)xcd * g.per_xcd + slot : (int64_t)xcd * pairs / g.nxcd);
-    if (p_cur >= p_end) return;  // uniform over the workgroup
+    Work w_cur = start(flat ? uniform64((int64_t)xcd * g.per_xcd + slot) : uniform64((int64_t)xcd * cut.pairs / g.nxcd));
+    if (w_cur.p >= p_end) return;  // uniform over the workgroup
 
-    // The refill cursor names the tile (r_p) and stage (r_k; QUAD: the first of a group of kDmaStages stages) that
+    // The refill cursor names the tile (r_w) and stage (r_k; QUAD: the first of a group of kDmaStages stages) that
     // the next refill loads.  Past the workgroup's last tile it stays on that tile's last stage (group): reloads of
     // bytes that are already there, which keep the number of loads per stage, and with it the s_waitcnt
     // arithmetic, constant.  Rows past the end of an operand are clamped (computed, never written).
-    int64_t r_p = p_cur;
+    Work r_w = w_cur;
     int r_k = 0, r_end = 0;
-    auto set_tile = [&](int64_t p) {
-        const Item it = locate(p);
+    auto set_tile = [&](const Work &w) {
+        const Item it = locate(w);
         r_k = it.s0;
         r_end = it.s1;
         opa.set_tile(it.mt);
         opb.set_tile(it.nt);
     };
-    set_tile(r_p);
+    set_tile(r_w);
     // direct load number q of one operand (0: A, 1: B) of stage r_k + u into ring slot sl
     auto refill = [&](int sl, int q, int u, int operand) {
         char *dst = lds + sl * kDmaStageBytes;
@@ -446,10 +496,10 @@ __global__ __launch_bounds__(kGemmThreads) void gemm_kernel(const GemmArgs g)
         if (r_k + step < r_end) {
             r_k += step;
         } else {
-            const int64_t np = next_tile(r_p + p_step);
-            if (np < p_end) {
-                r_p = np;
-                set_tile(np);
+            const Work next = next_item(r_w);
+            if (next.p < p_end) {
+                r_w = next;
+                set_tile(next);
             }
         }
     };
@@ -481,8 +531,8 @@ __global__ __launch_bounds__(kGemmThreads) void gemm_kernel(const GemmArgs g)
         run_s[b] = 0.0f;
     }
 
-    while (p_cur < p_end) {
-        const Item cur = locate(p_cur);
+    while (w_cur.p < p_end) {
+        const Item cur = locate(w_cur);
         const int64_t m0 = (int64_t)cur.mt * kGemmTile, n0 = (int64_t)cur.nt * kGemmTile;
         f32x4_t acc[8][4];
 #pragma unroll
@@ -543,7 +593,7 @@ __global__ __launch_bounds__(kGemmThreads) void gemm_kernel(const GemmArgs g)
         }
 
         // ---- the tile's epilogue, while the next tile's first stages arrive ----
-        const int64_t p_next = next_tile(p_cur + p_step);
+        const Work w_next = next_item(w_cur);
         const bool edge = m0 + kGemmTile > M || n0 + kGemmTile > N;  // uniform
         if constexpr (SPLIT) {
             float *stage_tile = reinterpret_cast<float *>(lds + kDmaRingBytes + kGemmRedBytes + wave_s * kStageBytes);
@@ -580,7 +630,7 @@ __global__ __launch_bounds__(kGemmThreads) void gemm_kernel(const GemmArgs g)
             }
             // end of this column group's sweep: merge the four lane groups, then the two row halves, and write the
             // workgroup's partial of its 256 columns (the reduction has LDS of its own: the ring keeps running)
-            if (p_next >= p_end || p_next / rounds != p_cur / rounds) {
+            if (w_next.p >= p_end || column_tile(w_next) != cur.nt) {
                 float2 *red = reinterpret_cast<float2 *>(lds + kDmaRingBytes);  // [2][256]
 #pragma unroll
                 for (int b = 0; b < 4; ++b) {
@@ -603,8 +653,11 @@ __global__ __launch_bounds__(kGemmThreads) void gemm_kernel(const GemmArgs g)
                     const f32x2_t q0 = lds_get<f32x2_t>(red + tid);
                     const f32x2_t q1 = lds_get<f32x2_t>(red + kGemmTile + tid);
                     const MaxSum tot = combine(MaxSum{q0[0], q0[1]}, MaxSum{q1[0], q1[1]});
-                    if (n0 + tid < N)
-                        g.partial[(int64_t)(xcd * shp.ml + ml) * N + n0 + tid] = make_float2(tot.m, tot.s);
+                    const int64_t c0 = min((int64_t)cut.tiles0 * kGemmTile, N);  // columns of part 0
+                    const bool two = n0 >= c0;
+                    float2 *partial = g.partial + (two ? (int64_t)g.nxcd * cut.part[0].ml * c0 + (xcd * cut.part[1].ml + ml1) * (N - c0) - c0
+                                                       : (xcd * cut.part[0].ml + ml0) * c0);
+                    if (n0 + tid < N) partial[n0 + tid] = make_float2(tot.m, tot.s);
                 }
                 asm volatile("" ::: "memory");
                 __builtin_amdgcn_s_waitcnt(waitcnt_imm(kNoVmWait, 0));  // red is read before anyone writes it again
@@ -612,7 +665,7 @@ __global__ __launch_bounds__(kGemmThreads) void gemm_kernel(const GemmArgs g)
                 asm volatile("" ::: "memory");
             }
         }
-        p_cur = p_next;
+        w_cur = w_next;
     }
     // drain: the reloads past the last stage must have landed before the workgroup ends
     __builtin_amdgcn_s_waitcnt(waitcnt_imm(0, 0));
@@ -679,6 +732,8 @@ hipError_t launch_gemm(const GemmArgs &args, int product, hipStream_t s)
     g.per_xcd = gg.per_xcd;
     const bool lse = product == kGemmLse || product == kGemmLseStore, quad = g.K % (kDmaK * kDmaStages) == 0;
     const bool panels = product == kGemmPanelsBf16 || product == kGemmPanelsF32;
+    if (lse && (!g.partial || g.room < (int64_t)gemm_partial_entries(g.N))) return hipErrorInvalidValue;
+    if (lse && g.dyn_dim == kDynNone) g.cut = gemm_cut(g.M, g.N, g.nxcd, g.per_xcd, g.room);
     // what the kernel's 32-bit offsets and its stage arithmetic assume
     if (g.M <= 0 || g.N <= 0 || g.K <= 0 || g.K % 64 != 0 || g.lda % 8 != 0 || g.ldb % 8 != 0 || g.lda > (1 << 22) ||
         g.ldb > (1 << 22))

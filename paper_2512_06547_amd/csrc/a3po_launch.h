@@ -150,6 +150,18 @@ __host__ __device__ inline int64_t dyn_extent(const DynCount &d, int64_t host_va
 
 enum GemmDynDim { kDynNone = 0, kDynM = 1, kDynN = 2, kDynK = 3 };
 
+// (see gemm_shape)
+struct GemmShape {
+    int mtiles, ntiles, ncol, ml, groups, rounds;
+};
+
+// (see gemm_cut)
+struct GemmCut {
+    GemmShape part[2];
+    int tiles0;           // column tiles of part 0
+    int64_t pairs0, pairs;
+};
+
 // Operand layouts (bfloat16, 16-byte aligned base, ld in elements):
 //   rows         [M, K] row-major, row stride ld: the contracted index is the fast one
 //   panels       panel layout (panel_offset) of [M, K]; ld = K extent of the buffer, rows padded to a multiple of 256
@@ -166,29 +178,27 @@ struct GemmArgs {
     void *C;            // row stride ldc elements; C^T: element (m, n) at C[n * ldc + m], M a multiple of the
     int64_t ldc;        // elements in 16 bytes
     float2 *partial;    // kGemmLse*: [slots][N] (max, sum) per column (see GemmShape), merged by the caller; room for
-                        // gemm_partial_entries(N) entries
+    int64_t room;       // this many entries, at least gemm_partial_entries(N)
     float *split;       // kGemmSplit*: room for split_max slices of M x N floats (overwritten)
     int split_max;
     int accumulate;     // kGemmPanelsF32
     int dyn_dim;        // GemmDynDim: which of M, N, K is replaced by dyn_extent(dyn, .) on the device (K: rounded up
     DynCount dyn;       // to 128; the host's M, N, K are then upper bounds).  A zero extent makes the launch a no-op.
     int nxcd, per_xcd;  // filled in by the launcher from the device: the persistent grid (nxcd x per_xcd workgroups)
+    GemmCut cut;        // filled in by the launcher: kGemmLse* whose extents the host knows
 };
 
 // How the workgroups of an XCD (per_xcd of them) share the tile grid: a block of ml rows x ncol columns of tiles, whose
 // operand tiles they share through that XCD's L2; the tile grid is cut into `groups` column groups of ncol tiles and
 // `rounds` of ml tile rows.  Four columns where there are enough of them (8 x 4 tiles on 32 compute units); up to three,
 // or five, six or nine, go as blocks of one to three columns, whose rows take the workgroups that this frees, and rows that
-// would leave XCDs without a block are cut into more rounds, whose columns then take them.  (Thirteen columns are
-// still 4 + 4 + 4 + 1.)  More blocks than XCDs for that would be a second round for some of them: 16 x 12 tiles as 9
+// would leave XCDs without a block are cut into more rounds, whose columns then take them (groups of different widths:
+// gemm_cut).  More blocks than XCDs for that would be a second round for some of them: 16 x 12 tiles as 9
 // blocks of 6 x 5 took two rounds for the one of 6 blocks of 8 x 4 (3,000 tokens x 4,096 x 4,000: 160 us, now 110).  A
 // launch with the log-sum-exp epilogue leaves one partial per column in each of nxcd * ml slots (slot = xcd * ml + row of
 // the block) that had a tile of that column.
 // (A fixed 8 x 4 block left three workgroups in four idle for a single column of tiles: log-probs of 200 tokens x
 // 4,096 x 151,936 925 us so, 333 us with blocks of 32 x 1; weight gradient with 6 tile rows 500 against 424 us.)
-struct GemmShape {
-    int mtiles, ntiles, ncol, ml, groups, rounds;
-};
 constexpr int kGemmTile = 256;  // tile edge, both sides
 constexpr int kGemmColTiles = 4;
 __host__ __device__ inline GemmShape gemm_shape(int64_t M, int64_t N, int nxcd, int per_xcd)
@@ -206,6 +216,54 @@ __host__ __device__ inline GemmShape gemm_shape(int64_t M, int64_t N, int nxcd, 
     s.ncol = per_xcd / s.ml < s.ntiles ? per_xcd / s.ml : s.ntiles;
     s.groups = (s.ntiles + s.ncol - 1) / s.ncol;
     return s;
+}
+
+// Cut of a tile grid for the products whose columns are tokens (kGemmLse*): up to two runs of column groups of different
+// widths, each with the blocks of rows that its width leaves room for; pairs are counted through both.  The columns are dealt
+// to as many groups of four as they need, or to one group less of four and five, as evenly as they go, and the cut with the
+// fewest tiles for the busiest workgroup is taken (the plain shape among them, which wins ties).  5 / 7 / 10 / 11 / 13 / 17
+// columns of 594 tile rows then take 13 / 17 / 25 / 27 / 32 / 41 rounds of tiles for the 15 / 19 / 29 / 29 / 38 / 47 of equal groups.
+// A cut whose partials do not fit the `room` entries there are is left out.
+// Log-probs of 1,100 / 1,700 / 2,400 / 3,200 / 4,200 tokens x 1,536 x 151,936 552 / 730 / 1,121 / 1,422 / 1,876 us with equal groups,
+// 502 / 700 / 1,011 / 1,280 / 1,634 so.
+__host__ __device__ inline int64_t gemm_cut_entries(const GemmCut &c, int64_t N, int nxcd)
+{
+    const int64_t n0 = (int64_t)c.tiles0 * kGemmTile < N ? (int64_t)c.tiles0 * kGemmTile : N;
+    return (int64_t)nxcd * (c.part[0].ml * n0 + c.part[1].ml * (N - n0));
+}
+__host__ __device__ inline GemmCut gemm_plain_cut(const GemmShape &s)
+{
+    GemmCut c;
+    c.part[0] = c.part[1] = s;
+    c.part[1].ntiles = c.part[1].ml = 0;  // (empty)
+    c.tiles0 = s.ntiles;
+    c.pairs0 = c.pairs = (int64_t)s.groups * s.rounds;
+    return c;
+}
+__host__ __device__ inline GemmCut gemm_cut(int64_t M, int64_t N, int nxcd, int per_xcd, int64_t room)
+{
+    GemmCut best = gemm_plain_cut(gemm_shape(M, N, nxcd, per_xcd));
+    const int nt = best.part[0].ntiles, mt = best.part[0].mtiles;
+    const int up = (nt + 3) / 4;
+    for (int g = up; nt > 4 && per_xcd >= 8 && best.pairs > nxcd && g >= 1 && g >= up - 1; --g) {
+        const int w = nt / g, more = nt % g;  // `more` groups of w + 1 columns, the others of w
+        if (w + (more > 0) > 5) continue;
+        GemmCut c;
+        for (int i = 0; i < 2; ++i) {
+            GemmShape &p = c.part[i];
+            p.mtiles = mt;
+            p.ncol = w + 1 - i;
+            p.groups = i ? g - more : more;
+            p.ntiles = p.groups * p.ncol;
+            p.rounds = (mt + per_xcd / p.ncol - 1) / (per_xcd / p.ncol);
+            p.ml = (mt + p.rounds - 1) / p.rounds;
+        }
+        c.tiles0 = c.part[0].ntiles;
+        c.pairs0 = (int64_t)c.part[0].groups * c.part[0].rounds;
+        c.pairs = c.pairs0 + (int64_t)c.part[1].groups * c.part[1].rounds;
+        if ((c.pairs + nxcd - 1) / nxcd < (best.pairs + nxcd - 1) / nxcd && gemm_cut_entries(c, N, nxcd) <= room) best = c;
+    }
+    return best;
 }
 
 // Slices of a kGemmSplit* launch.  A product with fewer tiles than compute units (or a last round of tiles that fills
@@ -309,11 +367,11 @@ hipError_t launch_fused_lmhead_logprob(const void *hidden, const void *weight, i
                                        const int32_t *chosen, float *logp, float *lse, void *workspace, hipStream_t s);
 
 // merges the (max, sum) partials of a token, adds the chosen logit (a dot product) and writes lse and log pi
-// (T is an upper bound when `count` names a device-side token count; slots > 0: that many partials per token, all of
+// (room: as given to the contraction; T is an upper bound when `count` names a device-side token count; slots > 0: that many partials per token, all of
 // them written, instead of those of a contraction)
 hipError_t launch_lmhead_lse_finish(const void *hidden, const void *weight, int64_t T, int64_t H, int64_t V,
                                     const int32_t *chosen, const float2 *partial, float *logp,
-                                    float *lse, hipStream_t s, DynCount count = DynCount(), int slots = 0);
+                                    float *lse, hipStream_t s, int64_t room, DynCount count = DynCount(), int slots = 0);
 
 size_t lmhead_bwd_workspace_bytes(int64_t T, int64_t V, int64_t H);
 

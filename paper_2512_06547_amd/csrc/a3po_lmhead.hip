@@ -218,7 +218,7 @@ __global__ __launch_bounds__(256) void lmhead_finish_kernel(const uint16_t *__re
                                                             const uint16_t *__restrict__ h, int64_t T, int64_t H,
                                                             int64_t V, const int32_t *__restrict__ chosen,
                                                             const float2 *__restrict__ partial, int nxcd, int per_xcd,
-                                                            int slots, float *logp, float *lse_out, DynCount count)
+                                                            GemmCut host_cut, int64_t room, int slots, float *logp, float *lse_out, DynCount count)
 {
     const int lane = threadIdx.x & 63;
     const int64_t t = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
@@ -226,22 +226,30 @@ __global__ __launch_bounds__(256) void lmhead_finish_kernel(const uint16_t *__re
     if (t >= N) return;
     const int32_t y = chosen[t];
     const bool ok = y >= 0 && (int64_t)y < V;
-    // slot (xcd, m) holds a partial of this token if that XCD's range of pairs met the token's column group in a round
-    // that has a tile for row m of the block (GemmShape)
-    const GemmShape shp = gemm_shape(V, N, nxcd, per_xcd);
-    const int64_t pairs = (int64_t)shp.groups * shp.rounds, g0 = (t / kGemmTile / shp.ncol) * shp.rounds;
     MaxSum tot = {kNegFloor, 0.0f};
     // (slots > 0: that many partials, all of them written)
     for (int p = lane; p < slots; p += kWave) {
         const float2 q = partial[(int64_t)p * N + t];
         tot = combine(tot, MaxSum{q.x, q.y});
     }
-    for (int p = lane; slots == 0 && p < nxcd * shp.ml; p += kWave) {
-        const int xcd = p / shp.ml, m = p % shp.ml;
-        const int64_t lo = max((int64_t)xcd * pairs / nxcd, g0), hi = min((int64_t)(xcd + 1) * pairs / nxcd, g0 + shp.rounds);
-        if (lo < hi && (lo - g0) * shp.ml + m < shp.mtiles) {
-            const float2 q = partial[(int64_t)p * N + t];
-            tot = combine(tot, MaxSum{q.x, q.y});
+    if (slots == 0) {
+        // slot (xcd, m) holds a partial of this token if that XCD's range of pairs met the token's column group in a round
+        // that has a tile for row m of the block (GemmCut)
+        const GemmCut cut = count.n ? gemm_cut(V, N, nxcd, per_xcd, room) : host_cut;
+        const int tile = (int)(t / kGemmTile);
+        const int64_t c0 = min((int64_t)cut.tiles0 * kGemmTile, N);
+        const bool two = tile >= cut.tiles0;
+        const int ml = two ? cut.part[1].ml : cut.part[0].ml, rounds = two ? cut.part[1].rounds : cut.part[0].rounds;
+        const int64_t g0 = two ? cut.pairs0 + (int64_t)((tile - cut.tiles0) / cut.part[1].ncol) * rounds : (int64_t)(tile / cut.part[0].ncol) * rounds;
+        const float2 *mine = two ? partial + (int64_t)nxcd * cut.part[0].ml * c0 + (t - c0) : partial + t;
+        const int64_t width = two ? N - c0 : c0;
+        for (int p = lane; p < nxcd * ml; p += kWave) {
+            const int xcd = p / ml, m = p % ml;
+            const int64_t lo = max((int64_t)xcd * cut.pairs / nxcd, g0), hi = min((int64_t)(xcd + 1) * cut.pairs / nxcd, g0 + rounds);
+            if (lo < hi && (lo - g0) * ml + m < cut.part[0].mtiles) {
+                const float2 q = mine[(int64_t)p * width];
+                tot = combine(tot, MaxSum{q.x, q.y});
+            }
         }
     }
     float dot = 0.0f;
@@ -287,12 +295,13 @@ size_t lmhead_workspace_bytes(int64_t T)
 
 hipError_t launch_lmhead_lse_finish(const void *hidden, const void *weight, int64_t T, int64_t H, int64_t V,
                                     const int32_t *chosen, const float2 *partial, float *logp,
-                                    float *lse, hipStream_t s, DynCount count, int slots)
+                                    float *lse, hipStream_t s, int64_t room, DynCount count, int slots)
 {
     const unsigned grid = (unsigned)((T + 3) / 4);
     const GemmGrid gg = gemm_grid();
+    const GemmCut cut = gemm_cut(V, T, gg.nxcd, gg.per_xcd, room);
     hipLaunchKernelGGL(lmhead_finish_kernel, dim3(grid), dim3(256), 0, s, reinterpret_cast<const uint16_t *>(weight),
-                       reinterpret_cast<const uint16_t *>(hidden), T, H, V, chosen, partial, gg.nxcd, gg.per_xcd, slots,
+                       reinterpret_cast<const uint16_t *>(hidden), T, H, V, chosen, partial, gg.nxcd, gg.per_xcd, cut, room, slots,
                        logp, lse, count);
     return hipGetLastError();
 }
@@ -332,7 +341,7 @@ hipError_t launch_fused_lmhead_logprob(const void *hidden, const void *weight, i
                              : T <= 192 ? launch_few_tokens<12>(hidden, weight, T, H, V, partial, ft, s)
                                         : launch_few_tokens<16>(hidden, weight, T, H, V, partial, ft, s);
         if (e != hipSuccess) return e;
-        return launch_lmhead_lse_finish(hidden, weight, T, H, V, chosen, partial, logp, lse, s, DynCount(), ft.slots);
+        return launch_lmhead_lse_finish(hidden, weight, T, H, V, chosen, partial, logp, lse, s, 0, DynCount(), ft.slots);
     }
     GemmArgs g = {};
     g.A = reinterpret_cast<const uint16_t *>(weight);
@@ -343,9 +352,10 @@ hipError_t launch_fused_lmhead_logprob(const void *hidden, const void *weight, i
     g.N = T;
     g.K = H;
     g.partial = partial;
+    g.room = (int64_t)gemm_partial_entries(T);
     hipError_t e = launch_gemm(g, kGemmLse, s);
     if (e != hipSuccess) return e;
-    return launch_lmhead_lse_finish(hidden, weight, T, H, V, chosen, g.partial, logp, lse, s);
+    return launch_lmhead_lse_finish(hidden, weight, T, H, V, chosen, g.partial, logp, lse, s, g.room);
 }
 
 }  // namespace a3po

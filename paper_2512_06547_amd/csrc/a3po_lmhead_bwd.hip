@@ -485,11 +485,12 @@ extern "C" int a3po_fused_lmhead_loss_fwd_bwd(const void *hidden, const void *we
         fw.C = zt;
         fw.ldc = lay.ldv;
         fw.partial = partial;
+        fw.room = (int64_t)gemm_partial_entries(lay.chunk);
         fw.dyn_dim = kDynN;
         fw.dyn = cnt;
         if (launch_gemm(fw, kGemmLseStore, s) != hipSuccess) return A3PO_E_LAUNCH;
         // 2. log pi_theta and the per-token terms
-        if (launch_lmhead_lse_finish(hc + c0 * H, W, nmax, H, V, ysel + c0, partial, logp_c + c0, lse + c0, s, cnt) != hipSuccess)
+        if (launch_lmhead_lse_finish(hc + c0 * H, W, nmax, H, V, ysel + c0, partial, logp_c + c0, lse + c0, s, fw.room, cnt) != hipSuccess)
             return A3PO_E_LAUNCH;
         hipLaunchKernelGGL(lmhead_token_terms_kernel, dim3((unsigned)((nmax + 255) / 256)), dim3(256), 0, s,
                            a.ws_records, index + c0, cnt, current_version, clip_eps, hdr, logp_c + c0, logp_out,

@@ -71,6 +71,12 @@ def test_fused_lmhead_logprob_last_round(a3po, T, H, V):
     test_fused_lmhead_logprob_small(a3po, T, H, V)
 
 
+@pytest.mark.parametrize("T", [1025, 1100, 1792, 2305, 2560, 2600, 3328])
+def test_fused_lmhead_logprob_uneven_column_groups(a3po, T):
+    """5, 7, 10, 11 and 13 columns of tiles over 80 rows of them: column groups of two widths, whose partials lie apart."""
+    test_fused_lmhead_logprob_small(a3po, T, 64, 20300)
+
+
 def test_fused_lmhead_matches_materialised_path(a3po):
     # same inputs through a bf16-materialised logits matrix + a3po_token_logprobs: differs only by
     # the bf16 rounding of the logits the fused path never performs

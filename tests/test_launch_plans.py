@@ -69,3 +69,7 @@ int main()
 }
 ''')
     assert run_on_host(str(source), tmp_path) == ""
+
+
+def test_uneven_column_groups_leave_no_tile_out_and_no_unit_worse_off(tmp_path):
+    assert run_on_host(os.path.join(HERE, "gemm_cut_driver.cpp"), tmp_path) == "ok\n"
