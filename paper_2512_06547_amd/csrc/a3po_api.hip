@@ -197,13 +197,14 @@ int a3po_loss_fwd_bwd_ex(const void *logits, a3po_dtype dt, int64_t T, int64_t V
     a.accumulate = o.accumulate;
     carve_loss_ws(a, workspace, T);
 
-    if (launch_loss_prep(a, s) != hipSuccess) return A3PO_E_LAUNCH;
+    const int parts = few_rows_parts(a, device_cu_count());
+    if (parts == 0 && launch_loss_prep(a, s) != hipSuccess) return A3PO_E_LAUNCH;
     if (o.event_before_rows && hipEventRecord(static_cast<hipEvent_t>(o.event_before_rows), s) != hipSuccess)
         return A3PO_E_LAUNCH;
-    if (launch_loss_rows(a, s) != hipSuccess) return A3PO_E_LAUNCH;
+    if ((parts ? launch_few_rows_loss(a, parts, s) : launch_loss_rows(a, s)) != hipSuccess) return A3PO_E_LAUNCH;
     if (o.event_after_rows && hipEventRecord(static_cast<hipEvent_t>(o.event_after_rows), s) != hipSuccess)
         return A3PO_E_LAUNCH;
-    if (launch_loss_finish(a, s) != hipSuccess) return A3PO_E_LAUNCH;
+    if (parts == 0 && launch_loss_finish(a, s) != hipSuccess) return A3PO_E_LAUNCH;
     return A3PO_OK;
 }
 

@@ -3,72 +3,9 @@
 // histograms of per-token quantities.
 #include "a3po_common.h"
 #include "a3po_launch.h"
+#include "a3po_tokens.h"
 
 namespace a3po {
-
-constexpr int kTokThreads = 1024;
-constexpr int kTokWaves = kTokThreads / kWave;
-
-// Counts of a range of tokens: those that enter the loss (mask != 0 and a valid chosen id), and those with
-// mask != 0 and an id outside [0, V).
-struct PrepPartial {
-    long long cnt, bad;
-};
-
-// Packs the inputs of tokens [t_begin, t_end) into one 16-byte record each for the row kernel (y = -1 when the
-// token does not enter the loss) and counts them; the totals of the workgroup are returned to thread 0.
-__device__ __forceinline__ PrepPartial pack_records(const int32_t *chosen, const uint8_t *mask, const float *lb,
-                                                    const int32_t *versions, const float *adv, const float *prox_in,
-                                                    int64_t t_begin, int64_t t_end, int64_t V, TokenRecord *records)
-{
-    __shared__ long long s_cnt[kTokWaves], s_bad[kTokWaves];
-    long long cnt = 0, bad = 0;
-    for (int64_t t = t_begin + threadIdx.x; t < t_end; t += kTokThreads) {
-        const bool m = mask[t] != 0;
-        const int32_t y = chosen[t];
-        const bool ok = y >= 0 && (int64_t)y < V;
-        cnt += (m && ok) ? 1 : 0;
-        bad += (m && !ok) ? 1 : 0;
-        TokenRecord r;
-        r.y = (m && ok) ? y : -1;
-        // a given proximal log-prob rides in the version slot; the coupled objective needs neither
-        r.ver = prox_in ? __float_as_int(prox_in[t]) : (versions ? versions[t] : 0);
-        r.lb = lb[t];
-        r.A = adv[t];
-        records[t] = r;
-    }
-#pragma unroll
-    for (int off = kWave / 2; off > 0; off >>= 1) {
-        cnt += __shfl_xor(cnt, off, kWave);
-        bad += __shfl_xor(bad, off, kWave);
-    }
-    const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
-    if (lane == 0) {
-        s_cnt[wave] = cnt;
-        s_bad[wave] = bad;
-    }
-    __syncthreads();
-    PrepPartial p = {0, 0};
-    if (threadIdx.x == 0) {
-        for (int w = 0; w < kTokWaves; ++w) {
-            p.cnt += s_cnt[w];
-            p.bad += s_bad[w];
-        }
-    }
-    return p;
-}
-
-// Header of a call: 1/N with N the number of counted tokens, or the caller's denominator when it is positive;
-// the counts for the statistics; the row kernel's work queue starts empty.
-__device__ __forceinline__ void write_header(PrepPartial total, float denom, WsHeader *hdr)
-{
-    const float n = denom > 0.0f ? denom : (float)total.cnt;
-    hdr->inv_n = n > 0.0f ? 1.0f / n : 0.0f;
-    hdr->n_as_float = n;
-    hdr->n_counted = total.cnt;
-    hdr->n_bad = total.bad;
-    *row_queue_of(hdr) = 0u;
-}
 
 // One workgroup does both (short batches).
 __global__ __launch_bounds__(kTokThreads) void loss_prep_kernel(const int32_t *chosen, const uint8_t *mask,
@@ -126,48 +63,6 @@ __global__ __launch_bounds__(kTokMaxBlocks) void loss_prep_header_kernel(const P
     }
 }
 
-// Totals of the finish pass over a range of tokens.
-struct FinishTotals {
-    double sum, esum;     // sum of obj and of the entropies over counted tokens
-    long long clip, neg;  // clipped tokens, tokens with negative staleness
-    float lo, hi;         // extrema of the importance weight
-};
-
-static_assert(sizeof(FinishTotals) <= 64 && sizeof(PrepPartial) <= 64, "a partial is at most 64 bytes of the scratch area");
-
-// loss_out / stats_out from the totals of the whole call (overwritten, or merged into what earlier micro-batches of
-// the same update left there)
-__device__ __forceinline__ void write_loss_and_stats(const FinishTotals &tot, bool have_entropy, const WsHeader *hdr,
-                                                     float *loss_out, a3po_stats *stats, int accumulate)
-{
-    const float share = (float)(-(tot.sum * (double)hdr->inv_n));
-    *loss_out = accumulate ? *loss_out + share : share;
-    if (!stats) return;
-    a3po_stats o;
-    o.n_tokens = hdr->n_counted;
-    o.n_clipped = tot.clip;
-    o.n_bad_index = hdr->n_bad;
-    o.n_negative_staleness = tot.neg;
-    o.iw_min = tot.lo;
-    o.iw_max = tot.hi;
-    o.entropy_mean = (have_entropy && hdr->n_counted > 0) ? (float)(tot.esum / (double)hdr->n_counted) : 0.0f;
-    o.reserved = 0.0f;
-    if (accumulate) {
-        const a3po_stats p = *stats;
-        const long long n = p.n_tokens + o.n_tokens;
-        o.entropy_mean = (have_entropy && n > 0)
-                             ? (float)(((double)p.entropy_mean * (double)p.n_tokens + tot.esum) / (double)n)
-                             : 0.0f;
-        o.n_tokens = n;
-        o.n_clipped += p.n_clipped;
-        o.n_bad_index += p.n_bad_index;
-        o.n_negative_staleness += p.n_negative_staleness;
-        o.iw_min = fminf(o.iw_min, p.iw_min);
-        o.iw_max = fmaxf(o.iw_max, p.iw_max);
-    }
-    *stats = o;
-}
-
 // loss = -(1/N) sum over counted tokens of obj, accumulated in double in a fixed order
 // (thread-strided partials, then a fixed tree), so repeated runs agree bit for bit.
 // ent (nullable): per-token entropies the row kernel wrote; their mean over counted tokens goes to
@@ -182,9 +77,6 @@ __global__ __launch_bounds__(kTokThreads) void loss_finish_kernel(const float *o
 {
     const int64_t t_begin = partial ? (int64_t)blockIdx.x * per_block : 0;
     const int64_t t_end = partial ? min(T, t_begin + per_block) : T;
-    __shared__ double s_sum[kTokWaves], s_ent[kTokWaves];
-    __shared__ long long s_clip[kTokWaves], s_neg[kTokWaves];
-    __shared__ float s_min[kTokWaves], s_max[kTokWaves];
     double sum = 0.0, esum = 0.0;
     long long clip = 0, neg = 0;
     float lo = INFINITY, hi = -INFINITY;
@@ -222,35 +114,8 @@ __global__ __launch_bounds__(kTokThreads) void loss_finish_kernel(const float *o
             }
         }
     }
-#pragma unroll
-    for (int off = kWave / 2; off > 0; off >>= 1) {
-        sum += __shfl_xor(sum, off, kWave);
-        esum += __shfl_xor(esum, off, kWave);
-        clip += __shfl_xor(clip, off, kWave);
-        neg += __shfl_xor(neg, off, kWave);
-        lo = fminf(lo, __shfl_xor(lo, off, kWave));
-        hi = fmaxf(hi, __shfl_xor(hi, off, kWave));
-    }
-    const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
-    if (lane == 0) {
-        s_sum[wave] = sum;
-        s_ent[wave] = esum;
-        s_clip[wave] = clip;
-        s_neg[wave] = neg;
-        s_min[wave] = lo;
-        s_max[wave] = hi;
-    }
-    __syncthreads();
+    const FinishTotals tot = block_totals({sum, esum, clip, neg, lo, hi});
     if (threadIdx.x == 0) {
-        FinishTotals tot = {0.0, 0.0, 0, 0, INFINITY, -INFINITY};
-        for (int w = 0; w < kTokWaves; ++w) {
-            tot.sum += s_sum[w];
-            tot.esum += s_ent[w];
-            tot.clip += s_clip[w];
-            tot.neg += s_neg[w];
-            tot.lo = fminf(tot.lo, s_min[w]);
-            tot.hi = fmaxf(tot.hi, s_max[w]);
-        }
         if (partial) partial[blockIdx.x] = tot;
         else write_loss_and_stats(tot, ent != nullptr, hdr, loss_out, stats, accumulate);
     }

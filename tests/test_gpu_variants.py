@@ -268,3 +268,114 @@ def test_long_batches_of_short_rows(a3po, S, L):
     # fixed summation order within and across workgroups: a second run gives the same bits
     again = run_ex(a3po, c, want_entropy=True)
     assert torch.equal(again["loss"], out["loss"])
+
+
+# Batches of no more rows than compute units (and no more bytes than the caches serve) go through kernels that cut every row
+# into parts: rows of one part short of too small, parts that are empty, a row in 32 parts, logits and gradient of equal and
+# different alignment, 256 rows.
+SHORT = [(1, "bf16", 151936, 0, 0, 0), (2, "bf16", 400001, 1, 3, 3), (2, "f32", 114690, 0, 0, 1), (110, "f32", 151936, 0, 0, 0), (2, "f32", 4096, 0, 0, 0), (3, "bf16", 8192, 0, 0, 0), (5, "bf16", 16391, 3, 1, 3),
+         (17, "f32", 65537, 0, 3, 3), (100, "f32", 16387, 2, 0, 2), (128, "bf16", 33001, 0, 8, 16), (256, "bf16", 8200, 8, 0, 0),
+         (256, "f32", 20001, 0, 1, 0)]
+
+
+@pytest.mark.parametrize("entropy", [False, True])
+@pytest.mark.parametrize("T,dtype,V,pad,z_off,dz_off", SHORT)
+def test_short_batches(a3po, T, dtype, V, pad, z_off, dz_off, entropy):
+    """Every output and every gradient element against the oracle (the bars of test_gpu_parity.py and of this file), padding
+    and neighbours untouched; chosen entries at both ends of a row, and a clipped token, a zero advantage, a masked token,
+    an invalid id and a row of -inf but for two entries among the rows."""
+    L = (T + 3) // 4
+    w = synth.WORKLOADS["tiny"].scaled(V=V, dtype=dtype, S=4, L=L, G=4, len_lo=L, len_hi=L, sigma=3.0, boost=6.0,
+                                       boost_prob=0.5, noise_std=0.2, stale_max=3)
+    c = make_case(w, T=T, ld=V + pad)
+    c["mask"][:] = 1
+    c["chosen"][0] = V - 1
+    c["adv"][:] = np.linspace(-1.5, 1.5, T, dtype=np.float32) + 0.25
+    if T >= 5:
+        c["chosen"][1] = 0
+        c["adv"][1] = 0.0
+        c["lb"][2], c["adv"][2], c["versions"][2] = c["lb"][2] - 1.0, 0.7, CUR
+        c["mask"][3] = 0
+        c["chosen"][4] = V
+    if T >= 17:
+        z, ninf = c["z"], (-np.inf if dtype == "f32" else 0xFF80)
+        keep = z[10, [5, V - 2]].copy()
+        z[10, :V] = ninf
+        z[10, [5, V - 2]] = keep
+        c["chosen"][10] = 5
+        c["lb"][10] = oracle.token_logprobs(z[10:11], c["chosen"][10:11], V=V)["logp"][0]
+    ld, dt = V + pad, torch.float32 if dtype == "f32" else torch.bfloat16
+
+    def place(off):
+        flat = torch.full((off + T * ld + 64,), 7.0, dtype=dt, device="cuda")
+        return flat, flat[off:off + T * ld].view(T, ld)
+
+    _, z_at = place(z_off)
+    z_at.copy_(dev_logits(c["z"]))
+    flat, dz_at = place(dz_off)
+    kw = dict(V=V, want_entropy=entropy, want_iw=True, want_clipped=True)
+    args = (cu(c["chosen"]), cu(c["lb"]), cu(c["versions"]), CUR, cu(c["adv"]), cu(c["mask"]), w.clip_eps)
+    out = a3po.loss_fwd_bwd(z_at, *args, dlogits=dz_at, **kw)
+    torch.cuda.synchronize()
+    check_against_oracle(a3po, c, out)
+    assert (flat[:dz_off].float() == 7.0).all() and (flat[dz_off + T * ld:].float() == 7.0).all()
+    assert (dz_at[:, V:].float() == 7.0).all(), "padding columns were written"
+    live = (c["mask"] != 0) & (c["chosen"] < V)
+    sur = oracle.surrogate(oracle.token_logprobs(c["z"], np.where(live, c["chosen"], 0), V=V)["logp"], c["lb"], c["versions"], CUR,
+                           c["adv"], live.astype(np.uint8), w.clip_eps, 0.0)
+    iw = out["iw"].cpu().numpy().astype(np.float64)
+    assert (np.abs(iw - sur["iw"] * live) <= 2e-5 * np.abs(sur["iw"]) + 1e-6).all()
+    assert int(out["clipped"].sum()) == a3po.stats_to_dict(out["stats"])["n_clipped"]
+    if entropy:
+        ref, lse = oracle.entropy(c["z"], V=V), oracle.token_logprobs(c["z"], np.where(live, c["chosen"], 0), V=V)["lse"]
+        assert_close_entropy(out["entropy"].cpu().numpy()[live], ref[live], lse[live], "entropy")
+        assert (out["entropy"].cpu().numpy()[~live] == 0).all()
+    # the gradient in the logits' place
+    inp = a3po.loss_fwd_bwd(z_at, *args, dlogits=z_at, **kw)
+    torch.cuda.synchronize()
+    check_against_oracle(a3po, c, inp)
+    if z_off == dz_off:  # (the cut into parts follows the gradient's address, the order of summation the cut)
+        assert torch.equal(inp["logp"], out["logp"]) and torch.equal(inp["loss"], out["loss"])
+        assert torch.equal(z_at[:, :V].contiguous().view(torch.uint8), dz_at[:, :V].contiguous().view(torch.uint8))
+
+
+# The row kernels' forms on batches that the short kernels do not take: 24 rows of every kind, twelve times over.
+LONG_BATCHES = ([(d, V, V + pad, 0, 0) for d, V, pad in ENTROPY_CASES] +
+                [("bf16", 8191, 8192, 0, 0), ("bf16", 12289, 12352, 0, 0), ("f32", 16385, 16416, 0, 0), ("bf16", 30001, 30016, 0, 0),
+                 ("bf16", 163833, 163840, 0, 0), ("f32", 86017, 86048, 0, 0), ("f32", 114690, 114720, 0, 0),
+                 ("bf16", 163841, 163904, 0, 0), ("bf16", 50001, 50001, 1, 3), ("f32", 32003, 32003, 1, 2),
+                 ("bf16", 151936, 151936, 8, 24), ("f32", 114690, 114692, 1, 1), ("f32", 90001, 90001, 1, 2)])
+
+
+@pytest.mark.parametrize("entropy", [False, True])
+@pytest.mark.parametrize("dtype,V,ld,z_off,dz_off", LONG_BATCHES)
+def test_rows_of_batches_longer_than_the_chip(a3po, dtype, V, ld, z_off, dz_off, entropy):
+    w = synth.WORKLOADS["tiny"].scaled(V=V, dtype=dtype, S=4, L=6, len_lo=4, len_hi=6, sigma=3.0, boost=6.0, boost_prob=0.5,
+                                       noise_std=0.15, stale_max=6)
+    c = make_case(w, ld=ld)
+    n, times = c["T"], 12
+    T, denom, dt = n * times, 100.0, torch.float32 if dtype == "f32" else torch.bfloat16
+
+    def place(off):
+        flat = torch.full((off + T * ld + 64,), 7.0, dtype=dt, device="cuda")
+        return flat, flat[off:off + T * ld].view(T, ld)
+
+    _, z_at = place(z_off)
+    z_at.copy_(dev_logits(c["z"]).repeat(times, 1))
+    flat, dz_at = place(dz_off)
+    rep = lambda k: cu(np.tile(c[k], times))
+    out = a3po.loss_fwd_bwd(z_at, rep("chosen"), rep("lb"), rep("versions"), CUR, rep("adv"), rep("mask"), w.clip_eps, V=V,
+                            denom=denom, dlogits=dz_at, want_entropy=entropy)
+    torch.cuda.synchronize()
+    assert (flat[:dz_off].float() == 7.0).all() and (flat[dz_off + T * ld:].float() == 7.0).all()
+    assert (dz_at[:, V:].float() == 7.0).all(), "padding columns were written"
+    ref = oracle.loss_fwd_bwd(c["z"], c["chosen"], c["lb"], c["versions"], CUR, c["adv"], c["mask"], w.clip_eps, denom=denom, V=V)
+    sur = oracle.surrogate(ref["logp"], c["lb"], c["versions"], CUR, c["adv"], ref["eff_mask"], w.clip_eps, denom)
+    away = (np.abs(np.abs(sur["r"] - 1) - w.clip_eps) >= 1e-3) | (ref["eff_mask"] == 0)  # the clip decision is certain
+    ent = np.where(c["mask"] != 0, oracle.entropy(c["z"], V=V), 0.0) if entropy else None
+    for i in range(times):
+        rows = slice(i * n, (i + 1) * n)
+        assert_close_logp(out["logp"][rows].cpu().numpy(), ref["logp"], f"logp {i}")
+        assert_close_dz(host_rows(dz_at[rows, :V])[away], ref["dz"][away][:, :V], ref["g"][away], dtype, f"dlogits {i}")
+        if entropy:
+            assert_close_entropy(out["entropy"][rows].cpu().numpy(), ent, c["fwd"]["lse"], f"entropy {i}")
