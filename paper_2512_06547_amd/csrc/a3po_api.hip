@@ -197,7 +197,7 @@ int a3po_loss_fwd_bwd_ex(const void *logits, a3po_dtype dt, int64_t T, int64_t V
     a.accumulate = o.accumulate;
     carve_loss_ws(a, workspace, T);
 
-    const int parts = few_rows_parts(a, device_cu_count());
+    const int parts = few_rows_parts(a);
     if (parts == 0 && launch_loss_prep(a, s) != hipSuccess) return A3PO_E_LAUNCH;
     if (o.event_before_rows && hipEventRecord(static_cast<hipEvent_t>(o.event_before_rows), s) != hipSuccess)
         return A3PO_E_LAUNCH;

@@ -22,6 +22,27 @@ namespace a3po {
 
 constexpr int kFewUnroll = 4;  // 16-byte vectors in flight per thread
 
+// 16 bytes from an address that is only aligned to the element (ANY), or a multiple of 16.  KEEP: read again soon.
+typedef u32x4_t few_elem_t __attribute__((aligned(2)));
+template <bool ANY, bool KEEP>
+__device__ __forceinline__ uint4 few_load(const char *p)
+{
+    u32x4_t t;
+    if constexpr (KEEP && ANY) t = *reinterpret_cast<const few_elem_t *>(p);
+    else if constexpr (KEEP) t = *reinterpret_cast<const u32x4_t *>(p);
+    else if constexpr (ANY) t = __builtin_nontemporal_load(reinterpret_cast<const few_elem_t *>(p));
+    else t = __builtin_nontemporal_load(reinterpret_cast<const u32x4_t *>(p));
+    return make_uint4(t.x, t.y, t.z, t.w);
+}
+
+// f (logits) -> gradient entries without the chosen column's +g; nls2 = -log2 of the row's sum of exp(z - row_max)
+template <int N>
+__device__ __forceinline__ void few_gradient(float *f, float g, float row_max, float nls2)
+{
+#pragma unroll
+    for (int e = 0; e < N; ++e) f[e] = -g * exp2_hw(fmaf(f[e] - row_max, kLog2e, nls2));
+}
+
 // this workgroup's part of a row: elements before the first line, vectors [first, last) of the body, elements behind it
 struct FewPart {
     int head, first, last, tail0, tail;
@@ -120,7 +141,7 @@ __global__ __launch_bounds__(kTokThreads) void few_rows_partials_kernel(const Lo
 #pragma unroll
         for (int u = 0; u < kFewUnroll; ++u) {
             const int i = i0 + u * kTokThreads + tid;
-            if (i < p.last) v[u] = row_load<ANY, true>(body + (size_t)i * 16);
+            if (i < p.last) v[u] = few_load<ANY, true>(body + (size_t)i * 16);
         }
 #pragma unroll
         for (int u = 0; u < kFewUnroll; ++u) {
@@ -210,13 +231,12 @@ __global__ __launch_bounds__(kTokThreads) void few_rows_gradient_kernel(const Lo
     }
     const uint32_t single_bits = single >= 0 ? load_raw<DT>(in_row, single) : 0u;
     const int yb = rec.y - p.head;
-    float pz = 0.0f;
     for (int i0 = p.first; i0 < p.last; i0 += kFewUnroll * kTokThreads) {
         uint4 v[kFewUnroll];
 #pragma unroll
         for (int u = 0; u < kFewUnroll; ++u) {
             const int i = i0 + u * kTokThreads + tid;
-            if (i < p.last) v[u] = row_load<ANY, false>(body + (size_t)i * 16);
+            if (i < p.last) v[u] = few_load<ANY, false>(body + (size_t)i * 16);
         }
 #pragma unroll
         for (int u = 0; u < kFewUnroll; ++u) {
@@ -224,7 +244,7 @@ __global__ __launch_bounds__(kTokThreads) void few_rows_gradient_kernel(const Lo
             if (i < p.last) {
                 float f[EPV];
                 unpack<DT>(v[u], f);
-                backward_vec<EPV, false>(f, -g, row_max, nls2, pz);
+                few_gradient<EPV>(f, g, row_max, nls2);
                 stream_store(out + (size_t)i * 16, pack<DT>(f));
                 // the chosen column gets +g from the thread that stored its vector (same thread, same address: program order)
                 if (yb >= 0 && yb / EPV == i) store_elem<DT>(out, yb, -g * exp2_hw(fmaf(zy - row_max, kLog2e, nls2)) + g);
@@ -233,7 +253,7 @@ __global__ __launch_bounds__(kTokThreads) void few_rows_gradient_kernel(const Lo
     }
     if (single >= 0) {
         float f[1] = {raw_to_float<DT>(single_bits)};
-        backward_vec<1, false>(f, -g, row_max, nls2, pz);
+        few_gradient<1>(f, g, row_max, nls2);
         store_elem<DT>(out_row, single, single == rec.y ? f[0] + g : f[0]);
     }
 }
@@ -251,8 +271,10 @@ constexpr int64_t kFewMaxRows = 256;  // (their partials fit the scratch area, a
 // (34 MB) 25.1 / 25.2; 150 x 151,936 (46 MB) 30.5 / 32.0; 170 (52 MB) 30.8 / 34.7, 32.6 / 29.1; 256 x 90,000 (46 MB) 27.6 / 31.7.
 // Rows beyond the registers cost the one unit more: fp32 40 x 151,936 35.4 / 20.8, 64: 39.6 / 21.2, 100 (61 MB) 39.5 / 35.6,
 // 110 (67 MB) 41.1 / 39.4.
-int few_rows_parts(const LossArgs &a, int64_t cus)
+int few_rows_parts(const LossArgs &a)
 {
+    const GemmGrid chip = gemm_grid();
+    const int64_t cus = (int64_t)chip.nxcd * chip.per_xcd;
     const int64_t row_bytes = a.V * (a.dt == A3PO_F32 ? 4 : 2);
     const int64_t most_bytes = (row_bytes > (int64_t)kMaxVec * kRowThreads * 16 ? 64 : 32) << 20;
     if (a.T <= 0 || a.T > kFewMaxRows || a.T > cus || a.T * row_bytes > most_bytes) return 0;

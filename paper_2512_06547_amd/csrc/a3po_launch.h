@@ -85,10 +85,9 @@ inline void carve_loss_ws(LossArgs &a, void *workspace, int64_t T)
 hipError_t launch_loss_prep(const LossArgs &a, hipStream_t s);
 hipError_t launch_loss_rows(const LossArgs &a, hipStream_t s);
 // Parts that each row of a short batch is cut into for the kernels of a3po_few.hip (0: the batch takes the row kernel) ...
-int few_rows_parts(const LossArgs &a, int64_t cus);
+int few_rows_parts(const LossArgs &a);
 // ... and the whole call (records, rows, loss and statistics) with that cut
 hipError_t launch_few_rows_loss(const LossArgs &a, int parts, hipStream_t s);
-int device_cu_count();
 hipError_t launch_loss_finish(const LossArgs &a, hipStream_t s);
 hipError_t launch_count_tokens(const int32_t *chosen, const uint8_t *mask, int64_t T, int64_t V, float *denom_out,
                                int64_t *count_out, hipStream_t s);
