@@ -310,7 +310,10 @@ __global__ void lmhead_token_terms_kernel(const TokenRecord *__restrict__ record
 // a tile of 64 tokens x 64 vocabulary entries: 16-byte loads and 8-byte stores along the vocabulary, then through
 // LDS 16-byte stores along the tokens.  Token columns n .. (next multiple of 128) of dzt are written as zeros (they
 // pad the contraction over the tokens); a token with g = 0 gives an exactly zero row.  lse, g, ysel: the chunk's
-// tokens in compacted order.
+// tokens in compacted order.  Bound by memory.  The logits, which nothing reads again, and the vocabulary-major gradient, which is
+// read after everything else, are non-temporal, so that the caches keep the token-major gradient for the product that follows
+// (steps of 1,000 / 5,000 tokens x 1,536 x 151,936 1,406 / 4,389 -> 1,389 / 4,382 us, 5,000 x 2,048 x 50,264 1,833 -> 1,824; with
+// that one non-temporal as well 1,400 / 4,396 / 1,835).
 constexpr int kDzTile = 64;
 __global__ __launch_bounds__(256) void lmhead_dz_kernel(const float *__restrict__ zc, int64_t V, DynCount count, int64_t ldv,
                                                         const float *__restrict__ lse, const float *__restrict__ g,
@@ -334,8 +337,9 @@ __global__ __launch_bounds__(256) void lmhead_dz_kernel(const float *__restrict_
             if (neg_g != 0.0f) {
                 const float tl = lse[t];
                 const int64_t y = ysel[t];
-                const float4 z = *reinterpret_cast<const float4 *>(zc + t * ldv + v);
-                const float zz[4] = {z.x, z.y, z.z, z.w};
+                const uint4 z = stream_load(reinterpret_cast<const char *>(zc + t * ldv + v));
+                float zz[4];
+                unpack<F32>(z, zz);
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
                     const float p = exp2_hw((zz[i] - tl) * kLog2e);
@@ -358,7 +362,7 @@ __global__ __launch_bounds__(256) void lmhead_dz_kernel(const float *__restrict_
 #pragma unroll
         for (int half = 0; half < 2; ++half) {
             const uint4 w = *reinterpret_cast<const uint4 *>(&tile[vr][32 * half + tq]);
-            *reinterpret_cast<uint4 *>(dzt + panel_offset(v0 + vr, col0 + t0 + 32 * half + tq, ldg)) = w;
+            stream_store(reinterpret_cast<char *>(dzt + panel_offset(v0 + vr, col0 + t0 + 32 * half + tq, ldg)), w);
         }
     }
 }
