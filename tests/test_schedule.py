@@ -86,13 +86,25 @@ def test_contraction_loop_computes_addresses_in_scalar_registers(assembly, numbe
     assert not re.findall(r"v_lshl_add_u64|v_mad_[ui]64|v_add_co|v_readfirstlane", loop)
 
 
+def vector_spills(text):
+    """[(kernel, vector registers it spills)] of a file's assembly."""
+    found = re.findall(r"\.name:\s+(_ZN4a3po\w+)\n(?:(?!\.name:).)*?\.vgpr_spill_count:\s+(\d+)", text, re.S)
+    return [(name, int(n)) for name, n in found]
+
+
 def test_row_kernels_keep_their_rows_in_registers(assembly):
     """The register-resident rows are only that if the compiler does not spill them: a handful of addresses may go to
     scratch memory (15 registers at most), rows may not."""
-    text = assembly("a3po_rows.hip")
-    spills = re.findall(r"\.name:\s+(_ZN4a3po\w+)\n(?:(?!\.name:).)*?\.vgpr_spill_count:\s+(\d+)", text, re.S)
+    spills = vector_spills(assembly("a3po_rows.hip"))
     assert len(spills) > 100
-    assert not [(name, n) for name, n in spills if int(n) > 15]
+    assert not [(name, n) for name, n in spills if n > 15]
+
+
+def test_short_batch_kernels_spill_nothing(assembly):
+    """They hold a few vectors and one token's terms: nothing in them needs scratch memory, with or without the entropy."""
+    spills = vector_spills(assembly("a3po_few.hip"))
+    assert len(spills) == 16
+    assert not [(name, n) for name, n in spills if n > 0]
 
 
 @pytest.mark.parametrize("blocks", [12, 16])
