@@ -262,6 +262,7 @@ __global__ __launch_bounds__(kTokThreads) void few_rows_gradient_kernel(const Lo
 // host side
 
 constexpr int64_t kFewMaxRows = 256;  // (their partials fit the scratch area, and the last workgroup has a thread for each)
+constexpr int64_t kFewPartBytes = 8192;
 
 // Which batches come here, and parts per row: two workgroups per compute unit in all (four: 64 / 128 / 170 rows of bfloat16 x
 // 151,936 24.2 / 30.0 / 31.3 us instead of 22.0 / 25.0 / 29.1), parts of at least 8 KiB, two at least.  A row of its own costs a
@@ -273,15 +274,16 @@ constexpr int64_t kFewMaxRows = 256;  // (their partials fit the scratch area, a
 // 110 (67 MB) 41.1 / 39.4.
 int few_rows_parts(const LossArgs &a)
 {
-    const GemmGrid chip = gemm_grid();
-    const int64_t cus = (int64_t)chip.nxcd * chip.per_xcd;
     const int64_t row_bytes = a.V * (a.dt == A3PO_F32 ? 4 : 2);
     const int64_t most_bytes = (row_bytes > (int64_t)kMaxVec * kRowThreads * 16 ? 64 : 32) << 20;
-    if (a.T <= 0 || a.T > kFewMaxRows || a.T > cus || a.T * row_bytes > most_bytes) return 0;
+    // (the batch first: most calls need not ask for the device)
+    if (a.T <= 0 || a.T > kFewMaxRows || row_bytes < 2 * kFewPartBytes || a.T * row_bytes > most_bytes) return 0;
+    const GemmGrid chip = gemm_grid();
+    const int64_t cus = (int64_t)chip.nxcd * chip.per_xcd;
+    if (a.T > cus) return 0;
     int64_t parts = 2 * cus / a.T;
-    if (parts > row_bytes / 8192) parts = row_bytes / 8192;
-    if (parts > 32) parts = 32;
-    return parts >= 2 ? (int)parts : 0;
+    if (parts > row_bytes / kFewPartBytes) parts = row_bytes / kFewPartBytes;
+    return (int)(parts < 32 ? parts : 32);
 }
 
 template <typename DT, bool ENT, bool ANY>

@@ -7,11 +7,12 @@ from paper_2512_06547_amd import build
 HERE = os.path.dirname(os.path.abspath(__file__))
 
 
-def run_on_host(source, tmp_path):
+def run_on_host(source, tmp_path, kernels=False):
+    """Compiles a program and runs it here; `kernels`: its source holds some, which are compiled along but not run."""
     exe = str(tmp_path / "plan")
-    subprocess.check_call([build.HIPCC, "-x", "hip", "--offload-arch=gfx950", "--offload-host-only", "-O2", "-std=c++17",
-                           "-I", os.path.join(build.ROOT, "include"), "-I", build.CSRC, source, "-o", exe],
-                          stderr=subprocess.DEVNULL)
+    how = build.FLAGS if kernels else ["--offload-arch=gfx950", "--offload-host-only", "-O2", "-std=c++17",
+                                       "-I", os.path.join(build.ROOT, "include"), "-I", build.CSRC]
+    subprocess.check_call([build.HIPCC, "-x", "hip", *how, source, "-o", exe], stderr=subprocess.DEVNULL)
     done = subprocess.run([exe], capture_output=True, text=True, timeout=120)
     assert done.returncode == 0, done.stdout
     return done.stdout
@@ -73,3 +74,7 @@ int main()
 
 def test_uneven_column_groups_leave_no_tile_out_and_no_unit_worse_off(tmp_path):
     assert run_on_host(os.path.join(HERE, "gemm_cut_driver.cpp"), tmp_path) == "ok\n"
+
+
+def test_short_batches_are_cut_to_fit_and_cost_the_others_nothing(tmp_path):
+    assert run_on_host(os.path.join(HERE, "few_rows_plan_driver.cpp"), tmp_path, kernels=True) == "ok\n"
