@@ -299,7 +299,8 @@ hipError_t launch_lmhead_lse_finish(const void *hidden, const void *weight, int6
 {
     const unsigned grid = (unsigned)((T + 3) / 4);
     const GemmGrid gg = gemm_grid();
-    const GemmCut cut = gemm_cut(V, T, gg.nxcd, gg.per_xcd, room);
+    // (the kernel searches the cut itself where the number of tokens is on the device, and needs none for `slots` partials)
+    const GemmCut cut = slots > 0 || count.n ? GemmCut() : gemm_cut(V, T, gg.nxcd, gg.per_xcd, room);
     hipLaunchKernelGGL(lmhead_finish_kernel, dim3(grid), dim3(256), 0, s, reinterpret_cast<const uint16_t *>(weight),
                        reinterpret_cast<const uint16_t *>(hidden), T, H, V, chosen, partial, gg.nxcd, gg.per_xcd, cut, room, slots,
                        logp, lse, count);
