@@ -24,6 +24,8 @@
  *    Base pointers of logits / dlogits must be aligned to their element size.  Each row
  *    is read once and written once when it fits the registers (V <= 163,840 bfloat16 / 81,920 float32); a longer
  *    row stays on chip as far as registers and LDS hold it (448 KiB) and only its remainder is read a second time.
+ *    Short batches (up to 256 rows of at least 16 KiB, 32 MiB in all, 64 MiB of longer rows) are read twice, the second
+ *    time from the caches: several compute units share a row.
  *    Rows that do not start on 128-byte lines are cut at the lines of the gradient, at nearly the same speed; only
  *    rows too long for the registers whose logits and gradient differ in alignment within 16 bytes, and gradients of
  *    unaligned vocabulary shards, take slower element-wise kernels.  Results are identical up to rounding order.
@@ -97,7 +99,11 @@ typedef struct {
                                /* counted)                                                      */
     uint8_t *clipped_out;      /* device [T], nullable: 1 where the clipped branch is the min   */
     void *event_before_rows;   /* hipEvent_t, nullable: recorded on `stream` immediately before */
-    void *event_after_rows;    /* and after the vocabulary-wide row kernel (never waited on)    */
+    void *event_after_rows;    /* and after the vocabulary-wide row kernel (never waited on).   */
+                               /* Short batches (see the conventions) have no kernel for that   */
+                               /* alone: there the events enclose their two kernels, which also */
+                               /* do the call's per-token work (records, outputs, loss,         */
+                               /* statistics)                                                   */
     const float *denom_dev;    /* device [1], nullable: when set, replaces the `denom` argument (read   */
                                /* on the stream, so a count produced by a3po_count_tokens needs no host */
                                /* round trip); a value <= 0 selects this call's own token count         */
@@ -162,7 +168,7 @@ int a3po_grpo_advantages(const float *rewards, int64_t S, int32_t G, float eps_a
 /*
  * The fused path: token log-probs, Eq. 4 / Eq. 3 proximal log-prob, the decoupled clipped
  * objective of Eq. 2 with a masked token mean, and the gradient of the loss with respect to
- * the logits, reading each live row once and writing each gradient row once.
+ * the logits, reading each live row once (short batches: twice) and writing each gradient row once.
  *
  *   lt = log pi_theta (as above), lp = alpha lb + (1-alpha) lt (held fixed: the proximal
  *   policy is a frozen anchor, Section 2.2), iw = exp(lp - lb), r = exp(lt - lp),
@@ -219,7 +225,8 @@ int a3po_loss_fwd_bwd_noalloc(const void *logits, a3po_dtype dt, int64_t T, int6
  *    mean over counted tokens in stats_out->entropy_mean;
  *  - per-token importance weights and clip decisions, for histograms beyond the extrema and the
  *    count in a3po_stats;
- *  - two events around the row kernel, so a caller can time that kernel without a profiler.
+ *  - two events around the row kernel (short batches: around both kernels of the call), so a caller can time it
+ *    without a profiler.
  *  - mini-batch support: a denominator read from device memory and accumulation of loss and
  *    statistics over the micro-batches of one gradient update (see a3po_plan_microbatches).
  * Returns A3PO_E_VALUE for an unknown prox_mode or an accumulate flag other than 0 / 1, A3PO_E_NULL

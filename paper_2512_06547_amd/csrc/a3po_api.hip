@@ -197,6 +197,7 @@ int a3po_loss_fwd_bwd_ex(const void *logits, a3po_dtype dt, int64_t T, int64_t V
     a.accumulate = o.accumulate;
     carve_loss_ws(a, workspace, T);
 
+    // (a short batch is two kernels, which do the per-token work of prep and finish as well)
     const int parts = few_rows_parts(a);
     if (parts == 0 && launch_loss_prep(a, s) != hipSuccess) return A3PO_E_LAUNCH;
     if (o.event_before_rows && hipEventRecord(static_cast<hipEvent_t>(o.event_before_rows), s) != hipSuccess)
@@ -230,8 +231,8 @@ int a3po_loss_fwd_bwd_noalloc(const void *logits, a3po_dtype dt, int64_t T, int6
     if (T > 0 && loss_ws_layout(T).total > kStaticWsBytes) return A3PO_E_SIZE;  // (cannot happen below the token limit)
     void *ws = static_workspace();
     if (!ws) return A3PO_E_LAUNCH;
-    // Nothing in the array needs clearing here: the prep kernel rewrites the header, the per-token records and the
-    // row-queue counter at the start of every call, and every other field is written before it is read.
+    // Nothing in the array needs clearing here: the first kernel of every call (the prep kernel, or that of a short batch)
+    // rewrites the header, the per-token records and the row-queue counter, and every other field is written before it is read.
     return a3po_loss_fwd_bwd_ex(logits, dt, T, V, ld, chosen, logp_behav, versions, current_version, advantages,
                                 loss_mask, clip_eps, denom, dlogits, logp_out, logp_prox_out, loss_out, stats_out, ws,
                                 kStaticWsBytes, stream, nullptr);

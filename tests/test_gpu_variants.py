@@ -379,3 +379,24 @@ def test_rows_of_batches_longer_than_the_chip(a3po, dtype, V, ld, z_off, dz_off,
         assert_close_dz(host_rows(dz_at[rows, :V])[away], ref["dz"][away][:, :V], ref["g"][away], dtype, f"dlogits {i}")
         if entropy:
             assert_close_entropy(out["entropy"][rows].cpu().numpy(), ent, c["fwd"]["lse"], f"entropy {i}")
+
+
+@pytest.mark.parametrize("T", [64, 300])
+def test_events_enclose_the_passes_over_the_rows(a3po, T):
+    """Both kernels of a short batch, the row kernel of a longer one: recorded in order inside the call, results untouched."""
+    c = make_case(synth.WORKLOADS["tiny"], T=T)
+    plain = run_ex(a3po, c)
+    outer, inner = [[torch.cuda.Event(enable_timing=True) for _ in range(2)] for _ in range(2)]
+    for e in outer + inner:
+        e.record()  # (the handle exists from the first record on)
+    torch.cuda.synchronize()
+    z_d, args = dev_logits(c["z"]), [cu(c[k]) for k in ("chosen", "lb", "versions")]
+    outer[0].record()
+    out = a3po.loss_fwd_bwd(z_d, *args, CUR, cu(c["adv"]), cu(c["mask"]), c["w"].clip_eps,
+                            events=tuple(e.cuda_event for e in inner))
+    outer[1].record()
+    torch.cuda.synchronize()
+    assert inner[0].elapsed_time(inner[1]) > 0
+    assert outer[0].elapsed_time(inner[0]) >= 0 and inner[1].elapsed_time(outer[1]) >= 0
+    for k in ("dlogits", "logp", "logp_prox", "loss"):
+        assert torch.equal(plain[k].view(torch.uint8), out[k].view(torch.uint8)), k
