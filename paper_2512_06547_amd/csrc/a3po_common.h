@@ -118,6 +118,20 @@ __device__ __forceinline__ void stream_store(char *p, const uint4 &v)
     __builtin_nontemporal_store(t, reinterpret_cast<u32x4_t *>(p));
 }
 
+// 16 bytes from an address that is a multiple of 16 or (ANY) only aligned to the element.  KEEP: not non-temporal, for
+// bytes that are read again soon.
+typedef u32x4_t u32x4_elem_t __attribute__((aligned(2)));
+template <bool ANY, bool KEEP = false>
+__device__ __forceinline__ uint4 row_load(const char *p)
+{
+    if constexpr (!ANY && !KEEP) return stream_load(p);
+    u32x4_t t;
+    if constexpr (KEEP && ANY) t = *reinterpret_cast<const u32x4_elem_t *>(p);
+    else if constexpr (KEEP) t = *reinterpret_cast<const u32x4_t *>(p);
+    else t = __builtin_nontemporal_load(reinterpret_cast<const u32x4_elem_t *>(p));
+    return make_uint4(t.x, t.y, t.z, t.w);
+}
+
 // ---- (max, sum) pairs of an online log-sum-exp:  sum_j exp(z_j) = s * exp(m) ----------------
 struct MaxSum {
     float m, s;
@@ -167,6 +181,22 @@ __device__ __forceinline__ void fold(MaxSum &acc, const float *f)
 __device__ __forceinline__ float finite_floor(float x)
 {
     return __uint_as_float(min(__float_as_uint(x), 0xF149F2CAu));
+}
+
+// One vector of the backward pass: f (logits) -> f (gradient entries without the chosen column's +g),
+// and for ENT the running sum of p_j z_j (elements past the row's end hold -inf: p = 0).
+// p_j = exp(z_j - lse) is evaluated as exp2((z_j - m) log2e - log2 s) with m the row's maximum and s its
+// sum of exp(z - m): the difference is taken before the scaling, so the exponent's rounding error is
+// relative to (z_j - m), not to the magnitude of the logits.
+template <int EPV, bool ENT>
+__device__ __forceinline__ void backward_vec(float *f, float neg_g, float row_max, float nls2, float &pz)
+{
+#pragma unroll
+    for (int e = 0; e < EPV; ++e) {
+        const float p = exp2_hw(fmaf(f[e] - row_max, kLog2e, nls2));
+        if constexpr (ENT) pz = fmaf(p, finite_floor(f[e]), pz);
+        f[e] = neg_g * p;
+    }
 }
 
 // The same online reduction with a third running quantity u = sum_j exp(z_j - m) * z_j, from which

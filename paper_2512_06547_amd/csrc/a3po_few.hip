@@ -22,27 +22,6 @@ namespace a3po {
 
 constexpr int kFewUnroll = 4;  // 16-byte vectors in flight per thread
 
-// 16 bytes from an address that is only aligned to the element (ANY), or a multiple of 16.  KEEP: read again soon.
-typedef u32x4_t few_elem_t __attribute__((aligned(2)));
-template <bool ANY, bool KEEP>
-__device__ __forceinline__ uint4 few_load(const char *p)
-{
-    u32x4_t t;
-    if constexpr (KEEP && ANY) t = *reinterpret_cast<const few_elem_t *>(p);
-    else if constexpr (KEEP) t = *reinterpret_cast<const u32x4_t *>(p);
-    else if constexpr (ANY) t = __builtin_nontemporal_load(reinterpret_cast<const few_elem_t *>(p));
-    else t = __builtin_nontemporal_load(reinterpret_cast<const u32x4_t *>(p));
-    return make_uint4(t.x, t.y, t.z, t.w);
-}
-
-// f (logits) -> gradient entries without the chosen column's +g; nls2 = -log2 of the row's sum of exp(z - row_max)
-template <int N>
-__device__ __forceinline__ void few_gradient(float *f, float g, float row_max, float nls2)
-{
-#pragma unroll
-    for (int e = 0; e < N; ++e) f[e] = -g * exp2_hw(fmaf(f[e] - row_max, kLog2e, nls2));
-}
-
 // this workgroup's part of a row: elements before the first line, vectors [first, last) of the body, elements behind it
 struct FewPart {
     int head, first, last, tail0, tail;
@@ -141,7 +120,7 @@ __global__ __launch_bounds__(kTokThreads) void few_rows_partials_kernel(const Lo
 #pragma unroll
         for (int u = 0; u < kFewUnroll; ++u) {
             const int i = i0 + u * kTokThreads + tid;
-            if (i < p.last) v[u] = few_load<ANY, true>(body + (size_t)i * 16);
+            if (i < p.last) v[u] = row_load<ANY, true>(body + (size_t)i * 16);
         }
 #pragma unroll
         for (int u = 0; u < kFewUnroll; ++u) {
@@ -231,12 +210,13 @@ __global__ __launch_bounds__(kTokThreads) void few_rows_gradient_kernel(const Lo
     }
     const uint32_t single_bits = single >= 0 ? load_raw<DT>(in_row, single) : 0u;
     const int yb = rec.y - p.head;
+    float unused = 0.0f;  // (the sum for an entropy, which comes from the partials here)
     for (int i0 = p.first; i0 < p.last; i0 += kFewUnroll * kTokThreads) {
         uint4 v[kFewUnroll];
 #pragma unroll
         for (int u = 0; u < kFewUnroll; ++u) {
             const int i = i0 + u * kTokThreads + tid;
-            if (i < p.last) v[u] = few_load<ANY, false>(body + (size_t)i * 16);
+            if (i < p.last) v[u] = row_load<ANY, false>(body + (size_t)i * 16);
         }
 #pragma unroll
         for (int u = 0; u < kFewUnroll; ++u) {
@@ -244,7 +224,7 @@ __global__ __launch_bounds__(kTokThreads) void few_rows_gradient_kernel(const Lo
             if (i < p.last) {
                 float f[EPV];
                 unpack<DT>(v[u], f);
-                few_gradient<EPV>(f, g, row_max, nls2);
+                backward_vec<EPV, false>(f, -g, row_max, nls2, unused);
                 stream_store(out + (size_t)i * 16, pack<DT>(f));
                 // the chosen column gets +g from the thread that stored its vector (same thread, same address: program order)
                 if (yb >= 0 && yb / EPV == i) store_elem<DT>(out, yb, -g * exp2_hw(fmaf(zy - row_max, kLog2e, nls2)) + g);
@@ -253,7 +233,7 @@ __global__ __launch_bounds__(kTokThreads) void few_rows_gradient_kernel(const Lo
     }
     if (single >= 0) {
         float f[1] = {raw_to_float<DT>(single_bits)};
-        few_gradient<1>(f, g, row_max, nls2);
+        backward_vec<1, false>(f, -g, row_max, nls2, unused);
         store_elem<DT>(out_row, single, single == rec.y ? f[0] + g : f[0]);
     }
 }

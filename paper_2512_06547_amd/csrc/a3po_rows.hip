@@ -35,22 +35,6 @@ constexpr int kRowWaves = kRowThreads / kWave;
 // Loads and stores of logit rows are non-temporal: every byte is touched exactly once.
 constexpr uint32_t kSweepBytes = kRowThreads * 16;
 
-// One vector of the backward pass: f (logits) -> f (gradient entries without the chosen column's +g),
-// and for ENT the running sum of p_j z_j (elements past the row's end hold -inf: p = 0).
-// p_j = exp(z_j - lse) is evaluated as exp2((z_j - m) log2e - log2 s) with m the row's maximum and s its
-// sum of exp(z - m): the difference is taken before the scaling, so the exponent's rounding error is
-// relative to (z_j - m), not to the magnitude of the logits.
-template <int EPV, bool ENT>
-__device__ __forceinline__ void backward_vec(float *f, float neg_g, float row_max, float nls2, float &pz)
-{
-#pragma unroll
-    for (int e = 0; e < EPV; ++e) {
-        const float p = exp2_hw(fmaf(f[e] - row_max, kLog2e, nls2));
-        if constexpr (ENT) pz = fmaf(p, finite_floor(f[e]), pz);
-        f[e] = neg_g * p;
-    }
-}
-
 // Overwrites elements rem.. of a packed vector with -inf (the ragged tail of a row).
 template <typename DT>
 __device__ __forceinline__ void mask_tail(uint4 &v, int rem)
@@ -99,16 +83,6 @@ __device__ __forceinline__ int edge_column(const EdgeSpan &e, int tid)
     if (tid < e.head) return tid;
     if (tid >= kEdgeTail0 && tid - kEdgeTail0 < e.tail) return e.head + e.nbody * DT::kPerVec + tid - kEdgeTail0;
     return -1;
-}
-
-// 16 bytes from an address that is only aligned to the element
-typedef u32x4_t u32x4_elem_t __attribute__((aligned(2)));
-template <bool ANY>
-__device__ __forceinline__ uint4 row_load(const char *p)
-{
-    if constexpr (!ANY) return stream_load(p);
-    const u32x4_t t = __builtin_nontemporal_load(reinterpret_cast<const u32x4_elem_t *>(p));
-    return make_uint4(t.x, t.y, t.z, t.w);
 }
 
 // ENT adds the policy entropy of each counted row, H = lse - sum_j p_j z_j.  The sum rides on the

@@ -82,7 +82,8 @@ static_assert(sizeof(FinishTotals) <= 64 && sizeof(PrepPartial) <= 64, "a partia
 // Totals of the workgroup's threads, in thread 0 (a fixed tree: repeated runs agree bit for bit).
 // (The last sum goes four wavefronts at a time: all sixteen at once are 160 registers, which few_rows_gradient_kernel, of whose
 // workgroups only one gets here, had to make room for: 127 or 128 registers and, with the entropy, 24 spilled; now 44 to 52.
-// That kernel, with the entropy: 64 rows of bfloat16 x 151,936 9.6 -> 8.6 us, 256 x 32,000 8.9 -> 7.0, 100 of fp32 x 151,936 14.7 and 14.8.)
+// That kernel, with the entropy: 64 rows of bfloat16 x 151,936 9.6 -> 8.6 us, 256 x 32,000 8.9 -> 7.0, 100 of fp32 x 151,936
+// 14.7 and 14.8.)
 __device__ __forceinline__ FinishTotals block_totals(FinishTotals t)
 {
     __shared__ FinishTotals s_tot[kTokWaves];
