@@ -27,15 +27,16 @@
 // use in stage i; the 4 column fragments, which every MFMA group of the stage needs, alternate between two sets.
 // The 4 direct loads of stage i + kDmaStages go into the freed slot, spread over the stage.  The ring runs through
 // a workgroup's whole sequence of tiles without a break: the refills of a tile's last stages already bring the
-// next tile's first stages, so a tile's epilogue overlaps with their arrival (but for the reduction at the end of a sweep of
-// kGemmLse*: the compiler holds its LDS for a part of the ring and waits for the direct loads in flight).
+// next tile's first stages, so a tile's epilogue overlaps with their arrival (what it keeps in LDS beside the ring is accessed
+// through lds_put and lds_get, for which the compiler waits for no direct load).
 //
 // Tile order.  One persistent workgroup per compute unit; the workgroups of an XCD (dispatch order deals
 // workgroups round-robin over the XCDs) form a block of ml x ncol tiles (8 x 4 in the usual case, GemmShape) that
 // share ml tiles of A and ncol tiles of B through that XCD's L2.  The tile grid is cut into such blocks ("pairs" of a
-// column group and a row round); pair p = group * rounds + round, counted on through the groups of both widths where there are two (GemmCut), and each XCD
-// takes a contiguous range of pairs, i.e. it sweeps down the rows of one column group before it moves to the next.  With kGemmLse* a workgroup therefore
-// keeps its running (max, sum) in registers over a whole sweep and writes one partial per column per sweep.
+// column group and a row round); pair p = group * rounds + round, counted on through the groups of both widths where there
+// are two (GemmCut), and each XCD takes a contiguous range of pairs, i.e. it sweeps down the rows of one column group before
+// it moves to the next.  With kGemmLse* a workgroup therefore keeps its running (max, sum) in registers over a whole sweep
+// and writes one partial per column per sweep.
 //
 // Results.  The logits and the weight gradient are stored transposed (element (m, n) at C[n ldc + m]): a lane's four
 // accumulator values of one MFMA tile are four consecutive m of one n, which a staging tile in LDS puts together to whole
@@ -152,9 +153,9 @@ __device__ __forceinline__ void add_tile_transposed(const f32x4_t (&acc)[8][4], 
 // pieces of lines far more slowly than whole ones: the weight gradient of 53 / 654 / 2,557 tokens (1,536 x 151,936, whose
 // 467 MB of stores bound it) 193 / 385 / 950 us so, 163 / 335 / 905 with pieces of 64 bytes, 140 / 335 / 890 with lines.
 // Non-temporal: nothing in this call reads the weight gradient again, and what it would displace from the caches is the
-// weight (119 us at 53 tokens, and the next projection 137 instead of 167; no gain from 654 tokens on); the logits (a few GB per chunk) do
-// not fit any cache (projection with stores of 2,557 tokens x 896 x 50,264 / 1,536 x 151,936 375 / 1,605 us before, 340 / 1,540
-// with lines that are not, 310 / 1,500 so).
+// weight (119 us at 53 tokens, and the next projection 137 instead of 167; no gain from 654 tokens on); the logits (a few GB
+// per chunk) do not fit any cache (projection with stores of 2,557 tokens x 896 x 50,264 / 1,536 x 151,936 375 / 1,605 us
+// before, 340 / 1,540 with lines that are not, 310 / 1,500 so).
 // EDGE: the tile reaches past M or N; M is a multiple of the elements in 16 bytes.
 template <typename DT, bool EDGE>
 __device__ __forceinline__ void store_tile_lines(const f32x4_t (&acc)[8][4], void *C, int64_t ldc, int64_t m0, int64_t n0,
