@@ -245,7 +245,8 @@ constexpr int64_t kFewMaxRows = 256;  // (their partials fit the scratch area, a
 constexpr int64_t kFewPartBytes = 8192;
 
 // Which batches come here, and parts per row: two workgroups per compute unit in all (four: 64 / 128 / 170 rows of bfloat16 x
-// 151,936 24.2 / 30.0 / 31.3 us instead of 22.0 / 25.0 / 29.1), parts of at least 8 KiB, two at least.  A row of its own costs a
+// 151,936, the last two of which lie beyond the line, 24.2 / 30.0 / 31.3 us instead of 22.0 / 25.0 / 29.1), parts of at least 8 KiB,
+// two at least.  A row of its own costs a
 // compute unit the same however many other units are busy, while here all of them together read the batch twice and
 // write it, so the line is one of bytes.  It lies where a batch of which every token counts is no slower (us, row kernel / here,
 // every token / 9 in 16): bfloat16 64 x 151,936 (19 MB) 28.9 / 22.6, 29.3 / 22.0; 250 x 32,000 (16 MB) 25.2 / 21.0; 256 x 65,536

@@ -226,10 +226,10 @@ __host__ __device__ inline GemmShape gemm_shape(int64_t M, int64_t N, int nxcd, 
 // widths, each with the blocks of rows that its width leaves room for; pairs are counted through both.  The columns are dealt
 // to as many groups of four as they need, or to one group less of four and five, as evenly as they go, and the cut with the
 // fewest tiles for the busiest workgroup is taken (the plain shape among them, which wins ties).  5 / 7 / 10 / 11 / 13 / 17
-// columns of 594 tile rows then take 13 / 17 / 25 / 27 / 32 / 41 rounds of tiles for the 15 / 19 / 29 / 29 / 38 / 47 of equal groups.
-// A cut whose partials do not fit the `room` entries there are is left out.
-// Log-probs of 1,100 / 1,700 / 2,400 / 3,200 / 4,200 tokens x 1,536 x 151,936 552 / 730 / 1,121 / 1,422 / 1,876 us with equal groups,
-// 502 / 700 / 1,011 / 1,280 / 1,634 so.
+// columns of 594 tile rows then take 13 / 17 / 25 / 27 / 32 / 41 rounds of tiles for the 15 / 19 / 29 / 29 / 38 / 47 of equal
+// groups.  A cut whose partials do not fit the `room` entries there are is left out.
+// Log-probs of 1,100 / 1,700 / 2,400 / 3,200 / 4,200 tokens x 1,536 x 151,936 552 / 730 / 1,121 / 1,422 / 1,876 us with equal
+// groups, 502 / 700 / 1,011 / 1,280 / 1,634 so.
 __host__ __device__ inline int64_t gemm_cut_entries(const GemmCut &c, int64_t N, int nxcd)
 {
     const int64_t n0 = (int64_t)c.tiles0 * kGemmTile < N ? (int64_t)c.tiles0 * kGemmTile : N;
@@ -337,8 +337,11 @@ struct GemmGrid {
 };
 constexpr int kGemmMaxBlocks = 256;
 GemmGrid gemm_grid();
-// (max, sum) partials of up to N columns: nxcd * ml slots of N entries, at most 256 / ncol slots, and blocks of fewer
-// than four columns exist only up to 256 (one), 512 (two) and 2,304 columns (three: 3, 5, 6 or 9 tiles)
+// (max, sum) partials of up to N columns: nxcd * ml slots of N entries, at most 256 / ncol slots, and plain blocks
+// (gemm_shape) of fewer than four columns exist only up to 256 (one), 512 (two) and 2,304 columns (three: 3, 5, 6 or 9
+// tiles).  Cuts of two widths (gemm_cut) have groups of three columns, of 80 slots each, at 7, 10 and 11 tiles as well (4 + 3,
+// 4 + 3 + 3, 4 + 4 + 3 of many rows), which this size happens to have room for; 3 + 2 at 5 tiles and 4 + 3 + 3 + 3 at 13 it has
+// not, and gemm_cut, which checks each against the room there is (gemm_cut_entries), takes 5 and 5 + 4 + 4.
 inline size_t gemm_partial_entries(int64_t N)
 {
     auto upto = [&](int64_t slots, int64_t most) { return (size_t)(slots * (N < most ? N : most)); };
@@ -371,8 +374,8 @@ hipError_t launch_fused_lmhead_logprob(const void *hidden, const void *weight, i
                                        const int32_t *chosen, float *logp, float *lse, void *workspace, hipStream_t s);
 
 // merges the (max, sum) partials of a token, adds the chosen logit (a dot product) and writes lse and log pi
-// (room: as given to the contraction; T is an upper bound when `count` names a device-side token count; slots > 0: that many partials per token, all of
-// them written, instead of those of a contraction)
+// (room: as given to the contraction; T is an upper bound when `count` names a device-side token count; slots > 0: that many
+// partials per token, all of them written, instead of those of a contraction)
 hipError_t launch_lmhead_lse_finish(const void *hidden, const void *weight, int64_t T, int64_t H, int64_t V,
                                     const int32_t *chosen, const float2 *partial, float *logp,
                                     float *lse, hipStream_t s, int64_t room, DynCount count = DynCount(), int slots = 0);

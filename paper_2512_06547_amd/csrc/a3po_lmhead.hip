@@ -11,22 +11,23 @@
 namespace a3po {
 
 // ---- few tokens -------------------------------------------------------------------------------------------------
-// Up to 256 tokens the projection is bound by reading the weight (at 256 by the products as much), and the contraction kernel, whose ring holds three
-// stages of 16 KiB of it ahead, reads 3.6 TB/s.  Here the weight does not pass through LDS at all: a wavefront owns two
-// blocks of 16 vocabulary entries and loads their rows straight into MFMA operands (lane l: row l & 15, 16 bytes at quarter l >> 4;
-// the two loads of a row block and chunk complete each 128-byte line), four chunks of 64 hidden elements ahead: 96 to 128 KiB
-// in flight per compute unit.  The workgroups start at different chunks: all of them at the same offset of rows 8 KiB
-// apart would meet on a few memory channels (16 tokens x 4,096 x 151,936: 309 us so, 247 us apart, before the last round was spread; non-temporal
-// loads, which let go of a line after its first half, are slower).  The hidden rows, which all wavefronts share, come
-// through a ring of four chunks in LDS by
-// direct loads; 16-byte piece p of row r sits at piece p ^ ((r >> 1) & 7), so that 16 consecutive rows of one piece fall
-// into distinct banks.  32 rows per wavefront, because every operand read from LDS then feeds two MFMAs (with 16 rows and
-// 256 tokens LDS would be the bound); kAhead of those reads are on the way (two, the compiler's choice: 376 instead of
-// 340 us for 200 tokens).  One workgroup per compute unit, static tiles of 256 vocabulary entries.
+// Up to 256 tokens the projection is bound by reading the weight (at 256 by the products as much), and the contraction
+// kernel, whose ring holds three stages of 16 KiB of it ahead, reads 3.6 TB/s.  Here the weight does not pass through LDS at
+// all: a wavefront owns two blocks of 16 vocabulary entries and loads their rows straight into MFMA operands (lane l: row
+// l & 15, 16 bytes at quarter l >> 4; the two loads of a row block and chunk complete each 128-byte line), four chunks of 64
+// hidden elements ahead: 96 to 128 KiB in flight per compute unit.  The workgroups start at different chunks: all of them at
+// the same offset of rows 8 KiB apart would meet on a few memory channels (16 tokens x 4,096 x 151,936: 309 us so, 247 us
+// apart, before the last round was spread; non-temporal loads, which let go of a line after its first half, are slower).  The
+// hidden rows, which all wavefronts share, come through a ring of four chunks in LDS by direct loads; 16-byte piece p of row r
+// sits at piece p ^ ((r >> 1) & 7), so that 16 consecutive rows of one piece fall into distinct banks.  32 rows per wavefront,
+// because every operand read from LDS then feeds two MFMAs (with 16 rows and 256 tokens LDS would be the bound); kAhead of
+// those reads are on the way (two, the compiler's choice: 376 instead of 340 us for 200 tokens).  One workgroup per compute
+// unit, static tiles of 256 vocabulary entries.
 //
 // NB: 16-token column blocks.  H is a multiple of 256 (the loop is unrolled by the ring).  Operations in flight are
 // counted by hand as in the contraction kernel: per chunk NB / 4 direct loads, then 4 operand loads (2 in the loop with one
-// row block, whose first chunks thus wait for a little more than they need), in this order (held to in the source by in_order; tests/test_schedule.py reads it off the compiled kernel).
+// row block, whose first chunks thus wait for a little more than they need), in this order (held to in the source by
+// in_order; tests/test_schedule.py reads it off the compiled kernel).
 //
 // A tile is 16 row blocks of 16, two per wavefront, but the tiles of the last round have only as many (last_blocks) as spread
 // its rows over all compute units (FewTiles): a wavefront without a first or second block multiplies the tile's first row,
@@ -330,8 +331,9 @@ hipError_t launch_fused_lmhead_logprob(const void *hidden, const void *weight, i
     // reads the T x H x 2 bytes of hidden rows, which at 256 tokens weigh as much as its 256 x H x 2 bytes of weight).
     // Contraction kernel / this one, us:
     // 16 / 128 / 192 / 200 tokens x 4,096 x 151,936 347 / 334 / 346 / 346 and 220 / 255 / 286 / 318; 192 x 4,096 x 16,000 / 40,000
-    // 79 / 113 and 73 / 94, 192 x 896 x 32,000 28.1 and 28.4; 250 x 2,048 x 128,256 156 and 139, 250 x 1,536 x 50,264 (197
-    // tiles) 58 and 57, 200 x 2,048 x 32,000 (125 tiles) 47 and 56.
+    // 79 / 113 and 70 / 94; small vocabularies, 129 x 256 x 2,000 / 16,000 17.6 / 17.1 and 15.1 / 16.3, 192 x 1,024 x 1,000 /
+    // 24,000 29.3 / 30.2 and 24.4 / 27.5, 160 x 4,096 x 500 / 12,000 77.1 / 78.1 and 64.9 / 68.8; 250 x 2,048 x 128,256 156 and
+    // 139, 250 x 1,536 x 50,264 (197 tiles) 58 and 57, 200 x 2,048 x 32,000 (125 tiles) 47 and 56.
     const GemmGrid gg = gemm_grid();
     const int64_t tiles = (V + kFewRows - 1) / kFewRows, cus = (int64_t)gg.nxcd * gg.per_xcd;
     const bool few = T <= 192 || (T <= kFewMaxTokens && tiles >= cus * 3 / 4);

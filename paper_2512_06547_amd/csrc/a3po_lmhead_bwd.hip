@@ -19,9 +19,9 @@
 //      bfloat16 straight from the accumulators when one group holds every token, else summed in an fp32
 //      accumulator across groups and rounded to bfloat16 once at the end).
 // All three contractions are the kernel of a3po_gemm.hip, which wants the contracted index contiguous in both
-// operands; h^T, and for long batches W^T, are therefore written once per call (short ones take W as it lies).  6 N V H flops per step for N counted tokens: the
-// logits of a chunk are kept (4 bytes each, 5 GB for 8,192 tokens at V = 151,936) rather than recomputed, which
-// would be a fourth contraction.  Finally the rows of dh are scattered back to their tokens.
+// operands; h^T, and for long batches W^T, are therefore written once per call (short ones take W as it lies).  6 N V H
+// flops per step for N counted tokens: the logits of a chunk are kept (4 bytes each, 5 GB for 8,192 tokens at V = 151,936)
+// rather than recomputed, which would be a fourth contraction.  Finally the rows of dh are scattered back to their tokens.
 #include "a3po_common.h"
 #include "a3po_launch.h"
 
@@ -310,10 +310,11 @@ __global__ void lmhead_token_terms_kernel(const TokenRecord *__restrict__ record
 // a tile of 64 tokens x 64 vocabulary entries: 16-byte loads and 8-byte stores along the vocabulary, then through
 // LDS 16-byte stores along the tokens.  Token columns n .. (next multiple of 128) of dzt are written as zeros (they
 // pad the contraction over the tokens); a token with g = 0 gives an exactly zero row.  lse, g, ysel: the chunk's
-// tokens in compacted order.  Bound by memory.  The logits, which nothing reads again, and the vocabulary-major gradient, which is
-// read after everything else, are non-temporal, so that the caches keep the token-major gradient for the product that follows
-// (steps of 1,000 / 5,000 tokens x 1,536 x 151,936 1,406 / 4,389 -> 1,389 / 4,382 us, 5,000 x 2,048 x 50,264 1,833 -> 1,824; with
-// that one non-temporal as well 1,400 / 4,396 / 1,835).
+// tokens in compacted order.  Bound by memory.  The logits, which nothing reads again, and the vocabulary-major gradient,
+// which is read after everything else, are non-temporal: the pass itself takes 154 instead of 168 us at 1,000 tokens x 1,536 x
+// 151,936, 665 instead of 688 at 5,000.  The token-major gradient is not: the product that follows reads it.  (That product
+// gains nothing by the other two: 352 / 351 and 983 / 996 us.  Whole steps 1,406 / 4,389 -> 1,389 / 4,382 us, 5,000 x 2,048 x
+// 50,264 1,833 -> 1,824; with all three non-temporal 1,400 / 4,396 / 1,835.)
 constexpr int kDzTile = 64;
 __global__ __launch_bounds__(256) void lmhead_dz_kernel(const float *__restrict__ zc, int64_t V, DynCount count, int64_t ldv,
                                                         const float *__restrict__ lse, const float *__restrict__ g,
