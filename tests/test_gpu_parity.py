@@ -172,7 +172,7 @@ def test_heavy_clipping_fp32(a3po):
 
 
 def test_bf16_full_vocabulary_rows_every_element(a3po):
-    # 151,936 columns: 18 full sweeps of the 1024-thread row kernel plus a 560-lane ragged sweep
+    # 151,936 columns, 96 rows of them: the kernels of short batches, five parts a row
     w = synth.WORKLOADS["1p5b"].scaled(S=8, L=12, G=8, len_lo=6, len_hi=12)
     c = make_case(w)
     out = run_gpu(a3po, c)
@@ -187,8 +187,8 @@ def test_bf16_full_vocabulary_rows_every_element(a3po):
 def test_ragged_vocabularies_and_strides(a3po, dtype, V, pad):
     # covers: single partial sweep, exact sweep multiples, ragged tail vectors, padded strides
     # (padding columns hold a 1e30 sentinel and must be neither read nor written), strides
-    # whose byte size is not a multiple of 16 (rows cut at the lines of the gradient), and rows too long for the
-    # registers (100,000 and 100,001 float32 / 170,000 bfloat16: registers plus LDS).
+    # whose byte size is not a multiple of 16 (rows cut at the lines of the gradient), and rows too long for a
+    # workgroup's registers (100,000 and 100,001 float32 / 170,000 bfloat16).
     w = synth.WORKLOADS["tiny"].scaled(V=V, dtype=dtype, S=4, L=6, len_lo=3, len_hi=6, sigma=3.0,
                                        boost=6.0, boost_prob=0.5, noise_std=0.15, stale_max=6)
     c = make_case(w, ld=V + pad)
@@ -198,7 +198,10 @@ def test_ragged_vocabularies_and_strides(a3po, dtype, V, pad):
         assert (out["dlogits"][:, V:].float() == 7.0).all(), "padding columns were written"
 
 
-@pytest.mark.parametrize("dtype,V,pad,z_off,dz_off", [
+# Up to 256 rows of 16 KiB or more go through the kernels of short batches, which know no difference between these lengths and
+# take most of the following shapes here.  The notes say what a shape is to the row kernels: test_gpu_variants.py repeats
+# its rows in batches that keep to them.
+ANY_ADDRESS = [
     ("bf16", 40, 1, 0, 0), ("bf16", 71, 0, 3, 3),       # rows shorter than a line; no whole vector in some
     ("bf16", 8254, 1, 0, 0), ("bf16", 8255, 0, 5, 5),   # one full sweep: surplus vectors in the tail; a second sweep
     ("f32", 4126, 1, 2, 2), ("f32", 4127, 0, 0, 0),     # the same in fp32
@@ -207,7 +210,10 @@ def test_ragged_vocabularies_and_strides(a3po, dtype, V, pad):
     ("bf16", 163902, 1, 0, 0), ("bf16", 163903, 0, 1, 1),  # last length of the registers, first beyond
     ("f32", 100001, 0, 1, 1), ("f32", 100001, 0, 1, 0),    # beyond the registers, alike and not (element-wise)
     ("bf16", 170001, 0, 1, 0), ("bf16", 170001, 3, 8, 1),  # the same element-wise kernel in bfloat16
-])
+]
+
+
+@pytest.mark.parametrize("dtype,V,pad,z_off,dz_off", ANY_ADDRESS)
 @pytest.mark.parametrize("entropy", [False, True])
 def test_rows_at_any_address(a3po, dtype, V, pad, z_off, dz_off, entropy):
     # rows that start anywhere inside a line, logits and gradient at their own element offsets: every element against
@@ -239,7 +245,7 @@ def test_rows_at_any_address(a3po, dtype, V, pad, z_off, dz_off, entropy):
         assert (err <= 1e-5 * np.abs(ent) + 2e-5 * (1 + np.abs(c["fwd"]["lse"]))).all()
 
 
-@pytest.mark.parametrize("dtype,V,pad", [
+BEYOND_REGISTERS = [
     ("f32", 151936, 0),    # the full vocabulary in fp32: 19 sweeps in registers, 9 in LDS, 9.1 streamed twice
     ("f32", 114688, 0),    # exactly 28 sweeps: nothing streamed, the last LDS sweep full
     ("f32", 114690, 2),    # rows cut at the lines of the gradient: a streamed part of a few vectors or none
@@ -249,10 +255,14 @@ def test_rows_at_any_address(a3po, dtype, V, pad, z_off, dz_off, entropy):
     ("bf16", 163848, 0),   # one vector more than the register-resident kernel holds
     ("bf16", 256000, 0),   # 31.25 sweeps
     ("bf16", 300005, 3),   # cut rows of 36.6 sweeps
-])
+]
+
+
+@pytest.mark.parametrize("dtype,V,pad", BEYOND_REGISTERS)
 def test_rows_beyond_the_registers(a3po, dtype, V, pad):
-    # rows of more than 20 sweeps of 1024 vectors, whole (those without padding) and cut at lines: kept in registers and LDS as far as they fit, the
-    # rest read twice; every element against the oracle, padding untouched, and the in-place form bit-identical
+    # rows of more than 20 sweeps of 1024 vectors, whole (those without padding) and cut at lines, which the row kernels keep in
+    # registers and LDS as far as they fit: every element against the oracle, padding untouched, and the in-place form
+    # bit-identical
     w = synth.WORKLOADS["tiny"].scaled(V=V, dtype=dtype, S=4, L=6, len_lo=3, len_hi=6, sigma=3.0,
                                        boost=6.0, boost_prob=0.5, noise_std=0.15, stale_max=6)
     c = make_case(w, ld=V + pad)
@@ -266,7 +276,7 @@ def test_rows_beyond_the_registers(a3po, dtype, V, pad):
     assert torch.equal(out["logp"], inp["logp"]) and torch.equal(out["loss"], inp["loss"])
 
 
-@pytest.mark.parametrize("dtype,V,ld", [
+RAGGED_ENDS = [
     ("bf16", 5, 64), ("f32", 3, 32), ("bf16", 1001, 1024), ("f32", 1001, 1024),  # 256 threads: one sweep, the ragged one
     ("bf16", 8191, 8192), ("f32", 4093, 4096),       # the last element of their last sweep's last vector is missing
     ("bf16", 12289, 12352), ("f32", 6145, 6176),     # 512 threads: a ragged vector alone in the last sweep
@@ -280,7 +290,10 @@ def test_rows_beyond_the_registers(a3po, dtype, V, pad):
     ("f32", 114690, 114720),   # the ragged vector is the first and only one of the streamed part
     ("f32", 130001, 130016),   # ragged end inside the streamed part, two batches
     ("bf16", 163841, 163904), ("bf16", 300005, 300032),  # ragged vector in LDS, in the last streamed batch
-])
+]
+
+
+@pytest.mark.parametrize("dtype,V,ld", RAGGED_ENDS)
 @pytest.mark.parametrize("entropy", [False, True])
 def test_whole_rows_with_a_ragged_end(a3po, dtype, V, ld, entropy):
     # rows that start on lines are taken whole, their last vector in part when the vocabulary is no multiple of a vector:
@@ -316,17 +329,18 @@ def test_whole_rows_with_a_ragged_end(a3po, dtype, V, ld, entropy):
                                          ("bf16", 50001, 1), ("bf16", 50048, 0), ("f32", 81921, 1), ("f32", 100001, 1),
                                          ("f32", 100000, 0), ("bf16", 170001, 5)])
 @pytest.mark.parametrize("entropy", [False, True])
-def test_rows_with_nan_and_infinite_logits(a3po, dtype, V, off, entropy):
+def test_rows_with_nan_and_infinite_logits(a3po, dtype, V, off, entropy, times=1):
+    # (times: the batch that often over, NaN and +inf in the first of them)
     # a NaN or +inf anywhere in a counted row (its first elements, its body, its last ones) makes that row's log-prob
     # and gradient NaN; a masked row is not looked at, and no other row changes by a bit
     w = synth.WORKLOADS["tiny"].scaled(V=V, dtype=dtype, S=4, L=6, len_lo=6, len_hi=6, sigma=3.0, noise_std=0.15)
     c = make_case(w)
     c["mask"][:] = 1
     c["mask"][7] = 0
-    dev = lambda k: torch.from_numpy(c[k]).cuda()
+    dev = lambda k: torch.from_numpy(np.tile(c[k], times)).cuda()
 
     def run(poison):
-        z_d = dev_logits(c["z"])
+        z_d = dev_logits(c["z"]).repeat(times, 1)
         for row, col, value in poison:
             z_d[row, col] = value
         flat = torch.zeros(z_d.numel() + off, dtype=z_d.dtype, device="cuda")
@@ -343,7 +357,7 @@ def test_rows_with_nan_and_infinite_logits(a3po, dtype, V, off, entropy):
     poison = [(1, 0, nan), (2, V // 2, nan), (3, V - 1, nan), (4, 0, inf), (5, V // 2, inf), (6, V - 1, inf),
               (7, 3, nan), (9, 1, nan), (9, V - 2, inf)]
     (clean, clean_lp), (out, lp) = run([]), run(poison)
-    bad = torch.zeros(c["T"], dtype=torch.bool, device="cuda")
+    bad = torch.zeros(c["T"] * times, dtype=torch.bool, device="cuda")
     bad[[1, 2, 3, 4, 5, 6, 9]] = True
     assert out["logp"][bad].isnan().all() and out["dlogits"][bad].isnan().all() and out["loss"].isnan().all()
     assert (out["dlogits"][7] == 0).all() and out["logp"][7] == 0
@@ -658,7 +672,7 @@ def test_graph_capture_and_replay(a3po, V, L, T):
 
 @pytest.mark.parametrize("dtype,V,sigma,offset", [("f32", 4099, 300.0, 0.0), ("f32", 32000, 1e4, 0.0), ("bf16", 8192, 30.0, 1e3),
                                                   ("f32", 1000, 1.0, -1e6), ("bf16", 151936, 3000.0, 0.0), ("f32", 64, 1.0, 1e8)])
-def test_large_logits(a3po, dtype, V, sigma, offset):
+def test_large_logits(a3po, dtype, V, sigma, offset, T=12):
     """Logits far beyond the magnitudes language models produce, and large common offsets: the kernels take
     differences (z - max) before any scaling, so the plain bars hold whatever the magnitude of the logits is.
     What remains is the float32 representation of the results themselves: a log-prob of -3e4 cannot be held
@@ -666,7 +680,6 @@ def test_large_logits(a3po, dtype, V, sigma, offset):
     (`rep` below, four float32 spacings of the log-prob; about 1e-6 for ordinary log-probs).
     Nothing overflows; a third of the entries are -inf."""
     r = np.random.default_rng(int(V + sigma))
-    T = 12
     z = (r.standard_normal((T, V)) * sigma + offset).astype(np.float32)
     z[r.random((T, V)) < 0.3] = -np.inf
     y = np.array([r.choice(np.nonzero(np.isfinite(z[t]))[0]) for t in range(T)], dtype=np.int32)

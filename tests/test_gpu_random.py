@@ -1,8 +1,8 @@
 """Seeded random shapes through the whole path and its variants, against the CPU oracle with the bars of
-test_gpu_parity.py: vocabularies from 1 to 170,000 entries around every kernel boundary (register-resident,
-registers plus LDS plus a streamed remainder, element-wise), padded strides, in-place gradients, entropy, the two
-baseline objectives, and vocabulary shards cut at random columns (views of the matrix or contiguous copies).  Every case prints its
-parameters first."""
+test_gpu_parity.py: vocabularies from 1 to 170,000 entries around every boundary of the row kernels, padded strides,
+in-place gradients, entropy, the two baseline objectives, and vocabulary shards cut at random columns (views of the
+matrix or contiguous copies).  (Most batches are short ones, whose loss takes kernels of its own; the row kernels at
+these boundaries: LONG_BATCHES of test_gpu_variants.py.)  Every case prints its parameters first."""
 import numpy as np
 import pytest
 

@@ -16,8 +16,10 @@ import synth
 
 torch = pytest.importorskip("torch")
 
-from test_gpu_parity import (CUR, a3po, assert_close_dz, assert_close_logp, check_against_oracle, dev_logits,  # noqa: E402,F401
-                             host_rows, make_case, run_gpu)
+from test_gpu_parity import (ANY_ADDRESS, BEYOND_REGISTERS, CUR, RAGGED_ENDS, a3po, assert_close_dz,  # noqa: E402,F401
+                             assert_close_logp, check_against_oracle, dev_logits, host_rows, make_case, run_gpu,
+                             test_large_logits as check_large_logits,
+                             test_rows_with_nan_and_infinite_logits as check_nan_and_infinite_logits)
 
 pytestmark = pytest.mark.gpu
 
@@ -42,6 +44,7 @@ def assert_close_entropy(gpu, ref, lse_ref, what):
     return float((err / bound).max())
 
 
+# (what the lengths are to the row kernels, which take them in batches of more than 256 rows: LONG_BATCHES)
 ENTROPY_CASES = [
     ("f32", 32000, 0),      # 8 sweeps, everything in registers
     ("bf16", 151936, 0),    # 19 sweeps: two vectors parked in LDS, two loads issued late
@@ -273,8 +276,8 @@ def test_long_batches_of_short_rows(a3po, S, L):
 # Batches of no more rows than compute units (and no more bytes than the caches serve) go through kernels that cut every row
 # into parts: rows of one part short of too small, parts that are empty, a row in 32 parts, logits and gradient of equal and
 # different alignment, 256 rows.
-SHORT = [(1, "bf16", 151936, 0, 0, 0), (2, "bf16", 400001, 1, 3, 3), (2, "f32", 114690, 0, 0, 1), (110, "f32", 151936, 0, 0, 0), (2, "f32", 4096, 0, 0, 0), (3, "bf16", 8192, 0, 0, 0), (5, "bf16", 16391, 3, 1, 3),
-         (17, "f32", 65537, 0, 3, 3), (100, "f32", 16387, 2, 0, 2), (128, "bf16", 33001, 0, 8, 16), (256, "bf16", 8200, 8, 0, 0),
+SHORT = [(1, "bf16", 151936, 0, 0, 0), (2, "bf16", 400001, 1, 3, 3), (2, "f32", 114690, 0, 0, 1), (110, "f32", 151936, 0, 0, 0),
+         (2, "f32", 4096, 0, 0, 0), (3, "bf16", 8192, 0, 0, 0), (5, "bf16", 16391, 3, 1, 3), (17, "f32", 65537, 0, 3, 3), (100, "f32", 16387, 2, 0, 2), (128, "bf16", 33001, 0, 8, 16), (256, "bf16", 8200, 8, 0, 0),
          (256, "f32", 20001, 0, 1, 0)]
 
 
@@ -339,20 +342,32 @@ def test_short_batches(a3po, T, dtype, V, pad, z_off, dz_off, entropy):
         assert torch.equal(z_at[:, :V].contiguous().view(torch.uint8), dz_at[:, :V].contiguous().view(torch.uint8))
 
 
-# The row kernels' forms on batches that the short kernels do not take: 24 rows of every kind, twelve times over.
+# The row kernels' forms on batches that the short kernels do not take: 24 rows of every kind, twelve times over.  The shapes of
+# test_gpu_parity.py that its own, shorter batches take elsewhere, and more.
 LONG_BATCHES = ([(d, V, V + pad, 0, 0) for d, V, pad in ENTROPY_CASES] +
-                [("bf16", 8191, 8192, 0, 0), ("bf16", 12289, 12352, 0, 0), ("f32", 16385, 16416, 0, 0), ("bf16", 30001, 30016, 0, 0),
-                 ("bf16", 163833, 163840, 0, 0), ("f32", 86017, 86048, 0, 0), ("f32", 114690, 114720, 0, 0),
-                 ("bf16", 163841, 163904, 0, 0), ("bf16", 50001, 50001, 1, 3), ("f32", 32003, 32003, 1, 2),
-                 ("bf16", 151936, 151936, 8, 24), ("f32", 114690, 114692, 1, 1), ("f32", 90001, 90001, 1, 2)])
+                [("bf16", 8191, 8192, 0, 0), ("bf16", 163833, 163840, 0, 0), ("f32", 114690, 114720, 0, 0),
+                 ("bf16", 50001, 50001, 1, 3), ("f32", 32003, 32003, 1, 2), ("bf16", 151936, 151936, 8, 24),
+                 ("f32", 114690, 114692, 1, 1), ("f32", 90001, 90001, 1, 2)] +
+                [(d, V, V + pad, z_off, dz_off) for d, V, pad, z_off, dz_off in ANY_ADDRESS] +
+                [(d, V, V + pad, 0, 0) for d, V, pad in BEYOND_REGISTERS] +
+                [(d, V, ld, 0, 0) for d, V, ld in RAGGED_ENDS])
+LONG_BATCHES = list(dict.fromkeys(LONG_BATCHES))
 
 
 @pytest.mark.parametrize("entropy", [False, True])
 @pytest.mark.parametrize("dtype,V,ld,z_off,dz_off", LONG_BATCHES)
 def test_rows_of_batches_longer_than_the_chip(a3po, dtype, V, ld, z_off, dz_off, entropy):
+    """Every output of every copy against the oracle, a row of -inf but for two entries among them, padding and neighbours
+    untouched, and the gradient in the logits' place the same."""
     w = synth.WORKLOADS["tiny"].scaled(V=V, dtype=dtype, S=4, L=6, len_lo=4, len_hi=6, sigma=3.0, boost=6.0, boost_prob=0.5,
                                        noise_std=0.15, stale_max=6)
     c = make_case(w, ld=ld)
+    keep = c["z"][2, [1, V - 1]].copy()
+    c["z"][2, :V] = -np.inf if dtype == "f32" else 0xFF80
+    c["z"][2, [1, V - 1]] = keep
+    c["chosen"][2], c["mask"][2] = V - 1, 1
+    fwd = oracle.token_logprobs(c["z"], c["chosen"], V=V)
+    c["lb"][2] = fwd["logp"][2]
     n, times = c["T"], 12
     T, denom, dt = n * times, 100.0, torch.float32 if dtype == "f32" else torch.bfloat16
 
@@ -363,22 +378,86 @@ def test_rows_of_batches_longer_than_the_chip(a3po, dtype, V, ld, z_off, dz_off,
     _, z_at = place(z_off)
     z_at.copy_(dev_logits(c["z"]).repeat(times, 1))
     flat, dz_at = place(dz_off)
-    rep = lambda k: cu(np.tile(c[k], times))
-    out = a3po.loss_fwd_bwd(z_at, rep("chosen"), rep("lb"), rep("versions"), CUR, rep("adv"), rep("mask"), w.clip_eps, V=V,
-                            denom=denom, dlogits=dz_at, want_entropy=entropy)
+    args = [cu(np.tile(c[k], times)) for k in ("chosen", "lb", "versions")] + [CUR] + [cu(np.tile(c[k], times)) for k in ("adv", "mask")]
+    kw = dict(V=V, denom=denom, want_entropy=entropy, want_iw=True, want_clipped=True)
+    out = a3po.loss_fwd_bwd(z_at, *args, w.clip_eps, dlogits=dz_at, **kw)
     torch.cuda.synchronize()
     assert (flat[:dz_off].float() == 7.0).all() and (flat[dz_off + T * ld:].float() == 7.0).all()
     assert (dz_at[:, V:].float() == 7.0).all(), "padding columns were written"
     ref = oracle.loss_fwd_bwd(c["z"], c["chosen"], c["lb"], c["versions"], CUR, c["adv"], c["mask"], w.clip_eps, denom=denom, V=V)
     sur = oracle.surrogate(ref["logp"], c["lb"], c["versions"], CUR, c["adv"], ref["eff_mask"], w.clip_eps, denom)
-    away = (np.abs(np.abs(sur["r"] - 1) - w.clip_eps) >= 1e-3) | (ref["eff_mask"] == 0)  # the clip decision is certain
-    ent = np.where(c["mask"] != 0, oracle.entropy(c["z"], V=V), 0.0) if entropy else None
-    for i in range(times):
-        rows = slice(i * n, (i + 1) * n)
-        assert_close_logp(out["logp"][rows].cpu().numpy(), ref["logp"], f"logp {i}")
-        assert_close_dz(host_rows(dz_at[rows, :V])[away], ref["dz"][away][:, :V], ref["g"][away], dtype, f"dlogits {i}")
-        if entropy:
-            assert_close_entropy(out["entropy"][rows].cpu().numpy(), ent, c["fwd"]["lse"], f"entropy {i}")
+    live = ref["eff_mask"] == 1
+    away = (np.abs(np.abs(sur["r"] - 1) - w.clip_eps) >= 1e-3) | ~live  # the clip decision is certain
+    ent = np.where(live, oracle.entropy(c["z"], V=V), 0.0) if entropy else None
+    st = a3po.stats_to_dict(out["stats"])
+    assert st["n_tokens"] == times * int(live.sum()) and st["n_bad_index"] == 0
+    assert abs(st["n_clipped"] - times * ref["stats"]["n_clipped"]) <= times * int((~away).sum())
+    assert abs(st["iw_min"] - ref["stats"]["iw_min"]) <= 1e-5 * ref["stats"]["iw_min"] + 1e-6
+    assert abs(st["iw_max"] - ref["stats"]["iw_max"]) <= 1e-5 * ref["stats"]["iw_max"] + 1e-6
+    # (a token of the band may take the other branch, whose objective differs by at most the band's width)
+    scale = (np.abs(sur["obj"]) * live).sum() / denom
+    bar = 1e-5 * abs(ref["loss"]) + 1e-5 * scale + np.abs(sur["obj"][~away]).sum() * 2e-3 / denom
+    assert abs(float(out["loss"].cpu()[0]) - times * ref["loss"]) <= times * bar + 1e-12
+
+    def check_rows(out, dz):
+        for i in range(times):
+            rows = slice(i * n, (i + 1) * n)
+            assert_close_logp(out["logp"][rows].cpu().numpy(), ref["logp"], f"logp {i}")
+            assert_close_logp(out["logp_prox"][rows].cpu().numpy()[live], ref["lp"][live], f"logp_prox {i}")
+            assert_close_dz(host_rows(dz[rows, :V])[away], ref["dz"][away][:, :V], ref["g"][away], dtype, f"dlogits {i}")
+            iw = out["iw"][rows].cpu().numpy().astype(np.float64)
+            assert (np.abs(iw - sur["iw"] * live) <= 2e-5 * np.abs(sur["iw"]) + 1e-6).all()
+            clipped = out["clipped"][rows].cpu().numpy()
+            assert np.array_equal(clipped[away], (sur["clipped"] * live)[away].astype(np.uint8))
+            if entropy:
+                assert_close_entropy(out["entropy"][rows].cpu().numpy(), ent, fwd["lse"], f"entropy {i}")
+
+    check_rows(out, dz_at)
+    assert int(out["clipped"].sum()) == st["n_clipped"]
+    inp = a3po.loss_fwd_bwd(z_at, *args, w.clip_eps, dlogits=z_at, **kw)
+    torch.cuda.synchronize()
+    if z_off == dz_off:  # (else rows are cut elsewhere, and long ones take another kernel)
+        for k in ("logp", "logp_prox", "loss", "iw", "clipped", "stats") + (("entropy",) if entropy else ()):
+            assert torch.equal(inp[k].view(torch.uint8), out[k].view(torch.uint8)), k
+        assert torch.equal(z_at[:, :V].contiguous().view(torch.uint8), dz_at[:, :V].contiguous().view(torch.uint8))
+    else:
+        check_rows(inp, z_at)
+
+
+@pytest.mark.parametrize("entropy", [False, True])
+@pytest.mark.parametrize("dtype,V,off", [("f32", 12288, 0), ("bf16", 20001, 3), ("bf16", 50001, 1), ("bf16", 50048, 0), ("f32", 81921, 1),
+                                         ("f32", 100001, 1), ("f32", 100000, 0), ("bf16", 170001, 5)])
+def test_nan_and_infinite_logits_in_batches_longer_than_the_chip(a3po, dtype, V, off, entropy):
+    check_nan_and_infinite_logits(a3po, dtype, V, off, entropy, times=12)
+
+
+@pytest.mark.parametrize("dtype,V,sigma,offset", [("f32", 32000, 1e4, 0.0), ("bf16", 8192, 30.0, 1e3), ("bf16", 151936, 3000.0, 0.0),
+                                                  ("f32", 90001, 300.0, 0.0)])
+def test_large_logits_in_batches_longer_than_the_chip(a3po, dtype, V, sigma, offset):
+    check_large_logits(a3po, dtype, V, sigma, offset, T=260)
+
+
+@pytest.mark.parametrize("mode", ["given", "coupled"])
+@pytest.mark.parametrize("dtype,V", [("bf16", 20001), ("bf16", 151936), ("f32", 100000)])
+def test_other_proximal_policies_in_batches_longer_than_the_chip(a3po, dtype, V, mode):
+    """The two baselines through the row kernels (rows of 512 and 1,024 threads, rows beyond the registers)."""
+    w = synth.WORKLOADS["tiny"].scaled(V=V, dtype=dtype, S=8, L=36, G=8, len_lo=20, len_hi=36, noise_std=0.3, sigma=3.0)
+    c = make_case(w)
+    cnt = c["mask"] != 0
+    if mode == "given":
+        noise = np.random.default_rng(12).standard_normal(c["T"]) * 0.15
+        lp = np.minimum(0.0, c["fwd"]["logp"] + noise).astype(np.float32)
+        kw = dict(prox_mode=a3po.A3PO_PROX_GIVEN, logp_prox_in=cu(lp))
+    else:
+        lp, kw = c["lb"], dict(prox_mode=a3po.A3PO_PROX_BEHAV)
+    out = run_ex(a3po, c, want_iw=True, want_clipped=True, no_versions=True, **kw)
+    ref, st, near = check_given_prox(a3po, c, out, lp)
+    assert np.array_equal(out["logp_prox"].cpu().numpy()[cnt], lp[cnt])
+    iw, clipped = out["iw"].cpu().numpy(), out["clipped"].cpu().numpy()
+    assert (np.abs(iw[cnt] - ref["iw"][cnt]) <= 1e-5 * ref["iw"][cnt]).all() and not iw[~cnt].any()
+    assert mode == "given" or (iw[cnt] == 1.0).all()
+    assert np.array_equal(clipped[cnt & ~near], ref["clipped"][cnt & ~near]) and not clipped[~cnt].any()
+    assert 3 < st["n_clipped"] == int(clipped.sum()) < int(cnt.sum()) - 3
 
 
 @pytest.mark.parametrize("T", [64, 300])
