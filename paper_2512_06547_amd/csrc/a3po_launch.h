@@ -352,21 +352,33 @@ inline size_t gemm_partial_entries(int64_t N)
 hipError_t launch_gemm(const GemmArgs &args, int product, hipStream_t s);
 
 // Tiles of the few-token kernel: nfull whole tiles of kFewRows vocabulary entries, one for each compute unit and round, then
-// those of the last round, each of last_blocks row blocks of 16 (16 for a whole tile).
+// those of the last round, each of last_blocks row blocks of 16: as many as an even share of them needs, or 16 (whole tiles
+// again, on fewer units) where that is more than `most`.
 constexpr int kFewWaves = 8;
 constexpr int kFewRows = 32 * kFewWaves;
 struct FewTiles {
     int nfull, ntiles, last_blocks, slots;
 };
-inline FewTiles few_tiles(int64_t V, int64_t cus)
+inline FewTiles few_tiles(int64_t V, int64_t cus, int most = 2 * kFewWaves)
 {
     const int64_t blocks = (V + 15) / 16, rounds = (blocks - 1) / (2 * kFewWaves * cus), left = blocks - rounds * 2 * kFewWaves * cus;
     FewTiles f;
     f.last_blocks = (int)((left + cus - 1) / cus);
+    if (f.last_blocks > most) f.last_blocks = 2 * kFewWaves;
     f.nfull = (int)(rounds * cus);
     f.ntiles = f.nfull + (int)((left + f.last_blocks - 1) / f.last_blocks);
     f.slots = (int)(f.ntiles < cus ? f.ntiles : cus);
     return f;
+}
+// Up to this many tokens the last round is always spread; beyond, where the products bind, only if no wavefront needs a second
+// row block: with nine to fifteen blocks a tile every unit multiplies whole tiles' worth, and reads all the hidden rows, for part
+// of one.  Whole tiles / spread, us: 200 tokens x 4,096 x 73,628 (2 blocks) 210 / 186, 98,204 (8) 224 / 207, 102,300 (9) 229 / 237,
+// 118,684 (13) 244 / 249, 126,876 (15) 252 / 256; 200 x 768 x 110,492 (11) 54.7 / 57.1; 256 x 2,048 x 53,000 (13, no round before) 57.5 /
+// 60.3; 160 x 4,096 x 102,300 (9) 205 / 200, 118,684 218 / 215, 160 x 1,024 x 118,684 56.5 / 57.2.
+constexpr int kFewSpreadTokens = 192;
+inline FewTiles few_tiles_of(int64_t T, int64_t V, int64_t cus)
+{
+    return few_tiles(V, cus, T <= kFewSpreadTokens ? 2 * kFewWaves : kFewWaves);
 }
 
 size_t lmhead_workspace_bytes(int64_t T);

@@ -30,7 +30,7 @@ namespace a3po {
 // in_order; tests/test_schedule.py reads it off the compiled kernel).
 //
 // A tile is 16 row blocks of 16, two per wavefront, but the tiles of the last round have only as many (last_blocks) as spread
-// its rows over all compute units (FewTiles): a wavefront without a first or second block multiplies the tile's first row,
+// its rows over all compute units (FewTiles, which keeps to whole tiles where that gains nothing): a wavefront without a first or second block multiplies the tile's first row,
 // whose lines all its lanes share, and leaves the products out of the fold.  A compute unit streams the weight at its own pace
 // whatever the others do, so a third round of 82 whole tiles took as long as the two full ones before it (16 tokens x 4,096 x
 // 151,936 247 us, now 220; x 2,048 x 32,000, 125 tiles on 256 units, 39 and 30; reading the rows of another block instead of
@@ -338,7 +338,7 @@ hipError_t launch_fused_lmhead_logprob(const void *hidden, const void *weight, i
     const int64_t tiles = (V + kFewRows - 1) / kFewRows, cus = (int64_t)gg.nxcd * gg.per_xcd;
     const bool few = T <= 192 || (T <= kFewMaxTokens && tiles >= cus * 3 / 4);
     if (few && H % 256 == 0 && V <= 0x7FFFFFFF - 256 * kFewRows) {
-        const FewTiles ft = few_tiles(V, cus);  // at most 256 slots: gemm_partial_entries(T) is 256 T here
+        const FewTiles ft = few_tiles_of(T, V, cus);  // at most 256 slots: gemm_partial_entries(T) is 256 T here
         const hipError_t e = T <= 64    ? launch_few_tokens<4>(hidden, weight, T, H, V, partial, ft, s)
                              : T <= 128 ? launch_few_tokens<8>(hidden, weight, T, H, V, partial, ft, s)
                              : T <= 192 ? launch_few_tokens<12>(hidden, weight, T, H, V, partial, ft, s)

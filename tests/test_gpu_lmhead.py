@@ -64,10 +64,12 @@ def test_fused_lmhead_logprob_small(a3po, T, H, V):
 
 @pytest.mark.parametrize("T,H,V", [(40, 256, 65536 + 16), (100, 256, 65536 + 4096 * 6 + 1), (129, 256, 65536), (150, 256, 65536 + 17),
                                    (192, 512, 65536 + 4096 * 8), (170, 256, 65536 + 4096 * 8 + 1), (250, 512, 131072 + 4096 * 3 + 5),
-                                   (192, 256, 15), (192, 1024, 4097)])
+                                   (192, 256, 15), (192, 1024, 4097), (193, 256, 65536 + 4096 * 8 + 1), (250, 256, 65536 + 4096 * 8),
+                                   (200, 512, 49153), (256, 256, 65536 + 4096 * 14 + 77)])
 def test_fused_lmhead_logprob_last_round(a3po, T, H, V):
-    """Up to 256 tokens: last rounds of one, two, three, seven, eight, nine and sixteen row blocks a tile, after whole tiles and alone,
-    with one and two blocks a wavefront, and a ragged last block."""
+    """Up to 256 tokens: last rounds of one, two, three, seven, eight, nine and sixteen row blocks a tile (from 193 tokens on
+    whole tiles in place of nine and more), after whole tiles and alone, with one and two blocks a wavefront, and a ragged
+    last block."""
     test_fused_lmhead_logprob_small(a3po, T, H, V)
 
 

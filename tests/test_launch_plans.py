@@ -72,6 +72,30 @@ int main()
     assert run_on_host(str(source), tmp_path) == ""
 
 
+def test_few_token_tiles_are_whole_where_the_products_bind(tmp_path):
+    """From 193 tokens on the last round is spread over all compute units only where a wavefront then has one row block;
+    up to 192 always.  Either way every row block lies in one tile."""
+    source = tmp_path / "few.cpp"
+    source.write_text('''#include <cstdio>
+#include "a3po_common.h"
+#include "a3po_launch.h"
+using namespace a3po;
+int main()
+{
+    for (int64_t T : {1, 64, 192, 193, 256})
+        for (int64_t V = 1; V < 300000; V += 61) {
+            const FewTiles f = few_tiles_of(T, V, 256), even = few_tiles(V, 256);
+            const int64_t blocks = (V + 15) / 16, held = f.nfull * 16ll + (int64_t)(f.ntiles - f.nfull) * f.last_blocks;
+            const bool whole = T > 192 && even.last_blocks > 8;
+            const bool ok = f.nfull == even.nfull && f.last_blocks == (whole ? 16 : even.last_blocks) && held >= blocks &&
+                            held - blocks < f.last_blocks && f.ntiles <= even.ntiles && f.slots == (f.ntiles < 256 ? f.ntiles : 256);
+            if (!ok) return std::printf("T %lld V %lld\\n", (long long)T, (long long)V), 1;
+        }
+}
+''')
+    assert run_on_host(str(source), tmp_path) == ""
+
+
 def test_uneven_column_groups_leave_no_tile_out_and_no_unit_worse_off(tmp_path):
     assert run_on_host(os.path.join(HERE, "gemm_cut_driver.cpp"), tmp_path) == "ok\n"
 
